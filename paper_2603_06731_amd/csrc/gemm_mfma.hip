@@ -29,6 +29,14 @@ bool mfma_supported(const Problem& p) {
         int64_t img = (int64_t)(p.M / (p.conv.OH * p.conv.OW)) * p.conv.H * p.conv.W * p.conv.Cin * esz;
         int64_t halo = ((int64_t)p.conv.pad_h * p.conv.W + p.conv.pad_w + p.conv.W) * p.conv.Cin * esz;
         if (img + halo >= lim) return false;
+        // (the transposed form reaches any weight row from the first one with such an offset)
+        if (p.conv.transposed) {
+            if ((int64_t)p.K * p.ldb * esz >= lim) return false;
+            // one set of tiles per residue class must stay a launchable grid
+            const int64_t nh = p.conv.stride_h < p.conv.OH ? p.conv.stride_h : p.conv.OH;
+            const int64_t nw = p.conv.stride_w < p.conv.OW ? p.conv.stride_w : p.conv.OW;
+            if (((int64_t)p.M / 128 + nh * nw * 2) * ((p.N + 127) / 128) >= lim) return false;
+        }
     } else {
         if (p.lda % per16 || p.ldb % per16) return false;
         if (!p.trans_b && p.N % per16) return false;

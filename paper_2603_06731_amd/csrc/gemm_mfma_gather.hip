@@ -360,7 +360,7 @@ __global__ __launch_bounds__(GWM * GWN * 64, 2) void gemm_mfma_gather_kernel(Pro
                   : (p.epi == EPI_GELU_TANH || p.epi == EPI_BIAS_GELU_TANH) ? 2 : 0;
     char* wlds = lds + wave * ((2 * G_STAGE) / (GWM * GWN));
     EpiCtx<T, f32x4, FM, FN, WTM, WTN, (2 * G_STAGE) / (GWM * GWN)> ctx{p, acc, wlds, m0 + wm * WTM, n0 + wn * WTN, lane,
-                                                                      (int64_t)b * p.stride_c};
+                                                                      (int64_t)b * p.stride_c, RowsPlain::of(p)};
     if (p.out_dtype == DT_F32) {
         if (act == 0) ctx.template run<0, true>(); else if (act == 1) ctx.template run<1, true>();
         else ctx.template run<2, true>();
@@ -379,7 +379,7 @@ hipError_t launch_gather_mode(const Problem& p, hipStream_t stream) {
     DeviceShape ds;
     e = device_shape(dev, &ds);
     if (e != hipSuccess) return e;
-    TileMap tm;
+    TileMap tm{};
     tm.tiles_m = (p.M + GBM - 1) / GBM;
     tm.tiles_n = (p.N + GBN - 1) / GBN;
     tm.tiles_per_batch = tm.tiles_m * tm.tiles_n;

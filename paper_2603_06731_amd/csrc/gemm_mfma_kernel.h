@@ -175,6 +175,9 @@ struct TileMap {
     int tiles_m, tiles_n, tiles_per_batch, total;
     int group_m;
     int xcds;
+    // transposed convolution only (see ConvTClass): residue classes along h and w, and the distance of the
+    // filter taps that meet one class
+    int ct_nh, ct_nw, ct_step_h, ct_step_w;
 };
 
 __device__ __forceinline__ void map_tile(const TileMap& tm, int bid, int& b, int& tile_m, int& tile_n) {
@@ -269,11 +272,53 @@ template <> __device__ __forceinline__ uint32_t pack2<f16_t>(float a, float b) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, f16x2));
 }
 
+// Transposed convolution by residue classes.  Output row oh meets filter tap kh where oh + pad_h - kh dil_h
+// divides by the stride, which depends on oh mod stride_h only: the output falls into stride_h x stride_w classes
+// (ph, pw), and within one the taps kh0, kh0 + step_h, ... (step = stride / gcd(stride, dil)) form an ordinary
+// convolution at stride 1 whose taps walk the image backwards.  A workgroup's tile lies inside one class, so the k loop
+// holds only the taps that contribute: 1 / (stride_h stride_w) of the filter.  (With all taps in the loop and the
+// others' pieces zero-filled, 32 x 28 x 28 x 256 -> 128, 4 x 4, stride 2, took 196 us.)
+struct ConvTClass {
+    int oh_n, ow_n;            // output rows and columns of the class
+    int rows;                  // GEMM rows: images x oh_n x ow_n
+    int ph, pw;
+    int kh0, kw0, nh, nw;      // first tap and number of taps along h and w
+    int ih_base, iw_base;      // input row of output row ph for tap kh0
+    int dh, dw;                // input rows (columns) between successive taps of the class: <= 0
+};
+__device__ __forceinline__ void convt_axis(int phase, int pad, int stride, int dil, int ktaps, int step,
+                                           int& k0, int& n, int& base, int& d) {
+    k0 = 0;
+    while (k0 < step && k0 < ktaps && (phase + pad - k0 * dil) % stride != 0) ++k0;
+    n = (k0 < step && k0 < ktaps) ? (ktaps - 1 - k0) / step + 1 : 0;
+    base = (phase + pad - k0 * dil) / stride;       // exact where n > 0
+    d = -(dil * step / stride);
+}
+
+// Which row of C a row of the tile grid is: the same one, except for the classes of a transposed convolution.
+struct RowsPlain {
+    static constexpr bool kPlain = true;
+    int m;                                          // rows beyond this one do not exist
+    static __device__ __forceinline__ RowsPlain of(const Problem& p) { return RowsPlain{p.M}; }
+    __device__ __forceinline__ int64_t at(int row) const { return row; }
+};
+struct RowsConvT {
+    static constexpr bool kPlain = false;
+    int m;
+    int oh_n, ow_n, ph, pw, sh, sw, OH, OW;
+    __device__ __forceinline__ int64_t at(int row) const {
+        const int pix = oh_n * ow_n;
+        const int n = row / pix, rem = row - n * pix;
+        const int oh = rem / ow_n, ow = rem - oh * ow_n;
+        return ((int64_t)n * OH + oh * sh + ph) * OW + ow * sw + pw;
+    }
+};
+
 // Epilogue of one wave: its WTM x WTN register tile -> global memory.
 // AV is the accumulator vector of one MFMA block and fixes the block layout:
 //   f32x16 (32x32 block): lane holds row lane%32, columns 8 g + 4 (lane/32) + 0..3 for g = 0..3;
 //   f32x4  (16x16 block): lane holds row lane%16, columns 4 (lane/16) + 0..3.
-template <typename T, typename AV, int FM, int FN, int WTM, int WTN, int LDS_PER_WAVE>
+template <typename T, typename AV, int FM, int FN, int WTM, int WTN, int LDS_PER_WAVE, class ROWS = RowsPlain>
 struct EpiCtx {
     static constexpr bool S16 = sizeof(AV) == 16;
     static constexpr int RB = S16 ? 16 : 32;       // rows (and columns) of one block
@@ -285,6 +330,7 @@ struct EpiCtx {
     int row0, col0;        // global coordinates of the wave tile's corner
     int lane;
     int64_t c_batch;
+    ROWS rows;
 
     __device__ __forceinline__ int lrow_of(int i) const { return i * RB + (lane & (RB - 1)); }
     __device__ __forceinline__ int lcol_of(int j, int g) const {
@@ -304,8 +350,8 @@ struct EpiCtx {
     // vec: whole aligned 4-element pieces may be loaded at once
     template <bool OUT_F32> __device__ __forceinline__ void res4(int gm, int gn, bool vec, float (&rv)[4]) const {
         rv[0] = rv[1] = rv[2] = rv[3] = 0.0f;
-        if (!p.R || gm >= p.M || gn >= p.N) return;
-        const int64_t o = c_batch + (int64_t)gm * p.ldr + gn;
+        if (!p.R || gm >= rows.m || gn >= p.N) return;
+        const int64_t o = c_batch + rows.at(gm) * p.ldr + gn;
         if (OUT_F32) {
             if (vec) { f32x4 q = *(const f32x4*)((const float*)p.R + o); rv[0] = q[0]; rv[1] = q[1]; rv[2] = q[2]; rv[3] = q[3]; }
             else {
@@ -418,7 +464,7 @@ struct EpiCtx {
             const int lrow0 = i0 * RB + ld_row;                     // row inside the wave tile
             char* cptr = (char*)p.C + (c_batch + (int64_t)(row0 + lrow0) * p.ldc + gn) * ESZ;
             const int64_t cstep = (int64_t)ROWS_PER_LD * p.ldc * ESZ;
-            const int rows_left = (p.M - row0 < WTM ? p.M - row0 : WTM) - lrow0;   // valid rows from lrow0 on
+            const int rows_left = (rows.m - row0 < WTM ? rows.m - row0 : WTM) - lrow0;   // valid rows from lrow0 on
 #pragma unroll
             for (int q0 = 0; q0 < NLD; q0 += BATCH) {
                 int4v w[BATCH];
@@ -430,8 +476,10 @@ struct EpiCtx {
                 }
 #pragma unroll
                 for (int q = 0; q < BATCH; ++q) {
-                    if ((q0 + q) * ROWS_PER_LD < rows_left && gn < p.N)
-                        *(int4v*)(cptr + (q0 + q) * cstep) = w[q];
+                    if ((q0 + q) * ROWS_PER_LD < rows_left && gn < p.N) {
+                        if (ROWS::kPlain) *(int4v*)(cptr + (q0 + q) * cstep) = w[q];
+                        else *(int4v*)((char*)p.C + (c_batch + rows.at(row0 + lrow0 + (q0 + q) * ROWS_PER_LD) * p.ldc + gn) * ESZ) = w[q];
+                    }
                 }
             }
         }
@@ -551,8 +599,8 @@ struct EpiCtx {
 #pragma unroll
                 for (int i = 0; i < FM; ++i) {
                     const int gm = row0 + lrow_of(i);
-                    if (gm >= p.M || gn >= p.N) continue;
-                    const int64_t o = c_batch + (int64_t)gm * p.ldc + gn;
+                    if (gm >= rows.m || gn >= p.N) continue;
+                    const int64_t o = c_batch + rows.at(gm) * p.ldc + gn;
                     float rv[4];
                     res4<OUT_F32>(gm, gn, false, rv);
 #pragma unroll
@@ -642,6 +690,24 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
 
     int b, tile_m, tile_n;
     map_tile(tmap, blockIdx.x, b, tile_m, tile_n);
+    // geometry of the rows and of the k axis: the problem's, or the tile's residue class's (ConvTClass)
+    ConvTClass ct;
+    int Mrows = p.M, Kall = p.K;
+    int row_oh = p.conv.OH, row_ow = p.conv.OW, tap_w = p.conv.KW, tap_dh = p.conv.dil_h, tap_dw = p.conv.dil_w;
+    if constexpr (CONVT) {
+        const int ncls = tmap.ct_nh * tmap.ct_nw;       // classes fastest: those of one region read the same pixels
+        const int cls = tile_m % ncls;
+        tile_m /= ncls;
+        ct.ph = cls / tmap.ct_nw; ct.pw = cls - ct.ph * tmap.ct_nw;
+        ct.oh_n = (p.conv.OH - ct.ph + p.conv.stride_h - 1) / p.conv.stride_h;
+        ct.ow_n = (p.conv.OW - ct.pw + p.conv.stride_w - 1) / p.conv.stride_w;
+        ct.rows = p.M / (p.conv.OH * p.conv.OW) * ct.oh_n * ct.ow_n;
+        convt_axis(ct.ph, p.conv.pad_h, p.conv.stride_h, p.conv.dil_h, p.conv.KH, tmap.ct_step_h, ct.kh0, ct.nh, ct.ih_base, ct.dh);
+        convt_axis(ct.pw, p.conv.pad_w, p.conv.stride_w, p.conv.dil_w, p.conv.KW, tmap.ct_step_w, ct.kw0, ct.nw, ct.iw_base, ct.dw);
+        if (tile_m * BM >= ct.rows) return;             // the grid is sized by the largest class
+        Mrows = ct.rows; Kall = ct.nh * ct.nw * p.conv.Cin;
+        row_oh = ct.oh_n; row_ow = ct.ow_n; tap_w = ct.nw; tap_dh = ct.dh; tap_dw = ct.dw;
+    }
     const int m0 = tile_m * BM, n0 = tile_n * BN;
 
     // ---- per-lane source offsets of the direct-to-LDS loads -----------------
@@ -677,25 +743,18 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
         int chunk = kma_slot ^ kmajor_swz<BKA, S16>(row);
         a_kofs[r] = chunk * 8;
         int gm = m0 + row;
-        a_ok[r] = gm < p.M;
+        a_ok[r] = gm < Mrows;
         if (CONV) {
-            int pix = p.conv.OH * p.conv.OW;
+            int pix = row_oh * row_ow;
             int gmc = a_ok[r] ? gm : 0;
             int n = gmc / pix;
             int rem = gmc - n * pix;
-            int oh = rem / p.conv.OW;
-            int ow = rem - oh * p.conv.OW;
-            if (CONVT) {
-                // output row oh receives tap kh from input row (oh + pad - kh*dil) / stride, if that divides
-                a_ih0[r] = oh + p.conv.pad_h;
-                a_iw0[r] = ow + p.conv.pad_w;
-                a_voff[r] = (unsigned)(n * p.conv.H * p.conv.W * p.conv.Cin * 2);    // image base
-            } else {
-                a_ih0[r] = oh * p.conv.stride_h - p.conv.pad_h;
-                a_iw0[r] = ow * p.conv.stride_w - p.conv.pad_w;
-                // byte offset of pixel (n, ih0, iw0), channel 0; may be "negative" (wraps), fixed up per tap
-                a_voff[r] = (unsigned)(((n * p.conv.H + a_ih0[r]) * p.conv.W + a_iw0[r]) * p.conv.Cin * 2);
-            }
+            int oh = rem / row_ow;
+            int ow = rem - oh * row_ow;
+            a_ih0[r] = CONVT ? oh + ct.ih_base : oh * p.conv.stride_h - p.conv.pad_h;
+            a_iw0[r] = CONVT ? ow + ct.iw_base : ow * p.conv.stride_w - p.conv.pad_w;
+            // byte offset of pixel (n, ih0, iw0), channel 0; may be "negative" (wraps), fixed up per tap
+            a_voff[r] = (unsigned)(((n * p.conv.H + a_ih0[r]) * p.conv.W + a_iw0[r]) * p.conv.Cin * 2);
         } else {
             a_voff[r] = a_ok[r] ? (unsigned)(row * (int)p.lda * 2 + chunk * 16) : kOob;
         }
@@ -763,27 +822,32 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
     int4v ld_ra = make_rsrc(a_tile), ld_rb = make_rsrc(b_tile);
     int ld_dh = 0, ld_dw = 0;
     unsigned ld_delta = 0;
-    int ld_c = 0;              // transposed convolution, one tap per k-tile: first channel of the tile
+    // transposed convolution: weight row of the class's tap (i, j), channel c
+    auto convt_brow = [&](int i, int j, int c) {
+        return ((ct.kh0 + i * tmap.ct_step_h) * p.conv.KW + ct.kw0 + j * tmap.ct_step_w) * p.conv.Cin + c;
+    };
 
     // Start issuing the k-tile at k0 into `stage`: descriptors rebased to k0.
     auto begin_tile = [&](int k0, int stage) {
         ld_k0 = k0;
         ld_sa = lds_base + stage * STAGE;
         ld_sb = ld_sa + A_BYTES;
+        int brow = k0;                  // transposed convolution: weight row of the tile's first k (one tap per tile)
         if (CONV) {
-            ld_dh = tap_kh * p.conv.dil_h; ld_dw = tap_kw * p.conv.dil_w;
+            ld_dh = tap_kh * tap_dh; ld_dw = tap_kw * tap_dw;
             ld_delta = (unsigned)(((ld_dh * p.conv.W + ld_dw) * p.conv.Cin + tap_c) * 2);
-            ld_c = tap_c;
+            if (CONVT) brow = one_tap ? convt_brow(tap_kh, tap_kw, tap_c) : 0;
             if (one_tap) {              // advance the uniform tap state to the next k-tile
                 tap_c += BK;
                 if (tap_c >= p.conv.Cin) {
                     tap_c = 0;
-                    if (++tap_kw == p.conv.KW) { tap_kw = 0; ++tap_kh; }
+                    if (++tap_kw == tap_w) { tap_kw = 0; ++tap_kh; }
                 }
             }
         } else {
             ld_ra = make_rsrc(a_tile + (int64_t)k0 * 2);
         }
+        if (CONVT) { ld_rb = make_rsrc(b_tile + (int64_t)brow * p.ldb * 2); return; }
         ld_rb = make_rsrc(TRANS_B ? b_tile + (int64_t)k0 * 2 : b_tile + (int64_t)k0 * p.ldb * (E8 ? 4 : E4 ? 1 : 2));
     };
 
@@ -794,25 +858,7 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
         constexpr bool TAIL = decltype(tail_tag)::value;
         if (r < CA) {
             unsigned off;
-            if (CONVT) {
-                int dh, dw, c;
-                if (one_tap) {
-                    dh = ld_dh; dw = ld_dw; c = ld_c + a_kofs[r];
-                } else {
-                    int k = ld_k0 + a_kofs[r];
-                    int tap = k / p.conv.Cin;
-                    c = k - tap * p.conv.Cin;
-                    int kh = tap / p.conv.KW;
-                    int kw = tap - kh * p.conv.KW;
-                    dh = kh * p.conv.dil_h; dw = kw * p.conv.dil_w;
-                }
-                const int th = a_ih0[r] - dh, tw = a_iw0[r] - dw;
-                const int ih = th / p.conv.stride_h, iw = tw / p.conv.stride_w;
-                bool ok = a_ok[r] && th >= 0 && tw >= 0 && ih * p.conv.stride_h == th && iw * p.conv.stride_w == tw &&
-                          ih < p.conv.H && iw < p.conv.W;
-                if (TAIL) ok = ok && (ld_k0 + a_kofs[r] < p.K);
-                off = ok ? a_voff[r] + (unsigned)(((ih * p.conv.W + iw) * p.conv.Cin + c) * 2) : kOob;
-            } else if (CONV) {
+            if (CONV) {
                 int dh, dw;
                 if (one_tap) {
                     dh = ld_dh; dw = ld_dw;
@@ -821,24 +867,29 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
                     int k = ld_k0 + a_kofs[r];
                     int tap = k / p.conv.Cin;
                     int c = k - tap * p.conv.Cin;
-                    int kh = tap / p.conv.KW;
-                    int kw = tap - kh * p.conv.KW;
-                    dh = kh * p.conv.dil_h; dw = kw * p.conv.dil_w;
+                    int kh = tap / tap_w;
+                    int kw = tap - kh * tap_w;
+                    dh = kh * tap_dh; dw = kw * tap_dw;
                     off = a_voff[r] + (unsigned)(((dh * p.conv.W + dw) * p.conv.Cin + c) * 2);
                 }
                 int ih = a_ih0[r] + dh, iw = a_iw0[r] + dw;
                 bool ok = a_ok[r] && ih >= 0 && ih < p.conv.H && iw >= 0 && iw < p.conv.W;
-                if (TAIL) ok = ok && (ld_k0 + a_kofs[r] < p.K);
+                if (TAIL) ok = ok && (ld_k0 + a_kofs[r] < Kall);
                 off = ok ? off : kOob;
             } else {
                 off = a_voff[r];
-                if (TAIL && ld_k0 + a_kofs[r] >= p.K) off = kOob;
+                if (TAIL && ld_k0 + a_kofs[r] >= Kall) off = kOob;
             }
             dma16(ld_ra, ld_sa + (wave * CA + r) * 1024, off);
         } else {
             const int rb = r - CA;
             unsigned off = b_voff[rb];
-            if (TAIL && ld_k0 + b_kofs[rb] >= p.K) off = kOob;
+            if (CONVT && !one_tap && off != kOob) {
+                // the piece's k-row of the class's k axis -> its row of the weights
+                const int k = ld_k0 + b_kofs[rb], tap = k / p.conv.Cin, i = tap / tap_w;
+                off += (unsigned)((convt_brow(i, tap - i * tap_w, k - tap * p.conv.Cin) - b_kofs[rb]) * (int)p.ldb * 2);
+            }
+            if (TAIL && ld_k0 + b_kofs[rb] >= Kall) off = kOob;
             dma16(ld_rb, ld_sb + (wave * CB + rb) * 1024, off);
         }
     };
@@ -883,8 +934,8 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
     // ---- main loop: NSTAGE LDS stages; the loads of k-tiles t+1 .. t+NSTAGE-1
     // are in flight while k-tile t is multiplied; one barrier per k-tile.
     // prime(): first fragment reads of k-tile 0; run_tile(...): one k-tile (see tile_body).
-    const int KT = (p.K + BK - 1) / BK;       // k-tiles
-    const int KF = p.K / BK;                  // of which full
+    const int KT = (Kall + BK - 1) / BK;      // k-tiles
+    const int KF = Kall / BK;                 // of which full
     // pairs_tag true: the steady state runs k-tiles in pairs and tells run_tile which of the pair
     // it is (phase 1, 2; 0 = a tile on its own), for pipelines whose register buffers alternate
     // from one tile to the next.
@@ -1732,8 +1783,12 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
                   : (p.epi == EPI_GELU_TANH || p.epi == EPI_BIAS_GELU_TANH) ? 2 : 0;
     const bool out_f32 = p.out_dtype == DT_F32;
     char* wlds = lds + wave * ((NSTAGE * STAGE) / NW);
-    EpiCtx<TO, AccV, FM, FN, WTM, WTN, (NSTAGE * STAGE) / NW> ctx{p, acc, wlds, m0 + wm * WTM, n0 + wn * WTN, lane,
-                                                         (int64_t)b * p.stride_c};
+    typedef typename std::conditional<CONVT, RowsConvT, RowsPlain>::type Rows;
+    Rows rows;
+    if constexpr (CONVT) rows = Rows{Mrows, ct.oh_n, ct.ow_n, ct.ph, ct.pw, p.conv.stride_h, p.conv.stride_w, p.conv.OH, p.conv.OW};
+    else rows = Rows::of(p);
+    EpiCtx<TO, AccV, FM, FN, WTM, WTN, (NSTAGE * STAGE) / NW, Rows> ctx{p, acc, wlds, m0 + wm * WTM, n0 + wn * WTN, lane,
+                                                               (int64_t)b * p.stride_c, rows};
     if constexpr (sizeof(T) == 1 && MfmaOp<T>::kChunks == 1) {      // int8 operands
         const bool has_mid = p.q_mid > 0.0f, has_bn = p.q_mean != nullptr;
         const bool fast = (!has_mid || make_step_div(p.q_mid).fast) && (p.out_dtype != DT_INT8 || make_step_div(p.q_out).fast);

@@ -66,9 +66,23 @@ hipError_t launch_one(const Problem& p, hipStream_t stream, int group_m) {
         if (e != hipSuccess) return e;
         attr_done.fetch_or(bit, std::memory_order_release);
     }
-    TileMap tm;
+    TileMap tm{};
     tm.tiles_m = (p.M + BM - 1) / BM;
     tm.tiles_n = (p.N + BN - 1) / BN;
+    if (MODE == MODE_CONVT) {
+        // one set of row tiles per residue class, sized by the largest class
+        const ConvGeom& g = p.conv;
+        auto gcd = [](int a, int b) { while (b) { const int r = a % b; a = b; b = r; } return a; };
+        tm.ct_nh = g.stride_h < g.OH ? g.stride_h : g.OH;
+        tm.ct_nw = g.stride_w < g.OW ? g.stride_w : g.OW;
+        tm.ct_step_h = g.stride_h / gcd(g.stride_h, g.dil_h);
+        tm.ct_step_w = g.stride_w / gcd(g.stride_w, g.dil_w);
+        const long long images = p.M / ((long long)g.OH * g.OW);
+        const long long rows = images * ((g.OH + g.stride_h - 1) / g.stride_h) * ((g.OW + g.stride_w - 1) / g.stride_w);
+        const long long tiles = (rows + BM - 1) / BM * tm.ct_nh * tm.ct_nw;
+        if (tiles * tm.tiles_n > 0x7FFFFFFFLL) return hipErrorInvalidValue;
+        tm.tiles_m = (int)tiles;
+    }
     tm.tiles_per_batch = tm.tiles_m * tm.tiles_n;
     long long total = (long long)tm.tiles_per_batch * p.batch;
     if (total <= 0 || total > 0x7FFFFFFFLL) return hipErrorInvalidValue;

@@ -1,0 +1,41 @@
+"""Transposed convolution by residue classes of the output (matrix-unit kernel): strides
+larger than the filter (classes without a tap), strides that share a factor with the
+dilation, strides beyond the output, images whose size does not divide by the stride,
+k-tiles that span taps, and rows stored one element at a time."""
+import numpy as np
+import pytest
+
+import workloads as wl
+from workloads import configs as C
+import pbk_testlib as T
+
+pytestmark = pytest.mark.gpu
+
+BF16, F16, F32 = wl.DTYPE_BF16, wl.DTYPE_F16, wl.DTYPE_F32
+
+CASES = [  # n, H, W, Cin, Cout, KH, KW, stride, pad, out_pad, dil
+    (2, 9, 7, 64, 72, 2, 3, (3, 4), (0, 1), (2, 1), (1, 1)),       # filter smaller than the stride: empty classes
+    (1, 8, 9, 32, 40, 3, 3, (4, 6), (2, 1), (1, 3), (2, 4)),       # gcd(stride, dil) = 2
+    (1, 7, 6, 32, 32, 5, 4, (2, 2), (3, 2), (1, 1), (2, 2)),       # dil a multiple of the stride: odd rows have no tap
+    (3, 1, 2, 64, 64, 3, 3, (7, 5), (1, 2), (0, 0), (1, 1)),       # stride beyond the output
+    (5, 13, 11, 40, 136, 4, 4, (2, 2), (1, 1), (1, 0), (1, 1)),    # a k-tile spans taps
+    (2, 24, 23, 128, 256, 4, 4, (2, 2), (1, 1), (0, 0), (1, 1)),
+]
+
+
+@pytest.mark.parametrize("dtype,out_dtype,cfg", [(BF16, BF16, 0), (BF16, BF16, 1), (BF16, BF16, 6), (F16, F32, None)])
+@pytest.mark.parametrize("case", CASES)
+def test_residue_classes(case, dtype, out_dtype, cfg):
+    import paper_2603_06731_amd as pbk
+    n, H, W, Cin, Cout, KH, KW, stride, pad, out_pad, dil = case
+    w = wl.Workload("convT_classes", "conv", dtype, out_dtype, C.EPI_BIAS_RELU, n=n, H=H, W=W, Cin=Cin, Cout=Cout,
+                    KH=KH, KW=KW, stride=stride, pad=pad, out_pad=out_pad, dil=dil, transposed=1,
+                    dist_b=("normal", float(np.sqrt(2.0 / (KH * KW * Cin)))))
+    host = wl.make_inputs(w)
+    with T.forced_kernel(None if cfg is None else f"mfma:{cfg}"):
+        st, out = T.run_workload(w, T.upload(host))
+    assert st == 0, pbk.pbk_status_string(st)
+    assert "mfma" in pbk.pbk_last_kernel()
+    ref, pre = T.oracle_full(w, host)
+    err = T.rel_err(T.to_host_f64(out, w.out_dtype).reshape(ref.shape), ref, pre)
+    assert err <= T.TIGHT[out_dtype], err        # the bound of the output rounding, as for every convolution
