@@ -17,7 +17,7 @@
 // Pieces go to LDS in the main kernel's layouts: k-major [rows][32 k] with the 16-byte chunk index
 // XOR-swizzled by the row (A, the image, a k-major B), n-major [32 k][128 n] read with the transposing
 // LDS read (row-major B, weights).
-// 128 x 128 x 32 tile, 2 x 2 waves, v_mfma_f32_16x16x32, LDS double-buffered: while k-tile t is
+// 128 x 128 x 32 tile (64 x 128 where the larger one leaves compute units without work), 2 x 2 waves, v_mfma_f32_16x16x32, LDS double-buffered: while k-tile t is
 // multiplied, the pieces of k-tiles t+1 .. t+3 are in flight to registers; one barrier per k-tile.
 // The epilogue is the main kernel's (registers, then the LDS shuffle or direct stores).
 #include "gemm_mfma_launch.h"
@@ -25,10 +25,8 @@
 namespace pbk {
 namespace {
 
-constexpr int GBM = 128, GBN = 128, GBK = 32;
+constexpr int GBN = 128, GBK = 32;                   // GBM: 128 or 64, a parameter of the kernel
 constexpr int GWM = 2, GWN = 2;
-constexpr int G_TILE_BYTES = GBM * GBK * 2;          // 8 KiB, the same for A and B
-constexpr int G_STAGE = 2 * G_TILE_BYTES;
 
 // 16 bytes from an address that is only known to be 2-byte aligned (one global_load_dwordx4)
 // (the pointer is stated to be a global-memory one: a generic load would also count as an LDS operation)
@@ -48,7 +46,7 @@ __device__ const int4v kZeroPiece = {0, 0, 0, 0};
 // before its place because 16 bytes from its place would have run over the end of the operand).
 // kPlain = keep everything.
 constexpr int kPlain = 8;
-constexpr int kAllPlain = kPlain * 0x01010101;       // four pieces, one byte each
+constexpr int kAllPlain = kPlain * 0x01010101;       // one byte per piece, up to four
 struct PieceSrc { const char* ptr; int meta; };
 
 // want: address of the piece's first element (anything at or above the operand's base when !ok);
@@ -79,15 +77,17 @@ __device__ __forceinline__ int4v piece_fix(int4v v, int meta) {
     return int4v{keep(w0, 0), keep(w1, 1), keep(w2, 2), keep(w3, 3)};
 }
 
-template <typename T, int MODE>
+template <typename T, int MODE, int GBM>
 __global__ __launch_bounds__(GWM * GWN * 64, 2) void gemm_mfma_gather_kernel(Problem p, TileMap tmap) {
     constexpr bool CONV = MODE == MODE_CONV;
     constexpr bool TRANS_B = MODE == MODE_TRANS_B;
     constexpr int NT = GWM * GWN * 64;
     constexpr int WTM = GBM / GWM, WTN = GBN / GWN;
     constexpr int FM = WTM / 16, FN = WTN / 16;
-    constexpr int PIECES = GBM * (GBK / 8) / NT;     // 16-byte pieces of a tile per thread (2)
-    static_assert(GBM == GBN && PIECES * NT == GBM * (GBK / 8), "tile geometry");
+    constexpr int A_TILE = GBM * GBK * 2, G_STAGE = A_TILE + GBN * GBK * 2;      // bytes
+    // 16-byte pieces of the two tiles per thread (1 or 2, and 2)
+    constexpr int PA = GBM * (GBK / 8) / NT, PB = GBN * (GBK / 8) / NT;
+    static_assert(PA * NT == GBM * (GBK / 8) && PB * NT == GBN * (GBK / 8) && PA + PB <= 4, "tile geometry");
 
     extern __shared__ __attribute__((aligned(1024))) char lds[];        // 2 x (A tile | B tile)
     const int t = threadIdx.x, lane = t & 63;
@@ -111,12 +111,12 @@ __global__ __launch_bounds__(GWM * GWN * 64, 2) void gemm_mfma_gather_kernel(Pro
     const char* b_last16 = Bbase + b_elems * 2 - 16;
 
     // ---- A (k-major source): piece = (row, chunk of 8 k); four neighbouring threads cover a row of the k-tile.
-    // The thread's two pieces differ in the row only (+64).
+    // The thread's pieces differ in the row only (+64).
     const int a_chunk = t & 3;
-    int a_row[PIECES];
-    bool a_ok[PIECES];
-    const char* a_cur[PIECES];       // dense: address of the piece in the next k-tile to fetch; conv: the pixel's image
-    int a_ih0[PIECES], a_iw0[PIECES];
+    int a_row[PA];
+    bool a_ok[PA];
+    const char* a_cur[PA];       // dense: address of the piece in the next k-tile to fetch; conv: the pixel's image
+    int a_ih0[PA], a_iw0[PA];
     // conv: (channel, tap) of the thread's pieces in the next k-tile to fetch
     int a_c = 0, a_tap = 0;
     if (CONV) {
@@ -130,7 +130,7 @@ __global__ __launch_bounds__(GWM * GWN * 64, 2) void gemm_mfma_gather_kernel(Pro
     const unsigned kw_magic = CONV ? (1u << 20) / (unsigned)p.conv.KW + 1u : 0u;
     const char* zero_piece = (const char*)&kZeroPiece;
 #pragma unroll
-    for (int i = 0; i < PIECES; ++i) {
+    for (int i = 0; i < PA; ++i) {
         a_row[i] = (t >> 2) + (NT / 4) * i;
         const int gm = m0 + a_row[i];
         a_ok[i] = gm < p.M;
@@ -150,12 +150,12 @@ __global__ __launch_bounds__(GWM * GWN * 64, 2) void gemm_mfma_gather_kernel(Pro
     // convolution): a piece is eight neighbouring n of one k-row: b_row = k-row in the tile, b_chunk = which
     // eight n; the thread's two pieces differ in the k-row only (+16).
     const int b_chunk = TRANS_B ? (t & 3) : (t & 15);
-    int b_row[PIECES];
-    bool b_ok[PIECES];
-    const char* b_cur[PIECES];       // address of the piece in the next k-tile to fetch (conv: of its first n in row 0)
-    int b_c[PIECES], b_tap[PIECES];  // conv: (channel, tap) of the piece's k-row in the next k-tile to fetch
+    int b_row[PB];
+    bool b_ok[PB];
+    const char* b_cur[PB];       // address of the piece in the next k-tile to fetch (conv: of its first n in row 0)
+    int b_c[PB], b_tap[PB];  // conv: (channel, tap) of the piece's k-row in the next k-tile to fetch
 #pragma unroll
-    for (int i = 0; i < PIECES; ++i) {
+    for (int i = 0; i < PB; ++i) {
         if (TRANS_B) {
             b_row[i] = (t >> 2) + (NT / 4) * i;
             b_ok[i] = n0 + b_row[i] < p.N;
@@ -186,7 +186,7 @@ __global__ __launch_bounds__(GWM * GWN * 64, 2) void gemm_mfma_gather_kernel(Pro
     // the pieces of NPF k-tiles are in flight to registers at any time: a workgroup is often alone on its
     // compute unit (these are the odd, small problems), so the memory latency is covered by depth
     constexpr int NPF = 3;
-    int4v avs[NPF][PIECES], bvs[NPF][PIECES];
+    int4v avs[NPF][PA], bvs[NPF][PB];
     int metas[NPF];                  // one byte per piece: A's, then B's
 
     // fetch the pieces of k-tile kt into register set S (loads are issued here and waited for at the first
@@ -198,7 +198,7 @@ __global__ __launch_bounds__(GWM * GWN * 64, 2) void gemm_mfma_gather_kernel(Pro
         const int k0 = kt * GBK;
         int meta = 0;
 #pragma unroll
-        for (int i = 0; i < PIECES; ++i) {
+        for (int i = 0; i < PA; ++i) {
             const char* want;
             bool ok = true;
             int cnt = 8;
@@ -234,7 +234,7 @@ __global__ __launch_bounds__(GWM * GWN * 64, 2) void gemm_mfma_gather_kernel(Pro
             if (a_c >= Cp) { a_c -= Cp; ++a_tap; }
         }
 #pragma unroll
-        for (int i = 0; i < PIECES; ++i) {
+        for (int i = 0; i < PB; ++i) {
             const char* want;
             bool ok = true;
             int cnt = 8;
@@ -260,27 +260,29 @@ __global__ __launch_bounds__(GWM * GWN * 64, 2) void gemm_mfma_gather_kernel(Pro
             if (CAREFUL) s = piece_src(want, b_last16, ok, cnt);
             else { s.ptr = want; s.meta = ok ? cnt : 0; }
             bvs[S][i] = ld_vec16(s.ptr);
-            meta |= s.meta << (8 * (PIECES + i));
+            meta |= s.meta << (8 * (PA + i));
         }
         metas[S] = meta;
     };
     auto stash = [&](int stage, auto set_tag) __attribute__((always_inline)) {
         constexpr int S = decltype(set_tag)::value;
         char* sa = lds + stage * G_STAGE;
-        char* sb = sa + G_TILE_BYTES;
-        int4v va[PIECES], vb[PIECES];
+        char* sb = sa + A_TILE;
+        int4v va[PA], vb[PB];
 #pragma unroll
-        for (int i = 0; i < PIECES; ++i) { va[i] = avs[S][i]; vb[i] = bvs[S][i]; }
-        if (metas[S] != kAllPlain) {                  // rare: one branch for the thread's four pieces
+        for (int i = 0; i < PA; ++i) va[i] = avs[S][i];
 #pragma unroll
-            for (int i = 0; i < PIECES; ++i) {
-                va[i] = piece_fix(va[i], (metas[S] >> (8 * i)) & 255);
-                vb[i] = piece_fix(vb[i], (metas[S] >> (8 * (PIECES + i))) & 255);
-            }
+        for (int i = 0; i < PB; ++i) vb[i] = bvs[S][i];
+        if (metas[S] != (int)((unsigned)kAllPlain >> (8 * (4 - PA - PB)))) {         // rare: one branch for the thread's pieces
+#pragma unroll
+            for (int i = 0; i < PA; ++i) va[i] = piece_fix(va[i], (metas[S] >> (8 * i)) & 255);
+#pragma unroll
+            for (int i = 0; i < PB; ++i) vb[i] = piece_fix(vb[i], (metas[S] >> (8 * (PA + i))) & 255);
         }
 #pragma unroll
-        for (int i = 0; i < PIECES; ++i) {
-            *(int4v*)(sa + kmajor_offset<GBK, true>(a_row[i], a_chunk)) = va[i];
+        for (int i = 0; i < PA; ++i) *(int4v*)(sa + kmajor_offset<GBK, true>(a_row[i], a_chunk)) = va[i];
+#pragma unroll
+        for (int i = 0; i < PB; ++i) {
             if (TRANS_B) *(int4v*)(sb + kmajor_offset<GBK, true>(b_row[i], b_chunk)) = vb[i];
             else *(int4v*)(sb + nmajor_offset<GBN>(b_row[i], b_chunk * 16)) = vb[i];
         }
@@ -305,7 +307,7 @@ __global__ __launch_bounds__(GWM * GWN * 64, 2) void gemm_mfma_gather_kernel(Pro
     auto step = [&](int kt, auto set_tag, auto careful_tag) __attribute__((always_inline)) {
         constexpr int S = decltype(set_tag)::value;
         const char* sa = lds + (kt & 1) * G_STAGE;
-        const char* sb = sa + G_TILE_BYTES;
+        const char* sb = sa + A_TILE;
         short8v af[FM], bf[FN];
 #pragma unroll
         for (int i = 0; i < FM; ++i)
@@ -370,9 +372,10 @@ __global__ __launch_bounds__(GWM * GWN * 64, 2) void gemm_mfma_gather_kernel(Pro
     }
 }
 
-template <typename T, int MODE>
+template <typename T, int MODE, int GBM>
 hipError_t launch_gather_mode(const Problem& p, hipStream_t stream) {
-    auto kern = gemm_mfma_gather_kernel<T, MODE>;
+    constexpr int LDS_BYTES = 2 * (GBM + GBN) * GBK * 2;
+    auto kern = gemm_mfma_gather_kernel<T, MODE, GBM>;
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
@@ -390,14 +393,14 @@ hipError_t launch_gather_mode(const Problem& p, hipStream_t stream) {
     tm.xcds = ds.xcds;
     Problem pa = p;
     void* args[] = {&pa, &tm};
-    return hipLaunchKernel((const void*)kern, dim3((unsigned)total), dim3(GWM * GWN * 64), args, 2 * G_STAGE, stream);
+    return hipLaunchKernel((const void*)kern, dim3((unsigned)total), dim3(GWM * GWN * 64), args, LDS_BYTES, stream);
 }
 
-template <typename T>
+template <typename T, int GBM>
 hipError_t launch_gather_type(const Problem& p, hipStream_t stream) {
-    if (p.is_conv) return launch_gather_mode<T, MODE_CONV>(p, stream);
-    if (p.trans_b) return launch_gather_mode<T, MODE_TRANS_B>(p, stream);
-    return launch_gather_mode<T, MODE_DENSE>(p, stream);
+    if (p.is_conv) return launch_gather_mode<T, MODE_CONV, GBM>(p, stream);
+    if (p.trans_b) return launch_gather_mode<T, MODE_TRANS_B, GBM>(p, stream);
+    return launch_gather_mode<T, MODE_DENSE, GBM>(p, stream);
 }
 
 }  // namespace
@@ -426,9 +429,16 @@ bool mfma_gather_supported(const Problem& p) {
     return a_elems >= 8 && b_elems >= 8;
 }
 
+// Up to one round of 128 x 128 tiles on the 256 compute units the 64-row tile wins, because a workgroup alone on its unit is
+// bound by latency: 8 x 44 x 44 x 127 -> 512, 3 x 3, stride 2 (112 tiles) 33.4 -> 25.4 us, 577 x 1021 x 4096 (40) 49.9 -> 35.0,
+// 1000 x 3001 x 1024 (192) 22.9 -> 22.1; beyond it two of the larger ones share a unit.
 hipError_t launch_mfma_gather(const Problem& p, hipStream_t stream, const char** name) {
+    if ((long long)((p.M + 127) / 128) * ((p.N + GBN - 1) / GBN) * p.batch <= 256) {
+        *name = "mfma16_gather_64x128x32_w2x2";
+        return p.in_dtype == DT_BF16 ? launch_gather_type<bf16_t, 64>(p, stream) : launch_gather_type<f16_t, 64>(p, stream);
+    }
     *name = "mfma16_gather_128x128x32_w2x2";
-    return p.in_dtype == DT_BF16 ? launch_gather_type<bf16_t>(p, stream) : launch_gather_type<f16_t>(p, stream);
+    return p.in_dtype == DT_BF16 ? launch_gather_type<bf16_t, 128>(p, stream) : launch_gather_type<f16_t, 128>(p, stream);
 }
 
 }  // namespace pbk
