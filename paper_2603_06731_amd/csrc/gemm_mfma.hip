@@ -54,6 +54,14 @@ bool mfma_preferred(const Problem& p) {
     return p.M >= 128 && p.N >= 128 && t >= 64;
 }
 
+// 128 x 128 tiles: with at most one per compute unit (256), the four-stage ring (three k-tiles in flight) covers the memory latency
+// that two workgroups per unit hide from each other otherwise: bf16 2048 x 2048 x 4096 36.2 against 52.2 us, 577 x 4096 x 1024
+// 11.7 against 16.0, FP8 512 x 4096 x 4096 16.1 against 27.5.  Beyond one round two workgroups share a unit (4 x 32 x 28 x 28
+// rows of a transposed convolution, 784 tiles: 52.8 against 79.2 us).
+static int square_config(const Problem& p) {
+    return (long long)((p.M + 127) / 128) * ((p.N + 127) / 128) * p.batch <= 256 ? 2 : 1;
+}
+
 // 16-bit operands.  Configurations 5-7 use the 16x16x32 MFMA blocks (measured against their
 // 32x32x16 twins 3, 0: 8192^3 786 against 816 us, 3x3 convolution 144 against 151 us, the
 // store-bound attention-score product equal); 7 also stages A 64 deep (762 us).
@@ -66,7 +74,7 @@ static int choose_config(const Problem& p) {
         // (9: both operands staged 64 deep, one barrier per pair of k-tiles: 715 against 800 us on 8192^3,
         // 5-7 % ahead of 5 from K = 1024 up and down to 4096^2 outputs)
         if (p.M >= 256 && p.N >= 256 && t256 >= 128) return 9;
-        return 1;
+        return square_config(p);
     }
     // Long contractions over many tiles: one 256x256x32 workgroup per CU with a 4-stage ring.
     // Short contractions (store-dominated) and convolutions: two 128x256 workgroups per CU, whose
@@ -84,7 +92,7 @@ static int choose_config(const Problem& p) {
     if (p.is_conv && !p.conv.transposed && p.conv.Cin % 64 == 0 && p.M >= 256 && p.N >= 256 && t256 >= 256 && p.K >= 1024)
         return 9;
     if (p.M >= 128 && p.N >= 256 && t >= 256) return 6;
-    return 1;
+    return square_config(p);
 }
 
 // 16-bit types: the translation unit (group) that holds a configuration
@@ -119,25 +127,25 @@ hipError_t launch_mfma(const Problem& p, hipStream_t stream, int force_cfg, cons
         long long t256 = (long long)((p.M + 255) / 256) * ((p.N + 255) / 256) * p.batch;
         // (with both operands k-major the 16x16x64 blocks: 0.54 against 0.59 ms on 8192^3)
         const bool kmajor = p.trans_b && !p.is_conv;
-        int c = (force_cfg == 0 || force_cfg == 1 || force_cfg == 4 || force_cfg == 8 || force_cfg == 9) ? force_cfg
-                : (p.M >= 256 && p.N >= 256 && t256 >= 128) ? (kmajor ? 9 : 4) : 1;
+        int c = (force_cfg == 0 || force_cfg == 1 || force_cfg == 2 || force_cfg == 4 || force_cfg == 8 || force_cfg == 9) ? force_cfg
+                : (p.M >= 256 && p.N >= 256 && t256 >= 128) ? (kmajor ? 9 : 4) : square_config(p);
         if ((c == 8 || c == 9) && !kmajor) c = 4;       // the 16x16 blocks are built for k-major operands only
         *name = kMfmaConfigs[c].name;
         const int gm = group_m_override() > 0 ? group_m_override() : 8;
         return launch_mfma_int8(p, stream, c, gm);
     }
     int cfg = (force_cfg >= 0 && force_cfg < kNumMfmaConfigs) ? force_cfg : choose_config(p);
-    if (p.is_conv && p.conv.transposed && cfg != 0 && cfg != 1 && cfg != 6) cfg = choose_config(p);   // the ones built
-    if (!fp8 && ((cfg >= 2 && cfg <= 4) || cfg == 8)) cfg = choose_config(p);   // 16-bit types: 0, 1, 5, 6, 7, 9 are built
+    if (p.is_conv && p.conv.transposed && cfg != 0 && cfg != 1 && cfg != 2 && cfg != 6) cfg = choose_config(p);   // the ones built
+    if (!fp8 && (cfg == 3 || cfg == 4 || cfg == 8)) cfg = choose_config(p);   // 16-bit types: 0, 1, 2, 5, 6, 7, 9 are built
     // 9 takes a convolution whose channel count is a multiple of 64 (not the transposed form)
     if (cfg == 9 && p.is_conv && (p.conv.transposed || p.conv.Cin % 64 != 0)) cfg = 7;
     if (fp8) {
         // the FP8 instruction consumes a 64-deep k-tile (in 2-byte units) in two steps:
         // only the 64-deep configurations are built for it
         const bool kmajor = p.trans_b && !p.is_conv;
-        if (force_cfg != 1 && force_cfg != 4 && !(force_cfg == 9 && kmajor)) {       // (also a forced 5-8)
+        if (force_cfg != 1 && force_cfg != 2 && force_cfg != 4 && !(force_cfg == 9 && kmajor)) {       // (also a forced 5-8)
             long long t256 = (long long)((p.M + 255) / 256) * ((p.N + 255) / 256) * p.batch;
-            cfg = (p.M >= 256 && p.N >= 256 && t256 >= 128) ? (kmajor ? 9 : 4) : 1;
+            cfg = (p.M >= 256 && p.N >= 256 && t256 >= 128) ? (kmajor ? 9 : 4) : square_config(p);
         } else {
             cfg = force_cfg;
         }

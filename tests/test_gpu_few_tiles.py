@@ -13,6 +13,50 @@ BF16, F16, F32, E4M3 = wl.DTYPE_BF16, wl.DTYPE_F16, wl.DTYPE_F32, wl.DTYPE_FP8_E
 # one rounding to the output type; fp32 output: sums of K products in another order
 TOL = {BF16: T.TIGHT[BF16], F16: T.TIGHT[F16], F32: T.TIGHT[F32]}
 
+SHAPES = [  # batch, M, N, K, padding of the rows
+    (1, 1, 8, 8, 0),            # one piece of everything
+    (1, 5, 72, 40, 0),          # k32 steps with a ragged second one, columns beyond the tile
+    (2, 16, 136, 1024, 8),      # one chunk per wave; views with NaN behind the rows
+    (1, 9, 200, 1096, 8),       # waves with unequal shares, a last chunk of one short step
+    (3, 33, 64, 392, 0),        # rounds of 128 with a ragged last one, a second row tile with one row
+    (1, 130, 264, 640, 8),      # more rounds than stages
+]
+
+
+@pytest.mark.parametrize("trans_b", [0, 1])
+@pytest.mark.parametrize("dtype,out_dtype,epi", [(BF16, BF16, C.EPI_BIAS_GELU_TANH), (F16, F16, C.EPI_BIAS_RELU), (BF16, F32, C.EPI_NONE)])
+@pytest.mark.parametrize("force", ["mfma:2"])
+def test_matmul(force, dtype, out_dtype, epi, trans_b):
+    for batch, M, N, K, pad in SHAPES:
+        err, kern = run_case(batch, M, N, K, dtype, out_dtype, trans_b, epi, pad_ld=pad, force=force,
+                             bias_on=epi != C.EPI_NONE)
+        assert force.split(":")[0].replace("mfma", "128x128x64_w2x2_s4") in kern
+        assert err <= TOL[out_dtype], (batch, M, N, K, err)
+
+
+CONVS = [  # n, H, W, Cin, Cout, KH, KW, stride, pad, dil
+    (1, 7, 7, 64, 40, 3, 3, (1, 1), (1, 1), (1, 1)),
+    (3, 9, 11, 96, 72, 3, 2, (2, 1), (1, 0), (1, 2)),      # rounds that span taps, dilation
+    (2, 6, 5, 8, 64, 1, 5, (1, 2), (0, 2), (1, 1)),        # eight channels: a round holds sixteen taps
+    (1, 13, 10, 256, 128, 3, 3, (1, 1), (1, 1), (1, 1)),
+]
+
+
+@pytest.mark.parametrize("force", ["mfma:2"])
+@pytest.mark.parametrize("dtype", [BF16, F16])
+@pytest.mark.parametrize("case", CONVS)
+def test_conv(case, dtype, force):
+    n, H, W, Cin, Cout, KH, KW, stride, pad, dil = case
+    w = wl.Workload("few_tiles_conv", "conv", dtype, dtype, C.EPI_BIAS_RELU, n=n, H=H, W=W, Cin=Cin, Cout=Cout, KH=KH, KW=KW,
+                    stride=stride, pad=pad, dil=dil, dist_b=("normal", float(np.sqrt(2.0 / (KH * KW * Cin)))))
+    host = wl.make_inputs(w)
+    with T.forced_kernel(force):
+        st, out = T.run_workload(w, T.upload(host))
+    assert st == 0
+    ref, pre = T.oracle_full(w, host)
+    err = T.rel_err(T.to_host_f64(out, w.out_dtype).reshape(ref.shape), ref, pre)
+    assert err <= TOL[dtype], err
+
 
 @pytest.mark.parametrize("trans_b", [0, 1])
 @pytest.mark.parametrize("M,N,K,tile", [(2100, 2049, 37, "128x128"), (2048, 2048, 37, "64x128"), (65, 131, 301, "64x128")])
