@@ -31,7 +31,7 @@ bool aligned(const void* p, int64_t a) { return (reinterpret_cast<uintptr_t>(p) 
 // configuration) or "gather" (the matrix-unit kernel that stages through registers).  The environment variables PBK_FORCE_KERNEL and PBK_GROUP_M are read ONCE,
 // at the first call of the process; pbk_force_kernel() overrides the former per thread.
 // force: 0 automatic, 1 generic, 2 mfma, 3 the gathering mfma kernel, 4 the small fp32 kernel, 5 "bstat" (the
-// B-stationary kernel for short contractions); cfg: -1 or id
+// B-stationary kernel for short contractions), 6 "ksplit[:<id>]" (a few rows), 7 "tile64[:<id>]" (64-wide tiles); cfg: -1 or id
 struct Choice { int force; int cfg; };
 
 bool parse_choice(const char* e, Choice* c) {
@@ -42,6 +42,10 @@ bool parse_choice(const char* e, Choice* c) {
     if (!std::strcmp(e, "gather")) { c->force = 3; return true; }
     if (!std::strcmp(e, "small")) { c->force = 4; return true; }
     if (!std::strcmp(e, "bstat")) { c->force = 5; return true; }
+    if (!std::strcmp(e, "tile64")) { c->force = 7; return true; }
+    if (!std::strncmp(e, "tile64:", 7) && e[7] >= '0' && e[7] <= '9') { c->force = 7; c->cfg = std::atoi(e + 7); return true; }
+    if (!std::strcmp(e, "ksplit")) { c->force = 6; return true; }
+    if (!std::strncmp(e, "ksplit:", 7) && e[7] >= '0' && e[7] <= '9') { c->force = 6; c->cfg = std::atoi(e + 7); return true; }
     if (!std::strncmp(e, "mfma:", 5) && e[5] >= '0' && e[5] <= '9') { c->force = 2; c->cfg = std::atoi(e + 5); return true; }
     return false;
 }
@@ -92,11 +96,17 @@ pbk_status dispatch(const pbk::Problem& p_in, hipStream_t stream) {
     const bool can_small = pbk::small_f32_supported(p);
     // short contractions over many rows: the B-stationary kernel
     const bool can_bstat = pbk::mfma_bstat_supported(p);
+    // a few rows, or too few 128-wide tiles for the chip: the contraction is split over the waves of a workgroup
+    const bool can_ksplit = pbk::mfma_ksplit_supported(p), can_tile64 = pbk::mfma_tile64_supported(p);
     if ((force == 2 && !can_mfma && !can_gather) || (force == 3 && !can_gather) || (force == 4 && !can_small) ||
-        (force == 5 && !can_bstat))
+        (force == 5 && !can_bstat) || (force == 6 && !can_ksplit) || (force == 7 && !can_tile64))
         return PBK_ERR_UNSUPPORTED;
     if (force == 5 || (force == 0 && can_bstat && pbk::mfma_bstat_preferred(p)))
         e = pbk::launch_mfma_bstat(p, stream, &name);
+    else if (force == 6 || (force == 0 && can_ksplit && pbk::mfma_ksplit_preferred(p)))
+        e = pbk::launch_mfma_ksplit(p, stream, cfg, &name);
+    else if (force == 7 || (force == 0 && can_tile64 && pbk::mfma_tile64_preferred(p)))
+        e = pbk::launch_mfma_tile64(p, stream, cfg, &name);
     else if (force == 4 || (force == 0 && can_small && pbk::small_f32_preferred(p) && !(can_mfma && pbk::mfma_preferred(p))))
         e = pbk::launch_small_f32(p, stream, &name);
     else if (can_mfma && force != 1 && force != 3 && (force == 2 || pbk::mfma_preferred(p)))

@@ -100,6 +100,15 @@ bool mfma_bstat_supported(const Problem& p);
 bool mfma_bstat_preferred(const Problem& p);
 hipError_t launch_mfma_bstat(const Problem& p, hipStream_t stream, const char** name);
 
+// Few rows, or too few 128-wide tiles for the chip: the contraction is split over the waves of a workgroup.
+// ksplit: operands straight into registers, each wave on its own; tile64: 64-wide tiles staged in LDS by all waves.
+bool mfma_ksplit_supported(const Problem& p);
+bool mfma_ksplit_preferred(const Problem& p);
+hipError_t launch_mfma_ksplit(const Problem& p, hipStream_t stream, int force_cfg, const char** name);
+bool mfma_tile64_supported(const Problem& p);
+bool mfma_tile64_preferred(const Problem& p);
+hipError_t launch_mfma_tile64(const Problem& p, hipStream_t stream, int force_cfg, const char** name);
+
 // PBK_GROUP_M of the environment as read at the process's first call (0 = not set): tile rows
 // per group of the block mapping, a benchmarking override.
 int group_m_override();

@@ -1,4 +1,5 @@
-"""Matrix-unit kernels for problems with few tiles, against the oracle."""
+"""Matrix-unit kernels for problems with few rows or few tiles: the split of k over the waves of a workgroup (16 rows,
+64-wide tiles) and the four-stage ring of the 128 x 128 tile, against the oracle."""
 import numpy as np
 import pytest
 
@@ -25,7 +26,7 @@ SHAPES = [  # batch, M, N, K, padding of the rows
 
 @pytest.mark.parametrize("trans_b", [0, 1])
 @pytest.mark.parametrize("dtype,out_dtype,epi", [(BF16, BF16, C.EPI_BIAS_GELU_TANH), (F16, F16, C.EPI_BIAS_RELU), (BF16, F32, C.EPI_NONE)])
-@pytest.mark.parametrize("force", ["mfma:2"])
+@pytest.mark.parametrize("force", ["ksplit:0", "ksplit:1", "tile64:0", "tile64:1", "tile64:2", "mfma:2"])
 def test_matmul(force, dtype, out_dtype, epi, trans_b):
     for batch, M, N, K, pad in SHAPES:
         err, kern = run_case(batch, M, N, K, dtype, out_dtype, trans_b, epi, pad_ld=pad, force=force,
@@ -42,7 +43,7 @@ CONVS = [  # n, H, W, Cin, Cout, KH, KW, stride, pad, dil
 ]
 
 
-@pytest.mark.parametrize("force", ["mfma:2"])
+@pytest.mark.parametrize("force", ["tile64:0", "tile64:1", "tile64:2", "mfma:2"])
 @pytest.mark.parametrize("dtype", [BF16, F16])
 @pytest.mark.parametrize("case", CONVS)
 def test_conv(case, dtype, force):
@@ -58,6 +59,18 @@ def test_conv(case, dtype, force):
     assert err <= TOL[dtype], err
 
 
+@pytest.mark.parametrize("M,N,K,trans_b,kernel", [
+    (16, 512, 512, 0, "ksplit"), (17, 512, 512, 0, "tile64_32x64"), (8, 8192, 512, 1, "tile64_32x64"), (8, 4096, 512, 1, "ksplit"),
+    (16, 4098, 512, 0, "ksplit_16x32"), (3, 8196, 512, 0, "ksplit_16x64"), (3, 8197, 512, 0, "gather"), (16, 512, 504, 0, "tile64"), (256, 4096, 512, 0, "tile64_64x64_s4"), (1024, 2048, 512, 0, "tile64_64x64_s2"),
+    (1152, 2048, 512, 0, "128x128x64_w2x2_s4"), (512, 512, 120, 0, "128x128x64_w2x2_s4"),
+])
+def test_dispatch(M, N, K, trans_b, kernel):
+    """Either side of each line of the rule, with the automatic choice."""
+    err, kern = run_case(1, M, N, K, BF16, BF16, trans_b, C.EPI_BIAS, force=None)
+    assert kernel in kern, kern
+    assert err <= TOL[BF16], err
+
+
 @pytest.mark.parametrize("trans_b", [0, 1])
 @pytest.mark.parametrize("M,N,K,tile", [(2100, 2049, 37, "128x128"), (2048, 2048, 37, "64x128"), (65, 131, 301, "64x128")])
 def test_gather_tiles(M, N, K, tile, trans_b):
@@ -65,3 +78,23 @@ def test_gather_tiles(M, N, K, tile, trans_b):
     err, kern = run_case(1, M, N, K, BF16, BF16, trans_b, C.EPI_BIAS, pad_ld=1, force="gather")
     assert tile in kern, kern
     assert err <= TOL[BF16], err
+
+
+@pytest.mark.parametrize("force", ["ksplit", "tile64"])
+def test_residual(force):
+    """The shortcut operand, with its own leading dimension, and columns that are stored one at a time."""
+    import torch
+    import paper_2603_06731_amd as pbk
+    M, N, K, ldr, ldc = 13, 45, 72, 53, 47
+    g = torch.Generator().manual_seed(7)
+    A, B = torch.randn(M, K, generator=g).bfloat16(), (torch.randn(N, K, generator=g) / K ** 0.5).bfloat16()
+    R = torch.randn(M, ldr, generator=g).bfloat16()
+    out = torch.zeros(M, ldc, dtype=torch.bfloat16, device="cuda")
+    with T.forced_kernel(force):
+        st = pbk.pbk_matmul_residual(A.cuda(), B.cuda(), out, None, R.cuda(), M, N, K, K, K, ldc, ldr, BF16, BF16, 1, 0.5, 2.0, C.EPI_RELU)
+    assert st == 0 and force in pbk.pbk_last_kernel()
+    ref = torch.relu(0.5 * (A.double() @ B.double().T) + 2.0 * R[:, :N].double())
+    got = out.cpu().double()
+    assert torch.all(got[:, N:] == 0)
+    # one rounding to bf16 (2^-9 of the value), fp32 sums of 72 terms of order one
+    assert torch.all((got[:, :N] - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-5)
