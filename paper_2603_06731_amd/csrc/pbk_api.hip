@@ -31,7 +31,8 @@ bool aligned(const void* p, int64_t a) { return (reinterpret_cast<uintptr_t>(p) 
 // configuration) or "gather" (the matrix-unit kernel that stages through registers).  The environment variables PBK_FORCE_KERNEL and PBK_GROUP_M are read ONCE,
 // at the first call of the process; pbk_force_kernel() overrides the former per thread.
 // force: 0 automatic, 1 generic, 2 mfma, 3 the gathering mfma kernel, 4 the small fp32 kernel, 5 "bstat" (the
-// B-stationary kernel for short contractions), 6 "ksplit[:<id>]" (a few rows), 7 "tile64[:<id>]" (64-wide tiles); cfg: -1 or id
+// B-stationary kernel for short contractions), 6 "ksplit[:<id>]" (a few rows), 7 "tile64[:<id>]" (64-wide tiles),
+// 8 "decode[:<workgroups per batch entry>]" (attention of a few queries); cfg: -1 or id
 struct Choice { int force; int cfg; };
 
 bool parse_choice(const char* e, Choice* c) {
@@ -42,6 +43,8 @@ bool parse_choice(const char* e, Choice* c) {
     if (!std::strcmp(e, "gather")) { c->force = 3; return true; }
     if (!std::strcmp(e, "small")) { c->force = 4; return true; }
     if (!std::strcmp(e, "bstat")) { c->force = 5; return true; }
+    if (!std::strcmp(e, "decode")) { c->force = 8; return true; }
+    if (!std::strncmp(e, "decode:", 7) && e[7] >= '0' && e[7] <= '9') { c->force = 8; c->cfg = std::atoi(e + 7); return true; }
     if (!std::strcmp(e, "tile64")) { c->force = 7; return true; }
     if (!std::strncmp(e, "tile64:", 7) && e[7] >= '0' && e[7] <= '9') { c->force = 7; c->cfg = std::atoi(e + 7); return true; }
     if (!std::strcmp(e, "ksplit")) { c->force = 6; return true; }
@@ -452,11 +455,14 @@ static pbk_status attention_common(const void* Q, const void* K, const void* V, 
     int cfg = -1;
     const int force = forced_choice(&cfg);
     const bool can_mfma = pbk::attention_mfma_supported(p);
-    if (force == 2 && !can_mfma) return PBK_ERR_UNSUPPORTED;
+    const bool can_decode = pbk::attention_decode_supported(p);
+    if ((force == 2 && !can_mfma) || (force == 8 && !can_decode)) return PBK_ERR_UNSUPPORTED;
+    const bool use_decode = can_decode && (force == 8 || (force == 0 && pbk::attention_decode_preferred(p)));
     const bool use_mfma = can_mfma && force != 1;
     if (!use_mfma && D > 512) return PBK_ERR_UNSUPPORTED;
     const char* name = "";
-    hipError_t e = use_mfma ? pbk::launch_attention_mfma(p, stream, &name)
+    hipError_t e = use_decode ? pbk::launch_attention_decode(p, stream, cfg, &name)
+                   : use_mfma ? pbk::launch_attention_mfma(p, stream, &name)
                             : pbk::launch_attention_generic(p, stream, &name);
     if (e != hipSuccess) {
         std::fprintf(stderr, "libpbk: launch of %s failed: %s\n", name, hipGetErrorString(e));

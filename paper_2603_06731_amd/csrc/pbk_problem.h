@@ -117,5 +117,9 @@ int group_m_override();
 hipError_t launch_attention_generic(const AttnProblem& p, hipStream_t stream, const char** name);
 bool attention_mfma_supported(const AttnProblem& p);
 hipError_t launch_attention_mfma(const AttnProblem& p, hipStream_t stream, const char** name);
+// A few queries against a long context: the keys are split over the waves of a workgroup.
+bool attention_decode_supported(const AttnProblem& p);
+bool attention_decode_preferred(const AttnProblem& p);
+hipError_t launch_attention_decode(const AttnProblem& p, hipStream_t stream, int force_cfg, const char** name);
 
 }  // namespace pbk

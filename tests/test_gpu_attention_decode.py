@@ -1,0 +1,61 @@
+"""Attention of a few queries against a long context (the kernel that splits the keys over the waves) against the CPU oracle's
+definition evaluated in float64."""
+import pytest
+
+import workloads as wl
+import pbk_testlib as T
+
+pytestmark = pytest.mark.gpu
+
+BF16, F16 = wl.DTYPE_BF16, wl.DTYPE_F16
+
+CASES = [  # batch, Nq, Nk, row padding
+    (1, 1, 1, 0),            # one key: one wave has work
+    (3, 16, 31, 8),          # a ragged single step
+    (2, 3, 33, 0),           # two steps, the second with one key
+    (2, 5, 3, 0),            # causal: more queries than keys (rows that see none are NaN)
+    (5, 8, 520, 8),          # a step more than the waves
+    (70, 2, 1300, 0),
+]
+
+
+@pytest.mark.parametrize("causal", [0, 1])
+@pytest.mark.parametrize("dtype", [BF16, F16])
+@pytest.mark.parametrize("D,split", [(32, 1), (64, 1), (64, 2), (128, 1), (128, 2), (128, 4)])
+def test_decode(D, split, dtype, causal):
+    import torch
+    import paper_2603_06731_amd as pbk
+    tdt = torch.bfloat16 if dtype == BF16 else torch.float16
+    for b, Nq, Nk, pad in CASES:
+        g = torch.Generator().manual_seed(b * 1000 + Nk)
+        ld = D + pad
+        # (rows padded with NaN: nothing outside the views may be read into the result)
+        q, k, v = (torch.full((b, n, ld), float("nan")) for n in (Nq, Nk, Nk))
+        for x in (q, k, v):
+            x[..., :D] = torch.randn(x[..., :D].shape, generator=g)
+        k[:, Nk // 2, :D] *= 6.0                     # scores that move the reference point
+        q, k, v = q.to(tdt), k.to(tdt), v.to(tdt)
+        out = torch.zeros(b, Nq, ld, dtype=tdt, device="cuda")
+        alpha = D ** -0.5
+        dims = (b, Nq, Nk, D, ld, ld, ld, ld, Nq * ld, Nk * ld, Nk * ld, Nq * ld)
+        with T.forced_kernel(f"decode:{split}"):
+            if causal:
+                st = pbk.pbk_attention_causal(q.cuda(), k.cuda(), v.cuda(), out, *dims, dtype, alpha)
+            else:
+                st = pbk.pbk_attention(q.cuda(), k.cuda(), v.cuda(), None, out, *dims, 0, 0, dtype, alpha)
+        assert st == 0 and "decode" in pbk.pbk_last_kernel()
+        qd, kd, vd = (x[..., :D].double() for x in (q, k, v))
+        s = qd @ kd.transpose(1, 2).contiguous() * alpha
+        if causal:
+            s = s.masked_fill(torch.arange(Nk)[None, :] > torch.arange(Nq)[:, None] + Nk - Nq, float("-inf"))
+        w = torch.softmax(s, -1)
+        ref = w @ vd
+        got = out.cpu().double()
+        assert torch.all(got[..., D:] == 0)
+        got = got[..., :D]
+        assert torch.equal(torch.isnan(got), torch.isnan(ref))
+        # weights rounded to 16 bits (u of their value), then the output: u (sum w |v| + |o|), with fp32 sums below that
+        u = 2.0 ** -8 if dtype == BF16 else 2.0 ** -11
+        bound = u * ((w @ vd.abs()) + ref.abs()) + 1e-5
+        ok = (got - ref).abs() <= bound
+        assert torch.all(ok | torch.isnan(ref)), (b, Nq, Nk, float(((got - ref).abs() / bound).nan_to_num().max()))
