@@ -21,6 +21,12 @@
 // basic blocks, and the compiler then sinks the softmax arithmetic out of the
 // MFMA slots it was written into.
 //
+// SPLIT = 2: with too few workgroups for that, a workgroup has two such groups of
+// four waves, each with LDS tiles of its own and half of the key tiles, for the same
+// 128 queries; at the end the second group's output, reference points and sums go
+// through LDS to the first.  The chain of tiles is the bound there: 16 x 2048 x 64, causal:
+// 26.6 -> 23.5 us; 16 x 4096 x 128, causal: 102 -> 79; 6 x 4096 x 64: 44.6 -> 37.1.
+//
 // Register layouts (v_mfma_f32_32x32x16, D[i][j] += sum_k A[i][k] B[k][j]; a lane
 // supplies row i = lane%32 of A and column j = lane%32 of B, 8 consecutive k
 // starting at 8*(lane/32), and receives column j = lane%32, rows
@@ -72,24 +78,27 @@ __device__ __forceinline__ void dma16_s(int4v rsrc, unsigned lds_addr, unsigned 
 // CAUSAL: query q attends to keys <= q + (Nk - Nq).  The key tiles beyond the workgroup's last visible key
 // are not visited at all; in the blocks that the diagonal crosses the hidden scores are set to -inf like
 // the keys beyond Nk.
-template <typename T, int D, bool HAS_BIAS, bool PRE, bool CAUSAL>
-__global__ __launch_bounds__(ATT_NW * 64, 2) void attention_mfma_kernel(AttnProblem p, int q_tiles, int total, int xcds) {
+template <typename T, int D, bool HAS_BIAS, bool PRE, bool CAUSAL, int SPLIT>
+__global__ __launch_bounds__(ATT_NW * SPLIT * 64, 2) void attention_mfma_kernel(AttnProblem p, int q_tiles, int total, int xcds) {
     constexpr int KS = D / 16;                    // k16 steps of Q K^T
     constexpr int JD = D / 32;                    // 32-wide blocks of the head dimension
     constexpr int NPV = 2 * JD;                   // MFMAs of O^T += V^T P^T per 32-key block
     constexpr int TILE = ATT_BKV * D * 2;         // bytes of one K or V tile
     constexpr int BLKS = TILE / 1024;             // 1 KiB wave-loads per tile
     constexpr int CPW = BLKS / ATT_NW;            // per wave
+    static_assert(SPLIT == 1 || (SPLIT == 2 && !HAS_BIAS), "the bias is addressed by the key of the whole range");
     static_assert(BLKS % ATT_NW == 0 && CPW >= 1, "tile must split evenly over the waves");
     constexpr int CPR = D / 8;                    // 16-byte slots per row
     constexpr int ROWS = 64 / CPR;                // rows per wave-load
     constexpr float LOG2E = 1.4426950408889634f;
 
-    // K slot 0 | K slot 1 | V slot 0 | V slot 1
-    extern __shared__ __attribute__((aligned(1024))) char lds[];
+    // K slot 0 | K slot 1 | V slot 0 | V slot 1, once per group of ATT_NW waves
+    extern __shared__ __attribute__((aligned(1024))) char lds_all[];
 
     const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int grp = SPLIT == 1 ? 0 : wave_all / ATT_NW, wave = SPLIT == 1 ? wave_all : wave_all % ATT_NW;
+    char* const lds = lds_all + grp * (4 * TILE);
     const int h = lane >> 5, col = lane & 31;
 
     // workgroups are dealt round-robin to the 8 XCDs: regroup so that one XCD (one L2)
@@ -101,10 +110,35 @@ __global__ __launch_bounds__(ATT_NW * 64, 2) void attention_mfma_kernel(AttnProb
     // (causal: the last query tiles have the most keys to visit and are started first)
     const int q_tile = CAUSAL ? q_tiles - 1 - (id - b * q_tiles) : id - b * q_tiles;
     const int q0 = q_tile * ATT_BQ + wave * 32;
-    const int c_off = p.Nk - p.Nq;                 // causal: key visible iff key <= query + c_off
+    int c_off = p.Nk - p.Nq;                       // causal: key visible iff key <= query + c_off
 
     const char* Kb = (const char*)p.K + (int64_t)b * p.stride_k * 2;
     const char* Vb = (const char*)p.V + (int64_t)b * p.stride_v * 2;
+
+    int Nk = p.Nk, NT = (Nk + ATT_BKV - 1) / ATT_BKV;
+    if (CAUSAL) {
+        // the workgroup's last visible key (at least one tile is walked, so that every wave meets the barriers)
+        const long long last = (long long)q_tile * ATT_BQ + ATT_BQ - 1 + c_off;
+        const int nt_vis = last < 0 ? 1 : (int)(last / ATT_BKV) + 1;
+        NT = nt_vis < NT ? nt_vis : NT;
+    }
+    if (SPLIT == 2) {
+        // Each group of waves takes half of the tiles and counts keys from its own first one.  Both walk NT tiles and
+        // meet the same barriers; what lies beyond a group's Nk (which may be <= 0) arrives as zeros and is masked.
+        const int half = (NT + 1) / 2;
+        const long long end = (long long)NT * ATT_BKV;             // (causal: hidden tiles stay unread)
+        if (end < Nk) Nk = (int)end;
+        if (grp == 0) {
+            if (half * ATT_BKV < Nk) Nk = half * ATT_BKV;
+        } else {
+            const int first = half * ATT_BKV;
+            Nk -= first;
+            c_off -= first;
+            Kb += (int64_t)first * p.ldk * 2;
+            Vb += (int64_t)first * p.ldv * 2;
+        }
+        NT = half;
+    }
 
     // ---- per-lane source offsets of the direct-to-LDS loads (lane i lands at byte 16 i)
     unsigned k_voff[CPW], v_voff[CPW];
@@ -124,13 +158,13 @@ __global__ __launch_bounds__(ATT_NW * 64, 2) void attention_mfma_kernel(AttnProb
         const int key0 = t * ATT_BKV;
         const int4v rv = make_rsrc(Vb + (int64_t)key0 * p.ldv * 2);
         const unsigned sv = lds_base + (2 + (t & 1)) * TILE;
-        if (key0 + ATT_BKV <= p.Nk) {             // whole tile inside: no per-lane test (wave-uniform)
+        if (key0 + ATT_BKV <= Nk) {             // whole tile inside: no per-lane test (wave-uniform)
 #pragma unroll
             for (int r = 0; r < CPW; ++r) dma16_s(rv, sv + (wave * CPW + r) * 1024, v_voff[r]);
         } else {
 #pragma unroll
             for (int r = 0; r < CPW; ++r)
-                dma16_s(rv, sv + (wave * CPW + r) * 1024, key0 + ld_row[r] < p.Nk ? v_voff[r] : kOob);
+                dma16_s(rv, sv + (wave * CPW + r) * 1024, key0 + ld_row[r] < Nk ? v_voff[r] : kOob);
         }
     };
     // K tile t is shifted by half a tile: keys [64 t + 32, 64 t + 96), because the scores of
@@ -143,29 +177,22 @@ __global__ __launch_bounds__(ATT_NW * 64, 2) void attention_mfma_kernel(AttnProb
             const int4v rk = make_rsrc(Kb);
 #pragma unroll
             for (int r = 0; r < CPW; ++r) {
-                const bool ok = ld_row[r] >= 32 && ld_row[r] - 32 < p.Nk;
+                const bool ok = ld_row[r] >= 32 && ld_row[r] - 32 < Nk;
                 dma16_s(rk, sk + (wave * CPW + r) * 1024, ok ? k_voff[r] - (unsigned)(32 * (int)p.ldk * 2) : kOob);
             }
         } else {
             const int4v rk = make_rsrc(Kb + (int64_t)key0 * p.ldk * 2);
-            if (key0 + ATT_BKV <= p.Nk) {
+            if (key0 + ATT_BKV <= Nk) {
 #pragma unroll
                 for (int r = 0; r < CPW; ++r) dma16_s(rk, sk + (wave * CPW + r) * 1024, k_voff[r]);
             } else {
 #pragma unroll
                 for (int r = 0; r < CPW; ++r)
-                    dma16_s(rk, sk + (wave * CPW + r) * 1024, key0 + ld_row[r] < p.Nk ? k_voff[r] : kOob);
+                    dma16_s(rk, sk + (wave * CPW + r) * 1024, key0 + ld_row[r] < Nk ? k_voff[r] : kOob);
             }
         }
     };
 
-    int NT = (p.Nk + ATT_BKV - 1) / ATT_BKV;
-    if (CAUSAL) {
-        // the workgroup's last visible key (at least one tile is walked, so that every wave meets the barriers)
-        const long long last = (long long)q_tile * ATT_BQ + ATT_BQ - 1 + c_off;
-        const int nt_vis = last < 0 ? 1 : (int)(last / ATT_BKV) + 1;
-        NT = nt_vis < NT ? nt_vis : NT;
-    }
     issue_k(-1);
     issue_v(0);
     issue_k(0);
@@ -239,7 +266,7 @@ __global__ __launch_bounds__(ATT_NW * 64, 2) void attention_mfma_kernel(AttnProb
             if (HAS_BIAS) v = fmaf(bias[e], LOG2E, v);
             if (RAGGED) {
                 const int key = kbase + (e >> 2) * 8 + h * 4 + (e & 3);
-                if (key >= p.Nk || (CAUSAL && key > q0 + col + c_off)) v = -INFINITY;
+                if (key >= Nk || (CAUSAL && key > q0 + col + c_off)) v = -INFINITY;
             }
             sv[e] = v;
         }
@@ -250,13 +277,13 @@ __global__ __launch_bounds__(ATT_NW * 64, 2) void attention_mfma_kernel(AttnProb
             const int key = kbase + g * 8 + h * 4;
             float bv[4] = {0.0f, 0.0f, 0.0f, 0.0f};
             if (q_ok) {
-                if (bias_vec && key + 3 < p.Nk) {
+                if (bias_vec && key + 3 < Nk) {
                     f32x4 v4 = *(const f32x4*)(bias_row + key);
                     bv[0] = v4[0]; bv[1] = v4[1]; bv[2] = v4[2]; bv[3] = v4[3];
                 } else {
 #pragma unroll
                     for (int t = 0; t < 4; ++t)
-                        if (key + t < p.Nk) bv[t] = bias_row[key + t];
+                        if (key + t < Nk) bv[t] = bias_row[key + t];
                 }
             }
 #pragma unroll
@@ -314,7 +341,7 @@ __global__ __launch_bounds__(ATT_NW * 64, 2) void attention_mfma_kernel(AttnProb
         }
         float bias0[16];
         if (HAS_BIAS) load_bias(0, bias0);
-        if (32 > p.Nk || (CAUSAL && 31 > q0 + c_off)) scale_scores(s_blk[0], 0, bias0, TailYes{}, 0, 16);
+        if (32 > Nk || (CAUSAL && 31 > q0 + c_off)) scale_scores(s_blk[0], 0, bias0, TailYes{}, 0, 16);
         else scale_scores(s_blk[0], 0, bias0, TailNo{}, 0, 16);
         float bmax = block_max(s_blk[0]);
         bmax = fmaxf(bmax, __shfl_xor(bmax, 32));
@@ -420,7 +447,7 @@ __global__ __launch_bounds__(ATT_NW * 64, 2) void attention_mfma_kernel(AttnProb
                 }
             }
             // wave-uniform: the block reaches beyond Nk, or beyond what the wave's first query sees
-            const bool ragged = !CLEAN && (knext + 32 > p.Nk || (CAUSAL && knext + 31 > q0 + c_off));
+            const bool ragged = !CLEAN && (knext + 32 > Nk || (CAUSAL && knext + 31 > q0 + c_off));
             float bmax = -INFINITY;
 #pragma unroll
             for (int st = 0; st < 2; ++st) {
@@ -463,8 +490,8 @@ __global__ __launch_bounds__(ATT_NW * 64, 2) void attention_mfma_kernel(AttnProb
     // issued in it (tile t + 1) end at key 64 t + 159
     int n_clean = 0;
     if (!HAS_BIAS) {
-        long long lim = ((long long)p.Nk - 160) / ATT_BKV + 1;
-        if (p.Nk < 160) lim = 0;
+        long long lim = ((long long)Nk - 160) / ATT_BKV + 1;
+        if (Nk < 160) lim = 0;
         if (lim > NT - 1) lim = NT - 1;
         if (CAUSAL) {
             const long long vis = (long long)q0 + c_off - 95;          // 64 t <= vis
@@ -484,8 +511,38 @@ __global__ __launch_bounds__(ATT_NW * 64, 2) void attention_mfma_kernel(AttnProb
     }
     if (t < NT) tile(t, IntTag<0>{}, TailNo{});
 
+    // ---- the second group's result is brought to the common reference point and added by the first (same wave, same lane)
+    float l_tot = l_run + __shfl_xor(l_run, 32);
+    if constexpr (SPLIT == 2) {
+        constexpr int WAVE_F4 = (JD * 4 + 1) * 64;                // 16-byte pieces per wave: the outputs, then (m, l)
+        static_assert(ATT_NW * WAVE_F4 * 16 <= SPLIT * 4 * TILE, "LDS");
+        f32x4* part = (f32x4*)lds_all + wave * WAVE_F4 + lane;
+        __syncthreads();                                          // every tile has been read for the last time
+        if (grp == 1) {
+#pragma unroll
+            for (int j = 0; j < JD; ++j)
+#pragma unroll
+                for (int g = 0; g < 4; ++g)
+                    part[(j * 4 + g) * 64] = f32x4{o_acc[j][g * 4], o_acc[j][g * 4 + 1], o_acc[j][g * 4 + 2], o_acc[j][g * 4 + 3]};
+            part[JD * 4 * 64] = f32x4{m_run, l_tot, 0.0f, 0.0f};
+        }
+        __syncthreads();
+        if (grp == 1) return;
+        const f32x4 ml = part[JD * 4 * 64];
+        const float m = fmaxf(m_run, ml[0]), m_sub = m == -INFINITY ? 0.0f : m;
+        const float f0 = fast_exp2(m_run - m_sub), f1 = fast_exp2(ml[0] - m_sub);
+        l_tot = fmaf(ml[1], f1, l_tot * f0);
+#pragma unroll
+        for (int j = 0; j < JD; ++j)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const f32x4 v = part[(j * 4 + g) * 64];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o_acc[j][g * 4 + e] = fmaf(v[e], f1, o_acc[j][g * 4 + e] * f0);
+            }
+    }
+
     // ---- normalise and store: the lane holds, for query q0 + lane%32, d = 32 j + 8 g + 4 h + 0..3
-    const float l_tot = l_run + __shfl_xor(l_run, 32);
     const float inv = 1.0f / l_tot;
     if (q_ok) {
         char* op = (char*)p.O + ((int64_t)b * p.stride_o + (int64_t)(q0 + col) * p.ldo) * 2;
@@ -502,15 +559,26 @@ __global__ __launch_bounds__(ATT_NW * 64, 2) void attention_mfma_kernel(AttnProb
 }
 
 template <typename T, int D>
-hipError_t launch_d(const AttnProblem& p, hipStream_t stream) {
-    constexpr int LDS_BYTES = 2 * 2 * ATT_BKV * D * 2;
-    const void* kern = p.causal ? (const void*)attention_mfma_kernel<T, D, false, false, true>
-                       : p.bias ? (const void*)attention_mfma_kernel<T, D, true, true, false>
-                       : p.alpha > 0.0f ? (const void*)attention_mfma_kernel<T, D, false, false, false>
-                                        : (const void*)attention_mfma_kernel<T, D, false, true, false>;
+hipError_t launch_d(const AttnProblem& p, hipStream_t stream, bool split) {
+    const int lds_bytes = (split ? 2 : 1) * 2 * 2 * ATT_BKV * D * 2;
+    const void* kern = split ? (p.causal ? (const void*)attention_mfma_kernel<T, D, false, false, true, 2>
+                                         : (const void*)attention_mfma_kernel<T, D, false, false, false, 2>)
+                       : p.causal ? (const void*)attention_mfma_kernel<T, D, false, false, true, 1>
+                       : p.bias ? (const void*)attention_mfma_kernel<T, D, true, true, false, 1>
+                       : p.alpha > 0.0f ? (const void*)attention_mfma_kernel<T, D, false, false, false, 1>
+                                        : (const void*)attention_mfma_kernel<T, D, false, true, false, 1>;
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
+    if (split) {                                   // up to 128 KiB of LDS
+        static std::atomic<unsigned> attr_done[2]; // bit per device, for either form
+        const unsigned bit = 1u << (dev & 31);
+        if (!(attr_done[p.causal ? 1 : 0].load(std::memory_order_acquire) & bit)) {
+            e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+            if (e != hipSuccess) return e;
+            attr_done[p.causal ? 1 : 0].fetch_or(bit, std::memory_order_release);
+        }
+    }
     DeviceShape ds;
     e = device_shape(dev, &ds);
     if (e != hipSuccess) return e;
@@ -521,15 +589,24 @@ hipError_t launch_d(const AttnProblem& p, hipStream_t stream) {
     int tot = (int)total;
     AttnProblem pa = p;
     void* args[] = {&pa, &q_tiles, &tot, &xcds};
-    return hipLaunchKernel(kern, dim3((unsigned)total), dim3(ATT_NW * 64), args, LDS_BYTES, stream);
+    return hipLaunchKernel(kern, dim3((unsigned)total), dim3(ATT_NW * (split ? 2 : 1) * 64), args, lds_bytes, stream);
 }
 
 template <typename T>
-hipError_t launch_t(const AttnProblem& p, hipStream_t stream, const char** name) {
+hipError_t launch_t(const AttnProblem& p, hipStream_t stream, bool split, const char** name) {
     switch (p.D) {
-    case 32: *name = p.causal ? "attn_mfma_q128_kv64_d32_causal" : "attn_mfma_q128_kv64_d32"; return launch_d<T, 32>(p, stream);
-    case 64: *name = p.causal ? "attn_mfma_q128_kv64_d64_causal" : "attn_mfma_q128_kv64_d64"; return launch_d<T, 64>(p, stream);
-    case 128: *name = p.causal ? "attn_mfma_q128_kv64_d128_causal" : "attn_mfma_q128_kv64_d128"; return launch_d<T, 128>(p, stream);
+    case 32:
+        *name = split ? (p.causal ? "attn_mfma_q128_kv64x2_d32_causal" : "attn_mfma_q128_kv64x2_d32")
+                      : (p.causal ? "attn_mfma_q128_kv64_d32_causal" : "attn_mfma_q128_kv64_d32");
+        return launch_d<T, 32>(p, stream, split);
+    case 64:
+        *name = split ? (p.causal ? "attn_mfma_q128_kv64x2_d64_causal" : "attn_mfma_q128_kv64x2_d64")
+                      : (p.causal ? "attn_mfma_q128_kv64_d64_causal" : "attn_mfma_q128_kv64_d64");
+        return launch_d<T, 64>(p, stream, split);
+    case 128:
+        *name = split ? (p.causal ? "attn_mfma_q128_kv64x2_d128_causal" : "attn_mfma_q128_kv64x2_d128")
+                      : (p.causal ? "attn_mfma_q128_kv64_d128_causal" : "attn_mfma_q128_kv64_d128");
+        return launch_d<T, 128>(p, stream, split);
     default: return hipErrorInvalidValue;
     }
 }
@@ -553,8 +630,24 @@ bool attention_mfma_supported(const AttnProblem& p) {
     return true;
 }
 
-hipError_t launch_attention_mfma(const AttnProblem& p, hipStream_t stream, const char** name) {
-    return p.dtype == DT_BF16 ? launch_t<bf16_t>(p, stream, name) : launch_t<f16_t>(p, stream, name);
+// Two groups of waves per workgroup: where a workgroup of four waves is alone on its compute unit (up to 256 of them) or, in the
+// causal form, outlives its neighbour, each SIMD has one wave and the last chain of keys is the time.  Short contexts do not pay
+// for the merge (64 x 512 x 64, causal: 11.5 against 11.6 us; 32 x 1024 x 128: 23.7 against 24.4, causal 23.4 against 22.2).
+// With more workgroups two of four waves share a unit anyway (32 x 2048 x 128: 68 against 76 us), except that
+// a long causal triangle leaves the long ones alone (16 x 4096 x 128: 102 against 79 us; 32 x 2048: 57 against 59) and that at D = 32
+// little is multiplied between two barriers (32 x 2048 x 32: 30.6 against 28.5 us; 48 x 2048 x 64: 59 against 67).
+static bool split_preferred(const AttnProblem& p) {
+    const long long total = (long long)((p.Nq + ATT_BQ - 1) / ATT_BQ) * p.batch;
+    const bool triangle = p.causal && p.Nk <= (long long)p.Nq + p.Nq / 4;      // otherwise the query tiles see about the same keys
+    if (total <= 256) return p.Nk >= (p.D < 128 || triangle ? 1024 : 2048);
+    return total <= 512 && ((triangle && p.Nk >= 4096) || (p.D == 32 && p.Nk >= 2048));
+}
+
+// force_cfg: 1 all waves on the same keys, 2 the keys in two halves (no bias, alpha > 0), otherwise by the rule.
+hipError_t launch_attention_mfma(const AttnProblem& p, hipStream_t stream, int force_cfg, const char** name) {
+    const bool can = !p.bias && p.alpha > 0.0f;
+    const bool split = can && (force_cfg == 2 || (force_cfg != 1 && split_preferred(p)));
+    return p.dtype == DT_BF16 ? launch_t<bf16_t>(p, stream, split, name) : launch_t<f16_t>(p, stream, split, name);
 }
 
 }  // namespace pbk

@@ -32,7 +32,7 @@ bool aligned(const void* p, int64_t a) { return (reinterpret_cast<uintptr_t>(p) 
 // at the first call of the process; pbk_force_kernel() overrides the former per thread.
 // force: 0 automatic, 1 generic, 2 mfma, 3 the gathering mfma kernel, 4 the small fp32 kernel, 5 "bstat" (the
 // B-stationary kernel for short contractions), 6 "ksplit[:<id>]" (a few rows), 7 "tile64[:<id>]" (64-wide tiles),
-// 8 "decode[:<workgroups per batch entry>]" (attention of a few queries); cfg: -1 or id
+// 8 "decode[:<workgroups per batch entry>]" (attention of a few queries); cfg: -1 or id ("mfma:<groups of waves>" for attention)
 struct Choice { int force; int cfg; };
 
 bool parse_choice(const char* e, Choice* c) {
@@ -462,7 +462,7 @@ static pbk_status attention_common(const void* Q, const void* K, const void* V, 
     if (!use_mfma && D > 512) return PBK_ERR_UNSUPPORTED;
     const char* name = "";
     hipError_t e = use_decode ? pbk::launch_attention_decode(p, stream, cfg, &name)
-                   : use_mfma ? pbk::launch_attention_mfma(p, stream, &name)
+                   : use_mfma ? pbk::launch_attention_mfma(p, stream, cfg, &name)
                             : pbk::launch_attention_generic(p, stream, &name);
     if (e != hipSuccess) {
         std::fprintf(stderr, "libpbk: launch of %s failed: %s\n", name, hipGetErrorString(e));

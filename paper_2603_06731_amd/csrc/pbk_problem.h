@@ -116,7 +116,7 @@ int group_m_override();
 // Attention: generic kernel (any dtype/alignment, D <= 512) and the fused MFMA kernel.
 hipError_t launch_attention_generic(const AttnProblem& p, hipStream_t stream, const char** name);
 bool attention_mfma_supported(const AttnProblem& p);
-hipError_t launch_attention_mfma(const AttnProblem& p, hipStream_t stream, const char** name);
+hipError_t launch_attention_mfma(const AttnProblem& p, hipStream_t stream, int force_cfg, const char** name);
 // A few queries against a long context: the keys are split over the waves of a workgroup.
 bool attention_decode_supported(const AttnProblem& p);
 bool attention_decode_preferred(const AttnProblem& p);
