@@ -286,9 +286,25 @@ bool attention_decode_supported(const AttnProblem& p) {
     return p.Nq <= 16 && !p.bias && p.alpha > 0.0f && attention_mfma_supported(p);
 }
 
-// Below four steps of keys there is nothing to split (48 x 1 x 149 x 64: 4.4 against 5.7 us for the kernel of whole sequences;
-// 16 x 8 x 130 x 32: 4.4 against 4.5).
-bool attention_decode_preferred(const AttnProblem& p) { return p.Nk >= 4 * DEC_KB; }
+// Against the kernel of whole sequences (bf16; times in us, that kernel's first; operands from memory, not from caches, unless noted).
+// - Below four steps of keys there is nothing to split (48 x 1 x 149 x 64: 4.4 against 5.7; 16 x 8 x 130 x 32: 4.4 against 4.5).
+// - Up to 128 entries: ahead everywhere (128 x 1 x 128 x 64: 4.7 against 4.2, cached).  Up to 256, one workgroup per compute unit: ahead
+//   (256 x 1 x 128 x 128: 7.4 against 7.2; x 8192: 194 against 185), except that one or two queries at D = 64 cost the kernel 0.7 us that
+//   three do not and a short context does not give back: 160 x 1 x 128: 5.1 against 5.6, x 192: 5.8 against 6.0, x 256: 6.4
+//   against 6.3; 256 x 1 x 256: 7.5 against 7.8, x 512: 10.9 against 10.2.
+// - Beyond 256 entries its 8 or 16 waves and up to 128 KiB of LDS still leave one workgroup per unit, and the other kernel keeps several: D = 64, 512 x 1 x
+//   128: 7.0 against 10.1 (cached), x 512: 16.7 against 19.2, x 2048: 50 against 53; D = 128, 257 x 1 x 4096: 103 against 129,
+//   448 x 2048: 85 against 86.  From 640 entries on the two take equally many rounds, and long contexts are ahead or equal (640 x
+//   1024 x 128: 72 against 65; 768 x 1536 x 64: 58 and 58, 1024 x 2048 x 64: 116 against 101; but 1536 x 1024 x 64: 75 against 79).
+// - At D = 32 it takes half of the LDS: ahead up to 512 entries (512 x 128: 5.0 against 4.9, cached), from 256 keys on with any number
+//   (1024 x 128: 7.5 against 8.3, x 256: 10.8 against 10.0, cached).
+bool attention_decode_preferred(const AttnProblem& p) {
+    if (p.Nk < 4 * DEC_KB) return false;
+    if (p.batch <= 128) return true;
+    if (p.batch <= 256) return p.D != 64 || p.Nq > 2 || p.Nk >= (p.batch <= 192 ? 256 : 384);
+    if (p.D == 32) return p.batch <= 512 || p.Nk >= 256;
+    return p.batch >= 640 && p.Nk >= (p.D == 64 ? 1536 : 1024);
+}
 
 // Workgroups per batch entry: K is read once by each of them, V once by all together.  With few entries a compute unit's load path
 // (about 95 GB/s here) bounds the kernel, and the more units take part in reading V the better (D = 128, context 8192: 16
@@ -296,7 +312,11 @@ bool attention_decode_preferred(const AttnProblem& p) { return p.Nk >= 4 * DEC_K
 // second reading of K costs (240 x 1104: 25.5 / 27.9 / 42.3; 223 x 5327: 102 / 108 / 159).
 hipError_t launch_attention_decode(const AttnProblem& p, hipStream_t stream, int force_split, const char** name) {
     const int split = force_split > 0 ? force_split : p.batch > 128 ? 1 : p.batch > 64 ? 2 : 4;
-    *name = p.causal ? "attn_mfma_decode_q16_kv32_causal" : "attn_mfma_decode_q16_kv32";
+    static const char* const names[3][2] = {{"attn_mfma_decode_q16_kv32_c1", "attn_mfma_decode_q16_kv32_c1_causal"},
+                                            {"attn_mfma_decode_q16_kv32_c2", "attn_mfma_decode_q16_kv32_c2_causal"},
+                                            {"attn_mfma_decode_q16_kv32_c4", "attn_mfma_decode_q16_kv32_c4_causal"}};
+    const int groups = split < p.D / 32 ? split : p.D / 32;        // column groups of launch_type
+    *name = names[groups >= 4 ? 2 : groups >= 2 ? 1 : 0][p.causal ? 1 : 0];
     return p.dtype == DT_BF16 ? launch_type<bf16_t>(p, stream, split) : launch_type<f16_t>(p, stream, split);
 }
 

@@ -59,3 +59,36 @@ def test_decode(D, split, dtype, causal):
         bound = u * ((w @ vd.abs()) + ref.abs()) + 1e-5
         ok = (got - ref).abs() <= bound
         assert torch.all(ok | torch.isnan(ref)), (b, Nq, Nk, float(((got - ref).abs() / bound).nan_to_num().max()))
+
+
+@pytest.mark.parametrize("batch,Nq,Nk,D,kernel", [
+    # queries and keys
+    (16, 16, 512, 64, "decode"), (16, 17, 512, 64, "q128"), (16, 1, 128, 128, "decode"), (16, 1, 127, 128, "q128"),
+    # workgroups per entry
+    (64, 1, 256, 128, "kv32_c4"), (65, 1, 256, 128, "kv32_c2"), (128, 2, 256, 128, "kv32_c2"), (129, 2, 256, 128, "kv32_c1"),
+    (128, 1, 128, 64, "kv32_c2"), (64, 1, 256, 32, "kv32_c1"),
+    # up to 256 entries, one or two queries at D = 64
+    (160, 2, 255, 64, "q128"), (160, 2, 256, 64, "decode"), (160, 3, 128, 64, "decode"), (200, 1, 383, 64, "q128"), (200, 1, 384, 64, "decode"),
+    (256, 1, 128, 128, "decode"),
+    # more than 256 entries
+    (257, 1, 1024, 128, "q128"), (512, 1, 512, 64, "q128"), (639, 1, 1536, 64, "q128"), (640, 1, 1535, 64, "q128"), (640, 1, 1536, 64, "decode"),
+    (640, 8, 1023, 128, "q128"), (640, 8, 1024, 128, "decode"), (512, 1, 128, 32, "decode"), (513, 1, 255, 32, "q128"), (513, 1, 256, 32, "decode"),
+])
+def test_dispatch(batch, Nq, Nk, D, kernel):
+    """Either side of each line of the rule, with the automatic choice."""
+    import torch
+    import paper_2603_06731_amd as pbk
+    g = torch.Generator(device="cuda").manual_seed(batch + Nk)
+    q, k, v = (torch.randn(batch, n, D, generator=g, device="cuda").bfloat16() for n in (Nq, Nk, Nk))
+    out = torch.empty_like(q)
+    with T.forced_kernel(None):
+        st = pbk.pbk_attention_causal(q, k, v, out, batch, Nq, Nk, D, D, D, D, D, Nq * D, Nk * D, Nk * D, Nq * D, BF16, D ** -0.5)
+    assert st == 0 and kernel in pbk.pbk_last_kernel(), pbk.pbk_last_kernel()
+    s = torch.stack([q[b].double() @ k[b].double().T * D ** -0.5 for b in range(batch)])
+    s = s.masked_fill(torch.arange(Nk, device="cuda")[None, :] > torch.arange(Nq, device="cuda")[:, None] + Nk - Nq, float("-inf"))
+    w = torch.softmax(s, -1)
+    for b in range(0, batch, max(1, batch // 16)):
+        vb = v[b].double()
+        ref = w[b] @ vb
+        # (the bound of test_decode)
+        assert torch.all((out[b].double() - ref).abs() <= 2.0 ** -8 * (w[b] @ vb.abs() + ref.abs()) + 1e-5), b
