@@ -636,10 +636,13 @@ bool attention_mfma_supported(const AttnProblem& p) {
 // With more workgroups two of four waves share a unit anyway (32 x 2048 x 128: 68 against 76 us), except that
 // a long causal triangle leaves the long ones alone (16 x 4096 x 128: 102 against 79 us; 32 x 2048: 57 against 59) and that at D = 32
 // little is multiplied between two barriers (32 x 2048 x 32: 30.6 against 28.5 us; 48 x 2048 x 64: 59 against 67).
+// A full round of entries with one query tile each at D = 128 (240 to 256) is bound by memory, not by the chain, below 3072 keys
+// (256 entries of 64 queries, K and V from memory: 2048 keys 53.6 against 54.7 us, 3072 78.3 against 77.2; of 128 queries: 57.0
+// against 59.0, 82.4 against 82.1; 224 entries of 64: 50.0 against 49.0, 73.4 against 69.2).
 static bool split_preferred(const AttnProblem& p) {
     const long long total = (long long)((p.Nq + ATT_BQ - 1) / ATT_BQ) * p.batch;
     const bool triangle = p.causal && p.Nk <= (long long)p.Nq + p.Nq / 4;      // otherwise the query tiles see about the same keys
-    if (total <= 256) return p.Nk >= (p.D < 128 || triangle ? 1024 : 2048);
+    if (total <= 256) return p.Nk >= (p.D == 128 && p.batch > 240 ? 3072 : p.D < 128 || triangle ? 1024 : 2048);
     return total <= 512 && ((triangle && p.Nk >= 4096) || (p.D == 32 && p.Nk >= 2048));
 }
 

@@ -87,3 +87,12 @@ def test_dispatch(batch, Nq, Nk, D, causal, split):
     w = torch.softmax(s, -1)
     ref = w @ vd
     assert torch.all((out[-1].double() - ref).abs() <= 2.0 ** -8 * (w @ vd.abs() + ref.abs()) + 1e-5)
+
+
+@pytest.mark.parametrize("batch,Nk,D,causal,split", [
+    (240, 2048, 128, 0, True), (241, 2048, 128, 0, False), (256, 2048, 128, 1, False), (256, 3071, 128, 1, False), (256, 3072, 128, 0, True),
+    (256, 2048, 64, 0, True),
+])
+def test_dispatch_a_round_of_entries(batch, Nk, D, causal, split):
+    """As many entries as compute units, one query tile each."""
+    test_dispatch(batch, 64, Nk, D, causal, split)
