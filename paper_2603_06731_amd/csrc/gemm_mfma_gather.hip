@@ -429,11 +429,20 @@ bool mfma_gather_supported(const Problem& p) {
     return a_elems >= 8 && b_elems >= 8;
 }
 
-// Up to one round of 128 x 128 tiles on the 256 compute units the 64-row tile wins, because a workgroup alone on its unit is
-// bound by latency: 8 x 44 x 44 x 127 -> 512, 3 x 3, stride 2 (112 tiles) 33.4 -> 25.4 us, 577 x 1021 x 4096 (40) 49.9 -> 35.0,
-// 1000 x 3001 x 1024 (192) 22.9 -> 22.1; beyond it two of the larger ones share a unit.
+// Up to one round of 64-row tiles on the 256 compute units the 64-row tile wins, because a workgroup alone on its unit is bound by
+// latency (8 x 44 x 44 x 127 -> 512, 3 x 3, stride 2, 224 tiles: 33.4 -> 25.4 us; 577 x 1021 x 4096, 80 tiles: 49.9 -> 35.0).  Where they
+// take a second round and the larger ones do not, a plain product gains only up to K = 512 (1024 x 2049: K = 259 1.11 times
+// faster, 515 1.09, 1143 0.98, 4097 0.82), a convolution, whose addresses cost vector instructions that a second workgroup
+// hides, with any K (3 x 3 ... 7 x 7, K = 27 ... 6223, 392 to 484 tiles: 1.04 to 1.24 times).  Beyond one round of
+// 128 x 128 tiles two of the larger ones share a unit.
+static bool gather_rows64(const Problem& p) {
+    const long long cols = (p.N + GBN - 1) / GBN;
+    const long long t128 = (long long)((p.M + 127) / 128) * cols * p.batch, t64 = (long long)((p.M + 63) / 64) * cols * p.batch;
+    return t128 <= 256 && (p.is_conv || t64 <= 256 || p.K <= 512);
+}
+
 hipError_t launch_mfma_gather(const Problem& p, hipStream_t stream, const char** name) {
-    if ((long long)((p.M + 127) / 128) * ((p.N + GBN - 1) / GBN) * p.batch <= 256) {
+    if (gather_rows64(p)) {
         *name = "mfma16_gather_64x128x32_w2x2";
         return p.in_dtype == DT_BF16 ? launch_gather_type<bf16_t, 64>(p, stream) : launch_gather_type<f16_t, 64>(p, stream);
     }

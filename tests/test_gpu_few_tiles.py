@@ -80,6 +80,16 @@ def test_gather_tiles(M, N, K, tile, trans_b):
     assert err <= TOL[BF16], err
 
 
+@pytest.mark.parametrize("M,N,K,tile", [
+    (900, 2049, 1143, "64x128"), (961, 2049, 1143, "128x128"), (961, 2049, 512, "64x128"), (961, 2049, 513, "128x128"),
+])
+def test_gather_tiles_second_round(M, N, K, tile):
+    """255 and 272 tiles of 64 rows: a second round of them only for a short contraction."""
+    err, kern = run_case(1, M, N, K, BF16, BF16, 0, C.EPI_BIAS, pad_ld=1, force=None)
+    assert tile in kern, kern
+    assert err <= TOL[BF16], err
+
+
 @pytest.mark.parametrize("force", ["ksplit", "tile64"])
 def test_residual(force):
     """The shortcut operand, with its own leading dimension, and columns that are stored one at a time."""
