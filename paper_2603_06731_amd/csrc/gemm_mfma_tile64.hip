@@ -309,10 +309,15 @@ static int tile64_choice(const Problem& p) {
 }
 
 // Up to half a round of 128 x 128 tiles on the 256 compute units (measured against their deep ring: 64 tiles, K = 4096: 20.7
-// against 27.5 us; 128 tiles, K = 2048: 16.4 against 17.3; 160 tiles, K = 1024: 18.0 against 11.7), and K of at least a round.
+// against 27.5 us; 128 tiles, K = 2048: 16.4 against 17.3; 160 tiles, K = 1024: 18.0 against 11.7), and enough rounds of k:
+// - one for the 32 x 64 tiles (577 x 1024 x 128: 4.9 against 5.7 us);
+// - two for one 64 x 64 tile per unit (256 x 4096, k-major B: K = 128 5.8 against 5.7, 192 6.25 against 6.05, 256 6.2 against 6.6);
+// - four for two of them, whose short rings do not fill before (1024 x 2048: K = 128 6.4 against 6.0, 192 7.2 against 6.5, 384
+//   8.0 against 7.8, 512 8.6 against 9.1; 4 x 56 x 56 x 128 -> 512, 1 x 1, stride 2: 7.9 against 7.1).
 bool mfma_tile64_preferred(const Problem& p) {
     const long long t128 = (long long)((p.M + 127) / 128) * ((p.N + 127) / 128) * p.batch;
-    return t128 <= 128 && p.K >= T64_BK;
+    const int c = tile64_choice(p), rounds = c == 1 ? 1 : c == 0 ? 2 : 4;
+    return t128 <= 128 && p.K >= rounds * T64_BK;
 }
 
 hipError_t launch_mfma_tile64(const Problem& p, hipStream_t stream, int cfg, const char** name) {

@@ -71,6 +71,17 @@ def test_dispatch(M, N, K, trans_b, kernel):
     assert err <= TOL[BF16], err
 
 
+@pytest.mark.parametrize("M,N,K,trans_b,kernel", [
+    (577, 1024, 128, 1, "tile64_32x64"), (577, 1024, 120, 1, "128x128x64"), (256, 4096, 248, 1, "128x128x64"), (256, 4096, 256, 1, "tile64_64x64_s4"),
+    (1024, 2048, 504, 0, "128x128x64"), (1024, 2048, 512, 0, "tile64_64x64_s2"),
+])
+def test_dispatch_rounds(M, N, K, trans_b, kernel):
+    """Rounds of k that each of the 64-wide tiles needs."""
+    err, kern = run_case(1, M, N, K, BF16, BF16, trans_b, C.EPI_BIAS, force=None)
+    assert kernel in kern, kern
+    assert err <= TOL[BF16], err
+
+
 @pytest.mark.parametrize("trans_b", [0, 1])
 @pytest.mark.parametrize("M,N,K,tile", [(2100, 2049, 37, "128x128"), (2048, 2048, 37, "64x128"), (65, 131, 301, "64x128")])
 def test_gather_tiles(M, N, K, tile, trans_b):
