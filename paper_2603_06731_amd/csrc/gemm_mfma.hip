@@ -58,8 +58,18 @@ bool mfma_preferred(const Problem& p) {
 // that two workgroups per unit hide from each other otherwise: bf16 2048 x 2048 x 4096 36.2 against 52.2 us, 577 x 4096 x 1024
 // 11.7 against 16.0, FP8 512 x 4096 x 4096 16.1 against 27.5.  Beyond one round two workgroups share a unit (4 x 32 x 28 x 28
 // rows of a transposed convolution, 784 tiles: 52.8 against 79.2 us).
+// Filling the deeper ring costs more than it gives
+// - in a convolution whose k-tiles span taps, so that every address is divided out, up to some eight k-tiles (3 x 3, bf16 32 -> 64, five:
+//   12.5 against 12.1 us; int8 64 -> 128, five: 25.0 against 24.4; bf16 96 -> 128, fourteen: 4 % ahead);
+// - in a 16-bit product of three or four k-tiles up to some 160 tiles (577 x 4096 x 256: 7.4 against 7.2 us; 1536 x 2048 x 256,
+//   192 tiles: 7.7 against 7.6, 2048 x 2048 x 256: 8.1 against 8.3; with two k-tiles or five it is even or ahead).
 static int square_config(const Problem& p) {
-    return (long long)((p.M + 127) / 128) * ((p.N + 127) / 128) * p.batch <= 256 ? 2 : 1;
+    const long long t = (long long)((p.M + 127) / 128) * ((p.N + 127) / 128) * p.batch;
+    if (t > 256) return 1;
+    const bool b8 = p.in_dtype != DT_BF16 && p.in_dtype != DT_F16;
+    const int bk = b8 ? 128 : 64, kt = (p.K + bk - 1) / bk;        // values per k-tile, k-tiles
+    if (p.is_conv) return p.conv.Cin % bk != 0 && kt <= 8 ? 1 : 2;
+    return !b8 && kt >= 3 && kt <= 4 && t <= 160 ? 1 : 2;
 }
 
 // 16-bit operands.  Configurations 5-7 use the 16x16x32 MFMA blocks (measured against their

@@ -71,6 +71,32 @@ def test_dispatch(M, N, K, trans_b, kernel):
     assert err <= TOL[BF16], err
 
 
+@pytest.mark.parametrize("M,N,K,kernel", [
+    (1280, 2048, 128, "w2x2_s4"), (1280, 2048, 136, "w2x2_s2"), (1280, 2048, 256, "w2x2_s2"), (1280, 2048, 264, "w2x2_s4"), (1408, 2048, 256, "w2x2_s4"),
+])
+def test_dispatch_ring(M, N, K, kernel):
+    """160 and 176 tiles of 128 x 128: the deeper ring with two k-tiles, or five, or more tiles."""
+    err, kern = run_case(1, M, N, K, BF16, BF16, 0, C.EPI_BIAS, force=None)
+    assert "128x128x64_" + kernel in kern, kern
+    assert err <= TOL[BF16], err
+
+
+@pytest.mark.parametrize("hw,Cin,Cout,k,kernel", [
+    (69, 56, 136, 3, "w2x2_s2"), (69, 64, 136, 3, "w2x2_s4"), (69, 24, 136, 5, "w2x2_s4"),
+])
+def test_dispatch_ring_conv(hw, Cin, Cout, k, kernel):
+    """More than 128 tiles of a convolution: eight k-tiles that span taps, nine that do not, ten that do."""
+    import paper_2603_06731_amd as pbk
+    w = wl.Workload("ring_conv", "conv", BF16, BF16, C.EPI_BIAS_RELU, n=2, H=hw, W=hw, Cin=Cin, Cout=Cout, KH=k, KW=k, pad=(k // 2, k // 2),
+                    dist_b=("normal", float(np.sqrt(2.0 / (k * k * Cin)))))
+    host = wl.make_inputs(w)
+    st, out = T.run_workload(w, T.upload(host))
+    assert st == 0 and "128x128x64_" + kernel in pbk.pbk_last_kernel(), pbk.pbk_last_kernel()
+    ref, pre = T.oracle_full(w, host)
+    err = T.rel_err(T.to_host_f64(out, w.out_dtype).reshape(ref.shape), ref, pre)
+    assert err <= TOL[BF16], err
+
+
 @pytest.mark.parametrize("M,N,K,trans_b,kernel", [
     (577, 1024, 128, 1, "tile64_32x64"), (577, 1024, 120, 1, "128x128x64"), (256, 4096, 248, 1, "128x128x64"), (256, 4096, 256, 1, "tile64_64x64_s4"),
     (1024, 2048, 504, 0, "128x128x64"), (1024, 2048, 512, 0, "tile64_64x64_s2"),
