@@ -243,20 +243,23 @@ static int ksplit_columns(const Problem& p) {
     return 0;
 }
 
-// Plain matrices.  A (and a k-major B) is read in aligned 16-byte pieces that lie entirely inside or outside K, a row-major B in
-// pieces of 8 or 4 bytes, so that N need only be even; per-lane buffer offsets are 32-bit and must stay below 2^31.
-bool mfma_ksplit_supported(const Problem& p) {
-    if ((p.in_dtype != DT_BF16 && p.in_dtype != DT_F16) || p.is_conv) return false;
-    if (p.K < 8 || p.K % 8 || p.lda % 8 || p.stride_a % 8 || !al(p.A, 16)) return false;
-    const int64_t lim = (int64_t)1 << 31;
-    return 256 * p.lda * 2 + 256 < lim && 256 * p.ldb * 2 + 1024 < lim && ksplit_columns(p) != 0;
-}
-
 // 64 columns per workgroup, 32 where that would leave more than half of the 256 compute units without one (N = 14336: 28.6
 // against 36.7 us; N = 4096, K = 4096: 15.1 against 13.1; N = 1024, K = 16384: 36 against 30) or pieces of 8 bytes are not aligned.
 static int ksplit_choice(const Problem& p) {
     if (ksplit_columns(p) == 2) return 1;
     return (long long)((p.N + 63) / 64) * ((p.M + 15) / 16) * p.batch >= 128 ? 0 : 1;
+}
+
+// Plain matrices.  A (and a k-major B) is read in aligned 16-byte pieces that lie entirely inside or outside K, a row-major B in
+// pieces of 8 or 4 bytes, so that N need only be even; per-lane buffer offsets are 32-bit and must stay below 2^31.
+// A launch holds fewer than 2^32 threads, 1024 here per tile: a batch of small products that share B can ask for more.
+bool mfma_ksplit_supported(const Problem& p) {
+    if ((p.in_dtype != DT_BF16 && p.in_dtype != DT_F16) || p.is_conv) return false;
+    if (p.K < 8 || p.K % 8 || p.lda % 8 || p.stride_a % 8 || !al(p.A, 16)) return false;
+    const int64_t lim = (int64_t)1 << 31;
+    if (256 * p.lda * 2 + 256 >= lim || 256 * p.ldb * 2 + 1024 >= lim || ksplit_columns(p) == 0) return false;
+    const int cols = ksplit_choice(p) == 0 ? 64 : 32;
+    return (long long)((p.N + cols - 1) / cols) * ((p.M + 15) / 16) * p.batch * 1024 < (1LL << 32);
 }
 
 // One row of tiles, and a contraction that gives half of the 16 waves a chunk.  A k-major B is read here in pieces of 64 bytes from

@@ -145,3 +145,22 @@ def test_residual(force):
     assert torch.all(got[:, N:] == 0)
     # one rounding to bf16 (2^-9 of the value), fp32 sums of 72 terms of order one
     assert torch.all((got[:, :N] - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-5)
+
+
+@pytest.mark.parametrize("batch,kernel", [(65535, "ksplit"), (65536, "128x128x64")])
+def test_launch_limit(batch, kernel):
+    """64 workgroups of 1024 threads per entry: one entry fewer than a launch can hold, and as many as it cannot (they run on
+    the larger tiles).  B is shared (stride 0)."""
+    import torch
+    import paper_2603_06731_amd as pbk
+    N, K = 4096, 512
+    g = torch.Generator(device="cuda").manual_seed(batch)
+    A = torch.randn(batch, K, generator=g, device="cuda").bfloat16()
+    B = (torch.randn(K, N, generator=g, device="cuda") * K ** -0.5).bfloat16()
+    out = torch.full((batch, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    with T.forced_kernel(None):
+        st = pbk.pbk_batched_matmul(A, B, out, None, batch, 1, N, K, K, N, N, K, 0, N, BF16, BF16, 0, 1.0, 0)
+    assert st == 0 and kernel in pbk.pbk_last_kernel(), (st, pbk.pbk_last_kernel())
+    ref = A.float() @ B.float()
+    err = ((out.float() - ref).abs() / ref.abs().clamp_min(float(ref.pow(2).mean().sqrt()))).max()
+    assert err <= TOL[BF16], float(err)
