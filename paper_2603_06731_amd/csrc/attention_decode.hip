@@ -281,9 +281,16 @@ hipError_t launch_type(const AttnProblem& p, hipStream_t stream, int split) {
 
 }  // namespace
 
-// The operand rules of attention_mfma_supported, at most 16 queries, no bias.
+// Workgroups per batch entry: K is read once by each of them, V once by all together.  With few entries a compute unit's load path
+// (about 95 GB/s here) bounds the kernel, and the more units take part in reading V the better (D = 128, context 8192: 16
+// entries 44.4 / 34.3 / 32.2 us with 1 / 2 / 4, 64 entries 84 / 67 / 61); with 128 entries the chip is occupied and the
+// second reading of K costs (240 x 1104: 25.5 / 27.9 / 42.3; 223 x 5327: 102 / 108 / 159).
+static int decode_split(const AttnProblem& p) { return p.batch > 128 ? 1 : p.batch > 64 ? 2 : 4; }
+
+// The operand rules of attention_mfma_supported, at most 16 queries, no bias.  A launch holds fewer than 2^32 threads, up to 1024 here
+// per workgroup (more than 128 entries have one workgroup each).
 bool attention_decode_supported(const AttnProblem& p) {
-    return p.Nq <= 16 && !p.bias && p.alpha > 0.0f && attention_mfma_supported(p);
+    return p.Nq <= 16 && !p.bias && p.alpha > 0.0f && p.batch < (1 << 22) && attention_mfma_supported(p);
 }
 
 // Against the kernel of whole sequences (bf16; times in us, that kernel's first; operands from memory, not from caches, unless noted).
@@ -306,12 +313,8 @@ bool attention_decode_preferred(const AttnProblem& p) {
     return p.batch >= 640 && p.Nk >= (p.D == 64 ? 1536 : 1024);
 }
 
-// Workgroups per batch entry: K is read once by each of them, V once by all together.  With few entries a compute unit's load path
-// (about 95 GB/s here) bounds the kernel, and the more units take part in reading V the better (D = 128, context 8192: 16
-// entries 44.4 / 34.3 / 32.2 us with 1 / 2 / 4, 64 entries 84 / 67 / 61); with 128 entries the chip is occupied and the
-// second reading of K costs (240 x 1104: 25.5 / 27.9 / 42.3; 223 x 5327: 102 / 108 / 159).
 hipError_t launch_attention_decode(const AttnProblem& p, hipStream_t stream, int force_split, const char** name) {
-    const int split = force_split > 0 ? force_split : p.batch > 128 ? 1 : p.batch > 64 ? 2 : 4;
+    const int split = force_split > 0 ? force_split : decode_split(p);
     static const char* const names[3][2] = {{"attn_mfma_decode_q16_kv32_c1", "attn_mfma_decode_q16_kv32_c1_causal"},
                                             {"attn_mfma_decode_q16_kv32_c2", "attn_mfma_decode_q16_kv32_c2_causal"},
                                             {"attn_mfma_decode_q16_kv32_c4", "attn_mfma_decode_q16_kv32_c4_causal"}};

@@ -92,3 +92,23 @@ def test_dispatch(batch, Nq, Nk, D, kernel):
         ref = w[b] @ vb
         # (the bound of test_decode)
         assert torch.all((out[b].double() - ref).abs() <= 2.0 ** -8 * (w[b] @ vb.abs() + ref.abs()) + 1e-5), b
+
+
+@pytest.mark.parametrize("batch,kernel", [((1 << 22) - 1, "decode"), (1 << 22, "q128")])
+def test_launch_limit(batch, kernel):
+    """1024 threads per entry: one entry fewer than a launch can hold, and as many as it cannot (they run on the kernel of
+    whole sequences).  K and V are shared (stride 0)."""
+    import torch
+    import paper_2603_06731_amd as pbk
+    D, Nk = 32, 256
+    g = torch.Generator(device="cuda").manual_seed(batch)
+    q = torch.randn(batch, D, generator=g, device="cuda").bfloat16()
+    k, v = (torch.randn(Nk, D, generator=g, device="cuda").bfloat16() for _ in range(2))
+    out = torch.full_like(q, float("nan"))
+    with T.forced_kernel(None):
+        st = pbk.pbk_attention(q, k, v, None, out, batch, 1, Nk, D, D, D, D, D, D, 0, 0, D, 0, 0, BF16, D ** -0.5)
+    assert st == 0 and kernel in pbk.pbk_last_kernel(), (st, pbk.pbk_last_kernel())
+    w = torch.softmax(q.float() @ k.float().T.contiguous() * D ** -0.5, -1)
+    ref, mag = w @ v.float(), w @ v.float().abs()
+    # one rounding of the weights and one of the output, 2^-8 each
+    assert bool(((out.float() - ref).abs() <= 2 ** -8 * (mag + ref.abs()) + 1e-5).all())
