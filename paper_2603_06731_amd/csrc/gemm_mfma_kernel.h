@@ -753,8 +753,9 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
             int ow = rem - oh * row_ow;
             a_ih0[r] = CONVT ? oh + ct.ih_base : oh * p.conv.stride_h - p.conv.pad_h;
             a_iw0[r] = CONVT ? ow + ct.iw_base : ow * p.conv.stride_w - p.conv.pad_w;
-            // byte offset of pixel (n, ih0, iw0), channel 0; may be "negative" (wraps), fixed up per tap
-            a_voff[r] = (unsigned)(((n * p.conv.H + a_ih0[r]) * p.conv.W + a_iw0[r]) * p.conv.Cin * 2);
+            // byte offset of pixel (n, ih0, iw0), channel 0, modulo 2^32: it may lie in front of the image or, for a class of a
+            // transposed convolution, beyond it by (KH - 1) dil / stride rows; adding the tap's offset brings it back
+            a_voff[r] = ((unsigned)(n * p.conv.H + a_ih0[r]) * (unsigned)p.conv.W + (unsigned)a_iw0[r]) * (unsigned)(p.conv.Cin * 2);
         } else {
             a_voff[r] = a_ok[r] ? (unsigned)(row * (int)p.lda * 2 + chunk * 16) : kOob;
         }
@@ -835,7 +836,7 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
         int brow = k0;                  // transposed convolution: weight row of the tile's first k (one tap per tile)
         if (CONV) {
             ld_dh = tap_kh * tap_dh; ld_dw = tap_kw * tap_dw;
-            ld_delta = (unsigned)(((ld_dh * p.conv.W + ld_dw) * p.conv.Cin + tap_c) * 2);
+            ld_delta = ((unsigned)ld_dh * (unsigned)p.conv.W + (unsigned)ld_dw) * (unsigned)(p.conv.Cin * 2) + (unsigned)(tap_c * 2);
             if (CONVT) brow = one_tap ? convt_brow(tap_kh, tap_kw, tap_c) : 0;
             if (one_tap) {              // advance the uniform tap state to the next k-tile
                 tap_c += BK;
@@ -870,7 +871,7 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
                     int kh = tap / tap_w;
                     int kw = tap - kh * tap_w;
                     dh = kh * tap_dh; dw = kw * tap_dw;
-                    off = a_voff[r] + (unsigned)(((dh * p.conv.W + dw) * p.conv.Cin + c) * 2);
+                    off = a_voff[r] + ((unsigned)dh * (unsigned)p.conv.W + (unsigned)dw) * (unsigned)(p.conv.Cin * 2) + (unsigned)(c * 2);
                 }
                 int ih = a_ih0[r] + dh, iw = a_iw0[r] + dw;
                 bool ok = a_ok[r] && ih >= 0 && ih < p.conv.H && iw >= 0 && iw < p.conv.W;

@@ -39,3 +39,45 @@ def test_residue_classes(case, dtype, out_dtype, cfg):
     ref, pre = T.oracle_full(w, host)
     err = T.rel_err(T.to_host_f64(out, w.out_dtype).reshape(ref.shape), ref, pre)
     assert err <= T.TIGHT[out_dtype], err        # the bound of the output rounding, as for every convolution
+
+
+def transpose(x, w, bias, geom, force=None):
+    """geom: n, H, W, Cin, Cout, KH, KW, stride, pad, dil; bf16 operands, bias epilogue.  Returns (y, kernel name)."""
+    import torch
+    import paper_2603_06731_amd as pbk
+    n, H, W, Cin, Cout, KH, KW, s, p, d = geom
+    OH, OW = ((size - 1) * s[i] - 2 * p[i] + d[i] * (k - 1) + 1 for i, (size, k) in enumerate(((H, KH), (W, KW))))
+    y = torch.full((n, OH, OW, Cout), float("nan"), dtype=torch.bfloat16, device="cuda")
+    with T.forced_kernel(force):
+        st = pbk.pbk_conv2d_transpose_nhwc(x, w, y, bias, n, H, W, Cin, Cout, KH, KW, *s, *p, 0, 0, *d, BF16, BF16, 1.0, C.EPI_BIAS)
+    assert st == 0, pbk.pbk_status_string(st)
+    return y, pbk.pbk_last_kernel()
+
+
+def operands(geom, seed):
+    import torch
+    n, H, W, Cin, Cout, KH, KW = geom[:7]
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    x = torch.randn(n, H, W, Cin, generator=g, device="cuda", dtype=torch.bfloat16)
+    w = torch.randn(KH, KW, Cin, Cout, generator=g, device="cuda", dtype=torch.bfloat16) * Cin ** -0.5
+    return x, w, torch.randn(Cout, generator=g, device="cuda")
+
+
+def close(got, ref):
+    """One rounding to bf16 (2^-9 of the value; twice that) and fp32 sums of order one."""
+    return bool(((got.float() - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-4).all())
+
+
+def test_rows_far_beyond_the_image():
+    """A dilation that puts the last tap's rows 2^31 bytes behind the image: the class's pixel offsets wrap and the tap's offset brings
+    them back."""
+    dil, taps = 4096, 5
+    geom = (1, 4, 1, 65536, 8, taps, 1, (1, 1), (0, 0), (dil, 1))
+    assert (taps - 1) * dil * 65536 * 2 >= 2 ** 31
+    x, w, bias = operands(geom, 1)
+    y, kern = transpose(x, w, bias, geom, "mfma")
+    assert "mfma" in kern, kern
+    ref = bias.double().expand(y.shape[1], 8).clone()
+    for kh in range(taps):
+        ref[kh * dil:kh * dil + 4] += x[0, :, 0].double() @ w[kh, 0].double()
+    assert close(y[0, :, 0], ref)
