@@ -32,10 +32,9 @@ bool mfma_supported(const Problem& p) {
         // (the transposed form reaches any weight row from the first one with such an offset)
         if (p.conv.transposed) {
             if ((int64_t)p.K * p.ldb * esz >= lim) return false;
-            // one set of tiles per residue class must stay a launchable grid
-            const int64_t nh = p.conv.stride_h < p.conv.OH ? p.conv.stride_h : p.conv.OH;
-            const int64_t nw = p.conv.stride_w < p.conv.OW ? p.conv.stride_w : p.conv.OW;
-            if (((int64_t)p.M / 128 + nh * nw * 2) * ((p.N + 127) / 128) >= lim) return false;
+            // A launch holds fewer than 2^32 threads: 2^24 tiles of 256.  (The 128 x 128 tiles are the most; a stride beyond the image
+            // makes nearly every output pixel a class, and a tile, of its own.)
+            if (convt_row_tiles(p, 128) * ((p.N + 127) / 128) >= (1 << 24)) return false;
         }
     } else {
         if (p.lda % per16 || p.ldb % per16) return false;

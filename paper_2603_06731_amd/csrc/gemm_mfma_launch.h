@@ -51,6 +51,15 @@ inline hipError_t device_shape(int dev, DeviceShape* out) {
     return hipSuccess;
 }
 
+// Tiles of bm rows of a transposed convolution: one set per residue class of the output, sized by the largest class.
+inline long long convt_row_tiles(const Problem& p, int bm) {
+    const ConvGeom& g = p.conv;
+    const long long images = p.M / ((long long)g.OH * g.OW);
+    const long long rows = images * ((g.OH + g.stride_h - 1) / g.stride_h) * ((g.OW + g.stride_w - 1) / g.stride_w);
+    const long long classes = (long long)(g.stride_h < g.OH ? g.stride_h : g.OH) * (g.stride_w < g.OW ? g.stride_w : g.OW);
+    return (rows + bm - 1) / bm * classes;
+}
+
 template <typename T, typename TO, int BM, int BN, int BK, int WM, int WN, int MODE, int NSTAGE, int OCC, int MI = 32,
           int ASTG = 0>
 hipError_t launch_one(const Problem& p, hipStream_t stream, int group_m) {
@@ -70,16 +79,13 @@ hipError_t launch_one(const Problem& p, hipStream_t stream, int group_m) {
     tm.tiles_m = (p.M + BM - 1) / BM;
     tm.tiles_n = (p.N + BN - 1) / BN;
     if (MODE == MODE_CONVT) {
-        // one set of row tiles per residue class, sized by the largest class
         const ConvGeom& g = p.conv;
         auto gcd = [](int a, int b) { while (b) { const int r = a % b; a = b; b = r; } return a; };
         tm.ct_nh = g.stride_h < g.OH ? g.stride_h : g.OH;
         tm.ct_nw = g.stride_w < g.OW ? g.stride_w : g.OW;
         tm.ct_step_h = g.stride_h / gcd(g.stride_h, g.dil_h);
         tm.ct_step_w = g.stride_w / gcd(g.stride_w, g.dil_w);
-        const long long images = p.M / ((long long)g.OH * g.OW);
-        const long long rows = images * ((g.OH + g.stride_h - 1) / g.stride_h) * ((g.OW + g.stride_w - 1) / g.stride_w);
-        const long long tiles = (rows + BM - 1) / BM * tm.ct_nh * tm.ct_nw;
+        const long long tiles = convt_row_tiles(p, BM);
         if (tiles * tm.tiles_n > 0x7FFFFFFFLL) return hipErrorInvalidValue;
         tm.tiles_m = (int)tiles;
     }

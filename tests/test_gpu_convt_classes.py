@@ -81,3 +81,17 @@ def test_rows_far_beyond_the_image():
     for kh in range(taps):
         ref[kh * dil:kh * dil + 4] += x[0, :, 0].double() @ w[kh, 0].double()
     assert close(y[0, :, 0], ref)
+
+
+def test_more_classes_than_a_launch_holds():
+    """A stride of 4096 over a 2 x 2 image: 2^24 classes, one tile of 256 threads each.  The matrix-unit kernel declines and the call runs."""
+    s = 4096
+    geom = (1, 2, 2, 8, 8, 1, 1, (s, s), (0, 0), (1, 1))
+    x, w, bias = operands(geom, 2)
+    y, kern = transpose(x, w, bias, geom)
+    assert "mfma" not in kern, kern
+    at = [(0, 0), (0, s), (s, 0), (s, s)]
+    for i, (oh, ow) in enumerate(at):
+        assert close(y[0, oh, ow], bias + x.reshape(4, 8)[i].float() @ w[0, 0].float())
+        y[0, oh, ow] = bias.bfloat16()
+    assert bool((y == bias.bfloat16()).all())
