@@ -29,9 +29,9 @@ bool mfma_supported(const Problem& p) {
         int64_t img = (int64_t)(p.M / (p.conv.OH * p.conv.OW)) * p.conv.H * p.conv.W * p.conv.Cin * esz;
         int64_t halo = ((int64_t)p.conv.pad_h * p.conv.W + p.conv.pad_w + p.conv.W) * p.conv.Cin * esz;
         if (img + halo >= lim) return false;
-        // (the transposed form reaches any weight row from the first one with such an offset)
         if (p.conv.transposed) {
-            if ((int64_t)p.K * p.ldb * esz >= lim) return false;
+            // where k-tiles (up to 64 deep) span taps, any weight row is reached from the first one with such an offset
+            if (p.conv.Cin % 64 != 0 && (int64_t)p.K * p.ldb * esz >= lim) return false;
             // A launch holds fewer than 2^32 threads: 2^24 tiles of 256.  (The 128 x 128 tiles are the most; a stride beyond the image
             // makes nearly every output pixel a class, and a tile, of its own.)
             if (convt_row_tiles(p, 128) * ((p.N + 127) / 128) >= (1 << 24)) return false;

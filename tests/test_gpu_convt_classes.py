@@ -95,3 +95,17 @@ def test_more_classes_than_a_launch_holds():
         assert close(y[0, oh, ow], bias + x.reshape(4, 8)[i].float() @ w[0, 0].float())
         y[0, oh, ow] = bias.bfloat16()
     assert bool((y == bias.bfloat16()).all())
+
+
+def test_weights_of_2_gib():
+    """k-tiles that lie inside one tap start at a 64-bit address: the weights may be of any size."""
+    geom = (1, 4, 4, 8192, 8192, 4, 4, (2, 2), (1, 1), (1, 1))
+    x, w, bias = operands(geom, 3)
+    y, kern = transpose(x, w, bias, geom)
+    assert "mfma" in kern, kern
+    ref = bias.expand(10, 10, 8192).clone()
+    for kh in range(4):
+        for kw in range(4):
+            # input pixel (ih, iw) paints output pixel (2 ih - 1 + kh, 2 iw - 1 + kw): one row and column of margin
+            ref[kh:kh + 7:2, kw:kw + 7:2] += (x.reshape(16, 8192).float() @ w[kh, kw].float()).reshape(4, 4, 8192)
+    assert close(y[0], ref[1:9, 1:9])
