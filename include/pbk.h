@@ -303,14 +303,24 @@ int pbk_version(void);
 const char* pbk_last_kernel(void);
 
 /*
- * Benchmarking and test aid, for the calls that follow ON THIS THREAD: "generic" forces
- * the fallback kernel, "mfma" the matrix-unit path with its automatic tile choice,
- * "mfma:<id>" one tile configuration (operands that the direct-to-LDS kernel cannot take
- * go to the gathering matrix-unit kernel instead), "gather" that kernel, "small" the
- * one-wave-per-tile fp32 kernel, "bstat" the B-stationary kernel for short contractions (K <= 256) over
- * many rows; a problem the choice cannot run gives PBK_ERR_UNSUPPORTED.  NULL or "" returns to the default.  The default is automatic
- * choice, or what the environment variable PBK_FORCE_KERNEL (same strings) held when the
- * process made its first call.  An unknown string is PBK_ERR_UNSUPPORTED and changes nothing.
+ * Benchmarking and test aid, for the calls that follow ON THIS THREAD:
+ *   "generic"     the fallback kernel;
+ *   "mfma"        the matrix-unit path with its automatic tile choice, "mfma:<id>" one tile configuration (one that is
+ *                 not built for the operands: the automatic choice; operands that the direct-to-LDS kernel
+ *                 cannot take go to the gathering matrix-unit kernel instead);
+ *   "gather"      that kernel;
+ *   "small"       the one-wave-per-tile fp32 kernel;
+ *   "bstat"       the B-stationary kernel for short contractions (K <= 256) over many rows;
+ *   "ksplit"      a few rows, k split over the waves: "ksplit:0" 64 columns per workgroup (32 where a row-major B has no aligned
+ *                 8-byte pieces), "ksplit:1" 32;
+ *   "tile64"      64-wide tiles: "tile64:0" 64 x 64 with a deep ring, "tile64:1" 32 x 64, "tile64:2" 64 x 64, two per compute unit;
+ *   "decode"      attention of up to 16 queries, keys split over the waves: "decode:1", "decode:2", "decode:4" workgroups per
+ *                 batch entry (as many as the head dimension has 32-column groups, at most).
+ * Attention takes "generic", "mfma" (the kernel of whole sequences; "mfma:1" all waves on the same keys, "mfma:2" the keys in
+ * two halves where that form is built) and "decode", and chooses automatically under the others.  A problem the choice cannot run, and
+ * "decode" for anything but attention, gives PBK_ERR_UNSUPPORTED.  NULL or "" returns to the default.  The default
+ * is automatic choice, or what the environment variable PBK_FORCE_KERNEL (same strings) held when the process made its first
+ * call.  An unknown string is PBK_ERR_UNSUPPORTED and changes nothing.
  */
 pbk_status pbk_force_kernel(const char* choice);
 

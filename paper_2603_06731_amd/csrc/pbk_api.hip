@@ -26,30 +26,29 @@ bool valid_out_dtype(int dt) { return dt == PBK_F32 || dt == PBK_BF16 || dt == P
 
 bool aligned(const void* p, int64_t a) { return (reinterpret_cast<uintptr_t>(p) % (uintptr_t)a) == 0; }
 
-// Kernel choice overrides (benchmarking and test aid).  A choice is "generic" (the fallback
-// kernel), "mfma" (the matrix-unit path, automatic tile configuration), "mfma:<id>" (one tile
-// configuration) or "gather" (the matrix-unit kernel that stages through registers).  The environment variables PBK_FORCE_KERNEL and PBK_GROUP_M are read ONCE,
-// at the first call of the process; pbk_force_kernel() overrides the former per thread.
-// force: 0 automatic, 1 generic, 2 mfma, 3 the gathering mfma kernel, 4 the small fp32 kernel, 5 "bstat" (the
-// B-stationary kernel for short contractions), 6 "ksplit[:<id>]" (a few rows), 7 "tile64[:<id>]" (64-wide tiles),
-// 8 "decode[:<workgroups per batch entry>]" (attention of a few queries); cfg: -1 or id ("mfma:<groups of waves>" for attention)
-struct Choice { int force; int cfg; };
+// Kernel choice overrides (benchmarking and test aid; the strings are listed at pbk_force_kernel).  The environment
+// variables PBK_FORCE_KERNEL and PBK_GROUP_M are read ONCE, at the first call of the process; pbk_force_kernel()
+// overrides the former per thread.
+enum { FORCE_NONE = 0, FORCE_GENERIC, FORCE_MFMA, FORCE_GATHER, FORCE_SMALL, FORCE_BSTAT, FORCE_KSPLIT, FORCE_TILE64, FORCE_DECODE };
+struct Choice { int force; int cfg; };           // cfg: the id behind the colon, or -1
 
 bool parse_choice(const char* e, Choice* c) {
     c->force = 0; c->cfg = -1;
     if (!e || !*e) return true;
-    if (!std::strcmp(e, "generic")) { c->force = 1; return true; }
-    if (!std::strcmp(e, "mfma")) { c->force = 2; return true; }
-    if (!std::strcmp(e, "gather")) { c->force = 3; return true; }
-    if (!std::strcmp(e, "small")) { c->force = 4; return true; }
-    if (!std::strcmp(e, "bstat")) { c->force = 5; return true; }
-    if (!std::strcmp(e, "decode")) { c->force = 8; return true; }
-    if (!std::strncmp(e, "decode:", 7) && e[7] >= '0' && e[7] <= '9') { c->force = 8; c->cfg = std::atoi(e + 7); return true; }
-    if (!std::strcmp(e, "tile64")) { c->force = 7; return true; }
-    if (!std::strncmp(e, "tile64:", 7) && e[7] >= '0' && e[7] <= '9') { c->force = 7; c->cfg = std::atoi(e + 7); return true; }
-    if (!std::strcmp(e, "ksplit")) { c->force = 6; return true; }
-    if (!std::strncmp(e, "ksplit:", 7) && e[7] >= '0' && e[7] <= '9') { c->force = 6; c->cfg = std::atoi(e + 7); return true; }
-    if (!std::strncmp(e, "mfma:", 5) && e[5] >= '0' && e[5] <= '9') { c->force = 2; c->cfg = std::atoi(e + 5); return true; }
+    if (!std::strncmp(e, "mfma:", 5) && e[5] >= '0' && e[5] <= '9') { c->force = FORCE_MFMA; c->cfg = std::atoi(e + 5); return true; }
+    // name and the ids it takes behind a colon (one digit each; any other string is unknown)
+    static const struct { const char* name; int force; const char* ids; } names[] = {
+        {"generic", FORCE_GENERIC, ""}, {"mfma", FORCE_MFMA, ""}, {"gather", FORCE_GATHER, ""}, {"small", FORCE_SMALL, ""}, {"bstat", FORCE_BSTAT, ""},
+        {"ksplit", FORCE_KSPLIT, "01"}, {"tile64", FORCE_TILE64, "012"}, {"decode", FORCE_DECODE, "124"}};
+    for (const auto& n : names) {
+        const size_t len = std::strlen(n.name);
+        if (std::strncmp(e, n.name, len)) continue;
+        if (!e[len]) { c->force = n.force; return true; }
+        if (e[len] == ':' && e[len + 1] && !e[len + 2] && std::strchr(n.ids, e[len + 1])) {
+            c->force = n.force; c->cfg = e[len + 1] - '0';
+            return true;
+        }
+    }
     return false;
 }
 
@@ -101,20 +100,21 @@ pbk_status dispatch(const pbk::Problem& p_in, hipStream_t stream) {
     const bool can_bstat = pbk::mfma_bstat_supported(p);
     // a few rows, or too few 128-wide tiles for the chip: the contraction is split over the waves of a workgroup
     const bool can_ksplit = pbk::mfma_ksplit_supported(p), can_tile64 = pbk::mfma_tile64_supported(p);
-    if ((force == 2 && !can_mfma && !can_gather) || (force == 3 && !can_gather) || (force == 4 && !can_small) ||
-        (force == 5 && !can_bstat) || (force == 6 && !can_ksplit) || (force == 7 && !can_tile64))
+    if ((force == FORCE_MFMA && !can_mfma && !can_gather) || (force == FORCE_GATHER && !can_gather) || (force == FORCE_SMALL && !can_small) ||
+        (force == FORCE_BSTAT && !can_bstat) || (force == FORCE_KSPLIT && !can_ksplit) || (force == FORCE_TILE64 && !can_tile64) ||
+        force == FORCE_DECODE)
         return PBK_ERR_UNSUPPORTED;
-    if (force == 5 || (force == 0 && can_bstat && pbk::mfma_bstat_preferred(p)))
+    if (force == FORCE_BSTAT || (force == FORCE_NONE && can_bstat && pbk::mfma_bstat_preferred(p)))
         e = pbk::launch_mfma_bstat(p, stream, &name);
-    else if (force == 6 || (force == 0 && can_ksplit && pbk::mfma_ksplit_preferred(p)))
+    else if (force == FORCE_KSPLIT || (force == FORCE_NONE && can_ksplit && pbk::mfma_ksplit_preferred(p)))
         e = pbk::launch_mfma_ksplit(p, stream, cfg, &name);
-    else if (force == 7 || (force == 0 && can_tile64 && pbk::mfma_tile64_preferred(p)))
+    else if (force == FORCE_TILE64 || (force == FORCE_NONE && can_tile64 && pbk::mfma_tile64_preferred(p)))
         e = pbk::launch_mfma_tile64(p, stream, cfg, &name);
-    else if (force == 4 || (force == 0 && can_small && pbk::small_f32_preferred(p) && !(can_mfma && pbk::mfma_preferred(p))))
+    else if (force == FORCE_SMALL || (force == FORCE_NONE && can_small && pbk::small_f32_preferred(p) && !(can_mfma && pbk::mfma_preferred(p))))
         e = pbk::launch_small_f32(p, stream, &name);
-    else if (can_mfma && force != 1 && force != 3 && (force == 2 || pbk::mfma_preferred(p)))
+    else if (can_mfma && force != FORCE_GENERIC && force != FORCE_GATHER && (force == FORCE_MFMA || pbk::mfma_preferred(p)))
         e = pbk::launch_mfma(p, stream, cfg, &name);
-    else if (force == 3 || (force == 2 && !can_mfma) || (force == 0 && want_gather))
+    else if (force == FORCE_GATHER || (force == FORCE_MFMA && !can_mfma) || (force == FORCE_NONE && want_gather))
         e = pbk::launch_mfma_gather(p, stream, &name);
     else
         e = pbk::launch_generic(p, stream, &name);
@@ -453,12 +453,16 @@ static pbk_status attention_common(const void* Q, const void* K, const void* V, 
     p.dtype = dtype; p.alpha = alpha; p.causal = causal;
 
     int cfg = -1;
-    const int force = forced_choice(&cfg);
+    int force = forced_choice(&cfg);
+    if (force != FORCE_GENERIC && force != FORCE_MFMA && force != FORCE_DECODE) {      // choices of the contractions: automatic here
+        force = FORCE_NONE;
+        cfg = -1;
+    }
     const bool can_mfma = pbk::attention_mfma_supported(p);
     const bool can_decode = pbk::attention_decode_supported(p);
-    if ((force == 2 && !can_mfma) || (force == 8 && !can_decode)) return PBK_ERR_UNSUPPORTED;
-    const bool use_decode = can_decode && (force == 8 || (force == 0 && pbk::attention_decode_preferred(p)));
-    const bool use_mfma = can_mfma && force != 1;
+    if ((force == FORCE_MFMA && !can_mfma) || (force == FORCE_DECODE && !can_decode)) return PBK_ERR_UNSUPPORTED;
+    const bool use_decode = can_decode && (force == FORCE_DECODE || (force == FORCE_NONE && pbk::attention_decode_preferred(p)));
+    const bool use_mfma = can_mfma && force != FORCE_GENERIC;
     if (!use_mfma && D > 512) return PBK_ERR_UNSUPPORTED;
     const char* name = "";
     hipError_t e = use_decode ? pbk::launch_attention_decode(p, stream, cfg, &name)

@@ -199,6 +199,23 @@ def test_force_kernel_choices(pbk):
     assert pbk.pbk_force_kernel("") == 0 and pbk.pbk_force_kernel(None) == 0
 
 
+def test_force_kernel_ids(pbk):
+    """An id that is not built is an unknown string; one that names another operation's kernel is not taken for a tile configuration."""
+    BF16 = 1
+    try:
+        for ok in ("ksplit", "ksplit:0", "ksplit:1", "tile64", "tile64:2", "decode", "decode:1", "decode:2", "decode:4"):
+            assert pbk.pbk_force_kernel(ok) == 0, ok
+        for bad in ("ksplit:2", "tile64:3", "tile64:9", "tile64:12", "decode:0", "decode:3", "decode:", "small:0", "bstat:1", "tile6", "tile640"):
+            assert pbk.pbk_force_kernel(bad) == 7, bad
+        P = 0x1000
+        for force in ("decode", "decode:1"):
+            assert pbk.pbk_force_kernel(force) == 0
+            assert pbk.pbk_matmul(P, P, P, None, 128, 128, 64, 64, 128, 128, BF16, BF16, 0, 1.0, 0) == 7
+            assert pbk.pbk_conv2d_nhwc(P, P, P, None, 1, 8, 8, 16, 16, 3, 3, 1, 1, 1, 1, 1, 1, BF16, BF16, 1.0, 0) == 7
+    finally:
+        pbk.pbk_force_kernel(None)
+
+
 def test_transposed_convolution_with_more_classes_than_a_launch_holds(pbk):
     """Residue classes of a stride of 4096 over a 2 x 2 image: 2^24 tiles of 256 threads.  The matrix-unit path declines before the launch."""
     BF16 = 1

@@ -47,13 +47,14 @@ CONVS = [  # n, H, W, Cin, Cout, KH, KW, stride, pad, dil
 @pytest.mark.parametrize("dtype", [BF16, F16])
 @pytest.mark.parametrize("case", CONVS)
 def test_conv(case, dtype, force):
+    import paper_2603_06731_amd as pbk
     n, H, W, Cin, Cout, KH, KW, stride, pad, dil = case
     w = wl.Workload("few_tiles_conv", "conv", dtype, dtype, C.EPI_BIAS_RELU, n=n, H=H, W=W, Cin=Cin, Cout=Cout, KH=KH, KW=KW,
                     stride=stride, pad=pad, dil=dil, dist_b=("normal", float(np.sqrt(2.0 / (KH * KW * Cin)))))
     host = wl.make_inputs(w)
     with T.forced_kernel(force):
         st, out = T.run_workload(w, T.upload(host))
-    assert st == 0
+    assert st == 0 and force.split(":")[0].replace("mfma", "128x128x64_w2x2_s4") in pbk.pbk_last_kernel(), pbk.pbk_last_kernel()
     ref, pre = T.oracle_full(w, host)
     err = T.rel_err(T.to_host_f64(out, w.out_dtype).reshape(ref.shape), ref, pre)
     assert err <= TOL[dtype], err
