@@ -441,8 +441,9 @@ static bool gather_rows64(const Problem& p) {
     return t128 <= 256 && (p.is_conv || t64 <= 256 || p.K <= 512);
 }
 
-hipError_t launch_mfma_gather(const Problem& p, hipStream_t stream, const char** name) {
-    if (gather_rows64(p)) {
+// force_cfg: 0 the 128-row tiles, 1 the 64-row ones, otherwise by the rule.
+hipError_t launch_mfma_gather(const Problem& p, hipStream_t stream, int force_cfg, const char** name) {
+    if (force_cfg == 1 || (force_cfg != 0 && gather_rows64(p))) {
         *name = "mfma16_gather_64x128x32_w2x2";
         return p.in_dtype == DT_BF16 ? launch_gather_type<bf16_t, 64>(p, stream) : launch_gather_type<f16_t, 64>(p, stream);
     }

@@ -38,7 +38,7 @@ bool parse_choice(const char* e, Choice* c) {
     if (!std::strncmp(e, "mfma:", 5) && e[5] >= '0' && e[5] <= '9') { c->force = FORCE_MFMA; c->cfg = std::atoi(e + 5); return true; }
     // name and the ids it takes behind a colon (one digit each; any other string is unknown)
     static const struct { const char* name; int force; const char* ids; } names[] = {
-        {"generic", FORCE_GENERIC, ""}, {"mfma", FORCE_MFMA, ""}, {"gather", FORCE_GATHER, ""}, {"small", FORCE_SMALL, ""}, {"bstat", FORCE_BSTAT, ""},
+        {"generic", FORCE_GENERIC, ""}, {"mfma", FORCE_MFMA, ""}, {"gather", FORCE_GATHER, "01"}, {"small", FORCE_SMALL, ""}, {"bstat", FORCE_BSTAT, ""},
         {"ksplit", FORCE_KSPLIT, "01"}, {"tile64", FORCE_TILE64, "012"}, {"decode", FORCE_DECODE, "124"}};
     for (const auto& n : names) {
         const size_t len = std::strlen(n.name);
@@ -115,7 +115,7 @@ pbk_status dispatch(const pbk::Problem& p_in, hipStream_t stream) {
     else if (can_mfma && force != FORCE_GENERIC && force != FORCE_GATHER && (force == FORCE_MFMA || pbk::mfma_preferred(p)))
         e = pbk::launch_mfma(p, stream, cfg, &name);
     else if (force == FORCE_GATHER || (force == FORCE_MFMA && !can_mfma) || (force == FORCE_NONE && want_gather))
-        e = pbk::launch_mfma_gather(p, stream, &name);
+        e = pbk::launch_mfma_gather(p, stream, force == FORCE_GATHER ? cfg : -1, &name);
     else
         e = pbk::launch_generic(p, stream, &name);
     if (e != hipSuccess) {

@@ -1,0 +1,71 @@
+"""Both row tiles of the gathering matrix-unit kernel (128 and 64 rows) on every mode that it is built for: the cases of
+the automatic choice, which takes one of the two by size, and contractions from one k-tile of 32 over the last one that only has
+careful steps (five) into the unrolled steady state."""
+import numpy as np
+import pytest
+
+import workloads as wl
+from workloads import configs as C
+import pbk_testlib as T
+import test_gpu_gather as G
+
+pytestmark = pytest.mark.gpu
+
+BF16, F16, F32 = wl.DTYPE_BF16, wl.DTYPE_F16, wl.DTYPE_F32
+NAMES = {"gather:0": "gather_128x128", "gather:1": "gather_64x128"}
+rows = pytest.mark.parametrize("force", list(NAMES))
+
+
+@rows
+@pytest.mark.parametrize("dtype,out_dtype", [(BF16, BF16), (F16, F16), (BF16, F32), (F16, F32)])
+@pytest.mark.parametrize("trans_b", [0, 1])
+def test_matmul(force, dtype, out_dtype, trans_b):
+    nan = 0x7FC0 if dtype == BF16 else 0x7E00
+    for M, N, K, pad in [(300, 261, 1143, 3), (129, 127, 37, 1), (65, 131, 301, 1), (63, 129, 160, 1), (191, 260, 193, 5), (257, 384, 4097, 1)]:
+        lda, ldb = K + pad, (K if trans_b else N) + 1
+        a = wl.tensor((M, lda), dtype, 1, "normal")
+        b = wl.tensor(((N if trans_b else K), ldb), dtype, 2, "normal", 1.0 / np.sqrt(K))
+        a[:, K:] = nan
+        b[:, ldb - 1:] = nan
+        bias = wl.tensor((N,), F32, 3, "normal", 0.5)
+        err, kern = G.run_views(a, b, bias, M, N, K, lda, ldb, N, dtype, out_dtype, trans_b, C.EPI_BIAS_GELU_TANH, alpha=0.75, force=force)
+        assert NAMES[force] in kern, kern
+        assert err <= T.TIGHT[out_dtype], (M, N, K, err)
+
+
+@rows
+@pytest.mark.parametrize("a_off,b_off", [(1, 0), (0, 3), (5, 7)])
+def test_unaligned_bases(force, a_off, b_off):
+    M, N, K = 200, 264, 328
+    a = wl.tensor((M * K + 16,), BF16, 1, "normal")
+    b = wl.tensor((K * N + 16,), BF16, 2, "normal", 1.0 / np.sqrt(K))
+    err, kern = G.run_views(a, b, None, M, N, K, K, N, N, BF16, BF16, 0, C.EPI_RELU, force=force, a_off=a_off, b_off=b_off)
+    assert NAMES[force] in kern and err <= T.TIGHT[BF16], (kern, err)
+
+
+@rows
+@pytest.mark.parametrize("dtype,out_dtype", [(F16, F32), (BF16, BF16)])
+@pytest.mark.parametrize("case", [
+    # n, H, W, Cin, Cout, KH, KW, stride, pad, dil
+    (2, 44, 44, 127, 24, 3, 3, (2, 2), (0, 0), (1, 1)),
+    (1, 20, 19, 127, 136, 3, 3, (1, 1), (1, 1), (1, 1)),
+    (2, 15, 17, 9, 40, 5, 3, (1, 2), (2, 1), (2, 1)),
+    (1, 30, 30, 3, 64, 7, 7, (2, 2), (3, 3), (1, 1)),
+    (1, 12, 13, 20, 40, 3, 3, (1, 1), (1, 1), (1, 1)),
+    (1, 12, 12, 30, 261, 1, 1, (1, 1), (0, 0), (1, 1)),
+    (6, 9, 11, 8, 12, 2, 2, (1, 1), (0, 1), (1, 1)),
+])
+def test_conv(case, dtype, out_dtype, force):
+    n, H, W, Cin, Cout, KH, KW, stride, pad, dil = case
+    w = wl.Workload("conv_gather_rows", "conv", dtype, out_dtype, C.EPI_BIAS_RELU, n=n, H=H, W=W, Cin=Cin, Cout=Cout, KH=KH, KW=KW,
+                    stride=stride, pad=pad, dil=dil, dist_b=("normal", float(np.sqrt(2.0 / (KH * KW * Cin)))))
+    with T.forced_kernel(force):
+        G.check_workload(w, NAMES[force])
+
+
+@rows
+@pytest.mark.parametrize("K", [61, 333])
+def test_batched(force, K):
+    w = wl.Workload("bmm_gather_rows", "batched", BF16, F32, C.EPI_NONE, alpha=0.5, batch=3, M=131, N=77, K=K, dist_b=("normal", K ** -0.5))
+    with T.forced_kernel(force):
+        G.check_workload(w, NAMES[force])
