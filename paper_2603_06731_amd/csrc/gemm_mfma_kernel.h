@@ -654,7 +654,7 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
     static_assert(MI == 32 || (MI == 16 && (sizeof(T) == 2 || (std::is_same<T, int8_t>::value && MODE == MODE_TRANS_B) ||
                                             (F8PAIR && MODE == MODE_TRANS_B))),
                   "16x16 blocks are built for the 16-bit types and for 8-bit types with both operands k-major");
-    constexpr bool CONVT = MODE == MODE_CONVT;               // transposed convolution: gather form
+    constexpr bool CONVT = MODE == MODE_CONVT;               // transposed convolution, by residue classes (ConvTClass)
     constexpr bool CONV = MODE == MODE_CONV || CONVT;        // A is an image, rows are output pixels
     constexpr bool TRANS_B = MODE == MODE_TRANS_B;
     constexpr int NW = WM * WN;

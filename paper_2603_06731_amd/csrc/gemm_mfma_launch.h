@@ -116,7 +116,7 @@ hipError_t launch_modes(const Problem& p, hipStream_t stream, int group_m) {
         return launch_one<T, T, BM, BN, BK, WM, WN, MODE_DENSE, NSTAGE, OCC, MI, ASTG>(p, stream, group_m);
     } else {
     if (p.is_conv && p.conv.transposed) {
-        // the transposed form is built for the two configurations the dispatcher picks
+        // the transposed form is built for the tile shapes the dispatcher picks: configurations 0, 1, 2 and 6
         if constexpr ((BM == 128 && BN == 256 && BK == 32) || (BM == 128 && BN == 128 && BK == 64))
             return launch_one<T, T, BM, BN, BK, WM, WN, MODE_CONVT, NSTAGE, OCC, MI>(p, stream, group_m);
         else
