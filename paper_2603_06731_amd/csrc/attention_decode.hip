@@ -282,7 +282,7 @@ hipError_t launch_type(const AttnProblem& p, hipStream_t stream, int split) {
 }  // namespace
 
 // Workgroups per batch entry: K is read once by each of them, V once by all together.  With few entries a compute unit's load path
-// (about 95 GB/s here) bounds the kernel, and the more units take part in reading V the better (D = 128, context 8192: 16
+// (about 95 GB/s with 64 of them at work) bounds the kernel, and the more units take part in reading V the better (D = 128, context 8192: 16
 // entries 44.4 / 34.3 / 32.2 us with 1 / 2 / 4, 64 entries 84 / 67 / 61); with 128 entries the chip is occupied and the
 // second reading of K costs (240 x 1104: 25.5 / 27.9 / 42.3; 223 x 5327: 102 / 108 / 159).
 static int decode_split(const AttnProblem& p) { return p.batch > 128 ? 1 : p.batch > 64 ? 2 : 4; }

@@ -5,9 +5,10 @@
 // staged in LDS by all waves (direct-to-LDS loads of 16 bytes per lane along the rows, whole lines), and then every
 // wave multiplies the WHOLE tile over its own 32 of the 128 k values, so that each staged byte is read from LDS once.
 // The waves' partial tiles meet in LDS at the end and are added in wave order (fixed: bit-exact from run to run).
-// What bounds it: a compute unit takes in about 32 bytes per clock, and a 64 x 64 tile moves K / 4 KiB through that
-// path: 14 us at K = 4096, to which the first loads and the reduction add about 6.  577 x 1024 x 4096 with bias and
-// residual: 48.6 us with 128 x 128 tiles (40 of them), 22.3 here.  Reading the next round's fragments under this
+// What bounds it: the chain of rounds of a workgroup that is alone on its compute unit (N = 1024: 64 x 64 tiles 5.4 us and
+// 0.47 us per round, 32 x 64 tiles 4.2 and 0.34, with 32 workgroups on the chip as with 256); with two on a unit, its load
+// path, 70 to 84 GB/s.  577 x 1024 x 4096 with bias and residual (304 tiles of 32 x 64, two on 48 of the units): 48.6 us with
+// 128 x 128 tiles (40 of them), 22.0 here.  Reading the next round's fragments under this
 // round's MFMAs, with loads issued between them, was 10 % slower (its ring has one stage less in flight).
 //
 // LDS images: k-major operands (A, B with trans_b) [rows][128 k], 16-byte chunk index XORed with row % 16; row-major B
@@ -297,7 +298,9 @@ bool mfma_tile64_supported(const Problem& p) {
 
 // Tile of a problem (the names in launch_type): where the 32 x 64 tiles, two workgroups per compute unit, make at
 // most little more than one round of the 256 units, they win (512 x 1024 x 1024: 6.6 against 8.8 us for one 64 x 64 tile per
-// unit; 577 x 1024 x 4096: 22.0 against 22.6), for a convolution, whose addresses cost vector instructions that a second
+// unit; up to 256 tiles 0.70 to 0.83 of its time for K = 256 ... 4096; 257 to 320 tiles, twelve shapes with N = 512 ... 4160: K up to
+// 1024 0.78 to 0.96, 2048 0.83 to 1.07, 4096 0.86 to 1.18, even on average: 577 x 1024 with residual 22.5 against 22.6 us; from
+// 321 to 400 tiles K up to 1024 0.80 to 0.97, 4096 0.96 to 1.08), for a convolution, whose addresses cost vector instructions that a second
 // workgroup hides, up to one round of 64 x 64 tiles (8 x 14 x 14 x 512 -> 512, 3 x 3: 25.6 against 33 us); then one 64 x 64
 // tile per unit with a deep ring (256 x 4096 x 4096: 20.7 against 22.7 and 24.0 us), beyond that two per unit
 // (1024 x 2048 x 2048: 16.4 against 24.3 us).
