@@ -148,10 +148,10 @@ pbk_status pbk_conv2d_nhwc_pad4(const void* x, const void* w, void* y, const flo
  *                      (iw, kw) likewise, and c, of x[n][ih][iw][c] * w[kh][kw][c][co]:
  * the adjoint of the convolution with the same filter and geometry.  out_pad must
  * be smaller than the stride or the dilation, OH and OW must be >= 1.  It runs as
- * the implicit GEMM with rows (n, oh, ow) grouped by (oh mod stride_h, ow mod
- * stride_w), each group over the taps that divide by the stride for it (the
- * generic kernel walks K = KH*KW*Cin with the others zero); the epilogue is the
- * usual one.
+ * the implicit GEMM with rows (n, oh, ow) and K = KH*KW*Cin in which the taps
+ * that do not divide by the stride are zero, or, where that shortens K by enough,
+ * with the rows grouped by (oh mod stride_h, ow mod stride_w) and each group over
+ * the taps that divide for it; the epilogue is the usual one.
  */
 pbk_status pbk_conv2d_transpose_nhwc(const void* x, const void* w, void* y, const float* bias,
                                      int64_t N, int64_t H, int64_t W, int64_t Cin, int64_t Cout,

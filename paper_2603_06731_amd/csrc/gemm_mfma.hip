@@ -29,13 +29,6 @@ bool mfma_supported(const Problem& p) {
         int64_t img = (int64_t)(p.M / (p.conv.OH * p.conv.OW)) * p.conv.H * p.conv.W * p.conv.Cin * esz;
         int64_t halo = ((int64_t)p.conv.pad_h * p.conv.W + p.conv.pad_w + p.conv.W) * p.conv.Cin * esz;
         if (img + halo >= lim) return false;
-        if (p.conv.transposed) {
-            // where k-tiles (up to 64 deep) span taps, any weight row is reached from the first one with such an offset
-            if (p.conv.Cin % 64 != 0 && (int64_t)p.K * p.ldb * esz >= lim) return false;
-            // A launch holds fewer than 2^32 threads: 2^24 tiles of 256.  (The 128 x 128 tiles are the most; a stride beyond the image
-            // makes nearly every output pixel a class, and a tile, of its own.)
-            if (convt_row_tiles(p, 128) * ((p.N + 127) / 128) >= (1 << 24)) return false;
-        }
     } else {
         if (p.lda % per16 || p.ldb % per16) return false;
         if (!p.trans_b && p.N % per16) return false;
@@ -98,10 +91,36 @@ static int choose_config(const Problem& p) {
     // convolutions whose channel count is a multiple of 64 (the image is then staged in 64-deep pieces): 9 from one
     // round of 256x256 tiles and K = 1024 up (32x56x56x256 -> 256, 3x3: 131 against 151 us; 64x28x28x256 -> 512: 121
     // against 133 us; K = 576 equal; 1x1 filters and fewer than 100 tiles: 6 or 1 stay ahead by 10-15 %)
-    if (p.is_conv && !p.conv.transposed && p.conv.Cin % 64 == 0 && p.M >= 256 && p.N >= 256 && t256 >= 256 && p.K >= 1024)
+    if (p.is_conv && p.conv.Cin % 64 == 0 && p.M >= 256 && p.N >= 256 && t256 >= 256 && p.K >= 1024)
         return 9;
     if (p.M >= 128 && p.N >= 256 && t >= 256) return 6;
     return square_config(p);
+}
+
+// Transposed convolution by residue classes (tile configurations 1 and 2): what the form can address and launch.
+static bool convt_classes_fit(const Problem& p) {
+    // where k-tiles (up to 64 deep) span taps, any weight row is reached from the first one with a 32-bit offset
+    if (p.conv.Cin % 64 != 0 && (int64_t)p.K * p.ldb * 2 >= ((int64_t)1 << 31)) return false;
+    // A launch holds fewer than 2^32 threads: 2^24 tiles of 256.  (A stride beyond the image makes nearly every output pixel a
+    // class, and a tile, of its own.)
+    return convt_row_tiles(p, 128) * ((p.N + 127) / 128) < (1 << 24);
+}
+
+// Classes, or all taps for every output pixel?  By how much the longest class shortens the k loop.  Its rows of C are apart, its tiles
+// are 128 x 128 (with 128 x 256 the row mapping of the epilogue does not fit the registers), and with too little to save that costs more
+// than it gives.  Times in us, all taps first, 2700 sizes of stride 1 to 4; with this rule none is more than 2.5 % behind all taps:
+// - nothing saved (stride 1, one tap, a dilation that is a multiple of the stride): 4 x 28 x 28 x 64 -> 128, 1 x 1, stride 2: 8.1
+//   against 10.1; 16 x 56 x 56 x 96 -> 256, 5 x 5, stride 1: 79 against 140;
+// - up to 128 columns, saved 24 (Cin = 8, 2 x 2, stride 2): 1.3 times as long by classes; 96: 0.9 to 1.15 times, 160 to 200: 0.7 to 0.9
+//   on average, from 384 at most 0.7;
+// - where the 128 x 256 tiles would be taken: saved 96: 1.3 to 1.5 times, 160 to 200: 1.0 on average and up to 1.27, from 320 on at most
+//   0.9, with k-tiles that span taps from 1152 on (480: 32 x 56 x 56 x 96 -> 512, 3 x 3: 261 against 271; 512: 32 x 28 x 28 x 32 -> 256,
+//   5 x 5: 52.5 against 55.5; 1536: 0.8).
+static bool convt_by_class(const Problem& p, bool wide) {
+    const ConvTAxis h = convt_axis_of(p.conv.OH, p.conv.stride_h, p.conv.dil_h, p.conv.KH);
+    const ConvTAxis w = convt_axis_of(p.conv.OW, p.conv.stride_w, p.conv.dil_w, p.conv.KW);
+    const long long taps = (long long)((p.conv.KH + h.step.d - 1) / h.step.d) * ((p.conv.KW + w.step.d - 1) / w.step.d);
+    return p.K - taps * p.conv.Cin >= (!wide ? 128 : p.conv.Cin % 64 == 0 ? 320 : 640) && convt_classes_fit(p);
 }
 
 // 16-bit types: the translation unit (group) that holds a configuration
@@ -121,6 +140,19 @@ hipError_t launch_mfma_f16(const Problem& p, hipStream_t stream, int cfg, int gr
     static GroupFn* const g[kNumGroups16] = {launch_mfma_f16_g0, launch_mfma_f16_g1, launch_mfma_f16_g2,
                                              launch_mfma_f16_g3, launch_mfma_f16_g4};
     return launch_group16(cfg, g, p, stream, group_m);
+}
+
+static hipError_t launch_convt(const Problem& p_in, hipStream_t stream, int force_cfg, const char** name) {
+    Problem p = p_in;
+    const long long t = (long long)((p.M + 127) / 128) * ((p.N + 255) / 256);
+    const bool wide = p.M >= 128 && p.N >= 256 && t >= 256;
+    const bool classes = force_cfg == 2 ? convt_classes_fit(p) : force_cfg != 0 && force_cfg != 6 && convt_by_class(p, wide && force_cfg != 1);
+    p.conv.transposed = classes ? 2 : 1;
+    const int cfg = classes ? (force_cfg == 1 || force_cfg == 2 ? force_cfg : square_config(p))
+                            : (force_cfg == 0 || force_cfg == 1 || force_cfg == 6 ? force_cfg : wide ? 6 : 1);
+    *name = !classes ? kMfmaConfigs[cfg].name : cfg == 1 ? "mfma_128x128x64_w2x2_s2_classes" : "mfma_128x128x64_w2x2_s4_classes";
+    const int group_m = group_m_override() > 0 ? group_m_override() : 8;
+    return p.in_dtype == DT_BF16 ? launch_mfma_bf16(p, stream, cfg, group_m) : launch_mfma_f16(p, stream, cfg, group_m);
 }
 
 hipError_t launch_mfma(const Problem& p, hipStream_t stream, int force_cfg, const char** name) {
@@ -143,11 +175,11 @@ hipError_t launch_mfma(const Problem& p, hipStream_t stream, int force_cfg, cons
         const int gm = group_m_override() > 0 ? group_m_override() : 8;
         return launch_mfma_int8(p, stream, c, gm);
     }
+    if (p.is_conv && p.conv.transposed) return launch_convt(p, stream, force_cfg, name);
     int cfg = (force_cfg >= 0 && force_cfg < kNumMfmaConfigs) ? force_cfg : choose_config(p);
-    if (p.is_conv && p.conv.transposed && cfg != 0 && cfg != 1 && cfg != 2 && cfg != 6) cfg = choose_config(p);   // the ones built
     if (!fp8 && (cfg == 3 || cfg == 4 || cfg == 8)) cfg = choose_config(p);   // 16-bit types: 0, 1, 2, 5, 6, 7, 9 are built
-    // 9 takes a convolution whose channel count is a multiple of 64 (not the transposed form)
-    if (cfg == 9 && p.is_conv && (p.conv.transposed || p.conv.Cin % 64 != 0)) cfg = 7;
+    // 9 takes a convolution whose channel count is a multiple of 64
+    if (cfg == 9 && p.is_conv && p.conv.Cin % 64 != 0) cfg = 7;
     if (fp8) {
         // the FP8 instruction consumes a 64-deep k-tile (in 2-byte units) in two steps:
         // only the 64-deep configurations are built for it

@@ -51,7 +51,7 @@ typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
 
 #define PBK_LDS_PTR(T, p) ((__attribute__((address_space(3))) T*)(p))
 
-enum : int { MODE_DENSE = 0, MODE_TRANS_B = 1, MODE_CONV = 2, MODE_CONVT = 3 };
+enum : int { MODE_DENSE = 0, MODE_TRANS_B = 1, MODE_CONV = 2, MODE_CONVT = 3, MODE_CONVT_ALL = 4 };
 
 // buffer offsets at or above this are out of range for every descriptor we
 // build (num_records = 2^31): the load returns zeros
@@ -175,9 +175,36 @@ struct TileMap {
     int tiles_m, tiles_n, tiles_per_batch, total;
     int group_m;
     int xcds;
-    // transposed convolution only (see ConvTClass): residue classes along h and w, and the distance of the
-    // filter taps that meet one class
-    int ct_nh, ct_nw, ct_step_h, ct_step_w;
+};
+
+// Quotient and remainder by a divisor that the host knows, for numerators 0 <= n < 2^31: the multiplier floor((2^32 - 1) / d) gives
+// the quotient or one less.  (An integer division by a variable is some 35 dependent instructions; this is six.)
+struct FastDiv {
+    unsigned magic;
+    int d;
+    static FastDiv of(int d) { return FastDiv{0xFFFFFFFFu / (unsigned)d, d}; }
+    __host__ __device__ __forceinline__ int div(int n, int& rem) const {
+        int q = (int)(((unsigned long long)(unsigned)n * magic) >> 32);
+        rem = n - q * d;
+        if (rem >= d) { ++q; rem -= d; }
+        return q;
+    }
+};
+
+// Transposed convolution (see ConvTClass): the part of the class geometry that the host works out, along h or w.
+struct ConvTAxis {
+    int classes;               // min(stride, output size)
+    FastDiv stride, step;      // step: distance of the filter taps that meet one class
+    int d;                     // input rows between two such taps: <= 0
+    int lift;                  // lift * stride is at least the filter's extent: keeps a numerator from being negative
+    int n, full;               // output rows of the classes below `full`; the others have one less
+};
+struct TileMapConvT : TileMap {
+    ConvTAxis h, w;
+    int images;
+    FastDiv classes, classes_w, cin;
+    FastDiv pix[2][2], ow[2];  // by output rows x columns, and columns, of a class; [1]: of the classes with one less
+    FastDiv taps_w[2];         // by the number of taps along w: KW / step, and one more
 };
 
 __device__ __forceinline__ void map_tile(const TileMap& tm, int bid, int& b, int& tile_m, int& tile_n) {
@@ -278,21 +305,25 @@ template <> __device__ __forceinline__ uint32_t pack2<f16_t>(float a, float b) {
 // convolution at stride 1 whose taps walk the image backwards.  A workgroup's tile lies inside one class, so the k loop
 // holds only the taps that contribute: 1 / (stride_h stride_w) of the filter.  (With all taps in the loop and the
 // others' pieces zero-filled, 32 x 28 x 28 x 256 -> 128, 4 x 4, stride 2, took 196 us.)
+// The class is worked out once per workgroup and the row of C once per stored piece.  With divisions by variables there, a call with
+// a short contraction paid some 2 us for them (4 x 16 x 16 x 8 -> 8, 2 x 2, stride 2: 11.8 us, 10.0 with multipliers from the host; all
+// taps 7.2).
+// Where the classes shorten the k loop by little, all taps stay in it (MODE_CONVT_ALL; the rule is convt_by_class).
 struct ConvTClass {
-    int oh_n, ow_n;            // output rows and columns of the class
-    int rows;                  // GEMM rows: images x oh_n x ow_n
+    int rows;                  // GEMM rows: images x output rows x columns of the class
     int ph, pw;
     int kh0, kw0, nh, nw;      // first tap and number of taps along h and w
     int ih_base, iw_base;      // input row of output row ph for tap kh0
-    int dh, dw;                // input rows (columns) between successive taps of the class: <= 0
 };
-__device__ __forceinline__ void convt_axis(int phase, int pad, int stride, int dil, int ktaps, int step,
-                                           int& k0, int& n, int& base, int& d) {
-    k0 = 0;
-    while (k0 < step && k0 < ktaps && (phase + pad - k0 * dil) % stride != 0) ++k0;
-    n = (k0 < step && k0 < ktaps) ? (ktaps - 1 - k0) / step + 1 : 0;
-    base = (phase + pad - k0 * dil) / stride;       // exact where n > 0
-    d = -(dil * step / stride);
+__device__ __forceinline__ void convt_axis(const ConvTAxis& ax, int phase, int pad, int dil, int ktaps, int& k0, int& n, int& base) {
+    const int last = ax.step.d < ktaps ? ax.step.d : ktaps, x = phase + pad + ax.lift * ax.stride.d;
+    int q = 0, rem;
+    n = 0;
+    for (k0 = 0; k0 < last; ++k0) {
+        q = ax.stride.div(x - k0 * dil, rem);
+        if (rem == 0) { n = ax.step.div(ktaps - 1 - k0, rem) + 1; break; }
+    }
+    base = q - ax.lift;                             // exact where n > 0
 }
 
 // Which row of C a row of the tile grid is: the same one, except for the classes of a transposed convolution.
@@ -305,11 +336,13 @@ struct RowsPlain {
 struct RowsConvT {
     static constexpr bool kPlain = false;
     int m;
-    int oh_n, ow_n, ph, pw, sh, sw, OH, OW;
+    bool one;                                       // a single class: its rows are C's
+    FastDiv pix, ow_n;
+    int ph, pw, sh, sw, OH, OW;
     __device__ __forceinline__ int64_t at(int row) const {
-        const int pix = oh_n * ow_n;
-        const int n = row / pix, rem = row - n * pix;
-        const int oh = rem / ow_n, ow = rem - oh * ow_n;
+        if (one) return row;
+        int rem, ow;
+        const int n = pix.div(row, rem), oh = ow_n.div(rem, ow);
         return ((int64_t)n * OH + oh * sh + ph) * OW + ow * sw + pw;
     }
 };
@@ -624,6 +657,11 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
     __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
 
+// (an expression with the unnamed enum of the modes in a kernel's signature would be mangled differently on host and device)
+template <int MODE> struct TileMapSel { typedef TileMap type; };
+template <> struct TileMapSel<MODE_CONVT> { typedef TileMapConvT type; };
+template <int MODE> using TileMapOf = typename TileMapSel<MODE>::type;
+
 // OCC: workgroups of this kernel meant to share a CU (bounds the register budget)
 // T: operand type fed to the MFMA; TO: 16-bit output type (used when out_dtype is not F32).
 // Sizes BK, lda, ldb, K and the batch strides are in 2-byte units whatever T is: for the FP8
@@ -639,7 +677,7 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
 // piece of the image then lies inside one filter tap.
 template <typename T, typename TO, int BM, int BN, int BK, int WM, int WN, int MODE, int NSTAGE, int OCC, int MI = 32,
           int ASTG = 0>
-__global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mfma_kernel(Problem p, TileMap tmap) {
+__global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mfma_kernel(Problem p, TileMapOf<MODE> tmap) {
     constexpr bool S16 = MI == 16;
     constexpr bool ADBL = ASTG != 0;          // A staged 64 deep
     constexpr bool PAIRB = ASTG == 2;         // ... with one barrier per pair of k-tiles
@@ -655,7 +693,8 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
                                             (F8PAIR && MODE == MODE_TRANS_B))),
                   "16x16 blocks are built for the 16-bit types and for 8-bit types with both operands k-major");
     constexpr bool CONVT = MODE == MODE_CONVT;               // transposed convolution, by residue classes (ConvTClass)
-    constexpr bool CONV = MODE == MODE_CONV || CONVT;        // A is an image, rows are output pixels
+    constexpr bool CONVA = MODE == MODE_CONVT_ALL;           // transposed convolution, all taps for every output pixel
+    constexpr bool CONV = MODE == MODE_CONV || CONVT || CONVA;   // A is an image, rows are output pixels
     constexpr bool TRANS_B = MODE == MODE_TRANS_B;
     constexpr int NW = WM * WN;
     constexpr int WTM = BM / WM, WTN = BN / WN;
@@ -668,7 +707,7 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
     // fp32: a unit is half a value; the n-major B tile has BK/2 rows of BN floats and is read with
     // plain 4-byte LDS reads (32 lanes along n)
     constexpr bool E4 = sizeof(T) == 4;
-    static_assert(sizeof(T) == 2 || MODE != MODE_CONVT, "transposed convolution is built for 16-bit types only");
+    static_assert(sizeof(T) == 2 || (MODE != MODE_CONVT && MODE != MODE_CONVT_ALL), "transposed convolution is built for 16-bit types only");
     constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2;
     constexpr int STAGE = A_BYTES + B_BYTES;
     constexpr int A_BLKS = BM * BKA * 2 / 1024, B_BLKS = B_BYTES / 1024;     // 1 KiB per wave-load
@@ -693,20 +732,23 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
     // geometry of the rows and of the k axis: the problem's, or the tile's residue class's (ConvTClass)
     ConvTClass ct;
     int Mrows = p.M, Kall = p.K;
-    int row_oh = p.conv.OH, row_ow = p.conv.OW, tap_w = p.conv.KW, tap_dh = p.conv.dil_h, tap_dw = p.conv.dil_w;
+    int tap_w = p.conv.KW, tap_dh = p.conv.dil_h, tap_dw = p.conv.dil_w;
+    FastDiv by_pix{}, by_ow{}, by_taps_w{};
     if constexpr (CONVT) {
-        const int ncls = tmap.ct_nh * tmap.ct_nw;       // classes fastest: those of one region read the same pixels
-        const int cls = tile_m % ncls;
-        tile_m /= ncls;
-        ct.ph = cls / tmap.ct_nw; ct.pw = cls - ct.ph * tmap.ct_nw;
-        ct.oh_n = (p.conv.OH - ct.ph + p.conv.stride_h - 1) / p.conv.stride_h;
-        ct.ow_n = (p.conv.OW - ct.pw + p.conv.stride_w - 1) / p.conv.stride_w;
-        ct.rows = p.M / (p.conv.OH * p.conv.OW) * ct.oh_n * ct.ow_n;
-        convt_axis(ct.ph, p.conv.pad_h, p.conv.stride_h, p.conv.dil_h, p.conv.KH, tmap.ct_step_h, ct.kh0, ct.nh, ct.ih_base, ct.dh);
-        convt_axis(ct.pw, p.conv.pad_w, p.conv.stride_w, p.conv.dil_w, p.conv.KW, tmap.ct_step_w, ct.kw0, ct.nw, ct.iw_base, ct.dw);
+        const int tile = tile_m;
+        int cls;                                        // classes fastest: those of one region read the same pixels
+        tile_m = tmap.classes.div(tile, cls);
+        ct.ph = tmap.classes_w.div(cls, ct.pw);
+        const bool less_h = ct.ph >= tmap.h.full, less_w = ct.pw >= tmap.w.full;
+        by_pix = less_h ? (less_w ? tmap.pix[1][1] : tmap.pix[1][0]) : (less_w ? tmap.pix[0][1] : tmap.pix[0][0]);
+        by_ow = less_w ? tmap.ow[1] : tmap.ow[0];
+        ct.rows = tmap.images * by_pix.d;
         if (tile_m * BM >= ct.rows) return;             // the grid is sized by the largest class
+        convt_axis(tmap.h, ct.ph, p.conv.pad_h, p.conv.dil_h, p.conv.KH, ct.kh0, ct.nh, ct.ih_base);
+        convt_axis(tmap.w, ct.pw, p.conv.pad_w, p.conv.dil_w, p.conv.KW, ct.kw0, ct.nw, ct.iw_base);
+        by_taps_w = ct.nw == tmap.taps_w[1].d ? tmap.taps_w[1] : tmap.taps_w[0];
         Mrows = ct.rows; Kall = ct.nh * ct.nw * p.conv.Cin;
-        row_oh = ct.oh_n; row_ow = ct.ow_n; tap_w = ct.nw; tap_dh = ct.dh; tap_dw = ct.dw;
+        tap_w = ct.nw; tap_dh = tmap.h.d; tap_dw = tmap.w.d;
     }
     const int m0 = tile_m * BM, n0 = tile_n * BN;
 
@@ -745,17 +787,26 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
         int gm = m0 + row;
         a_ok[r] = gm < Mrows;
         if (CONV) {
-            int pix = row_oh * row_ow;
             int gmc = a_ok[r] ? gm : 0;
-            int n = gmc / pix;
-            int rem = gmc - n * pix;
-            int oh = rem / row_ow;
-            int ow = rem - oh * row_ow;
-            a_ih0[r] = CONVT ? oh + ct.ih_base : oh * p.conv.stride_h - p.conv.pad_h;
-            a_iw0[r] = CONVT ? ow + ct.iw_base : ow * p.conv.stride_w - p.conv.pad_w;
+            int n, oh, ow;
+            if constexpr (CONVT) {
+                int rem;
+                n = by_pix.div(gmc, rem);
+                oh = by_ow.div(rem, ow);
+            } else {
+                int pix = p.conv.OH * p.conv.OW;
+                n = gmc / pix;
+                int rem = gmc - n * pix;
+                oh = rem / p.conv.OW;
+                ow = rem - oh * p.conv.OW;
+            }
+            // (all taps: output row oh receives tap kh from input row (oh + pad - kh dil) / stride, if that divides)
+            a_ih0[r] = CONVT ? oh + ct.ih_base : CONVA ? oh + p.conv.pad_h : oh * p.conv.stride_h - p.conv.pad_h;
+            a_iw0[r] = CONVT ? ow + ct.iw_base : CONVA ? ow + p.conv.pad_w : ow * p.conv.stride_w - p.conv.pad_w;
             // byte offset of pixel (n, ih0, iw0), channel 0, modulo 2^32: it may lie in front of the image or, for a class of a
             // transposed convolution, beyond it by (KH - 1) dil / stride rows; adding the tap's offset brings it back
-            a_voff[r] = ((unsigned)(n * p.conv.H + a_ih0[r]) * (unsigned)p.conv.W + (unsigned)a_iw0[r]) * (unsigned)(p.conv.Cin * 2);
+            if (CONVA) a_voff[r] = (unsigned)(n * p.conv.H * p.conv.W * p.conv.Cin * 2);             // the image's first pixel
+            else a_voff[r] = ((unsigned)(n * p.conv.H + a_ih0[r]) * (unsigned)p.conv.W + (unsigned)a_iw0[r]) * (unsigned)(p.conv.Cin * 2);
         } else {
             a_voff[r] = a_ok[r] ? (unsigned)(row * (int)p.lda * 2 + chunk * 16) : kOob;
         }
@@ -814,7 +865,8 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
 
     // Convolution: filter tap (kh, kw) and first channel of the current k-tile,
     // advanced incrementally (uniform) when a k-tile lies inside one tap.
-    const bool one_tap = CONV && (p.conv.Cin % BK) == 0;
+    // (a class that a single tap meets has no other)
+    const bool one_tap = CONV && ((p.conv.Cin % BK) == 0 || (CONVT && Kall == p.conv.Cin));
     int tap_kh = 0, tap_kw = 0, tap_c = 0;
 
     // State of the k-tile whose loads are being issued (uniform across the wave).
@@ -823,9 +875,11 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
     int4v ld_ra = make_rsrc(a_tile), ld_rb = make_rsrc(b_tile);
     int ld_dh = 0, ld_dw = 0;
     unsigned ld_delta = 0;
+    int ld_c = 0;              // all taps of a transposed convolution, one per k-tile: first channel of the tile
     // transposed convolution: weight row of the class's tap (i, j), channel c
     auto convt_brow = [&](int i, int j, int c) {
-        return ((ct.kh0 + i * tmap.ct_step_h) * p.conv.KW + ct.kw0 + j * tmap.ct_step_w) * p.conv.Cin + c;
+        if constexpr (CONVT) return ((ct.kh0 + i * tmap.h.step.d) * p.conv.KW + ct.kw0 + j * tmap.w.step.d) * p.conv.Cin + c;
+        else return 0;
     };
 
     // Start issuing the k-tile at k0 into `stage`: descriptors rebased to k0.
@@ -837,6 +891,7 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
         if (CONV) {
             ld_dh = tap_kh * tap_dh; ld_dw = tap_kw * tap_dw;
             ld_delta = ((unsigned)ld_dh * (unsigned)p.conv.W + (unsigned)ld_dw) * (unsigned)(p.conv.Cin * 2) + (unsigned)(tap_c * 2);
+            if (CONVA) ld_c = tap_c;
             if (CONVT) brow = one_tap ? convt_brow(tap_kh, tap_kw, tap_c) : 0;
             if (one_tap) {              // advance the uniform tap state to the next k-tile
                 tap_c += BK;
@@ -859,17 +914,35 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
         constexpr bool TAIL = decltype(tail_tag)::value;
         if (r < CA) {
             unsigned off;
-            if (CONV) {
+            if (CONVA) {
+                int dh = ld_dh, dw = ld_dw, c = ld_c + a_kofs[r];
+                if (!one_tap) {
+                    const int k = ld_k0 + a_kofs[r], tap = k / p.conv.Cin, kh = tap / p.conv.KW;
+                    c = k - tap * p.conv.Cin;
+                    dh = kh * p.conv.dil_h; dw = (tap - kh * p.conv.KW) * p.conv.dil_w;
+                }
+                const int th = a_ih0[r] - dh, tw = a_iw0[r] - dw;
+                const int ih = th / p.conv.stride_h, iw = tw / p.conv.stride_w;
+                bool ok = a_ok[r] && th >= 0 && tw >= 0 && ih * p.conv.stride_h == th && iw * p.conv.stride_w == tw &&
+                          ih < p.conv.H && iw < p.conv.W;
+                if (TAIL) ok = ok && (ld_k0 + a_kofs[r] < Kall);
+                off = ok ? a_voff[r] + (unsigned)(((ih * p.conv.W + iw) * p.conv.Cin + c) * 2) : kOob;
+            } else if (CONV) {
                 int dh, dw;
                 if (one_tap) {
                     dh = ld_dh; dw = ld_dw;
                     off = a_voff[r] + ld_delta + (unsigned)(a_kofs[r] * 2);
                 } else {
                     int k = ld_k0 + a_kofs[r];
-                    int tap = k / p.conv.Cin;
-                    int c = k - tap * p.conv.Cin;
-                    int kh = tap / tap_w;
-                    int kw = tap - kh * tap_w;
+                    int c, kh, kw;
+                    if constexpr (CONVT) {
+                        kh = by_taps_w.div(tmap.cin.div(k, c), kw);
+                    } else {
+                        int tap = k / p.conv.Cin;
+                        c = k - tap * p.conv.Cin;
+                        kh = tap / tap_w;
+                        kw = tap - kh * tap_w;
+                    }
                     dh = kh * tap_dh; dw = kw * tap_dw;
                     off = a_voff[r] + ((unsigned)dh * (unsigned)p.conv.W + (unsigned)dw) * (unsigned)(p.conv.Cin * 2) + (unsigned)(c * 2);
                 }
@@ -885,10 +958,13 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
         } else {
             const int rb = r - CA;
             unsigned off = b_voff[rb];
-            if (CONVT && !one_tap && off != kOob) {
-                // the piece's k-row of the class's k axis -> its row of the weights
-                const int k = ld_k0 + b_kofs[rb], tap = k / p.conv.Cin, i = tap / tap_w;
-                off += (unsigned)((convt_brow(i, tap - i * tap_w, k - tap * p.conv.Cin) - b_kofs[rb]) * (int)p.ldb * 2);
+            if constexpr (CONVT) {
+                if (!one_tap && off != kOob) {
+                    // the piece's k-row of the class's k axis -> its row of the weights
+                    int c, j;
+                    const int i = by_taps_w.div(tmap.cin.div(ld_k0 + b_kofs[rb], c), j);
+                    off += (unsigned)((convt_brow(i, j, c) - b_kofs[rb]) * (int)p.ldb * 2);
+                }
             }
             if (TAIL && ld_k0 + b_kofs[rb] >= Kall) off = kOob;
             dma16(ld_rb, ld_sb + (wave * CB + rb) * 1024, off);
@@ -1786,7 +1862,7 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
     char* wlds = lds + wave * ((NSTAGE * STAGE) / NW);
     typedef typename std::conditional<CONVT, RowsConvT, RowsPlain>::type Rows;
     Rows rows;
-    if constexpr (CONVT) rows = Rows{Mrows, ct.oh_n, ct.ow_n, ct.ph, ct.pw, p.conv.stride_h, p.conv.stride_w, p.conv.OH, p.conv.OW};
+    if constexpr (CONVT) rows = Rows{Mrows, tmap.classes.d == 1, by_pix, by_ow, ct.ph, ct.pw, p.conv.stride_h, p.conv.stride_w, p.conv.OH, p.conv.OW};
     else rows = Rows::of(p);
     EpiCtx<TO, AccV, FM, FN, WTM, WTN, (NSTAGE * STAGE) / NW, Rows> ctx{p, acc, wlds, m0 + wm * WTM, n0 + wn * WTN, lane,
                                                                (int64_t)b * p.stride_c, rows};

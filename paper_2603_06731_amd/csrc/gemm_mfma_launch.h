@@ -60,6 +60,37 @@ inline long long convt_row_tiles(const Problem& p, int bm) {
     return (rows + bm - 1) / bm * classes;
 }
 
+inline ConvTAxis convt_axis_of(int O, int stride, int dil, int ktaps) {
+    int g = stride;
+    for (int b = dil; b;) { const int r = g % b; g = b; b = r; }             // gcd(stride, dil)
+    ConvTAxis a{};
+    a.classes = stride < O ? stride : O;
+    a.stride = FastDiv::of(stride);
+    a.step = FastDiv::of(stride / g);
+    a.d = -(dil / g);
+    a.lift = (ktaps * dil + stride - 1) / stride;
+    a.n = (O + stride - 1) / stride;
+    a.full = O - (a.n - 1) * stride;
+    return a;
+}
+
+inline void convt_geometry(const Problem& p, TileMapConvT* t) {
+    const ConvGeom& g = p.conv;
+    t->h = convt_axis_of(g.OH, g.stride_h, g.dil_h, g.KH);
+    t->w = convt_axis_of(g.OW, g.stride_w, g.dil_w, g.KW);
+    t->images = (int)(p.M / ((long long)g.OH * g.OW));
+    t->classes = FastDiv::of(t->h.classes * t->w.classes);
+    t->classes_w = FastDiv::of(t->w.classes);
+    t->cin = FastDiv::of(g.Cin);
+    auto at_least_1 = [](int v) { return v > 1 ? v : 1; };                   // (no class has none: not reached)
+    for (int j = 0; j < 2; ++j) {
+        const int cols = at_least_1(t->w.n - j);
+        t->ow[j] = FastDiv::of(cols);
+        for (int i = 0; i < 2; ++i) t->pix[i][j] = FastDiv::of(at_least_1(t->h.n - i) * cols);
+        t->taps_w[j] = FastDiv::of(at_least_1(g.KW / t->w.step.d + j));
+    }
+}
+
 template <typename T, typename TO, int BM, int BN, int BK, int WM, int WN, int MODE, int NSTAGE, int OCC, int MI = 32,
           int ASTG = 0>
 hipError_t launch_one(const Problem& p, hipStream_t stream, int group_m) {
@@ -75,19 +106,14 @@ hipError_t launch_one(const Problem& p, hipStream_t stream, int group_m) {
         if (e != hipSuccess) return e;
         attr_done.fetch_or(bit, std::memory_order_release);
     }
-    TileMap tm{};
+    TileMapOf<MODE> tm{};
     tm.tiles_m = (p.M + BM - 1) / BM;
     tm.tiles_n = (p.N + BN - 1) / BN;
-    if (MODE == MODE_CONVT) {
-        const ConvGeom& g = p.conv;
-        auto gcd = [](int a, int b) { while (b) { const int r = a % b; a = b; b = r; } return a; };
-        tm.ct_nh = g.stride_h < g.OH ? g.stride_h : g.OH;
-        tm.ct_nw = g.stride_w < g.OW ? g.stride_w : g.OW;
-        tm.ct_step_h = g.stride_h / gcd(g.stride_h, g.dil_h);
-        tm.ct_step_w = g.stride_w / gcd(g.stride_w, g.dil_w);
+    if constexpr (MODE == MODE_CONVT) {
         const long long tiles = convt_row_tiles(p, BM);
         if (tiles * tm.tiles_n > 0x7FFFFFFFLL) return hipErrorInvalidValue;
         tm.tiles_m = (int)tiles;
+        convt_geometry(p, &tm);
     }
     tm.tiles_per_batch = tm.tiles_m * tm.tiles_n;
     long long total = (long long)tm.tiles_per_batch * p.batch;
@@ -116,9 +142,13 @@ hipError_t launch_modes(const Problem& p, hipStream_t stream, int group_m) {
         return launch_one<T, T, BM, BN, BK, WM, WN, MODE_DENSE, NSTAGE, OCC, MI, ASTG>(p, stream, group_m);
     } else {
     if (p.is_conv && p.conv.transposed) {
-        // the transposed form is built for the tile shapes the dispatcher picks: configurations 0, 1, 2 and 6
-        if constexpr ((BM == 128 && BN == 256 && BK == 32) || (BM == 128 && BN == 128 && BK == 64))
-            return launch_one<T, T, BM, BN, BK, WM, WN, MODE_CONVT, NSTAGE, OCC, MI>(p, stream, group_m);
+        // by residue classes (2): configurations 1 and 2; all taps (1): configurations 0, 1 and 6
+        if constexpr (BM == 128 && BN == 128 && BK == 64) {
+            if (p.conv.transposed == 2) return launch_one<T, T, BM, BN, BK, WM, WN, MODE_CONVT, NSTAGE, OCC, MI>(p, stream, group_m);
+        }
+        if constexpr ((BM == 128 && BN == 256 && BK == 32) || (BM == 128 && BN == 128 && BK == 64 && NSTAGE == 2))
+            return p.conv.transposed == 2 ? hipErrorInvalidValue
+                                          : launch_one<T, T, BM, BN, BK, WM, WN, MODE_CONVT_ALL, NSTAGE, OCC, MI>(p, stream, group_m);
         else
             return hipErrorInvalidValue;
     }

@@ -19,6 +19,7 @@ struct ConvGeom {
     // 0: row (n, oh, ow) reads input rows oh*stride - pad + kh*dil.
     // 1: transposed convolution in gather form: it reads input row (oh + pad - kh*dil)/stride
     //    for the taps where the division is exact.
+    // 2: the same, rows walked by residue classes (set inside the matrix-unit path only).
     int transposed;
 };
 

@@ -216,17 +216,6 @@ def test_force_kernel_ids(pbk):
         pbk.pbk_force_kernel(None)
 
 
-def test_transposed_convolution_with_more_classes_than_a_launch_holds(pbk):
-    """Residue classes of a stride of 4096 over a 2 x 2 image: 2^24 tiles of 256 threads.  The matrix-unit path declines before the launch."""
-    BF16 = 1
-    P = 0x1000
-    try:
-        assert pbk.pbk_force_kernel("mfma") == 0
-        assert pbk.pbk_conv2d_transpose_nhwc(P, P, P, None, 1, 2, 2, 8, 8, 1, 1, 4096, 4096, 0, 0, 0, 0, 1, 1, BF16, BF16, 1.0, 0) == 7
-    finally:
-        pbk.pbk_force_kernel(None)
-
-
 def test_int8_unfolded_batch_norm_argument_errors(pbk):
     P = 0x1000
     mm = pbk.pbk_matmul_int8_bn

@@ -41,6 +41,20 @@ def test_residue_classes(case, dtype, out_dtype, cfg):
     assert err <= T.TIGHT[out_dtype], err        # the bound of the output rounding, as for every convolution
 
 
+@pytest.mark.parametrize("cfg", [0, 1, 2, 6])
+@pytest.mark.parametrize("case", [
+    (2, 9, 7, 32, 40, 2, 2, (2, 2), (0, 0), (0, 0), (1, 1)),        # one tap per class, half a k-tile of channels
+    (3, 11, 5, 72, 136, 2, 2, (2, 2), (0, 0), (1, 0), (1, 1)),      # ... a k-tile and a ragged one; classes of unequal size
+    (2, 13, 12, 8, 264, 1, 1, (1, 1), (0, 0), (0, 0), (1, 1)),      # a single class: rows of C in order
+    (1, 6, 9, 200, 72, 3, 3, (3, 4), (1, 1), (0, 0), (2, 3)),       # three k-tiles of 64 and a remainder; classes without a tap
+    (2, 10, 9, 40, 48, 3, 5, (2, 2), (1, 2), (1, 1), (1, 1)),       # classes of one tap beside classes of two, three and six
+    (1, 1, 300, 24, 32, 2, 3, (4, 2), (0, 1), (0, 0), (1, 1)),      # one image row, stride beyond the output along h
+])
+def test_single_tap_classes(case, cfg):
+    """A class that one tap meets walks its channels as they are, whatever their number."""
+    test_residue_classes(case, BF16, BF16, cfg)
+
+
 def transpose(x, w, bias, geom, force=None):
     """geom: n, H, W, Cin, Cout, KH, KW, stride, pad, dil; bf16 operands, bias epilogue.  Returns (y, kernel name)."""
     import torch
@@ -68,33 +82,71 @@ def close(got, ref):
     return bool(((got.float() - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-4).all())
 
 
-def test_rows_far_beyond_the_image():
+@pytest.mark.parametrize("cfg", [1, 2])
+def test_rows_far_beyond_the_image(cfg):
     """A dilation that puts the last tap's rows 2^31 bytes behind the image: the class's pixel offsets wrap and the tap's offset brings
     them back."""
     dil, taps = 4096, 5
     geom = (1, 4, 1, 65536, 8, taps, 1, (1, 1), (0, 0), (dil, 1))
     assert (taps - 1) * dil * 65536 * 2 >= 2 ** 31
     x, w, bias = operands(geom, 1)
-    y, kern = transpose(x, w, bias, geom, "mfma")
-    assert "mfma" in kern, kern
+    y, kern = transpose(x, w, bias, geom, f"mfma:{cfg}")
+    assert ("classes" in kern) == (cfg == 2), kern
     ref = bias.double().expand(y.shape[1], 8).clone()
     for kh in range(taps):
         ref[kh * dil:kh * dil + 4] += x[0, :, 0].double() @ w[kh, 0].double()
     assert close(y[0, :, 0], ref)
 
 
-def test_more_classes_than_a_launch_holds():
-    """A stride of 4096 over a 2 x 2 image: 2^24 classes, one tile of 256 threads each.  The matrix-unit kernel declines and the call runs."""
-    s = 4096
-    geom = (1, 2, 2, 8, 8, 1, 1, (s, s), (0, 0), (1, 1))
+@pytest.mark.parametrize("force", [None, "mfma:2"])
+def test_more_classes_than_a_launch_holds(force):
+    """A stride of 4096 over a 2 x 2 image: 2^24 classes, one tile of 256 threads each.  All taps then, on the same matrix units."""
+    s, Cin = 4096, 128
+    geom = (1, 2, 2, Cin, 8, 2, 2, (s, s), (0, 0), (1, 1))
     x, w, bias = operands(geom, 2)
-    y, kern = transpose(x, w, bias, geom)
-    assert "mfma" not in kern, kern
-    at = [(0, 0), (0, s), (s, 0), (s, s)]
-    for i, (oh, ow) in enumerate(at):
-        assert close(y[0, oh, ow], bias + x.reshape(4, 8)[i].float() @ w[0, 0].float())
-        y[0, oh, ow] = bias.bfloat16()
+    y, kern = transpose(x, w, bias, geom, force)
+    assert "mfma" in kern and "classes" not in kern, kern
+    for ih in range(2):
+        for iw in range(2):
+            for kh in range(2):
+                for kw in range(2):
+                    at = y[0, ih * s + kh, iw * s + kw]
+                    assert close(at, bias + x[0, ih, iw].float() @ w[kh, kw].float()), (ih, iw, kh, kw)
+                    at.copy_(bias)
     assert bool((y == bias.bfloat16()).all())
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_residue_classes_ring(case):
+    """The classes themselves, also where the automatic choice keeps all taps in the loop."""
+    import paper_2603_06731_amd as pbk
+    test_residue_classes(case, F16, F16, 2)
+    assert "classes" in pbk.pbk_last_kernel(), pbk.pbk_last_kernel()
+
+
+@pytest.mark.parametrize("n,hw,Cin,Cout,k,stride,dil,kernel", [
+    (2, 14, 40, 64, 2, 2, 1, "s2"), (2, 14, 48, 64, 2, 2, 1, "classes"),         # saved 120, 144
+    (2, 14, 512, 64, 1, 2, 1, "s2"), (2, 14, 64, 64, 3, 1, 1, "s2"), (2, 14, 64, 64, 3, 2, 2, "s2"),      # nothing saved
+    (2, 14, 64, 64, 3, 4, 2, "classes"),                                         # a stride that shares a factor with the dilation
+    (8, 64, 64, 256, 2, 2, 1, "128x256x32"), (8, 64, 128, 256, 2, 2, 1, "classes"),                         # wide tiles: saved 192, 384
+    (8, 64, 208, 256, 2, 2, 1, "128x256x32"), (8, 64, 216, 256, 2, 2, 1, "classes"),                        # ... channels across k-tiles: 624, 648
+    (8, 64, 56, 248, 2, 2, 1, "classes"), (1, 32, 56, 256, 2, 2, 1, "classes"),  # not wide: columns, tiles
+])
+def test_dispatch(n, hw, Cin, Cout, k, stride, dil, kernel):
+    """Classes or all taps, with the automatic choice, on either side of each line."""
+    import torch
+    geom = (n, hw, hw, Cin, Cout, k, k, (stride, stride), (0, 0), (dil, dil))
+    x, w, bias = operands(geom, 5)
+    y, kern = transpose(x, w, bias, geom)
+    assert kern.endswith(kernel) or (kernel[0] == "1" and kernel in kern), kern
+    # image 0: every input pixel painted through every tap
+    E = (hw - 1) * stride + 1
+    ref = bias.expand(y.shape[1], y.shape[2], Cout).clone()
+    for kh in range(k):
+        for kw in range(k):
+            part = x[0].reshape(hw * hw, Cin).float() @ w[kh, kw].float()
+            ref[kh * dil:kh * dil + E:stride, kw * dil:kw * dil + E:stride] += part.reshape(hw, hw, Cout)
+    assert close(y[0], ref)
 
 
 def test_weights_of_2_gib():
