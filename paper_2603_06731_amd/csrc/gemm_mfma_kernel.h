@@ -521,10 +521,10 @@ struct EpiCtx {
     // ---- int8 path: the accumulators are 32-bit integers; quantised epilogue, stores straight
     // from registers (4 consecutive columns per lane: one dword of int8 codes, or 16 bytes of fp32)
     // WM_ x WN_ waves form the workgroup tile; lds_all: the workgroup's LDS (free after the k loop, at least
-    // one byte per element of the tile); wm, wn: this wave's place
+    // one byte per element of the tile); wm, wn: this wave's place; table: the columns' parameters (QuantColumn::put)
     // PATH 0: any parameters (a division per element and step); 1 + HAS_MID + 2 HAS_BN: both steps allow the
     // reciprocal sequence, the element code is free of branches
-    template <int WM_, int WN_, int PATH> __device__ __forceinline__ void run_quant(char* lds_all, int wm, int wn) {
+    template <int WM_, int WN_, int PATH> __device__ __forceinline__ void run_quant(char* lds_all, const float* table, int wm, int wn) {
         constexpr bool FAST = PATH > 0, F_MID = ((PATH - 1) & 1) != 0, F_BN = ((PATH - 1) & 2) != 0;
         const bool out_i8 = p.out_dtype == DT_INT8;
         const bool has_bias = p.bias != nullptr, has_mul = p.q_mul != nullptr, has_add = p.q_add != nullptr;
@@ -548,17 +548,13 @@ struct EpiCtx {
             for (int g = 0; g < G; ++g) {
                 const int lcol = lcol_of(j, g);
                 const int gn = col0 + lcol;
+                const float* col = table + wn * WTN + lcol;
+                f32x4 v[QuantColumn::kValues];
+#pragma unroll
+                for (int k = 0; k < QuantColumn::kValues; ++k) v[k] = *(const f32x4*)(col + k * WN_ * WTN);
                 QuantParams c[4];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const bool in = gn + e < p.N;
-                    c[e].scale = in ? p.q_scale[gn + e] : 0.0f;
-                    c[e].bias = (in && has_bias) ? p.bias[gn + e] : (FAST ? -0.0f : 0.0f);
-                    c[e].mul = (in && has_mul) ? p.q_mul[gn + e] : 1.0f;
-                    c[e].add = (in && has_add) ? p.q_add[gn + e] : (FAST ? -0.0f : 0.0f);
-                    c[e].mean = (in && has_bn) ? p.q_mean[gn + e] : 0.0f;
-                    c[e].rinv = (in && has_bn) ? bn_rinv(p.q_var[gn + e], p.q_eps) : 1.0f;
-                }
+                for (int e = 0; e < 4; ++e) c[e] = QuantParams{v[0][e], v[1][e], v[2][e], v[3][e], v[4][e], v[5][e]};
 #pragma unroll
                 for (int i = 0; i < FM; ++i) {
                     const int lrow = lrow_of(i);
@@ -751,6 +747,9 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
         tap_w = ct.nw; tap_dh = tmap.h.d; tap_dw = tmap.w.d;
     }
     const int m0 = tile_m * BM, n0 = tile_n * BN;
+    constexpr bool INT8 = E8 && CH == 1;
+    QuantColumn qcol;                       // of column n0 + t, for the epilogue: on its way while the k loop runs
+    if constexpr (INT8) qcol.load(p, n0 + (t < BN ? t : 0));
 
     // ---- per-lane source offsets of the direct-to-LDS loads -----------------
     // k-major tile ([rows][BK]): 1 KiB block = KM_ROWS rows; lane -> (row, slot)
@@ -1866,14 +1865,18 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
     else rows = Rows::of(p);
     EpiCtx<TO, AccV, FM, FN, WTM, WTN, (NSTAGE * STAGE) / NW, Rows> ctx{p, acc, wlds, m0 + wm * WTM, n0 + wn * WTN, lane,
                                                                (int64_t)b * p.stride_c, rows};
-    if constexpr (sizeof(T) == 1 && MfmaOp<T>::kChunks == 1) {      // int8 operands
+    if constexpr (INT8) {
+        static_assert(BM * BN + BN * QuantColumn::kValues * 4 <= NSTAGE * STAGE && BN <= NW * 64, "codes and table of the columns");
+        float* table = (float*)(lds + BM * BN);
+        if (t < BN) qcol.put(p, table + t, BN);
+        __syncthreads();
         const bool has_mid = p.q_mid > 0.0f, has_bn = p.q_mean != nullptr;
         const bool fast = (!has_mid || make_step_div(p.q_mid).fast) && (p.out_dtype != DT_INT8 || make_step_div(p.q_out).fast);
-        if (!fast) ctx.template run_quant<WM, WN, 0>(lds, wm, wn);
-        else if (!has_mid && !has_bn) ctx.template run_quant<WM, WN, 1>(lds, wm, wn);
-        else if (has_mid && !has_bn) ctx.template run_quant<WM, WN, 2>(lds, wm, wn);
-        else if (!has_mid) ctx.template run_quant<WM, WN, 3>(lds, wm, wn);
-        else ctx.template run_quant<WM, WN, 4>(lds, wm, wn);
+        if (!fast) ctx.template run_quant<WM, WN, 0>(lds, table, wm, wn);
+        else if (!has_mid && !has_bn) ctx.template run_quant<WM, WN, 1>(lds, table, wm, wn);
+        else if (has_mid && !has_bn) ctx.template run_quant<WM, WN, 2>(lds, table, wm, wn);
+        else if (!has_mid) ctx.template run_quant<WM, WN, 3>(lds, table, wm, wn);
+        else ctx.template run_quant<WM, WN, 4>(lds, table, wm, wn);
     } else if (out_f32) {
         if (act == 0) ctx.template run<0, true>(); else if (act == 1) ctx.template run<1, true>();
         else ctx.template run<2, true>();
