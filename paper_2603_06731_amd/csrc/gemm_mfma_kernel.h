@@ -199,6 +199,11 @@ struct ConvTAxis {
     int lift;                  // lift * stride is at least the filter's extent: keeps a numerator from being negative
     int n, full;               // output rows of the classes below `full`; the others have one less
 };
+// A convolution's divisors: rows -> image, row, column of the output; k -> tap, channel.
+struct TileMapConv : TileMap {
+    FastDiv pix, ow, cin, kw;
+    FastDiv stride_h, stride_w;    // all taps of a transposed convolution
+};
 struct TileMapConvT : TileMap {
     ConvTAxis h, w;
     int images;
@@ -530,7 +535,7 @@ struct EpiCtx {
         const bool has_bias = p.bias != nullptr, has_mul = p.q_mul != nullptr, has_add = p.q_add != nullptr;
         const bool has_bn = p.q_mean != nullptr;
         const StepDiv mid_div = make_step_div(p.q_mid), out_div = make_step_div(p.q_out);
-        const bool relu = p.q_relu != 0;
+        const float least = p.q_relu ? 0.0f : -__builtin_inff();
         const int esz = out_i8 ? 1 : 4;
         const bool vec = (p.N % 4 == 0) && (p.ldc % 4 == 0) &&
                          (((uintptr_t)p.C + (uintptr_t)c_batch * esz) % (4 * esz) == 0);
@@ -565,15 +570,17 @@ struct EpiCtx {
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const int a = __float_as_int(val(i, j, g, e));
-                        t[e] = FAST ? quant_value_fast<F_MID, F_BN>(a, c[e], mid_div, relu)
+                        t[e] = FAST ? quant_value_fast<F_MID, F_BN>(a, c[e], mid_div, least)
                                     : quant_value(a, c[e], has_bias, has_bn, has_mul, has_add, mid_div, p.q_relu);
                     }
                     if (out_i8) {
-                        int8_t q[4];
+                        unsigned w = 0;
+                        if (FAST) {
+                            w = quant_codes_fast(t, out_div);
+                        } else {
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) q[e] = FAST ? (int8_t)quant_code_fast(t[e], out_div) : quant_code(t[e], out_div);
-                        const unsigned w = (unsigned)(uint8_t)q[0] | ((unsigned)(uint8_t)q[1] << 8) |
-                                           ((unsigned)(uint8_t)q[2] << 16) | ((unsigned)(uint8_t)q[3] << 24);
+                            for (int e = 0; e < 4; ++e) w |= (unsigned)(uint8_t)quant_code(t[e], out_div) << (8 * e);
+                        }
                         if (staged) {
                             const int trow = wm * WTM + lrow, tcol = wn * WTN + lcol;       // place in the workgroup tile
                             *(unsigned*)(lds_all + trow * ROW_BYTES + ((((tcol >> 4) ^ (trow % CPR))) << 4) + (tcol & 15)) = w;
@@ -582,7 +589,7 @@ struct EpiCtx {
                         } else {
 #pragma unroll
                             for (int e = 0; e < 4; ++e)
-                                if (gn + e < p.N) ((int8_t*)p.C)[o + e] = q[e];
+                                if (gn + e < p.N) ((int8_t*)p.C)[o + e] = (int8_t)(w >> (8 * e));
                         }
                     } else if (vec) {
                         f32x4 w = {t[0], t[1], t[2], t[3]};
@@ -655,6 +662,8 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
 
 // (an expression with the unnamed enum of the modes in a kernel's signature would be mangled differently on host and device)
 template <int MODE> struct TileMapSel { typedef TileMap type; };
+template <> struct TileMapSel<MODE_CONV> { typedef TileMapConv type; };
+template <> struct TileMapSel<MODE_CONVT_ALL> { typedef TileMapConv type; };
 template <> struct TileMapSel<MODE_CONVT> { typedef TileMapConvT type; };
 template <int MODE> using TileMapOf = typename TileMapSel<MODE>::type;
 
@@ -729,7 +738,8 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
     ConvTClass ct;
     int Mrows = p.M, Kall = p.K;
     int tap_w = p.conv.KW, tap_dh = p.conv.dil_h, tap_dw = p.conv.dil_w;
-    FastDiv by_pix{}, by_ow{}, by_taps_w{};
+    FastDiv by_pix{}, by_ow{}, by_taps_w{}, by_cin{};
+    if constexpr (MODE == MODE_CONV || CONVA) { by_pix = tmap.pix; by_ow = tmap.ow; by_taps_w = tmap.kw; by_cin = tmap.cin; }
     if constexpr (CONVT) {
         const int tile = tile_m;
         int cls;                                        // classes fastest: those of one region read the same pixels
@@ -743,6 +753,7 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
         convt_axis(tmap.h, ct.ph, p.conv.pad_h, p.conv.dil_h, p.conv.KH, ct.kh0, ct.nh, ct.ih_base);
         convt_axis(tmap.w, ct.pw, p.conv.pad_w, p.conv.dil_w, p.conv.KW, ct.kw0, ct.nw, ct.iw_base);
         by_taps_w = ct.nw == tmap.taps_w[1].d ? tmap.taps_w[1] : tmap.taps_w[0];
+        by_cin = tmap.cin;
         Mrows = ct.rows; Kall = ct.nh * ct.nw * p.conv.Cin;
         tap_w = ct.nw; tap_dh = tmap.h.d; tap_dw = tmap.w.d;
     }
@@ -776,7 +787,6 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
     unsigned a_voff[CA];       // dense / trans: byte offset from the tile's row block at k0; conv: pixel base
     int a_kofs[CA];            // k offset (elements) of the piece inside the k-tile
     int a_ih0[CA], a_iw0[CA];  // conv: top-left tap coordinates
-    bool a_ok[CA];
 #pragma unroll
     for (int r = 0; r < CA; ++r) {
         int blk = wave * CA + r;
@@ -784,21 +794,10 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
         int chunk = kma_slot ^ kmajor_swz<BKA, S16>(row);
         a_kofs[r] = chunk * 8;
         int gm = m0 + row;
-        a_ok[r] = gm < Mrows;
-        if (CONV) {
-            int gmc = a_ok[r] ? gm : 0;
-            int n, oh, ow;
-            if constexpr (CONVT) {
-                int rem;
-                n = by_pix.div(gmc, rem);
-                oh = by_ow.div(rem, ow);
-            } else {
-                int pix = p.conv.OH * p.conv.OW;
-                n = gmc / pix;
-                int rem = gmc - n * pix;
-                oh = rem / p.conv.OW;
-                ow = rem - oh * p.conv.OW;
-            }
+        const bool row_ok = gm < Mrows;
+        if constexpr (CONV) {
+            int rem, ow;
+            const int n = by_pix.div(row_ok ? gm : 0, rem), oh = by_ow.div(rem, ow);
             // (all taps: output row oh receives tap kh from input row (oh + pad - kh dil) / stride, if that divides)
             a_ih0[r] = CONVT ? oh + ct.ih_base : CONVA ? oh + p.conv.pad_h : oh * p.conv.stride_h - p.conv.pad_h;
             a_iw0[r] = CONVT ? ow + ct.iw_base : CONVA ? ow + p.conv.pad_w : ow * p.conv.stride_w - p.conv.pad_w;
@@ -806,8 +805,10 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
             // transposed convolution, beyond it by (KH - 1) dil / stride rows; adding the tap's offset brings it back
             if (CONVA) a_voff[r] = (unsigned)(n * p.conv.H * p.conv.W * p.conv.Cin * 2);             // the image's first pixel
             else a_voff[r] = ((unsigned)(n * p.conv.H + a_ih0[r]) * (unsigned)p.conv.W + (unsigned)a_iw0[r]) * (unsigned)(p.conv.Cin * 2);
+            // a row beyond M starts so far above the image that no tap reaches it (taps span less than 2^25 rows)
+            if (!row_ok) a_ih0[r] = -(1 << 30);
         } else {
-            a_voff[r] = a_ok[r] ? (unsigned)(row * (int)p.lda * 2 + chunk * 16) : kOob;
+            a_voff[r] = row_ok ? (unsigned)(row * (int)p.lda * 2 + chunk * 16) : kOob;
         }
     }
     // (pair pipeline with a k-major B: the pieces of B are 64 deep like A's, 2 CB loads per wave and PAIR)
@@ -881,6 +882,45 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
         else return 0;
     };
 
+    // Input pixel (ih, iw) inside the image?  One unsigned comparison per axis and no branch: with the four comparisons and the row's
+    // own flag joined by &&, the compiler put two branches in front of every load of the k loop.
+    auto in_image = [&](int ih, int iw) __attribute__((always_inline)) -> bool {
+        return ((unsigned)ih < (unsigned)p.conv.H) & ((unsigned)iw < (unsigned)p.conv.W);
+    };
+    // k-tiles that span taps: every piece has a tap of its own; its offsets are worked out when the tile begins
+    unsigned ld_aoff[CONV ? CA : 1], ld_boff[CONVT ? CB : 1];
+    auto spanning_offsets = [&](int k0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < CA; ++r) {
+            const int k = k0 + a_kofs[r];
+            int c, kw;
+            const int kh = by_taps_w.div(by_cin.div(k, c), kw);
+            const int dh = kh * tap_dh, dw = kw * tap_dw;
+            bool ok;
+            unsigned off;
+            if constexpr (CONVA) {
+                const int th = a_ih0[r] - dh, tw = a_iw0[r] - dw;
+                int rh, rw;
+                const int ih = tmap.stride_h.div(th > 0 ? th : 0, rh), iw = tmap.stride_w.div(tw > 0 ? tw : 0, rw);
+                ok = (th >= 0) & (tw >= 0) & (rh == 0) & (rw == 0) & (ih < p.conv.H) & (iw < p.conv.W);
+                off = a_voff[r] + (unsigned)(((ih * p.conv.W + iw) * p.conv.Cin + c) * 2);
+            } else {
+                ok = in_image(a_ih0[r] + dh, a_iw0[r] + dw);
+                off = a_voff[r] + ((unsigned)dh * (unsigned)p.conv.W + (unsigned)dw) * (unsigned)(p.conv.Cin * 2) + (unsigned)(c * 2);
+            }
+            ld_aoff[r] = (ok & (k < Kall)) ? off : kOob;
+        }
+        if constexpr (CONVT) {
+            // the piece's k-row of the class's k axis -> its row of the weights
+#pragma unroll
+            for (int r = 0; r < CB; ++r) {
+                int c, j;
+                const int i = by_taps_w.div(by_cin.div(k0 + b_kofs[r], c), j);
+                ld_boff[r] = b_voff[r] == kOob ? kOob : b_voff[r] + (unsigned)((convt_brow(i, j, c) - b_kofs[r]) * (int)p.ldb * 2);
+            }
+        }
+    };
+
     // Start issuing the k-tile at k0 into `stage`: descriptors rebased to k0.
     auto begin_tile = [&](int k0, int stage) {
         ld_k0 = k0;
@@ -898,6 +938,8 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
                     tap_c = 0;
                     if (++tap_kw == tap_w) { tap_kw = 0; ++tap_kh; }
                 }
+            } else if constexpr (CONV) {
+                spanning_offsets(k0);
             }
         } else {
             ld_ra = make_rsrc(a_tile + (int64_t)k0 * 2);
@@ -913,42 +955,18 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
         constexpr bool TAIL = decltype(tail_tag)::value;
         if (r < CA) {
             unsigned off;
-            if (CONVA) {
-                int dh = ld_dh, dw = ld_dw, c = ld_c + a_kofs[r];
-                if (!one_tap) {
-                    const int k = ld_k0 + a_kofs[r], tap = k / p.conv.Cin, kh = tap / p.conv.KW;
-                    c = k - tap * p.conv.Cin;
-                    dh = kh * p.conv.dil_h; dw = (tap - kh * p.conv.KW) * p.conv.dil_w;
-                }
-                const int th = a_ih0[r] - dh, tw = a_iw0[r] - dw;
-                const int ih = th / p.conv.stride_h, iw = tw / p.conv.stride_w;
-                bool ok = a_ok[r] && th >= 0 && tw >= 0 && ih * p.conv.stride_h == th && iw * p.conv.stride_w == tw &&
-                          ih < p.conv.H && iw < p.conv.W;
-                if (TAIL) ok = ok && (ld_k0 + a_kofs[r] < Kall);
-                off = ok ? a_voff[r] + (unsigned)(((ih * p.conv.W + iw) * p.conv.Cin + c) * 2) : kOob;
-            } else if (CONV) {
-                int dh, dw;
-                if (one_tap) {
-                    dh = ld_dh; dw = ld_dw;
-                    off = a_voff[r] + ld_delta + (unsigned)(a_kofs[r] * 2);
-                } else {
-                    int k = ld_k0 + a_kofs[r];
-                    int c, kh, kw;
-                    if constexpr (CONVT) {
-                        kh = by_taps_w.div(tmap.cin.div(k, c), kw);
-                    } else {
-                        int tap = k / p.conv.Cin;
-                        c = k - tap * p.conv.Cin;
-                        kh = tap / tap_w;
-                        kw = tap - kh * tap_w;
-                    }
-                    dh = kh * tap_dh; dw = kw * tap_dw;
-                    off = a_voff[r] + ((unsigned)dh * (unsigned)p.conv.W + (unsigned)dw) * (unsigned)(p.conv.Cin * 2) + (unsigned)(c * 2);
-                }
-                int ih = a_ih0[r] + dh, iw = a_iw0[r] + dw;
-                bool ok = a_ok[r] && ih >= 0 && ih < p.conv.H && iw >= 0 && iw < p.conv.W;
-                if (TAIL) ok = ok && (ld_k0 + a_kofs[r] < Kall);
-                off = ok ? off : kOob;
+            if constexpr (CONVA) {
+                const int th = a_ih0[r] - ld_dh, tw = a_iw0[r] - ld_dw;
+                int rh, rw;
+                const int ih = tmap.stride_h.div(th > 0 ? th : 0, rh), iw = tmap.stride_w.div(tw > 0 ? tw : 0, rw);
+                const bool ok = (th >= 0) & (tw >= 0) & (rh == 0) & (rw == 0) & (ih < p.conv.H) & (iw < p.conv.W);
+                off = ok ? a_voff[r] + (unsigned)(((ih * p.conv.W + iw) * p.conv.Cin + ld_c + a_kofs[r]) * 2) : kOob;
+                off = one_tap ? off : ld_aoff[r];
+            } else if constexpr (CONV) {
+                bool ok = in_image(a_ih0[r] + ld_dh, a_iw0[r] + ld_dw);
+                if (TAIL) ok = ok & (ld_k0 + a_kofs[r] < Kall);       // (a class of one tap may end inside a k-tile)
+                off = ok ? a_voff[r] + ld_delta + (unsigned)(a_kofs[r] * 2) : kOob;
+                off = one_tap ? off : ld_aoff[r];
             } else {
                 off = a_voff[r];
                 if (TAIL && ld_k0 + a_kofs[r] >= Kall) off = kOob;
@@ -957,14 +975,7 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
         } else {
             const int rb = r - CA;
             unsigned off = b_voff[rb];
-            if constexpr (CONVT) {
-                if (!one_tap && off != kOob) {
-                    // the piece's k-row of the class's k axis -> its row of the weights
-                    int c, j;
-                    const int i = by_taps_w.div(tmap.cin.div(ld_k0 + b_kofs[rb], c), j);
-                    off += (unsigned)((convt_brow(i, j, c) - b_kofs[rb]) * (int)p.ldb * 2);
-                }
-            }
+            if constexpr (CONVT) off = one_tap ? off : ld_boff[rb];
             if (TAIL && ld_k0 + b_kofs[rb] >= Kall) off = kOob;
             dma16(ld_rb, ld_sb + (wave * CB + rb) * 1024, off);
         }
@@ -1026,7 +1037,8 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
             slot_in = (slot_in + 1 == NSTAGE) ? 0 : slot_in + 1;
         };
         while (issued < NSTAGE - 1 && issued < KT) {
-            if (issued < KF) issue_next(TailNo{}); else issue_next(TailYes{});
+            // (a convolution's addresses are long code: one copy of it in front of the loop)
+            if (!CONV && issued < KF) issue_next(TailNo{}); else issue_next(TailYes{});
         }
         wait_newer(issued - 1);
         __syncthreads();
@@ -1301,9 +1313,9 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
             unsigned ad_delta = 0;
             auto begin_a = [&](int k0, int dst) {
                 ad_ka = k0; ad_sa = lds_base + dst;
-                if (CONV) {
-                    const int tap = k0 / p.conv.Cin, c = k0 - tap * p.conv.Cin;
-                    const int kh = tap / p.conv.KW, kw = tap - kh * p.conv.KW;
+                if constexpr (CONV) {
+                    int c, kw;
+                    const int kh = by_taps_w.div(by_cin.div(k0, c), kw);
                     ad_dh = kh * p.conv.dil_h; ad_dw = kw * p.conv.dil_w;
                     ad_delta = (unsigned)(((ad_dh * p.conv.W + ad_dw) * p.conv.Cin + c) * 2);
                 } else {
@@ -1319,8 +1331,7 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
                 if (CONV) {
                     off = a_voff[r] + ad_delta + (unsigned)(a_kofs[r] * 2);
                     const int ih = a_ih0[r] + ad_dh, iw = a_iw0[r] + ad_dw;
-                    const bool ok = a_ok[r] && ih >= 0 && ih < p.conv.H && iw >= 0 && iw < p.conv.W;
-                    off = ok ? off : kOob;
+                    off = in_image(ih, iw) ? off : kOob;
                 }
                 if (decltype(tail_tag)::value && ad_ka + a_kofs[r] >= p.K) off = kOob;
                 dma16(ad_ra, ad_sa + (wave * CA + r) * 1024, off);
@@ -1855,23 +1866,28 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
     // holds what, so that the global stores are 16 bytes per lane along rows:
     // every store instruction writes whole 128-byte (or longer) row segments.
     __syncthreads();                           // all waves are done reading the last stage
-    const int act = (p.epi == EPI_RELU || p.epi == EPI_BIAS_RELU) ? 1
-                  : (p.epi == EPI_GELU_TANH || p.epi == EPI_BIAS_GELU_TANH) ? 2 : 0;
-    const bool out_f32 = p.out_dtype == DT_F32;
+    // The epilogue reads the problem from the kernel's argument block again.  Held in scalar registers through the k loop, what only
+    // the epilogue needs spilled others to vector lanes (a transposed convolution's epilogue had 10000 such moves, over all its forms).
+    auto args = __builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(args));
+    const Problem& pe = *(const Problem*)args;
+    const int act = (pe.epi == EPI_RELU || pe.epi == EPI_BIAS_RELU) ? 1
+                  : (pe.epi == EPI_GELU_TANH || pe.epi == EPI_BIAS_GELU_TANH) ? 2 : 0;
+    const bool out_f32 = pe.out_dtype == DT_F32;
     char* wlds = lds + wave * ((NSTAGE * STAGE) / NW);
     typedef typename std::conditional<CONVT, RowsConvT, RowsPlain>::type Rows;
     Rows rows;
-    if constexpr (CONVT) rows = Rows{Mrows, tmap.classes.d == 1, by_pix, by_ow, ct.ph, ct.pw, p.conv.stride_h, p.conv.stride_w, p.conv.OH, p.conv.OW};
-    else rows = Rows::of(p);
-    EpiCtx<TO, AccV, FM, FN, WTM, WTN, (NSTAGE * STAGE) / NW, Rows> ctx{p, acc, wlds, m0 + wm * WTM, n0 + wn * WTN, lane,
-                                                               (int64_t)b * p.stride_c, rows};
+    if constexpr (CONVT) rows = Rows{Mrows, tmap.classes.d == 1, by_pix, by_ow, ct.ph, ct.pw, pe.conv.stride_h, pe.conv.stride_w, pe.conv.OH, pe.conv.OW};
+    else rows = Rows::of(pe);
+    EpiCtx<TO, AccV, FM, FN, WTM, WTN, (NSTAGE * STAGE) / NW, Rows> ctx{pe, acc, wlds, m0 + wm * WTM, n0 + wn * WTN, lane,
+                                                               (int64_t)b * pe.stride_c, rows};
     if constexpr (INT8) {
         static_assert(BM * BN + BN * QuantColumn::kValues * 4 <= NSTAGE * STAGE && BN <= NW * 64, "codes and table of the columns");
         float* table = (float*)(lds + BM * BN);
-        if (t < BN) qcol.put(p, table + t, BN);
+        if (t < BN) qcol.put(pe, table + t, BN);
         __syncthreads();
-        const bool has_mid = p.q_mid > 0.0f, has_bn = p.q_mean != nullptr;
-        const bool fast = (!has_mid || make_step_div(p.q_mid).fast) && (p.out_dtype != DT_INT8 || make_step_div(p.q_out).fast);
+        const bool has_mid = pe.q_mid > 0.0f, has_bn = pe.q_mean != nullptr;
+        const bool fast = (!has_mid || make_step_div(pe.q_mid).fast) && (pe.out_dtype != DT_INT8 || make_step_div(pe.q_out).fast);
         if (!fast) ctx.template run_quant<WM, WN, 0>(lds, table, wm, wn);
         else if (!has_mid && !has_bn) ctx.template run_quant<WM, WN, 1>(lds, table, wm, wn);
         else if (has_mid && !has_bn) ctx.template run_quant<WM, WN, 2>(lds, table, wm, wn);

@@ -115,6 +115,14 @@ hipError_t launch_one(const Problem& p, hipStream_t stream, int group_m) {
         tm.tiles_m = (int)tiles;
         convt_geometry(p, &tm);
     }
+    if constexpr (MODE == MODE_CONV || MODE == MODE_CONVT_ALL) {
+        tm.pix = FastDiv::of(p.conv.OH * p.conv.OW);
+        tm.ow = FastDiv::of(p.conv.OW);
+        tm.cin = FastDiv::of(p.conv.Cin);
+        tm.kw = FastDiv::of(p.conv.KW);
+        tm.stride_h = FastDiv::of(p.conv.stride_h);
+        tm.stride_w = FastDiv::of(p.conv.stride_w);
+    }
     tm.tiles_per_batch = tm.tiles_m * tm.tiles_n;
     long long total = (long long)tm.tiles_per_batch * p.batch;
     if (total <= 0 || total > 0x7FFFFFFFLL) return hipErrorInvalidValue;

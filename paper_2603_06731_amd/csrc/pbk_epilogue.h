@@ -186,17 +186,18 @@ __device__ __forceinline__ float quant_value(int acc, const QuantParams& c, bool
 
 // Branch-free form for the matrix-unit kernels: both steps `fast`; a part of the epilogue that is absent is
 // given its neutral value in `c` (bias and add: -0.0f, which leaves every value and the sign of zero as they
-// are; mul and rinv: 1.0f; mean: +0.0f).  Same operations in the same order as quant_value.
+// are; mul and rinv: 1.0f; mean: +0.0f).  Same operations in the same order as quant_value.  `least`: 0 with a ReLU, -inf without
+// (v_maximum / v_minimum keep a NaN, and the larger of -0 and +0 is +0: one instruction each where a comparison and a
+// selection, and for the ReLU its switch, were two and three).
 template <bool HAS_MID, bool HAS_BN>
-__device__ __forceinline__ float quant_value_fast(int acc, const QuantParams& c, const StepDiv& mid, bool relu) {
+__device__ __forceinline__ float quant_value_fast(int acc, const QuantParams& c, const StepDiv& mid, float least) {
 #pragma clang fp contract(off)
     float t = (float)acc;
     t = t * c.scale;
     t = t + c.bias;
     if (HAS_MID) {
         float q = __builtin_rintf(step_quotient_fast(t, mid));
-        q = q < -128.0f ? -128.0f : q;                // (compare and select: NaN stays NaN)
-        q = q > 127.0f ? 127.0f : q;
+        q = __builtin_elementwise_minimum(__builtin_elementwise_maximum(q, -128.0f), 127.0f);
         t = q * mid.step;
     }
     if (HAS_BN) {
@@ -205,15 +206,21 @@ __device__ __forceinline__ float quant_value_fast(int acc, const QuantParams& c,
     }
     t = t * c.mul;
     t = t + c.add;
-    const bool zero = (t <= 0.0f) & relu;
-    return zero ? 0.0f : t;
+    return __builtin_elementwise_maximum(t, least);
 }
-// the output code; a NaN has no code that the method defines
-__device__ __forceinline__ int quant_code_fast(float t, const StepDiv& out_scale) {
+// Four output codes in one dword; a NaN has no code that the method defines.  Clamping first gives the code that rounding first
+// does (both bounds are whole numbers); adding 1.5 * 2^23 then rounds to nearest even and leaves the whole number, in two's
+// complement, in the low bits.
+__device__ __forceinline__ unsigned quant_codes_fast(const float (&t)[4], const StepDiv& out_scale) {
 #pragma clang fp contract(off)
-    float q = __builtin_rintf(step_quotient_fast(t, out_scale));
-    q = __builtin_amdgcn_fmed3f(q, -128.0f, 127.0f);
-    return (int)q;
+    unsigned b[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const float q = __builtin_amdgcn_fmed3f(step_quotient_fast(t[e], out_scale), -128.0f, 127.0f);
+        b[e] = __builtin_bit_cast(unsigned, q + 12582912.0f);
+    }
+    const unsigned lo = __builtin_amdgcn_perm(b[1], b[0], 0x0C0C0400u), hi = __builtin_amdgcn_perm(b[3], b[2], 0x04000C0Cu);
+    return lo | hi;
 }
 
 __device__ __forceinline__ int8_t quant_code(float t, const StepDiv& out_scale) {
