@@ -14,6 +14,12 @@
  *  - All data pointers are DEVICE pointers valid on the device that `stream`
  *    belongs to.  The library never allocates, frees or keeps them.  The
  *    output must not alias any input.
+ *  - Calls that leave most of the device idle otherwise split one output over
+ *    several workgroups, which exchange partial results through scratch memory
+ *    of the library's own: 16 MiB per stream, obtained at the stream's first
+ *    such call, for up to 32 streams of a device, kept until
+ *    pbk_release_scratch().  Where there is none (the stream is being captured,
+ *    more streams, no memory) the call runs without a split.
  *  - Calls only enqueue work on `stream` (a hipStream_t; NULL = the default
  *    stream) and return; ordering is stream ordering.
  *  - Matrices are row-major with leading dimensions in ELEMENTS.
@@ -36,7 +42,7 @@
  *  - Elements outside the M x K / K x N views (beyond K up to lda, etc.) are
  *    never allowed to influence the result, even if they hold NaN or Inf.
  *  - Re-entrant; no global mutable state besides a read-only cache of device
- *    properties.
+ *    properties and the list of the streams' scratch memory.
  */
 #ifndef PBK_H
 #define PBK_H
@@ -315,7 +321,8 @@ const char* pbk_last_kernel(void);
  *                 8-byte pieces), "ksplit:1" 32;
  *   "tile64"      64-wide tiles: "tile64:0" 64 x 64 with a deep ring, "tile64:1" 32 x 64, "tile64:2" 64 x 64, two per compute unit;
  *   "decode"      attention of up to 16 queries, keys split over the waves: "decode:1", "decode:2", "decode:4" workgroups per
- *                 batch entry (as many as the head dimension has 32-column groups, at most).
+ *                 batch entry (as many as the head dimension has 32-column groups, at most), each with its own columns of V;
+ *                 "decode:8" the keys split over workgroups, up to 96 entries, with any context of two steps of 32 keys.
  * Attention takes "generic", "mfma" (the kernel of whole sequences; "mfma:1" all waves on the same keys, "mfma:2" the keys in
  * two halves where that form is built) and "decode", and chooses automatically under the others.  A problem the choice cannot run, and
  * "decode" for anything but attention, gives PBK_ERR_UNSUPPORTED.  NULL or "" returns to the default.  The default
@@ -323,6 +330,13 @@ const char* pbk_last_kernel(void);
  * call.  An unknown string is PBK_ERR_UNSUPPORTED and changes nothing.
  */
 pbk_status pbk_force_kernel(const char* choice);
+
+/*
+ * Gives back the scratch memory of all streams of the current device, after
+ * waiting for the device.  No call of this library may be under way on that
+ * device meanwhile; later calls obtain scratch memory again.
+ */
+pbk_status pbk_release_scratch(void);
 
 #ifdef __cplusplus
 }

@@ -21,7 +21,7 @@ SOURCES += [("gemm_mfma_16bit.hip", f"gemm_mfma_{name}_g{g}",
             for g in reversed(range(N_GROUPS_16)) for name in ("bf16", "f16")]
 SOURCES += [(f, f[:-4], []) for f in ("gemm_mfma_bstat.hip", "gemm_mfma_gather.hip", "gemm_mfma_ksplit.hip", "gemm_mfma_tile64.hip", "gemm_mfma_f32.hip", "attention_mfma.hip", "attention_decode.hip", "gemm_mfma_fp8.hip",
                                       "gemm_mfma.hip", "pbk_api.hip", "gemm_generic.hip", "gemm_small_f32.hip",
-                                      "attention_generic.hip")]
+                                      "attention_generic.hip", "scratch.hip")]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

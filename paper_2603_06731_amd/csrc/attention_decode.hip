@@ -8,9 +8,12 @@
 // compute unit and its load path stays busy: that path bounds the kernel with few batch entries, memory with many.  16 entries,
 // context 8192, D = 128: 122 -> 32 us; 64 entries 133 -> 61 us (4.4 TB/s).  With fewer batch entries than compute
 // units, 2 or 4 workgroups share an entry: each computes all scores but multiplies only its own DV columns of V,
-// and the re-read K comes out of the L2 they share.  (A split of the keys over workgroups would read less but needs
-// memory for the partial results, which this library does not allocate.)  At the end the waves' outputs are brought
-// to one reference point and added in wave order in LDS.
+// and the re-read K comes out of the L2 they share.  At the end the waves' outputs are brought to one reference point and added in
+// wave order in LDS.
+// With up to 96 entries and a context long enough, the keys are split over workgroups as well (SPLIT): every workgroup reads its own
+// keys and values only, and the parts of an entry meet in scratch memory (scratch.h).  16 entries, context 8192, D = 128, operands
+// from memory: 53 -> 20 us (4 TB/s would be 17); 16 x 4096 x 64: 17.5 -> 10.3.  It then is bound by memory and by a chain of latencies:
+// first loads, the waves' meeting, the parts' meeting (some 3 us).
 //
 // Layouts (v_mfma_f32_16x16x32: lane l supplies operand index l%16 and 8 contraction values of group l/16; it receives
 // column l%16 and rows 4 (l/16) + 0..3):
@@ -18,6 +21,7 @@
 //   O^T = V^T P^T: its own 8 weights are the B operand as they are; the transposing LDS read fetches V rows in
 //   that key order.  No weight changes lane.
 #include "gemm_mfma_launch.h"
+#include "scratch.h"
 #include <type_traits>
 
 namespace pbk {
@@ -30,9 +34,11 @@ constexpr float DEC_SLACK = 8.0f;       // log2 of how far a score may exceed th
 template <int D> __device__ __forceinline__ int dec_kswz(int key) { return D == 128 ? key & 15 : D == 64 ? (key >> 1) & 7 : (key >> 2) & 3; }
 template <int DV> __device__ __forceinline__ int dec_vswz(int key) { return DV == 128 ? key & 7 : DV == 64 ? (key >> 1) & 3 : (key >> 2) & 1; }
 
-template <typename T, int D, int DV, int NW, bool CAUSAL>
-__global__ __launch_bounds__(NW * 64, NW / 4) void attention_decode_kernel(AttnProblem p, int total, int xcds) {
-    constexpr int DS = D / DV;                     // workgroups per batch entry
+// SPLIT: `parts` workgroups per batch entry, each with a run of the steps of 32 keys
+template <typename T, int D, int DV, int NW, bool CAUSAL, bool SPLIT>
+__global__ __launch_bounds__(NW * 64, NW / 4) void attention_decode_kernel(AttnProblem p, int total, int xcds, int parts, Scratch scratch) {
+    static_assert(!SPLIT || DV == D, "keys or columns are split, not both");
+    const int DS = SPLIT ? parts : D / DV;         // workgroups per batch entry
     constexpr int KS = D / 32, JD = DV / 16;
     constexpr int K_BYTES = DEC_KB * D * 2, V_BYTES = DEC_KB * DV * 2, WLDS = K_BYTES + V_BYTES;
     constexpr int KL = K_BYTES / 1024, VL = V_BYTES / 1024;          // loads per step
@@ -46,7 +52,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void attention_decode_kernel(AttnP
     // one XCD (one L2) owns a contiguous run of (batch entry, column group) pairs
     const int xq = total / xcds, xr = total % xcds, xcd = blockIdx.x % xcds, local = blockIdx.x / xcds;
     const int id = xcd * xq + (xcd < xr ? xcd : xr) + local;
-    const int b = id / DS, d0 = (id - b * DS) * DV;
+    const int b = id / DS, part = id - b * DS, d0 = SPLIT ? 0 : part * DV;
     const int c_off = p.Nk - p.Nq;                 // causal: key visible iff key <= query + c_off
 
     const char* Kb = (const char*)p.K + (int64_t)b * p.stride_k * 2;
@@ -71,7 +77,9 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void attention_decode_kernel(AttnP
     auto dma = [&](int4v rsrc, unsigned addr, unsigned voff) {
         asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" :: "s"(addr), "v"(voff), "s"(rsrc) : "memory", "m0");
     };
-    const int S = (p.Nk + DEC_KB - 1) / DEC_KB;    // steps of 32 keys, dealt round-robin to the waves
+    // steps of 32 keys: this workgroup's are S0 .. S - 1, dealt round-robin to the waves
+    const int all = (p.Nk + DEC_KB - 1) / DEC_KB, each = SPLIT ? all / parts : all, rest = SPLIT ? all - each * parts : 0;
+    const int S0 = SPLIT ? part * each + (part < rest ? part : rest) : 0, S = SPLIT ? S0 + each + (part < rest ? 1 : 0) : all;
     auto issue_k = [&](int s) {
         const int key0 = s * DEC_KB;
         const int4v r = make_rsrc(Kb + (int64_t)key0 * p.ldk * 2);
@@ -98,7 +106,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void attention_decode_kernel(AttnP
     }
     // (the query rows are in registers before the first uncounted load is issued)
     wait_vmcnt<0>();
-    if (wave < S) { issue_k(wave); issue_v(wave); }
+    if (S0 + wave < S) { issue_k(S0 + wave); issue_v(S0 + wave); }
 
     f32x4 o_acc[JD];
 #pragma unroll
@@ -130,7 +138,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void attention_decode_kernel(AttnP
         __builtin_amdgcn_sched_barrier(0);
     };
 
-    for (int s = wave; s < S; s += NW) {
+    for (int s = S0 + wave; s < S; s += NW) {
         const int key0 = s * DEC_KB;
         const bool more = s + NW < S;
         // ---- scores: K of this step is older than V of this step
@@ -212,39 +220,90 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void attention_decode_kernel(AttnP
     constexpr int PIECES = JD * 64;
     float* m_all = (float*)(lds + NW * PIECES * 16);
     float* l_all = m_all + NW * 16;
-    static_assert(NW * (PIECES * 16 + 128) <= NW * WLDS, "LDS");
+    static_assert(NW % 8 == 0 && NW * (PIECES * 16 + 128) + 4 <= NW * WLDS, "LDS");
 #pragma unroll
     for (int j = 0; j < JD; ++j) red[wave * PIECES + j * 64 + lane] = o_acc[j];
     if (g == 0) { m_all[wave * 16 + c] = m_run; l_all[wave * 16 + c] = l_run; }
     __syncthreads();
-    for (int e = threadIdx.x; e < PIECES; e += NW * 64) {
-        const int q = e & 15;
-        if (q >= p.Nq) continue;
-        float m = m_all[q];
-#pragma unroll
-        for (int w = 1; w < NW; ++w) m = fmaxf(m, m_all[w * 16 + q]);
+    // outputs of n parts brought to one reference point and added; `v` holds the first eight of them already, the others come from o_of
+    constexpr int AHEAD = 8;
+    auto combine = [&](int n, auto&& m_of, auto&& l_of, auto&& o_of, f32x4 (&v)[AHEAD], float& m, float& l, f32x4& o) __attribute__((always_inline)) {
+        m = m_of(0);
+        for (int w = 1; w < n; ++w) m = fmaxf(m, m_of(w));
         const float m_sub = m == -INFINITY ? 0.0f : m;
-        float l = 0.0f;
-        f32x4 o = {0.0f, 0.0f, 0.0f, 0.0f};
+        l = 0.0f;
+        o = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int w0 = 0; w0 < n; w0 += AHEAD) {
 #pragma unroll
-        for (int w = 0; w < NW; ++w) {
-            const float f = __builtin_amdgcn_exp2f(m_all[w * 16 + q] - m_sub);
-            l = fmaf(l_all[w * 16 + q], f, l);
-            const f32x4 v = red[w * PIECES + e];
+            for (int i = 0; i < AHEAD; ++i) {
+                if (w0 + i >= n) break;
+                const float f = __builtin_amdgcn_exp2f(m_of(w0 + i) - m_sub);
+                l = fmaf(l_of(w0 + i), f, l);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) o[i] = fmaf(v[i], f, o[i]);
+                for (int k = 0; k < 4; ++k) o[k] = fmaf(v[i][k], f, o[k]);
+            }
+            if (w0 + AHEAD >= n) break;
+#pragma unroll
+            for (int i = 0; i < AHEAD; ++i) v[i] = o_of(w0 + AHEAD + i < n ? w0 + AHEAD + i : n - 1);
         }
+    };
+    auto store = [&](int q, int e, float l, f32x4 o) __attribute__((always_inline)) {
         const float inv = 1.0f / l;
         const int d = d0 + (e >> 6) * 16 + ((e & 63) >> 4) * 4;
         *(int2v*)((char*)p.O + ((int64_t)b * p.stride_o + (int64_t)q * p.ldo + d) * 2) =
             int2v{(int)pack2<T>(o[0] * inv, o[1] * inv), (int)pack2<T>(o[2] * inv, o[3] * inv)};
+    };
+    // scratch memory of a part: PIECES pieces of the output at its reference points, then reference point and sum per query
+    constexpr int PART = PIECES * 4 + 64;
+    float* part_of_entry = SPLIT ? (float*)scratch.data + (size_t)b * parts * PART : nullptr;
+    f32x4 v[AHEAD];
+    const int e = threadIdx.x, q = e & 15;         // a piece of the output, its query
+    static_assert(PIECES <= NW * 64, "one piece per thread");
+    const bool mine = e < PIECES && q < p.Nq;
+    float m, l;
+    f32x4 o;
+    if (mine) {
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i) v[i] = red[i * PIECES + e];
+        combine(NW, [&](int w) { return m_all[w * 16 + q]; }, [&](int w) { return l_all[w * 16 + q]; },
+                [&](int w) { return red[w * PIECES + e]; }, v, m, l, o);
+        if constexpr (!SPLIT) store(q, e, l, o);
+    }
+    if constexpr (SPLIT) {
+        // scratch memory of a part: PIECES pieces of the output at its reference points, then reference point and sum per query
+        constexpr int PART = PIECES * 4 + 64;
+        float* entry = (float*)scratch.data + (size_t)b * parts * PART;
+        if (mine) {
+            scratch_put(entry + (size_t)part * PART + e * 4, o);
+            if (e < 16) scratch_put(entry + (size_t)part * PART + PIECES * 4 + q * 4, f32x4{m, l, 0.0f, 0.0f});
+        }
+        if (!scratch_last(scratch.tickets + b, parts, (int*)(l_all + NW * 16))) return;
+        auto o_of = [&](int w) { return scratch_get(entry + (size_t)w * PART + e * 4); };
+        if (mine) {
+#pragma unroll
+            for (int i = 0; i < AHEAD; ++i) v[i] = o_of(i < parts ? i : parts - 1);
+        }
+        float* ml = (float*)lds;                   // (the waves' outputs have been read) reference points and sums of the parts
+        for (int i = threadIdx.x; i < parts * 16; i += NW * 64) {
+            if ((i & 15) >= p.Nq) continue;
+            const f32x4 x = scratch_get(entry + (size_t)(i >> 4) * PART + PIECES * 4 + (i & 15) * 4);
+            ml[i * 2] = x[0];
+            ml[i * 2 + 1] = x[1];
+        }
+        __syncthreads();
+        if (mine) {
+            combine(parts, [&](int w) { return ml[(w * 16 + q) * 2]; }, [&](int w) { return ml[(w * 16 + q) * 2 + 1]; }, o_of, v, m, l, o);
+            store(q, e, l, o);
+        }
     }
 }
 
-template <typename T, int D, int DV, int NW>
-hipError_t launch_split(const AttnProblem& p, hipStream_t stream) {
+// parts: workgroups that share an entry's keys (1: none, and no scratch memory)
+template <typename T, int D, int DV, int NW, bool SPLIT = false>
+hipError_t launch_split(const AttnProblem& p, hipStream_t stream, int parts = 1, Scratch scratch = Scratch{}) {
     constexpr int LDS_BYTES = NW * DEC_KB * (D + DV) * 2;
-    const void* kern = p.causal ? (const void*)attention_decode_kernel<T, D, DV, NW, true> : (const void*)attention_decode_kernel<T, D, DV, NW, false>;
+    const void* kern = p.causal ? (const void*)attention_decode_kernel<T, D, DV, NW, true, SPLIT>
+                                : (const void*)attention_decode_kernel<T, D, DV, NW, false, SPLIT>;
     static std::atomic<unsigned> attr_done[2];     // bit per device, for either form
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -259,11 +318,11 @@ hipError_t launch_split(const AttnProblem& p, hipStream_t stream) {
     e = device_shape(dev, &ds);
     if (e != hipSuccess) return e;
     int xcds = ds.xcds;
-    const long long n = (long long)p.batch * (D / DV);
+    const long long n = (long long)p.batch * (SPLIT ? parts : D / DV);
     if (n <= 0 || n > 0x7FFFFFFFLL) return hipErrorInvalidValue;
     int total = (int)n;
     AttnProblem pa = p;
-    void* args[] = {&pa, &total, &xcds};
+    void* args[] = {&pa, &total, &xcds, &parts, &scratch};
     return hipLaunchKernel(kern, dim3((unsigned)total), dim3(NW * 64), args, LDS_BYTES, stream);
 }
 
@@ -279,6 +338,16 @@ hipError_t launch_type(const AttnProblem& p, hipStream_t stream, int split) {
     }
 }
 
+template <typename T>
+hipError_t launch_keys(const AttnProblem& p, hipStream_t stream, int parts, Scratch scratch) {
+    switch (p.D) {
+    case 32: return launch_split<T, 32, 32, 16, true>(p, stream, parts, scratch);
+    case 64: return launch_split<T, 64, 64, 16, true>(p, stream, parts, scratch);
+    case 128: return launch_split<T, 128, 128, 8, true>(p, stream, parts, scratch);
+    default: return hipErrorInvalidValue;
+    }
+}
+
 }  // namespace
 
 // Workgroups per batch entry: K is read once by each of them, V once by all together.  With few entries a compute unit's load path
@@ -286,6 +355,24 @@ hipError_t launch_type(const AttnProblem& p, hipStream_t stream, int split) {
 // entries 44.4 / 34.3 / 32.2 us with 1 / 2 / 4, 64 entries 84 / 67 / 61); with 128 entries the chip is occupied and the
 // second reading of K costs (240 x 1104: 25.5 / 27.9 / 42.3; 223 x 5327: 102 / 108 / 159).
 static int decode_split(const AttnProblem& p) { return p.batch > 128 ? 1 : p.batch > 64 ? 2 : 4; }
+
+// Workgroups that share an entry's keys (1: they are not split).  Up to 192 workgroups on the 256 compute units and at least 384 keys for
+// each (16 entries, context 8192, D = 128, operands from memory: 33.3 us with 3 parts, 22.2 with 6, 19.4 with 10, 20.1 with 12, 21.0 with
+// 16; context 2048: 13.1 with 2, 10.6 with 4, 10.1 with 6, 10.6 with 8).  The meeting costs some 3 us, which a short context
+// does not give back, nor do two parts a middling one.  Unsplit first:
+// - D = 128: 16 x 1024: 7.6 against 8.6, x 2048: 11.4 against 10.1; 64 x 2048: 19.0 against 17.6; 96 x 2048: 22.3 against 23.0, x 4096: 41.1
+//   against 40.2; 128 x 8192: 90 against 96;
+// - D = 64: 16 x 2048: 8.5 against 8.7, x 4096: 17.5 against 10.3; 96 x 4096: 24.8 against 22.3; 128 x 8192: 49.5 and 49.5;
+// - D = 32: 16 x 3072: 7.7 against 8.0, x 4096: 9.0 against 7.9; 96 x 4096: 15.0 against 13.4.
+static int decode_parts(const AttnProblem& p, int force) {
+    if ((force > 0 && force < 8) || p.batch > 96) return 1;
+    const int least = p.batch > 64 ? 4096 : p.D == 128 ? 1536 : p.D == 64 ? 2560 : 3584;
+    if (force != 8 && p.Nk < least) return 1;
+    const int most = force == 8 ? (p.Nk + DEC_KB - 1) / DEC_KB : p.Nk / 384;        // (chosen by hand: a step of keys is enough)
+    int parts = 192 / p.batch;
+    if (parts > most) parts = most;
+    return parts > 64 ? 64 : parts < 1 ? 1 : parts;
+}
 
 // The operand rules of attention_mfma_supported, at most 16 queries, no bias.  A launch holds fewer than 2^32 threads, up to 1024 here
 // per workgroup (more than 128 entries have one workgroup each).
@@ -314,7 +401,15 @@ bool attention_decode_preferred(const AttnProblem& p) {
 }
 
 hipError_t launch_attention_decode(const AttnProblem& p, hipStream_t stream, int force_split, const char** name) {
-    const int split = force_split > 0 ? force_split : decode_split(p);
+    const int parts = decode_parts(p, force_split);
+    int dev = 0;
+    Scratch scratch;
+    static_assert(96 <= kScratchTickets && 192 * (128 * 16 + 64) * 4 <= kScratchBytes, "what decode_parts asks for at most");
+    if (parts > 1 && hipGetDevice(&dev) == hipSuccess && stream_scratch(dev, stream, &scratch)) {
+        *name = p.causal ? "attn_mfma_decode_q16_kv32_split_causal" : "attn_mfma_decode_q16_kv32_split";
+        return p.dtype == DT_BF16 ? launch_keys<bf16_t>(p, stream, parts, scratch) : launch_keys<f16_t>(p, stream, parts, scratch);
+    }
+    const int split = force_split > 0 && force_split < 8 ? force_split : decode_split(p);
     static const char* const names[3][2] = {{"attn_mfma_decode_q16_kv32_c1", "attn_mfma_decode_q16_kv32_c1_causal"},
                                             {"attn_mfma_decode_q16_kv32_c2", "attn_mfma_decode_q16_kv32_c2_causal"},
                                             {"attn_mfma_decode_q16_kv32_c4", "attn_mfma_decode_q16_kv32_c4_causal"}};

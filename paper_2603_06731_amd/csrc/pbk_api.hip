@@ -1,5 +1,5 @@
-// C ABI of libpbk: argument validation and dispatch.  No allocation, no
-// synchronisation; every call enqueues at most one kernel on the caller's stream.
+// C ABI of libpbk: argument validation and dispatch.  No synchronisation, no allocation but the scratch memory of a stream
+// (scratch.h); every call enqueues at most one kernel on the caller's stream.
 #include <hip/hip_runtime.h>
 #include <cstdio>
 #include <cstdlib>
@@ -39,7 +39,7 @@ bool parse_choice(const char* e, Choice* c) {
     // name and the ids it takes behind a colon (one digit each; any other string is unknown)
     static const struct { const char* name; int force; const char* ids; } names[] = {
         {"generic", FORCE_GENERIC, ""}, {"mfma", FORCE_MFMA, ""}, {"gather", FORCE_GATHER, "01"}, {"small", FORCE_SMALL, ""}, {"bstat", FORCE_BSTAT, ""},
-        {"ksplit", FORCE_KSPLIT, "01"}, {"tile64", FORCE_TILE64, "012"}, {"decode", FORCE_DECODE, "124"}};
+        {"ksplit", FORCE_KSPLIT, "01"}, {"tile64", FORCE_TILE64, "012"}, {"decode", FORCE_DECODE, "1248"}};
     for (const auto& n : names) {
         const size_t len = std::strlen(n.name);
         if (std::strncmp(e, n.name, len)) continue;

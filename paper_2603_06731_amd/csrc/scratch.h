@@ -1,0 +1,64 @@
+// Scratch memory of a stream, and the meeting of the workgroups that share one output tile.
+//
+// A problem with few output tiles leaves most of the chip idle unless several workgroups share a tile, each with its part of the
+// contraction (or of the keys).  Their partial results are put into scratch memory; the workgroup that arrives last adds them, in
+// the order of the parts and not of arrival, so that a call repeats itself bit for bit.  No workgroup waits for another one.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+namespace pbk {
+
+constexpr size_t kScratchBytes = (size_t)16 << 20;   // partial results
+constexpr int kScratchTickets = 4096;                // one per output tile; every launch leaves them at zero
+
+struct Scratch {
+    char* data;
+    unsigned* tickets;
+};
+
+// The scratch memory of `stream` on device `dev` (the current one).  Launches that share it are ordered by the stream.  False where
+// there is none: the caller then takes a kernel that needs none.
+// - Not while the stream is being captured: a graph is replayed on any stream, and next to eager work on this one.
+// - Not for the handles that stand for another stream in each thread.
+// - Up to kScratchStreams streams per device, and only if the memory can be had.
+bool stream_scratch(int dev, hipStream_t stream, Scratch* out);
+constexpr int kScratchStreams = 32;
+
+
+typedef __attribute__((ext_vector_type(4))) float scratch_f32x4;
+
+// Partial results pass between compute units that do not share a cache: stores and loads of device scope, which go to the memory
+// that all of them see, instead of ordinary ones with a write-back of the whole L2.
+__device__ __forceinline__ void scratch_put(float* dst, scratch_f32x4 v) {
+    typedef __attribute__((ext_vector_type(2))) float f2;
+    const f2 lo = {v[0], v[1]}, hi = {v[2], v[3]};
+    uint64_t* d = (uint64_t*)dst;
+    __hip_atomic_store(d, __builtin_bit_cast(uint64_t, lo), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(d + 1, __builtin_bit_cast(uint64_t, hi), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ scratch_f32x4 scratch_get(const float* src) {
+    typedef __attribute__((ext_vector_type(2))) float f2;
+    const uint64_t* s = (const uint64_t*)src;
+    const f2 lo = __builtin_bit_cast(f2, __hip_atomic_load(s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    const f2 hi = __builtin_bit_cast(f2, __hip_atomic_load(s + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    return scratch_f32x4{lo[0], lo[1], hi[0], hi[1]};
+}
+
+// Called by all threads of a workgroup after they have put their partial results: true in the workgroup that arrives last of
+// `parts`, which then finds all of them in scratch memory.  `flag`: a word of LDS.
+__device__ __forceinline__ bool scratch_last(unsigned* ticket, int parts, int* flag) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // this thread's stores have arrived in memory
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const unsigned before = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        *flag = before == (unsigned)(parts - 1);
+        // nobody else comes to this ticket: the next launch finds it at zero
+        if (before == (unsigned)(parts - 1)) __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    asm volatile("" ::: "memory");
+    return *flag != 0;
+}
+
+}  // namespace pbk
