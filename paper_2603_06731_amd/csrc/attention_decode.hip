@@ -272,13 +272,13 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void attention_decode_kernel(AttnP
     if constexpr (SPLIT) {
         // scratch memory of a part: PIECES pieces of the output at its reference points, then reference point and sum per query
         constexpr int PART = PIECES * 4 + 64;
-        float* entry = (float*)scratch.data + (size_t)b * parts * PART;
+        const __amdgpu_buffer_rsrc_t entry = scratch_buffer(scratch.data + (size_t)b * parts * PART * 4);
         if (mine) {
-            scratch_put(entry + (size_t)part * PART + e * 4, o);
-            if (e < 16) scratch_put(entry + (size_t)part * PART + PIECES * 4 + q * 4, f32x4{m, l, 0.0f, 0.0f});
+            scratch_put(entry, (part * PART + e * 4) * 4, o);
+            if (e < 16) scratch_put(entry, (part * PART + PIECES * 4 + q * 4) * 4, f32x4{m, l, 0.0f, 0.0f});
         }
         if (!scratch_last(scratch.tickets + b, parts, (int*)(l_all + NW * 16))) return;
-        auto o_of = [&](int w) { return scratch_get(entry + (size_t)w * PART + e * 4); };
+        auto o_of = [&](int w) { return scratch_get(entry, (w * PART + e * 4) * 4); };
         if (mine) {
 #pragma unroll
             for (int i = 0; i < AHEAD; ++i) v[i] = o_of(i < parts ? i : parts - 1);
@@ -286,7 +286,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void attention_decode_kernel(AttnP
         float* ml = (float*)lds;                   // (the waves' outputs have been read) reference points and sums of the parts
         for (int i = threadIdx.x; i < parts * 16; i += NW * 64) {
             if ((i & 15) >= p.Nq) continue;
-            const f32x4 x = scratch_get(entry + (size_t)(i >> 4) * PART + PIECES * 4 + (i & 15) * 4);
+            const f32x4 x = scratch_get(entry, ((i >> 4) * PART + PIECES * 4 + (i & 15) * 4) * 4);
             ml[i * 2] = x[0];
             ml[i * 2 + 1] = x[1];
         }

@@ -127,8 +127,9 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void gemm_mfma_ksplit_kernel(Probl
     constexpr int E = 4 * 64;
     static_assert(E <= NW * 64, "one entry per thread");
     FVec* red = (FVec*)lds;
-    float bias_v[NF], res_v[NF];
-    const bool has_bias = epi_has_bias(p.epi);
+    float bias_v[NF];
+    unsigned res_v[NF];                             // as they lie in memory: converted after the barrier, not behind every load
+    const bool has_bias = epi_has_bias(p.epi), out_f32 = p.out_dtype == DT_F32;
     const int64_t c_batch = (int64_t)b * p.stride_c;
     const int e = threadIdx.x, row = m0 + ((e & 63) >> 4) * 4 + ((e >> 6) & 3), col = n0 + (e & 15) * NF;
     const bool mine = e < E && row < p.M && col < p.N;
@@ -136,10 +137,10 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void gemm_mfma_ksplit_kernel(Probl
     for (int j = 0; j < NF; ++j) {                  // requested before the barrier, used after it
         const bool in = mine && col + j < p.N;
         bias_v[j] = has_bias && in ? p.bias[col + j] : 0.0f;
-        res_v[j] = 0.0f;
+        res_v[j] = 0;
         if (p.R && in) {
             const int64_t o = c_batch + (int64_t)row * p.ldr + col + j;
-            res_v[j] = p.out_dtype == DT_F32 ? ((const float*)p.R)[o] : widen<T>(((const T*)p.R)[o]);
+            if (out_f32) res_v[j] = ((const unsigned*)p.R)[o]; else res_v[j] = ((const uint16_t*)p.R)[o];
         }
     }
 #pragma unroll
@@ -156,7 +157,10 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void gemm_mfma_ksplit_kernel(Probl
     for (int w = 1; w < NW; ++w) v += red[w * E + e];
     float t[NF];
 #pragma unroll
-    for (int j = 0; j < NF; ++j) t[j] = apply_epilogue(v[j], p.alpha, bias_v[j], p.epi, p.R ? p.beta : 0.0f, res_v[j]);
+    for (int j = 0; j < NF; ++j) {
+        const float res = out_f32 ? __uint_as_float(res_v[j]) : widen<T>(__builtin_bit_cast(T, (uint16_t)res_v[j]));
+        t[j] = apply_epilogue(v[j], p.alpha, bias_v[j], p.epi, p.R ? p.beta : 0.0f, res);
+    }
     const int osz = p.out_dtype == DT_F32 ? 4 : 2;
     const bool vec = col + NF <= p.N && p.ldc % NF == 0 && ((uintptr_t)p.C + (uintptr_t)c_batch * osz) % (NF * osz) == 0;
     const int64_t o = c_batch + (int64_t)row * p.ldc + col;

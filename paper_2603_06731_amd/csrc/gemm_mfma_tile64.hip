@@ -5,6 +5,7 @@
 // staged in LDS by all waves (direct-to-LDS loads of 16 bytes per lane along the rows, whole lines), and then every
 // wave multiplies the WHOLE tile over its own 32 of the 128 k values, so that each staged byte is read from LDS once.
 // The waves' partial tiles meet in LDS at the end and are added in wave order (fixed: bit-exact from run to run).
+// With few tiles several workgroups share one, each with a run of the rounds (SPLIT); their sums meet in scratch memory (scratch.h).
 // What bounds it: the chain of rounds of a workgroup that is alone on its compute unit (N = 1024: 64 x 64 tiles 5.4 us and
 // 0.47 us per round, 32 x 64 tiles 4.2 and 0.34, with 32 workgroups on the chip as with 256); with two on a unit, its load
 // path, 70 to 84 GB/s.  577 x 1024 x 4096 with bias and residual (304 tiles of 32 x 64, two on 48 of the units): 48.6 us with
@@ -16,6 +17,7 @@
 // k..k+3 and k+8..k+11 of one slot).  Both are free of bank conflicts.  The MFMA takes B as its first operand, so a lane
 // holds 4 neighbouring columns of one row.
 #include "gemm_mfma_launch.h"
+#include "scratch.h"
 
 namespace pbk {
 namespace {
@@ -27,8 +29,10 @@ __device__ __forceinline__ int t64_row_slot(int k) { return ((k >> 1) & 1) | (((
 // exact quotient by a divisor d for numerators n with n * d < 2^32: magic = ceil(2^32 / d) (d = 1: 0 stands for 2^32)
 __device__ __forceinline__ int t64_div(int n, unsigned magic) { return magic ? (int)__umulhi((unsigned)n, magic) : n; }
 
-template <typename T, int MODE, int BM, int NSTAGE>
-__global__ __launch_bounds__(T64_NW * 64, 1) void gemm_mfma_tile64_kernel(Problem p, TileMap tm, unsigned cin_magic, unsigned kw_magic) {
+// SPLIT: `parts` workgroups per tile, each with a run of the rounds of k
+template <typename T, int MODE, int BM, int NSTAGE, bool SPLIT>
+__global__ __launch_bounds__(T64_NW * 64, 1) void gemm_mfma_tile64_kernel(Problem p, TileMap tm, unsigned cin_magic, unsigned kw_magic, int parts,
+                                                                          Scratch scratch) {
     constexpr bool TRANS_B = MODE == MODE_TRANS_B, CONV = MODE == MODE_CONV;
     constexpr int FM = BM / 16, FN = T64_BN / 16;
     constexpr int A_BYTES = BM * T64_BK * 2, STAGE = A_BYTES + T64_BN * T64_BK * 2;
@@ -42,6 +46,9 @@ __global__ __launch_bounds__(T64_NW * 64, 1) void gemm_mfma_tile64_kernel(Proble
 
     int b, tile_m, tile_n;
     map_tile(tm, blockIdx.x, b, tile_m, tile_n);
+    // (split: the map's batches are the parts, so that an XCD works on few runs of k, each of them on many tiles)
+    const int part = SPLIT ? b / p.batch : 0;
+    if (SPLIT) b -= part * p.batch;
     const int m0 = tile_m * BM, n0 = tile_n * T64_BN;
     const char* Ab = (const char*)p.A + (CONV ? 0 : ((int64_t)b * p.stride_a + (int64_t)m0 * p.lda) * 2);
     const char* Bb = (const char*)p.B + ((int64_t)b * p.stride_b + (TRANS_B ? (int64_t)n0 * p.ldb : (int64_t)n0)) * 2;
@@ -86,7 +93,10 @@ __global__ __launch_bounds__(T64_NW * 64, 1) void gemm_mfma_tile64_kernel(Proble
     auto dma = [&](int4v rsrc, unsigned addr, unsigned voff) {
         asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" :: "s"(addr), "v"(voff), "s"(rsrc) : "memory", "m0");
     };
-    const int R = (p.K + T64_BK - 1) / T64_BK;      // rounds; only the last can be ragged
+    const int all = (p.K + T64_BK - 1) / T64_BK;    // rounds; only the last can be ragged
+    // this workgroup's: r0 .. r0 + R - 1
+    const int each = SPLIT ? all / parts : all, rest = SPLIT ? all - each * parts : 0;
+    const int r0 = SPLIT ? part * each + (part < rest ? part : rest) : 0, R = SPLIT ? each + (part < rest ? 1 : 0) : all;
     auto issue = [&](int r, int stage) {
         const int k0 = r * T64_BK;
         const bool tail = k0 + T64_BK > p.K;        // wave-uniform
@@ -134,7 +144,7 @@ __global__ __launch_bounds__(T64_NW * 64, 1) void gemm_mfma_tile64_kernel(Proble
     for (int j = 0; j < FN; ++j)
         b_off[j] = A_BYTES + (TRANS_B ? kmaj + j * 4096 : tr_k * 128 + ((j ^ t64_row_slot(tr_k)) << 5) + (c & 3) * 8);
 
-    for (int r = 0; r < NSTAGE - 1 && r < R; ++r) issue(r, r);
+    for (int r = 0; r < NSTAGE - 1 && r < R; ++r) issue(r0 + r, r);
     int stage = 0, slot_in = NSTAGE - 1;
     for (int r = 0; r < R; ++r) {
         // round r has landed once only the younger rounds' loads are outstanding
@@ -146,7 +156,7 @@ __global__ __launch_bounds__(T64_NW * 64, 1) void gemm_mfma_tile64_kernel(Proble
         }
         static_assert(NSTAGE >= 2 && NSTAGE <= 4, "cases above");
         __syncthreads();                            // everyone's pieces landed; everyone is done with the stage refilled next
-        if (r + NSTAGE - 1 < R) issue(r + NSTAGE - 1, slot_in);
+        if (r + NSTAGE - 1 < R) issue(r0 + r + NSTAGE - 1, slot_in);
         const char* s = lds + stage * STAGE;
         short8v af[FM], bf[FN];
 #pragma unroll
@@ -176,22 +186,46 @@ __global__ __launch_bounds__(T64_NW * 64, 1) void gemm_mfma_tile64_kernel(Proble
     const int osz = out_f32 ? 4 : 2;
     const bool vec = p.N % 4 == 0 && p.ldc % 4 == 0 && ((uintptr_t)p.C + (uintptr_t)c_batch * osz) % (4 * osz) == 0;
     const int col = n0 + (threadIdx.x & 15) * 4;    // the same columns in every piece of the thread
-    float bias_v[4], res_v[PPT][4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) bias_v[e] = has_bias && col + e < p.N ? p.bias[col + e] : 0.0f;
+    const bool r_vec = p.R && p.N % 4 == 0 && p.ldr % 4 == 0 && ((uintptr_t)p.R + (uintptr_t)c_batch * osz) % (4 * osz) == 0;
+    float bias_v[4];
+    f32x4 res_v[PPT];                               // four values of the residual as they lie in memory (16-bit types: the first half)
     auto row_of = [&](int q) { return m0 + (int)(threadIdx.x >> 4) + q * 16; };
+    // bias and residual of the thread's pieces.  Whole pieces, and nothing is converted here: with a conversion behind every load the
+    // thread waited for each of its values in turn (577 x 1024 x 4096: 2.5 us).
+    auto fetch_tail = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int q = 0; q < PPT; ++q) {
-        const int row = row_of(q);
+        for (int e = 0; e < 4; ++e) bias_v[e] = has_bias && col + e < p.N ? p.bias[col + e] : 0.0f;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            res_v[q][e] = 0.0f;
-            if (p.R && row < p.M && col + e < p.N) {
-                const int64_t o = c_batch + (int64_t)row * p.ldr + col + e;
-                res_v[q][e] = out_f32 ? ((const float*)p.R)[o] : widen<T>(((const T*)p.R)[o]);
+        for (int q = 0; q < PPT; ++q) res_v[q] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        if (!p.R) return;
+#pragma unroll
+        for (int q = 0; q < PPT; ++q) {
+            const int row = row_of(q);
+            if (row >= p.M || col >= p.N) continue;
+            const int64_t o = c_batch + (int64_t)row * p.ldr + col;
+            if (r_vec && out_f32) {
+                res_v[q] = *(const f32x4*)((const float*)p.R + o);
+            } else if (r_vec) {
+                const int2v w = *(const int2v*)((const uint16_t*)p.R + o);
+                res_v[q][0] = __int_as_float(w[0]);
+                res_v[q][1] = __int_as_float(w[1]);
+            } else if (out_f32) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) if (col + e < p.N) res_v[q][e] = ((const float*)p.R)[o + e];
+            } else {
+                unsigned w[2] = {0, 0};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) if (col + e < p.N) w[e >> 1] |= (unsigned)((const uint16_t*)p.R)[o + e] << (16 * (e & 1));
+                res_v[q][0] = __uint_as_float(w[0]);
+                res_v[q][1] = __uint_as_float(w[1]);
             }
         }
-    }
+    };
+    auto res_of = [&](int q, int e) __attribute__((always_inline)) -> float {
+        if (out_f32) return res_v[q][e];
+        return widen<T>(__builtin_bit_cast(T, (uint16_t)(__float_as_uint(res_v[q][e >> 1]) >> (16 * (e & 1)))));
+    };
+    if constexpr (!SPLIT) fetch_tail();
     __syncthreads();                                // the ring is free
     f32x4* red = (f32x4*)lds;
 #pragma unroll
@@ -201,17 +235,48 @@ __global__ __launch_bounds__(T64_NW * 64, 1) void gemm_mfma_tile64_kernel(Proble
             red[wave * PIECES + (i * FN + j) * 64 + g * 16 + (c ^ (j * 4 + g))] = acc[i][j];
     __syncthreads();
     const int rj = (threadIdx.x & 15) >> 2, rg = threadIdx.x & 3;
+    f32x4 sum[PPT];
 #pragma unroll
     for (int q = 0; q < PPT; ++q) {
         const int at = (q * FN + rj) * 64 + rg * 16 + ((int)(threadIdx.x >> 4) ^ (rj * 4 + rg));
-        f32x4 v = red[at];
+        sum[q] = red[at];
 #pragma unroll
-        for (int w = 1; w < T64_NW; ++w) v += red[w * PIECES + at];
+        for (int w = 1; w < T64_NW; ++w) sum[q] += red[w * PIECES + at];
+    }
+    if constexpr (SPLIT) {
+        // the parts of the tile meet: part w, piece q, thread
+        const int tile = b * tm.tiles_per_batch + tile_m * tm.tiles_n + tile_n;
+        const __amdgpu_buffer_rsrc_t buf = scratch_buffer(scratch.data + (size_t)tile * parts * PIECES * 16);
+        auto at = [&](int w, int q) { return (int)((w * PIECES + q * (T64_NW * 64) + threadIdx.x) * 16); };
+#pragma unroll
+        for (int q = 0; q < PPT; ++q) scratch_put(buf, at(part, q), sum[q]);
+        if (!scratch_last(scratch.tickets + tile, parts, (int*)lds)) return;       // (the sums have been read by its first barrier)
+        fetch_tail();
+#pragma unroll
+        for (int q = 0; q < PPT; ++q) sum[q] = scratch_get(buf, at(0, q));
+        constexpr int AHEAD = 4;                    // parts requested together
+        for (int w = 1; w < parts; w += AHEAD) {
+            f32x4 v[AHEAD][PPT];
+#pragma unroll
+            for (int i = 0; i < AHEAD; ++i)
+#pragma unroll
+                for (int q = 0; q < PPT; ++q) v[i][q] = scratch_get(buf, at(w + i < parts ? w + i : parts - 1, q));
+#pragma unroll
+            for (int i = 0; i < AHEAD; ++i) {
+                if (w + i >= parts) break;
+#pragma unroll
+                for (int q = 0; q < PPT; ++q) sum[q] += v[i][q];
+            }
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < PPT; ++q) {
+        const f32x4 v = sum[q];
         const int row = row_of(q);
         if (row >= p.M || col >= p.N) continue;
         float t[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) t[e] = apply_epilogue(v[e], p.alpha, bias_v[e], p.epi, p.R ? p.beta : 0.0f, res_v[q][e]);
+        for (int e = 0; e < 4; ++e) t[e] = apply_epilogue(v[e], p.alpha, bias_v[e], p.epi, p.R ? p.beta : 0.0f, res_of(q, e));
         const int64_t o = c_batch + (int64_t)row * p.ldc + col;
         if (out_f32) {
             float* cp = (float*)p.C + o;
@@ -233,10 +298,11 @@ __global__ __launch_bounds__(T64_NW * 64, 1) void gemm_mfma_tile64_kernel(Proble
     }
 }
 
-template <typename T, int MODE, int BM, int NSTAGE>
-hipError_t launch_tile(const Problem& p, hipStream_t stream) {
+// parts: workgroups that share a tile's rounds (1: none, and no scratch memory)
+template <typename T, int MODE, int BM, int NSTAGE, bool SPLIT>
+hipError_t launch_tile(const Problem& p, hipStream_t stream, int parts, Scratch scratch) {
     constexpr int LDS_BYTES = NSTAGE * (BM + T64_BN) * T64_BK * 2;
-    auto kern = gemm_mfma_tile64_kernel<T, MODE, BM, NSTAGE>;
+    auto kern = gemm_mfma_tile64_kernel<T, MODE, BM, NSTAGE, SPLIT>;
     static std::atomic<unsigned> attr_done{0};      // bit per device
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -253,7 +319,7 @@ hipError_t launch_tile(const Problem& p, hipStream_t stream) {
     TileMap tm{};
     tm.tiles_m = (p.M + BM - 1) / BM;
     tm.tiles_n = (p.N + T64_BN - 1) / T64_BN;
-    const long long total = (long long)tm.tiles_m * tm.tiles_n * p.batch;
+    const long long total = (long long)tm.tiles_m * tm.tiles_n * p.batch * parts;
     if (total <= 0 || total > 0x7FFFFFFFLL) return hipErrorInvalidValue;
     tm.tiles_per_batch = tm.tiles_m * tm.tiles_n;
     tm.total = (int)total;
@@ -262,14 +328,17 @@ hipError_t launch_tile(const Problem& p, hipStream_t stream) {
     auto magic = [](int d) { return d > 1 ? (unsigned)(((1ull << 32) + d - 1) / d) : 0u; };
     unsigned cin_magic = p.is_conv ? magic(p.conv.Cin) : 0, kw_magic = p.is_conv ? magic(p.conv.KW) : 0;
     Problem pa = p;
-    void* args[] = {&pa, &tm, &cin_magic, &kw_magic};
+    void* args[] = {&pa, &tm, &cin_magic, &kw_magic, &parts, &scratch};
     return hipLaunchKernel((const void*)kern, dim3((unsigned)total), dim3(T64_NW * 64), args, LDS_BYTES, stream);
 }
 
-template <typename T, int BM, int NSTAGE>
-hipError_t launch_mode(const Problem& p, hipStream_t stream) {
-    if (p.is_conv) return launch_tile<T, MODE_CONV, BM, NSTAGE>(p, stream);
-    return p.trans_b ? launch_tile<T, MODE_TRANS_B, BM, NSTAGE>(p, stream) : launch_tile<T, MODE_DENSE, BM, NSTAGE>(p, stream);
+constexpr int kDeepK = 16;               // tile64_choice only
+
+template <typename T, int BM, int NSTAGE, bool SPLIT = false>
+hipError_t launch_mode(const Problem& p, hipStream_t stream, int parts = 1, Scratch scratch = Scratch{}) {
+    if (p.is_conv) return launch_tile<T, MODE_CONV, BM, NSTAGE, SPLIT>(p, stream, parts, scratch);
+    return p.trans_b ? launch_tile<T, MODE_TRANS_B, BM, NSTAGE, SPLIT>(p, stream, parts, scratch)
+                     : launch_tile<T, MODE_DENSE, BM, NSTAGE, SPLIT>(p, stream, parts, scratch);
 }
 
 template <typename T>
@@ -278,6 +347,7 @@ hipError_t launch_type(const Problem& p, hipStream_t stream, int cfg, const char
     case 0: *name = "mfma16_tile64_64x64_s4"; return launch_mode<T, 64, 4>(p, stream);
     case 1: *name = "mfma16_tile64_32x64_s3"; return launch_mode<T, 32, 3>(p, stream);
     case 2: *name = "mfma16_tile64_64x64_s2"; return launch_mode<T, 64, 2>(p, stream);
+    case kDeepK: *name = "mfma16_tile64_64x64_s3"; return launch_mode<T, 64, 3>(p, stream);
     default: return hipErrorInvalidValue;
     }
 }
@@ -299,16 +369,18 @@ bool mfma_tile64_supported(const Problem& p) {
 // Tile of a problem (the names in launch_type): where the 32 x 64 tiles, two workgroups per compute unit, make at
 // most little more than one round of the 256 units, they win (512 x 1024 x 1024: 6.6 against 8.8 us for one 64 x 64 tile per
 // unit; up to 256 tiles 0.70 to 0.83 of its time for K = 256 ... 4096; 257 to 320 tiles, twelve shapes with N = 512 ... 4160: K up to
-// 1024 0.78 to 0.96, 2048 0.83 to 1.07, 4096 0.86 to 1.18, even on average: 577 x 1024 with residual 22.5 against 22.6 us; from
+// 1024 0.78 to 0.96, 2048 0.83 to 1.07, 4096 0.86 to 1.18 of the four-stage form; 577 x 1024 x 4096: 22.5 against 19.3 us with three stages; from
 // 321 to 400 tiles K up to 1024 0.80 to 0.97, 4096 0.96 to 1.08), for a convolution, whose addresses cost vector instructions that a second
 // workgroup hides, up to one round of 64 x 64 tiles (8 x 14 x 14 x 512 -> 512, 3 x 3: 25.6 against 33 us); then one 64 x 64
-// tile per unit with a deep ring (256 x 4096 x 4096: 20.7 against 22.7 and 24.0 us), beyond that two per unit
+// tile per unit with a deep ring (256 x 4096 x 4096: 20.7 against 22.7 and 24.0 us; three stages are as good for short contractions and
+// ahead for long ones: 577 x 1024 x 4096 20.1 against 19.3, k-major B 19.4 against 18.2, 256 x 1024 x 1024 8.6 and 8.5), beyond that two per unit
 // (1024 x 2048 x 2048: 16.4 against 24.3 us).
 static int tile64_choice(const Problem& p) {
     const long long t32 = (long long)((p.M + 31) / 32) * ((p.N + 63) / 64) * p.batch;
     const long long t64 = (long long)((p.M + 63) / 64) * ((p.N + 63) / 64) * p.batch;
-    if (p.M <= 32 || t32 <= 320 || (p.is_conv && t64 <= 256)) return 1;
-    return t64 <= 256 ? 0 : 2;
+    if (p.M <= 32 || t32 <= 256 || (p.is_conv && t64 <= 256)) return 1;
+    if (t32 <= 320 && p.K < 3072) return 1;
+    return t64 > 256 ? 2 : p.K >= 2048 ? kDeepK : 0;
 }
 
 // Up to half a round of 128 x 128 tiles on the 256 compute units (measured against their deep ring: 64 tiles, K = 4096: 20.7
@@ -323,8 +395,42 @@ bool mfma_tile64_preferred(const Problem& p) {
     return t128 <= 128 && p.K >= rounds * T64_BK;
 }
 
+// Workgroups that share a 32 x 64 tile (1: tiles are not split).  Up to 128 tiles, so that 192 to 256 workgroups share the work, each with at
+// least four rounds.  Times in us, unsplit (ksplit up to 16 rows) first:
+// - 31 x 1344 x 13312, 21 tiles: 36.3 against 12.6 with 8 parts; 48 x 1024 x 16384: 45.4 and 13.1; 18 x 2112 x 4096: 13.7 and 8.6; 256 x
+//   1024 x 3968, 128 tiles: 13.9 and 11.0 with 2; 3 x 3 convolutions 196 x 512 x 4608: 21.3 and 11.3, 48 x 256 x 4608: 20.6 and 9.4;
+// - the parts' meeting takes some 3 us, which short contractions do not give back: 128 x 1024 x 1024: 6.4 and 6.9, 20 x 1024 x 1024: 6.3 and
+//   6.3, 376 x 576 x 1856: 8.4 and 8.2; a convolution, whose rounds take longer, 784 x 128 x 1152: 8.0 and 7.6;
+// - up to 16 rows against ksplit: 8 x 1024 x 4096: 7.0 and 8.0, 14 x 1472 x 6144: 13.8 and 9.2, 16 x 4096 x 4096: 13.2 and 10.3, 8 x 1024 x
+//   16384: 33.6 and 12.5, but 6 x 3456 x 2368: 6.7 and 7.9;
+// - more tiles: 1024 x 320 x 4096, 160 tiles: 14.2 and 13.8, 1024 x 480 x 4096: 14.9 and 15.8.
+static int tile64_parts(const Problem& p, bool forced) {
+    const long long tiles = (long long)((p.M + 31) / 32) * ((p.N + 63) / 64) * p.batch;
+    const int rounds = (p.K + T64_BK - 1) / T64_BK;
+    if (tiles > 128) return 1;
+    if (!forced && rounds < (p.is_conv ? 9 : 12)) return 1;
+    if (!forced && p.M <= 16 && !p.is_conv && (p.K < 4096 || (int64_t)p.N * p.K < (p.trans_b ? 4000000 : 6000000))) return 1;
+    int parts = (int)((192 + tiles / 2) / tiles);
+    const int most = forced ? rounds : rounds / 4;
+    parts = parts < 8 ? parts : 8;
+    return parts < most ? parts : most;
+}
+
+bool mfma_tile64_split_preferred(const Problem& p) { return tile64_parts(p, false) > 1; }
+
+bool launch_mfma_tile64_split(const Problem& p, hipStream_t stream, bool forced, const char** name, hipError_t* e) {
+    static_assert(128 <= kScratchTickets && 256 * 32 * T64_BN * 4 <= kScratchBytes, "up to 192 + 128 / 2 parts");
+    const int parts = tile64_parts(p, forced);
+    int dev = 0;
+    Scratch scratch;
+    if (parts <= 1 || hipGetDevice(&dev) != hipSuccess || !stream_scratch(dev, stream, &scratch)) return false;
+    *name = "mfma16_tile64_32x64_s3_split";
+    *e = p.in_dtype == DT_BF16 ? launch_mode<bf16_t, 32, 3, true>(p, stream, parts, scratch) : launch_mode<f16_t, 32, 3, true>(p, stream, parts, scratch);
+    return true;
+}
+
 hipError_t launch_mfma_tile64(const Problem& p, hipStream_t stream, int cfg, const char** name) {
-    const int c = cfg >= 0 ? cfg : tile64_choice(p);
+    const int c = cfg >= 0 && cfg <= 2 ? cfg : cfg == kSplitChoice ? 1 : tile64_choice(p);
     return p.in_dtype == DT_BF16 ? launch_type<bf16_t>(p, stream, c, name) : launch_type<f16_t>(p, stream, c, name);
 }
 

@@ -39,7 +39,7 @@ bool parse_choice(const char* e, Choice* c) {
     // name and the ids it takes behind a colon (one digit each; any other string is unknown)
     static const struct { const char* name; int force; const char* ids; } names[] = {
         {"generic", FORCE_GENERIC, ""}, {"mfma", FORCE_MFMA, ""}, {"gather", FORCE_GATHER, "01"}, {"small", FORCE_SMALL, ""}, {"bstat", FORCE_BSTAT, ""},
-        {"ksplit", FORCE_KSPLIT, "01"}, {"tile64", FORCE_TILE64, "012"}, {"decode", FORCE_DECODE, "1248"}};
+        {"ksplit", FORCE_KSPLIT, "01"}, {"tile64", FORCE_TILE64, "0128"}, {"decode", FORCE_DECODE, "1248"}};
     for (const auto& n : names) {
         const size_t len = std::strlen(n.name);
         if (std::strncmp(e, n.name, len)) continue;
@@ -94,7 +94,7 @@ pbk_status dispatch(const pbk::Problem& p_in, hipStream_t stream) {
     // unaligned bases) still run on the matrix units, staged through registers, when there is enough work
     const bool can_gather = pbk::mfma_gather_supported(p);
     const bool want_gather = !can_mfma && can_gather && (long long)p.M * p.N >= 4096 && p.K >= 16;
-    // fp32 problems of a few hundred 16 x 16 tiles: one wave per tile
+    // fp32 problems of up to some thousand 16 x 16 tiles: the operands go straight to registers
     const bool can_small = pbk::small_f32_supported(p);
     // short contractions over many rows: the B-stationary kernel
     const bool can_bstat = pbk::mfma_bstat_supported(p);
@@ -104,7 +104,11 @@ pbk_status dispatch(const pbk::Problem& p_in, hipStream_t stream) {
         (force == FORCE_BSTAT && !can_bstat) || (force == FORCE_KSPLIT && !can_ksplit) || (force == FORCE_TILE64 && !can_tile64) ||
         force == FORCE_DECODE)
         return PBK_ERR_UNSUPPORTED;
-    if (force == FORCE_BSTAT || (force == FORCE_NONE && can_bstat && pbk::mfma_bstat_preferred(p)))
+    // (a call that finds no scratch memory goes on to the kernels that need none)
+    const bool split = (force == FORCE_TILE64 && cfg == pbk::kSplitChoice) || (force == FORCE_NONE && can_tile64 && pbk::mfma_tile64_split_preferred(p));
+    if (split && pbk::launch_mfma_tile64_split(p, stream, force == FORCE_TILE64, &name, &e)) {
+        // launched
+    } else if (force == FORCE_BSTAT || (force == FORCE_NONE && can_bstat && pbk::mfma_bstat_preferred(p)))
         e = pbk::launch_mfma_bstat(p, stream, &name);
     else if (force == FORCE_KSPLIT || (force == FORCE_NONE && can_ksplit && pbk::mfma_ksplit_preferred(p)))
         e = pbk::launch_mfma_ksplit(p, stream, cfg, &name);

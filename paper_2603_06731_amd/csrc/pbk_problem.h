@@ -109,6 +109,11 @@ hipError_t launch_mfma_ksplit(const Problem& p, hipStream_t stream, int force_cf
 bool mfma_tile64_supported(const Problem& p);
 bool mfma_tile64_preferred(const Problem& p);
 hipError_t launch_mfma_tile64(const Problem& p, hipStream_t stream, int force_cfg, const char** name);
+// tile64 with the contraction split over workgroups as well, in scratch memory of the stream; launch: false where the problem is not
+// split (forced: any that makes two parts of a round) or there is no scratch memory, and nothing was launched then.
+constexpr int kSplitChoice = 8;          // its id behind "tile64:"
+bool mfma_tile64_split_preferred(const Problem& p);
+bool launch_mfma_tile64_split(const Problem& p, hipStream_t stream, bool forced, const char** name, hipError_t* e);
 
 // PBK_GROUP_M of the environment as read at the process's first call (0 = not set): tile rows
 // per group of the block mapping, a benchmarking override.

@@ -9,7 +9,7 @@
 
 namespace pbk {
 
-constexpr size_t kScratchBytes = (size_t)16 << 20;   // partial results
+constexpr size_t kScratchBytes = (size_t)4 << 20;    // partial results
 constexpr int kScratchTickets = 4096;                // one per output tile; every launch leaves them at zero
 
 struct Scratch {
@@ -28,21 +28,20 @@ constexpr int kScratchStreams = 32;
 
 typedef __attribute__((ext_vector_type(4))) float scratch_f32x4;
 
-// Partial results pass between compute units that do not share a cache: stores and loads of device scope, which go to the memory
-// that all of them see, instead of ordinary ones with a write-back of the whole L2.
-__device__ __forceinline__ void scratch_put(float* dst, scratch_f32x4 v) {
-    typedef __attribute__((ext_vector_type(2))) float f2;
-    const f2 lo = {v[0], v[1]}, hi = {v[2], v[3]};
-    uint64_t* d = (uint64_t*)dst;
-    __hip_atomic_store(d, __builtin_bit_cast(uint64_t, lo), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(d + 1, __builtin_bit_cast(uint64_t, hi), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// Partial results pass between compute units that do not share a cache: stores and loads of device scope (cache policy sc1), which go
+// to the memory that all of them see, instead of ordinary ones with a write-back of the whole L2.  16 bytes a lane, whole lines a
+// wave: as two 8-byte atomic stores a lane, 6 MB of partial results took some 10 us longer.
+// Buffer over a workgroup-uniform base; offsets in bytes below 2^31.
+constexpr int kScratchDeviceScope = 16;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t scratch_buffer(const void* base) {
+    return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)0x80000000u, 0x00020000);
 }
-__device__ __forceinline__ scratch_f32x4 scratch_get(const float* src) {
-    typedef __attribute__((ext_vector_type(2))) float f2;
-    const uint64_t* s = (const uint64_t*)src;
-    const f2 lo = __builtin_bit_cast(f2, __hip_atomic_load(s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-    const f2 hi = __builtin_bit_cast(f2, __hip_atomic_load(s + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-    return scratch_f32x4{lo[0], lo[1], hi[0], hi[1]};
+__device__ __forceinline__ void scratch_put(__amdgpu_buffer_rsrc_t buf, int offset, scratch_f32x4 v) {
+    typedef __attribute__((ext_vector_type(4))) unsigned u4;
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, v), buf, offset, 0, kScratchDeviceScope);
+}
+__device__ __forceinline__ scratch_f32x4 scratch_get(__amdgpu_buffer_rsrc_t buf, int offset) {
+    return __builtin_bit_cast(scratch_f32x4, __builtin_amdgcn_raw_buffer_load_b128(buf, offset, 0, kScratchDeviceScope));
 }
 
 // Called by all threads of a workgroup after they have put their partial results: true in the workgroup that arrives last of

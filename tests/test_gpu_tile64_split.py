@@ -1,0 +1,138 @@
+"""64-wide tiles with the contraction split over workgroups, whose sums meet in a stream's scratch memory: against the oracle, bit-for-bit
+repetition on one stream and on two at once, distance from 64 bits, and the calls that go without a split."""
+import numpy as np
+import pytest
+
+import workloads as wl
+from workloads import configs as C
+import pbk_testlib as T
+from test_gpu_bstat import run_case
+from test_gpu_few_tiles import CONVS, TOL
+
+pytestmark = pytest.mark.gpu
+
+BF16, F16, F32 = wl.DTYPE_BF16, wl.DTYPE_F16, wl.DTYPE_F32
+
+SHAPES = [  # batch, M, N, K, padding of the rows, split
+    (1, 1, 8, 136, 0, True),         # two parts, the second of one piece
+    (1, 5, 72, 264, 0, True),        # three parts, columns beyond the tile
+    (2, 16, 136, 1096, 8, True),     # more parts than are requested together; views with NaN behind the rows
+    (3, 33, 64, 392, 0, True),       # a second row tile with one row, batches
+    (1, 1024, 256, 384, 0, True),    # 128 tiles, two parts with unequal shares
+    (1, 1024, 264, 384, 0, False),   # 160 tiles: not split
+    (1, 33, 64, 128, 0, False),      # a single round
+]
+
+
+@pytest.mark.parametrize("trans_b", [0, 1])
+@pytest.mark.parametrize("dtype,out_dtype,epi", [(BF16, BF16, C.EPI_BIAS_GELU_TANH), (F16, F16, C.EPI_BIAS_RELU), (BF16, F32, C.EPI_NONE)])
+def test_matmul(dtype, out_dtype, epi, trans_b):
+    for batch, M, N, K, pad, split in SHAPES:
+        err, kern = run_case(batch, M, N, K, dtype, out_dtype, trans_b, epi, pad_ld=pad, force="tile64:8", bias_on=epi != C.EPI_NONE)
+        assert "tile64_32x64" in kern and ("split" in kern) == split, kern
+        assert err <= TOL[out_dtype], (batch, M, N, K, err)
+
+
+@pytest.mark.parametrize("dtype", [BF16, F16])
+@pytest.mark.parametrize("case", CONVS)
+def test_conv(case, dtype):
+    import paper_2603_06731_amd as pbk
+    n, H, W, Cin, Cout, KH, KW, stride, pad, dil = case
+    w = wl.Workload("tile64_split_conv", "conv", dtype, dtype, C.EPI_BIAS_RELU, n=n, H=H, W=W, Cin=Cin, Cout=Cout, KH=KH, KW=KW,
+                    stride=stride, pad=pad, dil=dil, dist_b=("normal", float(np.sqrt(2.0 / (KH * KW * Cin)))))
+    host = wl.make_inputs(w)
+    with T.forced_kernel("tile64:8"):
+        st, out = T.run_workload(w, T.upload(host))
+    assert st == 0 and ("split" in pbk.pbk_last_kernel()) == (KH * KW * Cin > 128), pbk.pbk_last_kernel()
+    ref, pre = T.oracle_full(w, host)
+    err = T.rel_err(T.to_host_f64(out, w.out_dtype).reshape(ref.shape), ref, pre)
+    assert err <= TOL[dtype], err
+
+
+def product(M, N, K, trans_b=0, seed=0):
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(M + K + seed)
+    a = torch.randn(M, K, generator=g, device="cuda").bfloat16()
+    b = (torch.randn(*((N, K) if trans_b else (K, N)), generator=g, device="cuda") * K ** -0.5).bfloat16()
+    return a, b
+
+
+def call(a, b, out, trans_b=0, r=None, stream=None):
+    import paper_2603_06731_amd as pbk
+    (M, K), N = a.shape, out.shape[1]
+    if r is not None:
+        return pbk.pbk_matmul_residual(a, b, out, None, r, M, N, K, K, K if trans_b else N, N, N, BF16, BF16, trans_b, 1.0, 2.0, 0, stream)
+    return pbk.pbk_matmul(a, b, out, None, M, N, K, K, K if trans_b else N, N, BF16, BF16, trans_b, 1.0, 0, stream)
+
+
+def reference(a, b, trans_b=0):
+    bd = b.double().T.contiguous() if trans_b else b.double()
+    return a.double() @ bd
+
+
+@pytest.mark.parametrize("M,N,K,trans_b,kernel", [
+    (32, 1024, 1409, 0, "gather"), (32, 1024, 1408, 0, "tile64_32x64_s3"), (32, 1024, 1416, 0, "split"),      # eleven rounds, twelve
+    (256, 1024, 4096, 1, "split"), (257, 1024, 4096, 1, "tile64_32x64_s3"),                                   # 128 tiles, 144
+    (16, 1024, 5856, 0, "ksplit"), (16, 1024, 5864, 0, "split"),                                              # values of B
+    (16, 8192, 4096, 0, "split"), (16, 8256, 4096, 0, "ksplit"),
+    (513, 1024, 3064, 0, "tile64_32x64"), (513, 1024, 3072, 0, "64x64_s3"), (640, 1024, 2048, 0, "tile64_32x64"), (641, 1024, 2048, 0, "64x64_s3"),
+    (641, 1024, 2040, 0, "64x64_s4"),
+])
+def test_dispatch(M, N, K, trans_b, kernel):
+    """Either side of each line of the rules, with the automatic choice."""
+    import torch
+    import paper_2603_06731_amd as pbk
+    a, b = product(M, N, K, trans_b)
+    out = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    with T.forced_kernel(None):
+        assert call(a, b, out, trans_b) == 0
+    name = pbk.pbk_last_kernel()
+    assert kernel in name and ("_split" in name) == (kernel == "split"), name
+    ref = reference(a, b, trans_b)
+    # one rounding to bf16 (2^-9 of the value), fp32 sums of K terms of order K^-1/2
+    assert torch.all((out.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-4)
+
+
+def test_repeats_streams_and_residual():
+    """The same bits call after call, with the parts arriving in any order, while another stream does the same with other operands; the
+    distance from 64 bits is that of the kernel without a split."""
+    import torch
+    M, N, K = 70, 1024, 4096
+    (a, b), (c, d) = product(M, N, K), product(M, N, K, seed=1)
+    r = torch.randn(M, N, device="cuda").bfloat16()
+    oa, oc = [[torch.empty(M, N, dtype=torch.bfloat16, device="cuda") for _ in range(24)] for _ in range(2)]
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+    for x, y in zip(oa, oc):
+        assert call(a, b, x, r=r, stream=streams[0]) == 0 and call(c, d, y, stream=streams[1]) == 0
+    torch.cuda.synchronize()
+    assert all(torch.equal(x, oa[0]) for x in oa) and all(torch.equal(y, oc[0]) for y in oc)
+    ra, rc = reference(a, b) + 2.0 * r.double(), reference(c, d)
+    for got, ref in ((oa[0], ra), (oc[0], rc)):
+        assert torch.all((got.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-4)
+    whole = torch.empty_like(oc[0])
+    with T.forced_kernel("tile64:1"):
+        assert call(c, d, whole) == 0
+    far = [float((x.double() - rc).norm() / rc.norm()) for x in (oc[0], whole)]
+    assert far[0] <= far[1] * 1.01, far          # (the rounding of the output, to four digits)
+
+
+def test_captured():
+    """A captured call goes without a split and replays next to eager ones."""
+    import torch
+    import paper_2603_06731_amd as pbk
+    a, b = product(16, 2048, 8192)
+    out, cap = (torch.empty(16, 2048, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    assert call(a, b, out, stream=torch.cuda.current_stream()) == 0 and "split" in pbk.pbk_last_kernel().replace("ksplit", "")
+    eager, ref = out.clone(), reference(a, b)
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        assert call(a, b, cap, stream=torch.cuda.current_stream()) == 0 and "ksplit" in pbk.pbk_last_kernel()
+    for _ in range(3):
+        cap.zero_()
+        graph.replay()
+        assert call(a, b, out, stream=torch.cuda.current_stream()) == 0
+        torch.cuda.synchronize()
+        assert torch.equal(out, eager)
+        assert torch.all((cap.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-4)
