@@ -9,7 +9,7 @@ hipError_t launch_mfma_int8(const Problem& p, hipStream_t stream, int cfg, int g
     const Problem q = to_k_units(p);
     switch (cfg) {
     case 0: return launch_typed_modes<int8_t, bf16_t, 128, 256, 32, 1, 4, 3, 2>(q, stream, group_m);
-    case 1: return launch_typed_modes<int8_t, bf16_t, 128, 128, 64, 2, 2, 2, 1>(q, stream, group_m);
+    case 1: return launch_typed_modes<int8_t, bf16_t, 128, 128, 64, 2, 2, 2, 2>(q, stream, group_m);
     case 2: return launch_typed_modes<int8_t, bf16_t, 128, 128, 64, 2, 2, 4, 1>(q, stream, group_m);
     case 4: return launch_typed_modes<int8_t, bf16_t, 256, 256, 64, 2, 4, 2, 1>(q, stream, group_m);
     case 8:     // 16x16x64 blocks: both operands k-major only

@@ -384,28 +384,14 @@ struct EpiCtx {
         return t;
     }
 
-    // residual values R[gm][gn..gn+3] widened to float (zero where there is no residual operand);
-    // vec: whole aligned 4-element pieces may be loaded at once
-    template <bool OUT_F32> __device__ __forceinline__ void res4(int gm, int gn, bool vec, float (&rv)[4]) const {
+    // residual values R[gm][gn..gn+3] widened to float (zero where there is no residual operand)
+    template <bool OUT_F32> __device__ __forceinline__ void res4(int gm, int gn, float (&rv)[4]) const {
         rv[0] = rv[1] = rv[2] = rv[3] = 0.0f;
         if (!p.R || gm >= rows.m || gn >= p.N) return;
         const int64_t o = c_batch + rows.at(gm) * p.ldr + gn;
-        if (OUT_F32) {
-            if (vec) { f32x4 q = *(const f32x4*)((const float*)p.R + o); rv[0] = q[0]; rv[1] = q[1]; rv[2] = q[2]; rv[3] = q[3]; }
-            else {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) if (gn + e < p.N) rv[e] = ((const float*)p.R)[o + e];
-            }
-        } else {
-            T h[4] = {(T)0.0f, (T)0.0f, (T)0.0f, (T)0.0f};
-            if (vec) { int2v q = *(const int2v*)((const uint16_t*)p.R + o); __builtin_memcpy(h, &q, 8); }
-            else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) if (gn + e < p.N) h[e] = ((const T*)p.R)[o + e];
-            }
-#pragma unroll
-            for (int e = 0; e < 4; ++e) rv[e] = (float)h[e];
-        }
+        for (int e = 0; e < 4; ++e)
+            if (gn + e < p.N) rv[e] = OUT_F32 ? ((const float*)p.R)[o + e] : widen(((const T*)p.R)[o + e]);
     }
 
     // bias for columns gn..gn+3 (zero where there is none)
@@ -432,7 +418,7 @@ struct EpiCtx {
         // the residual operand is a compile-time property of the staged path: its loads and bounds tests
         // would otherwise sit, as branches, in front of every 4-wide piece of every epilogue
         if (!fast) run_direct<OUT_F32>(bias_vec, ACT);
-        else if (p.R) run_staged<ACT, OUT_F32, true>(bias_vec);
+        else if (ROWS::kPlain && p.R) run_staged<ACT, OUT_F32, true>(bias_vec);      // (a transposed convolution has none)
         else run_staged<ACT, OUT_F32, false>(bias_vec);
     }
 
@@ -450,8 +436,8 @@ struct EpiCtx {
         constexpr int ROWS_PER_LD = 64 / CPR;               // rows covered by one wave-wide 16-byte read
         static_assert((RB % ROWS_PER_LD) == 0, "reads must tile a row block");
         const int ld_row = lane / CPR, ld_chunk = lane % CPR;
-        const bool res_vec = HAS_RES && (p.ldr % 4 == 0) &&
-                             (((uintptr_t)p.R + (uintptr_t)c_batch * ESZ) % (4 * ESZ) == 0);
+        // rows of R in whole aligned 16-byte chunks, like those of C?
+        const bool res_vec = HAS_RES && (p.ldr % EPC == 0) && (((uintptr_t)p.R + (uintptr_t)c_batch * ESZ) % 16 == 0);
 
         // every bias value this lane needs, loaded once and together
         float bias_r[FN][G][4];
@@ -463,6 +449,47 @@ struct EpiCtx {
 
 #pragma unroll
         for (int i0 = 0; i0 < FM; i0 += PASS_BLOCKS) {
+            constexpr int PASS_ROWS = PASS_BLOCKS * RB;
+            constexpr int NLD = PASS_ROWS / ROWS_PER_LD;
+            const int gn = col0 + ld_chunk * EPC;
+            const int lrow0 = i0 * RB + ld_row;                     // row inside the wave tile
+            const int rows_left = (rows.m - row0 < WTM ? rows.m - row0 : WTM) - lrow0;   // valid rows from lrow0 on
+            if (HAS_RES) {
+                // The residual takes the way of the results in the other direction: row chunks of 16 bytes, many of them requested
+                // together, into the places in LDS where the results of the same elements will be put.  (Read in the accumulator
+                // layout, 8 bytes at a time behind a test each, a lane waited for up to 32 of them in turn: 4096 x 1024 x 512, 8 MB of
+                // residual, 13.6 against 9.8 us without.)
+                const char* rptr = (const char*)p.R;
+                auto r_of = [&](int q) { return (c_batch + rows.at(row0 + lrow0 + q * ROWS_PER_LD) * p.ldr + gn) * ESZ; };
+                auto place = [&](int q) -> int4v* {
+                    const int lrow = q * ROWS_PER_LD + ld_row;
+                    return (int4v*)(wlds + lrow * ROW_BYTES + ((ld_chunk ^ ((lrow / RP) % CPR)) << 4));
+                };
+                if (res_vec) {
+                    constexpr int RBATCH = NLD < 16 ? NLD : 16;
+#pragma unroll
+                    for (int q0 = 0; q0 < NLD; q0 += RBATCH) {
+                        int4v w[RBATCH];
+#pragma unroll
+                        for (int q = 0; q < RBATCH && q0 + q < NLD; ++q) {        // (NLD need not be a multiple)
+                            w[q] = int4v{0, 0, 0, 0};
+                            if ((q0 + q) * ROWS_PER_LD < rows_left && gn < p.N) w[q] = *(const int4v*)(rptr + r_of(q0 + q));
+                        }
+#pragma unroll
+                        for (int q = 0; q < RBATCH && q0 + q < NLD; ++q) *place(q0 + q) = w[q];
+                    }
+                } else {
+                    for (int q = 0; q < NLD; ++q) {
+                        if (q * ROWS_PER_LD >= rows_left || gn >= p.N) continue;
+                        const int64_t o = r_of(q);
+#pragma unroll
+                        for (int e = 0; e < EPC; ++e) {
+                            if (OUT_F32) ((float*)place(q))[e] = ((const float*)(rptr + o))[e];
+                            else ((uint16_t*)place(q))[e] = ((const uint16_t*)(rptr + o))[e];
+                        }
+                    }
+                }
+            }
             // registers -> LDS (row-major [rows][WTN], 16-byte chunks XOR-swizzled by row)
 #pragma unroll
             for (int ii = 0; ii < PASS_BLOCKS; ++ii) {
@@ -476,11 +503,21 @@ struct EpiCtx {
                     for (int g = 0; g < G; ++g) {
                         const int lcol = lcol_of(j, g);
                         float v[4], rv[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-                        if (HAS_RES) res4<OUT_F32>(row0 + lrow_of(i), col0 + lcol, res_vec, rv);
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) v[e] = act_of<ACT, HAS_RES>(val(i, j, g, e), bias_r[j][g][e], rv[e]);
                         const int cbyte = lcol * ESZ;
                         char* dst = wlds + lrow * ROW_BYTES + ((((cbyte >> 4) ^ sw)) << 4) + (cbyte & 15);
+                        if (HAS_RES && OUT_F32) {
+                            const f32x4 h = *(const f32x4*)dst;
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) rv[e] = h[e];
+                        } else if (HAS_RES) {
+                            T h[4];
+                            const int2v w = *(const int2v*)dst;
+                            __builtin_memcpy(h, &w, 8);
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) rv[e] = widen(h[e]);
+                        }
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) v[e] = act_of<ACT, HAS_RES>(val(i, j, g, e), bias_r[j][g][e], rv[e]);
                         if (OUT_F32) {
                             f32x4 w = {v[0], v[1], v[2], v[3]};
                             *(f32x4*)dst = w;
@@ -495,14 +532,9 @@ struct EpiCtx {
             }
             // LDS -> global, 16 bytes per lane, lanes running along rows; reads are
             // batched ahead of the stores so their latency is paid once per batch
-            constexpr int PASS_ROWS = PASS_BLOCKS * RB;
-            constexpr int NLD = PASS_ROWS / ROWS_PER_LD;
             constexpr int BATCH = NLD < 8 ? NLD : 8;
-            const int gn = col0 + ld_chunk * EPC;
-            const int lrow0 = i0 * RB + ld_row;                     // row inside the wave tile
             char* cptr = (char*)p.C + (c_batch + (int64_t)(row0 + lrow0) * p.ldc + gn) * ESZ;
             const int64_t cstep = (int64_t)ROWS_PER_LD * p.ldc * ESZ;
-            const int rows_left = (rows.m - row0 < WTM ? rows.m - row0 : WTM) - lrow0;   // valid rows from lrow0 on
 #pragma unroll
             for (int q0 = 0; q0 < NLD; q0 += BATCH) {
                 int4v w[BATCH];
@@ -638,7 +670,7 @@ struct EpiCtx {
                     if (gm >= rows.m || gn >= p.N) continue;
                     const int64_t o = c_batch + rows.at(gm) * p.ldc + gn;
                     float rv[4];
-                    res4<OUT_F32>(gm, gn, false, rv);
+                    res4<OUT_F32>(gm, gn, rv);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         if (gn + e >= p.N) break;

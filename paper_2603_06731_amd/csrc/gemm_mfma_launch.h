@@ -178,7 +178,7 @@ template <typename T, unsigned MASK>
 hipError_t launch_config(const Problem& p, hipStream_t stream, int cfg, int group_m) {
     switch (cfg) {
     PBK_CASE(0, 128, 256, 32, 1, 4, 3, 2)
-    PBK_CASE(1, 128, 128, 64, 2, 2, 2)
+    PBK_CASE(1, 128, 128, 64, 2, 2, 2, 2)
     PBK_CASE(2, 128, 128, 64, 2, 2, 4)
     // 3, 4 (32x32 blocks) are not built for the 16-bit types: their 16x16 twins 5-7 replaced them
     PBK_CASE(5, 256, 256, 32, 2, 4, 4, 1, 16)
