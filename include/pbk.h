@@ -315,7 +315,7 @@ const char* pbk_last_kernel(void);
  *                 not built for the operands: the automatic choice; operands that the direct-to-LDS kernel
  *                 cannot take go to the gathering matrix-unit kernel instead);
  *   "gather"      that kernel: "gather:0" with 128-row tiles, "gather:1" with 64-row tiles;
- *   "small"       the one-wave-per-tile fp32 kernel;
+ *   "small"       the fp32 kernel that loads its operands straight into registers;
  *   "bstat"       the B-stationary kernel for short contractions (K <= 256) over many rows;
  *   "ksplit"      a few rows, k split over the waves: "ksplit:0" 64 columns per workgroup (32 where a row-major B has no aligned
  *                 8-byte pieces), "ksplit:1" 32;

@@ -38,8 +38,8 @@ bool mfma_supported(const Problem& p) {
     return true;
 }
 
-// fp32 operands take the matrix units only when there is enough work to fill the chip with
-// 128-row tiles; small problems (cfg1-sized) are quicker on the generic kernel's 64x64 tiles.
+// fp32 operands take the staged kernel only when there is enough work to fill the chip with 128-row tiles.  (Plain products of up to
+// 4096 tiles of 16 x 16 take the kernel without staging before this is asked: small_f32_preferred.)
 bool mfma_preferred(const Problem& p) {
     if (p.in_dtype != DT_F32) return true;
     long long t = (long long)((p.M + 127) / 128) * ((p.N + 127) / 128) * p.batch;

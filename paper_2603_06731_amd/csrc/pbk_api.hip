@@ -114,7 +114,7 @@ pbk_status dispatch(const pbk::Problem& p_in, hipStream_t stream) {
         e = pbk::launch_mfma_ksplit(p, stream, cfg, &name);
     else if (force == FORCE_TILE64 || (force == FORCE_NONE && can_tile64 && pbk::mfma_tile64_preferred(p)))
         e = pbk::launch_mfma_tile64(p, stream, cfg, &name);
-    else if (force == FORCE_SMALL || (force == FORCE_NONE && can_small && pbk::small_f32_preferred(p) && !(can_mfma && pbk::mfma_preferred(p))))
+    else if (force == FORCE_SMALL || (force == FORCE_NONE && can_small && pbk::small_f32_preferred(p)))
         e = pbk::launch_small_f32(p, stream, &name);
     else if (can_mfma && force != FORCE_GENERIC && force != FORCE_GATHER && (force == FORCE_MFMA || pbk::mfma_preferred(p)))
         e = pbk::launch_mfma(p, stream, cfg, &name);

@@ -1,0 +1,54 @@
+"""The fp32 kernel that loads its operands straight into registers: k split over waves, 32 x 32 tiles, and its place in the dispatcher."""
+import pytest
+
+import workloads as wl
+from workloads import configs as C
+import pbk_testlib as T
+from test_gpu_small_f32 import run
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("trans_b", [0, 1])
+@pytest.mark.parametrize("M,N,K,lds,kernel", [
+    (16, 16, 4096, (None, None, None), "small_f32"),           # sixteen waves
+    (33, 130, 1037, (None, None, None), "small_f32"),          # waves with unequal shares, the last one ragged
+    (520, 512, 250, (None, None, None), "direct_f32_16x16"),   # beyond one tile per SIMD
+    (768, 783, 67, (None, None, None), "direct_f32_16x16"),    # 2352 tiles: odd N, no pairs of columns
+    (785, 786, 131, (None, None, None), "direct_f32_32x32"),   # 2500: N even, rows of B only 8-byte aligned, last pair at the edge
+    (800, 770, 64, (None, 786, 772), "direct_f32_32x32"),      # one full register set, padded rows
+    (801, 801, 65, (68, 804, 803), "direct_f32_32x32"),        # everything odd
+    (1024, 1024, 128, (None, None, None), "direct_f32_32x32"),
+    (1025, 1024, 32, (None, None, None), "mfma_f32"),          # 4160 tiles
+])
+def test_parity_and_dispatch(M, N, K, lds, kernel, trans_b):
+    lda, ldb, ldc = lds
+    if trans_b:
+        ldb = None if ldb is None else K + 5
+    err, kern = run(M, N, K, trans_b, C.EPI_BIAS_RELU, lda=lda, ldb=ldb, ldc=ldc, alpha=0.75)
+    assert kernel in kern, kern
+    assert err <= T.TOL_F32, err
+
+
+def test_residual_and_batch():
+    err, kern = run(790, 780, 40, 0, C.EPI_GELU_TANH, residual=True)
+    assert "direct_f32_32x32" in kern and err <= T.TOL_F32, (kern, err)
+    err, kern = run(100, 900, 150, 0, C.EPI_BIAS, batch=8)
+    assert "direct_f32_32x32" in kern and err <= T.TOL_F32, (kern, err)
+
+
+def test_repeats():
+    """The waves' sums are added in a fixed order: the same bits call after call."""
+    import torch
+    import paper_2603_06731_amd as pbk
+    M, N, K = 70, 90, 2050
+    a, b = torch.randn(M, K, device="cuda"), torch.randn(K, N, device="cuda")
+    out, first = torch.empty(M, N, device="cuda"), None
+    for _ in range(8):
+        out.fill_(float("nan"))
+        assert pbk.pbk_matmul(a, b, out, None, M, N, K, K, N, N, wl.DTYPE_F32, wl.DTYPE_F32, 0, 1.0, 0) == 0
+        first = out.clone() if first is None else first
+        assert torch.equal(out, first)
+    ref = a.double() @ b.double()
+    # fp32 sums of K terms of order one: well below K^(1/2) * 2^-24 * K^(1/2)
+    assert float((first.double() - ref).abs().max()) <= K * 2.0 ** -24 * 4
