@@ -16,7 +16,7 @@
  *    output must not alias any input.
  *  - Calls that leave most of the device idle otherwise split one output over
  *    several workgroups, which exchange partial results through scratch memory
- *    of the library's own: 4 MiB per stream, obtained at the stream's first
+ *    of the library's own: 8 MiB per stream, obtained at the stream's first
  *    such call, for up to 32 streams of a device, kept until
  *    pbk_release_scratch().  Where there is none (the stream is being captured,
  *    more streams, no memory) the call runs without a split.

@@ -17,16 +17,16 @@
 // Pieces go to LDS in the main kernel's layouts: k-major [rows][32 k] with the 16-byte chunk index
 // XOR-swizzled by the row (A, the image, a k-major B), n-major [32 k][128 n] read with the transposing
 // LDS read (row-major B, weights).
-// 128 x 128 x 32 tile (64 x 128 where the larger one leaves compute units without work), 2 x 2 waves, v_mfma_f32_16x16x32, LDS double-buffered: while k-tile t is
-// multiplied, the pieces of k-tiles t+1 .. t+3 are in flight to registers; one barrier per k-tile.
+// 128 x 128 x 32 tile, 64 x 128 x 32 or 64 x 128 x 64 (the rules are gather_rows64, gather_deep and gather_parts), v_mfma_f32_16x16x32, LDS double-buffered: while
+// k-tile t is multiplied, the pieces of k-tiles t+1 .. t+3 are in flight to registers; one barrier per k-tile.
 // The epilogue is the main kernel's (registers, then the LDS shuffle or direct stores).
 #include "gemm_mfma_launch.h"
+#include "scratch.h"
 
 namespace pbk {
 namespace {
 
-constexpr int GBN = 128, GBK = 32;                   // GBM: 128 or 64, a parameter of the kernel
-constexpr int GWM = 2, GWN = 2;
+constexpr int GBN = 128, GWN = 2;                    // GBM: 128 or 64, a parameter of the kernel
 
 // 16 bytes from an address that is only known to be 2-byte aligned (one global_load_dwordx4)
 // (the pointer is stated to be a global-memory one: a generic load would also count as an LDS operation)
@@ -77,9 +77,19 @@ __device__ __forceinline__ int4v piece_fix(int4v v, int meta) {
     return int4v{keep(w0, 0), keep(w1, 1), keep(w2, 2), keep(w3, 3)};
 }
 
-template <typename T, int MODE, int GBM>
-__global__ __launch_bounds__(GWM * GWN * 64, 2) void gemm_mfma_gather_kernel(Problem p, TileMap tmap) {
+// FAST (convolutions whose image tensor and weights are below 2 GiB each): the k-tiles before the careful ones are fetched with 32-bit
+// offsets that only ever grow by constants from one k-tile to the next; what must not be read has the out-of-range offset, for
+// which a buffer load gives zeros.  (With a tap worked out by multiplication, 64-bit addresses and the tests of a piece joined by && for
+// every piece of every k-tile, the address code took longer than the loads: 8 x 44 x 44 x 127 -> 512, 3 x 3, stride 2: 25.4 against 24.0 us.)
+// DEEP: eight waves and k-tiles of 64 instead of four and 32, for a workgroup that is alone on its compute unit: a k-tile of 32 takes one wave per
+// SIMD some 0.5 us, most of it issuing instructions and waiting for LDS and the barrier in turn; two waves per SIMD take little longer for 64
+// (8 x 44 x 44 x 127 -> 512, 3 x 3, stride 2, 224 tiles: 24.0 against 18.6 us; 1 x 68 x 68 x 127 -> 64, 7 x 7: 103 against 68).
+// SPLIT: `parts` workgroups per tile, each with a run of the k-tiles.
+template <typename T, int MODE, int GBM, bool FAST, bool DEEP, bool SPLIT>
+__global__ __launch_bounds__(DEEP ? 512 : 256, 2) void gemm_mfma_gather_kernel(Problem p, TileMapOf<MODE> tmap, int parts, Scratch scratch) {
+    constexpr int GBK = DEEP ? 64 : 32, GWM = DEEP ? 4 : 2;
     constexpr bool CONV = MODE == MODE_CONV;
+    static_assert(CONV || !FAST, "plain matrices advance by pointers");
     constexpr bool TRANS_B = MODE == MODE_TRANS_B;
     constexpr int NT = GWM * GWN * 64;
     constexpr int WTM = GBM / GWM, WTN = GBN / GWN;
@@ -96,6 +106,9 @@ __global__ __launch_bounds__(GWM * GWN * 64, 2) void gemm_mfma_gather_kernel(Pro
 
     int b, tile_m, tile_n;
     map_tile(tmap, blockIdx.x, b, tile_m, tile_n);
+    // (split: the map's batches are the parts)
+    const int part = SPLIT ? b / p.batch : 0;
+    if (SPLIT) b -= part * p.batch;
     const int m0 = tile_m * GBM, n0 = tile_n * GBN;
     const char* Abase = (const char*)p.A + (int64_t)b * p.stride_a * 2;
     const char* Bbase = (const char*)p.B + (int64_t)b * p.stride_b * 2;
@@ -104,26 +117,51 @@ __global__ __launch_bounds__(GWM * GWN * 64, 2) void gemm_mfma_gather_kernel(Pro
     const int taps = CONV ? p.conv.KH * p.conv.KW : 0;
     const int Kloop = CONV ? taps * Cp : p.K;
     // the last addresses from which 16 bytes can be read (each operand holds at least 8 elements)
+    // this workgroup's k-tiles: kt0 .. kt1 - 1
+    const int KT = (Kloop + GBK - 1) / GBK;
+    const int each = SPLIT ? KT / parts : KT, rest = SPLIT ? KT - each * parts : 0;
+    const int kt0 = SPLIT ? part * each + (part < rest ? part : rest) : 0, kt1 = SPLIT ? kt0 + each + (part < rest ? 1 : 0) : KT;
     const int64_t a_elems = CONV ? (int64_t)(p.M / (p.conv.OH * p.conv.OW)) * p.conv.H * p.conv.W * p.conv.Cin
                                  : (int64_t)(p.M - 1) * p.lda + p.K;
     const int64_t b_elems = TRANS_B ? (int64_t)(p.N - 1) * p.ldb + p.K : (int64_t)(p.K - 1) * p.ldb + p.N;
     const char* a_last16 = Abase + a_elems * 2 - 16;
     const char* b_last16 = Bbase + b_elems * 2 - 16;
 
-    // ---- A (k-major source): piece = (row, chunk of 8 k); four neighbouring threads cover a row of the k-tile.
+    // ---- A (k-major source): piece = (row, chunk of 8 k); eight neighbouring threads cover a row of the k-tile.
     // The thread's pieces differ in the row only (+64).
-    const int a_chunk = t & 3;
+    constexpr int CPR = GBK / 8, NPR = GBN / 8;       // pieces per row of a k-major tile, per k-row of an n-major one
+    const int a_chunk = t % CPR;
     int a_row[PA];
     bool a_ok[PA];
     const char* a_cur[PA];       // dense: address of the piece in the next k-tile to fetch; conv: the pixel's image
     int a_ih0[PA], a_iw0[PA];
+    unsigned a_off[FAST ? PA : 1];
+    int a_first[FAST ? PA : 1];
     // conv: (channel, tap) of the thread's pieces in the next k-tile to fetch
     int a_c = 0, a_tap = 0;
     if (CONV) {
-        const int k = a_chunk * 8;                    // the pieces' place on the padded K axis in k-tile 0
+        const int k = kt0 * GBK + a_chunk * 8;        // the pieces' place on the padded K axis in the first k-tile
         a_tap = k / Cp;
         a_c = k - a_tap * Cp;
     }
+    // FAST: the same place as offsets (of A's pieces from the row's first tap; of B's k-row from row 0) and as tap coordinates
+    const int row_step = FAST ? (p.conv.dil_h * p.conv.W) * p.conv.Cin * 2 : 0, col_step = FAST ? p.conv.dil_w * p.conv.Cin * 2 : 0;
+    int f_kw = 0, f_dh = 0, f_dw = 0;
+    unsigned f_delta = 0;
+    if constexpr (FAST) {
+        const int kh = a_tap / p.conv.KW;
+        f_kw = a_tap - kh * p.conv.KW;
+        f_dh = kh * p.conv.dil_h;
+        f_dw = f_kw * p.conv.dil_w;
+        f_delta = (unsigned)(kh * row_step + f_kw * col_step + a_c * 2);
+    }
+    auto next_tap = [&]() __attribute__((always_inline)) {         // one tap on, its first channel where the place was
+        const bool wrap = ++f_kw == p.conv.KW;
+        f_kw = wrap ? 0 : f_kw;
+        f_dw = wrap ? 0 : f_dw + p.conv.dil_w;
+        f_dh += wrap ? p.conv.dil_h : 0;
+        f_delta += wrap ? (unsigned)(row_step - (p.conv.KW - 1) * col_step) : (unsigned)col_step;
+    };
     // one k-tile further on the padded K axis: adv_tap taps and adv_c channels, with at most one carry
     const int adv_tap = CONV ? GBK / Cp : 0, adv_c = CONV ? GBK - adv_tap * Cp : 0;
     // tap / KW by multiplication (exact for tap < 2^20 / KW)
@@ -131,47 +169,57 @@ __global__ __launch_bounds__(GWM * GWN * 64, 2) void gemm_mfma_gather_kernel(Pro
     const char* zero_piece = (const char*)&kZeroPiece;
 #pragma unroll
     for (int i = 0; i < PA; ++i) {
-        a_row[i] = (t >> 2) + (NT / 4) * i;
+        a_row[i] = t / CPR + (NT / CPR) * i;
         const int gm = m0 + a_row[i];
         a_ok[i] = gm < p.M;
         const int gmc = a_ok[i] ? gm : p.M - 1;       // rows beyond M read a row that exists
         if (CONV) {
-            const int pix = p.conv.OH * p.conv.OW;
-            const int n = gmc / pix, rem = gmc - n * pix;
-            const int oh = rem / p.conv.OW, ow = rem - oh * p.conv.OW;
-            a_ih0[i] = oh * p.conv.stride_h - p.conv.pad_h;
-            a_iw0[i] = ow * p.conv.stride_w - p.conv.pad_w;
-            a_cur[i] = Abase + (int64_t)n * p.conv.H * p.conv.W * p.conv.Cin * 2;
+            if constexpr (CONV) {
+                int rem, ow;
+                const int n = tmap.pix.div(gmc, rem), oh = tmap.ow.div(rem, ow);
+                a_ih0[i] = oh * p.conv.stride_h - p.conv.pad_h;
+                a_iw0[i] = ow * p.conv.stride_w - p.conv.pad_w;
+                a_cur[i] = Abase + (int64_t)n * p.conv.H * p.conv.W * p.conv.Cin * 2;
+                if constexpr (FAST) {
+                    // (modulo 2^32: the row's first tap may lie in front of the image)
+                    a_off[i] = (unsigned)(((n * p.conv.H + a_ih0[i]) * p.conv.W + a_iw0[i]) * p.conv.Cin * 2);
+                    a_first[i] = a_ok[i] ? a_ih0[i] : -(1 << 30);      // a row beyond M meets no tap
+                }
+            }
         } else {
-            a_cur[i] = Abase + ((int64_t)gmc * p.lda + a_chunk * 8) * 2;
+            a_cur[i] = Abase + ((int64_t)gmc * p.lda + (int64_t)kt0 * GBK + a_chunk * 8) * 2;
         }
     }
     // ---- B: k-major source (trans_b): pieces like A's.  n-major source (row-major B, the weights of a
     // convolution): a piece is eight neighbouring n of one k-row: b_row = k-row in the tile, b_chunk = which
-    // eight n; the thread's two pieces differ in the k-row only (+16).
-    const int b_chunk = TRANS_B ? (t & 3) : (t & 15);
+    // eight n; the thread's two pieces differ in the k-row only (+32).
+    const int b_chunk = TRANS_B ? t % CPR : t % NPR;
     int b_row[PB];
     bool b_ok[PB];
     const char* b_cur[PB];       // address of the piece in the next k-tile to fetch (conv: of its first n in row 0)
     int b_c[PB], b_tap[PB];  // conv: (channel, tap) of the piece's k-row in the next k-tile to fetch
+    unsigned b_off[FAST ? PB : 1];
+    const unsigned b_adv = FAST ? (unsigned)((adv_tap * p.conv.Cin + adv_c) * (int)p.ldb * 2) : 0u;        // one k-tile on
+    const unsigned b_carry = FAST ? (unsigned)((Cp - p.conv.Cin) * (int)p.ldb * 2) : 0u;                  // less for every tap begun
 #pragma unroll
     for (int i = 0; i < PB; ++i) {
         if (TRANS_B) {
-            b_row[i] = (t >> 2) + (NT / 4) * i;
+            b_row[i] = t / CPR + (NT / CPR) * i;
             b_ok[i] = n0 + b_row[i] < p.N;
-            b_cur[i] = Bbase + ((int64_t)(b_ok[i] ? n0 + b_row[i] : p.N - 1) * p.ldb + b_chunk * 8) * 2;
+            b_cur[i] = Bbase + ((int64_t)(b_ok[i] ? n0 + b_row[i] : p.N - 1) * p.ldb + (int64_t)kt0 * GBK + b_chunk * 8) * 2;
         } else {
-            b_row[i] = (t >> 4) + (NT / 16) * i;
+            b_row[i] = t / NPR + (NT / NPR) * i;
             b_ok[i] = n0 + b_chunk * 8 < p.N;
             // (a piece beyond N reads column N - 1 onwards: it stays inside B wherever the careful path is not taken)
             b_cur[i] = Bbase + (int64_t)(b_ok[i] ? n0 + b_chunk * 8 : p.N - 1) * 2;
-            if (CONV) { b_tap[i] = b_row[i] / Cp; b_c[i] = b_row[i] - b_tap[i] * Cp; }
-            else b_cur[i] += (int64_t)b_row[i] * p.ldb * 2;
+            if (CONV) { b_tap[i] = (kt0 * GBK + b_row[i]) / Cp; b_c[i] = kt0 * GBK + b_row[i] - b_tap[i] * Cp; }
+            if constexpr (FAST)
+                b_off[i] = (unsigned)((b_tap[i] * p.conv.Cin + b_c[i]) * (int)p.ldb * 2) + (unsigned)((b_ok[i] ? n0 + b_chunk * 8 : p.N - 1) * 2);
+            else b_cur[i] += ((int64_t)kt0 * GBK + b_row[i]) * p.ldb * 2;
         }
     }
     const int64_t b_step = TRANS_B ? GBK * 2 : (int64_t)GBK * p.ldb * 2;     // dense: B's advance per k-tile
 
-    const int KT = (Kloop + GBK - 1) / GBK;
     // k-tiles from kt_careful on are fetched by the careful path (it keeps every load inside its operand and
     // works out what to keep of each piece); before it no piece can run over the end of an operand:
     //  - dense: every piece of a k-tile before the last lies inside its row (k-major) or in a k-row that has
@@ -189,12 +237,51 @@ __global__ __launch_bounds__(GWM * GWN * 64, 2) void gemm_mfma_gather_kernel(Pro
     int4v avs[NPF][PA], bvs[NPF][PB];
     int metas[NPF];                  // one byte per piece: A's, then B's
 
+    // the k-tiles before the careful ones
+    const __amdgpu_buffer_rsrc_t a_buf = __builtin_amdgcn_make_buffer_rsrc((void*)Abase, 0, (int)kOob, 0x00020000);
+    const __amdgpu_buffer_rsrc_t b_buf = __builtin_amdgcn_make_buffer_rsrc((void*)Bbase, 0, (int)kOob, 0x00020000);
+    auto gather_fast = [&](auto set_tag) __attribute__((always_inline)) {
+        if constexpr (FAST) {
+            constexpr int S = decltype(set_tag)::value;
+            // the piece at the end of a tap is read Cp - Cin channels earlier and marked to be shifted down by as many
+            const int left = p.conv.Cin - a_c, back = left < 8 ? Cp - p.conv.Cin : 0;
+            const unsigned at = f_delta - 2 * (unsigned)back;
+            const int marked = 8 | (back << 4);
+            int meta = (int)(((unsigned)kAllPlain << (8 * PA)) & (0xFFFFFFFFu >> (8 * (4 - PA - PB))));
+#pragma unroll
+            for (int i = 0; i < PA; ++i) {
+                const bool ok = ((unsigned)(a_first[i] + f_dh) < (unsigned)p.conv.H) & ((unsigned)(a_iw0[i] + f_dw) < (unsigned)p.conv.W);
+                avs[S][i] = __builtin_bit_cast(int4v, __builtin_amdgcn_raw_buffer_load_b128(a_buf, ok ? (int)(a_off[i] + at) : (int)kOob, 0, 0));
+                meta |= (ok ? marked : kPlain) << (8 * i);
+            }
+            a_c += adv_c;
+            f_delta += 2 * adv_c;
+            for (int n = 0; n < adv_tap; ++n) next_tap();                      // (channel counts below the depth of a k-tile)
+            a_tap += adv_tap;
+            const bool carry = a_c >= Cp;
+            if (carry) {
+                a_c -= Cp; ++a_tap;
+                f_delta -= 2 * (unsigned)Cp;
+                next_tap();
+            }
+#pragma unroll
+            for (int i = 0; i < PB; ++i) {
+                const bool ok = b_c[i] < p.conv.Cin;                          // a weight row that exists
+                bvs[S][i] = __builtin_bit_cast(int4v, __builtin_amdgcn_raw_buffer_load_b128(b_buf, ok ? (int)b_off[i] : (int)kOob, 0, 0));
+                b_c[i] += adv_c; b_tap[i] += adv_tap; b_off[i] += b_adv;
+                const bool c = b_c[i] >= Cp;
+                b_c[i] -= c ? Cp : 0; b_tap[i] += c ? 1 : 0; b_off[i] -= c ? b_carry : 0u;
+            }
+            metas[S] = meta;
+        }
+    };
     // fetch the pieces of k-tile kt into register set S (loads are issued here and waited for at the first
     // use); called for kt = 0, 1, 2, ... in order, also for up to NPF k-tiles beyond the last (those pieces
     // are cleared).  No load sits under a branch.
     auto gather = [&](int kt, auto set_tag, auto careful_tag) __attribute__((always_inline)) {
         constexpr int S = decltype(set_tag)::value;
         constexpr bool CAREFUL = decltype(careful_tag)::value != 0;
+        if constexpr (FAST && !CAREFUL) { gather_fast(set_tag); return; }
         const int k0 = kt * GBK;
         int meta = 0;
 #pragma unroll
@@ -264,8 +351,10 @@ __global__ __launch_bounds__(GWM * GWN * 64, 2) void gemm_mfma_gather_kernel(Pro
         }
         metas[S] = meta;
     };
-    auto stash = [&](int stage, auto set_tag) __attribute__((always_inline)) {
+    // (careful: the pieces may come from the careful path)
+    auto stash = [&](int stage, auto set_tag, auto careful_tag) __attribute__((always_inline)) {
         constexpr int S = decltype(set_tag)::value;
+        constexpr bool CAREFUL = decltype(careful_tag)::value != 0;
         char* sa = lds + stage * G_STAGE;
         char* sb = sa + A_TILE;
         int4v va[PA], vb[PB];
@@ -276,8 +365,10 @@ __global__ __launch_bounds__(GWM * GWN * 64, 2) void gemm_mfma_gather_kernel(Pro
         if (metas[S] != (int)((unsigned)kAllPlain >> (8 * (4 - PA - PB)))) {         // rare: one branch for the thread's pieces
 #pragma unroll
             for (int i = 0; i < PA; ++i) va[i] = piece_fix(va[i], (metas[S] >> (8 * i)) & 255);
+            if constexpr (CAREFUL || !FAST) {
 #pragma unroll
-            for (int i = 0; i < PB; ++i) vb[i] = piece_fix(vb[i], (metas[S] >> (8 * (PA + i))) & 255);
+                for (int i = 0; i < PB; ++i) vb[i] = piece_fix(vb[i], (metas[S] >> (8 * (PA + i))) & 255);
+            }
         }
 #pragma unroll
         for (int i = 0; i < PA; ++i) *(int4v*)(sa + kmajor_offset<GBK, true>(a_row[i], a_chunk)) = va[i];
@@ -296,6 +387,7 @@ __global__ __launch_bounds__(GWM * GWN * 64, 2) void gemm_mfma_gather_kernel(Pro
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.0f;
 
+    constexpr int KS = GBK / 32;                      // MFMA k-steps per k-tile
     const int f_row = lane & 15, f_kc = lane >> 4;
     // transposing read of the n-major B tile: 16-lane block q covers k rows 8q .. 8q+3 (second read: +4);
     // lane -> row (lane % 16) / 4, n piece lane % 4
@@ -308,54 +400,98 @@ __global__ __launch_bounds__(GWM * GWN * 64, 2) void gemm_mfma_gather_kernel(Pro
         constexpr int S = decltype(set_tag)::value;
         const char* sa = lds + (kt & 1) * G_STAGE;
         const char* sb = sa + A_TILE;
-        short8v af[FM], bf[FN];
+        short8v af[KS][FM], bf[KS][FN];
 #pragma unroll
-        for (int i = 0; i < FM; ++i)
-            af[i] = *(const short8v*)(sa + kmajor_offset<GBK, true>(wm * WTM + i * 16 + f_row, f_kc));
+        for (int ks = 0; ks < KS; ++ks) {
 #pragma unroll
-        for (int j = 0; j < FN; ++j) {
-            if (TRANS_B) {
-                bf[j] = *(const short8v*)(sb + kmajor_offset<GBK, true>(wn * WTN + j * 16 + f_row, f_kc));
-            } else {
-                const char* r0 = sb + nmajor_offset<GBN>(t16_k, (wn * WTN + j * 16) * 2 + t16_nbyte);
-                short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(PBK_LDS_PTR(short4v, r0));
-                short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(PBK_LDS_PTR(short4v, r0 + 4 * (GBN * 2)));
-                bf[j] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+            for (int i = 0; i < FM; ++i)
+                af[ks][i] = *(const short8v*)(sa + kmajor_offset<GBK, true>(wm * WTM + i * 16 + f_row, ks * 4 + f_kc));
+#pragma unroll
+            for (int j = 0; j < FN; ++j) {
+                if (TRANS_B) {
+                    bf[ks][j] = *(const short8v*)(sb + kmajor_offset<GBK, true>(wn * WTN + j * 16 + f_row, ks * 4 + f_kc));
+                } else {
+                    const char* r0 = sb + nmajor_offset<GBN>(t16_k, (wn * WTN + j * 16) * 2 + t16_nbyte) + ks * 32 * (GBN * 2);
+                    short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(PBK_LDS_PTR(short4v, r0));
+                    short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(PBK_LDS_PTR(short4v, r0 + 4 * (GBN * 2)));
+                    bf[ks][j] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+                }
             }
         }
         gather(kt + NPF, set_tag, careful_tag);
 #pragma unroll
-        for (int i = 0; i < FM; ++i)
+        for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-            for (int j = 0; j < FN; ++j) acc[i][j] = MfmaOp16<T>::run(bf[j], af[i], acc[i][j]);
-        stash((kt + 1) & 1, IntTag<(S + 1) % NPF>{});
+            for (int i = 0; i < FM; ++i)
+#pragma unroll
+                for (int j = 0; j < FN; ++j) acc[i][j] = MfmaOp16<T>::run(bf[ks][j], af[ks][i], acc[i][j]);
+        stash((kt + 1) & 1, IntTag<(S + 1) % NPF>{}, careful_tag);
         __syncthreads();
     };
-    int kt = 0;
-    if (kt_careful >= NPF) {
-        gather(0, IntTag<0>{}, IntTag<0>{});
-        gather(1, IntTag<1>{}, IntTag<0>{});
-        gather(2, IntTag<2>{}, IntTag<0>{});
+    int kt = kt0;
+    if (kt0 + NPF <= kt_careful) {
+        gather(kt0, IntTag<0>{}, IntTag<0>{});
+        gather(kt0 + 1, IntTag<1>{}, IntTag<0>{});
+        gather(kt0 + 2, IntTag<2>{}, IntTag<0>{});
     } else {
-        gather(0, IntTag<0>{}, IntTag<1>{});
-        gather(1, IntTag<1>{}, IntTag<1>{});
-        gather(2, IntTag<2>{}, IntTag<1>{});
+        gather(kt0, IntTag<0>{}, IntTag<1>{});
+        gather(kt0 + 1, IntTag<1>{}, IntTag<1>{});
+        gather(kt0 + 2, IntTag<2>{}, IntTag<1>{});
         kt_careful = 0;
     }
-    stash(0, IntTag<0>{});
+    stash(kt0 & 1, IntTag<0>{}, IntTag<1>{});
     __syncthreads();
     // steps whose fetches (k-tiles kt + 3 .. kt + 5) all come before the careful ones
-    for (; kt + 2 * NPF - 1 < kt_careful; kt += NPF) {
+    for (; kt + 2 * NPF - 1 < kt_careful && kt + NPF <= kt1; kt += NPF) {
         step(kt, IntTag<0>{}, IntTag<0>{});
         step(kt + 1, IntTag<1>{}, IntTag<0>{});
         step(kt + 2, IntTag<2>{}, IntTag<0>{});
     }
-    for (; kt < KT; kt += NPF) {
+    for (; kt < kt1; kt += NPF) {
         step(kt, IntTag<0>{}, IntTag<1>{});
-        if (kt + 1 >= KT) break;
+        if (kt + 1 >= kt1) break;
         step(kt + 1, IntTag<1>{}, IntTag<1>{});
-        if (kt + 2 >= KT) break;
+        if (kt + 2 >= kt1) break;
         step(kt + 2, IntTag<2>{}, IntTag<1>{});
+    }
+    if constexpr (SPLIT) {
+        // the parts of the tile meet: part w, block, thread.  A wave without rows of C has nothing to bring.
+        const int tile = b * tmap.tiles_per_batch + tile_m * tmap.tiles_n + tile_n;
+        const __amdgpu_buffer_rsrc_t buf = scratch_buffer(scratch.data + (size_t)tile * parts * (GBM * GBN * 4));
+        const bool live = m0 + wm * WTM < p.M;
+        auto at = [&](int w, int i, int j) { return w * (GBM * GBN * 4) + ((i * FN + j) * NT + t) * 16; };
+        if (live) {
+#pragma unroll
+            for (int i = 0; i < FM; ++i)
+#pragma unroll
+                for (int j = 0; j < FN; ++j) scratch_put(buf, at(part, i, j), acc[i][j]);
+        }
+        if (!scratch_last(scratch.tickets + tile, parts, (int*)lds)) return;
+        if (live) {
+#pragma unroll
+            for (int i = 0; i < FM; ++i)
+#pragma unroll
+                for (int j = 0; j < FN; ++j) acc[i][j] = scratch_get(buf, at(0, i, j));
+            constexpr int AHEAD = 4;                // parts requested together
+            for (int w = 1; w < parts; w += AHEAD) {
+                f32x4 v[AHEAD][FM][FN];
+#pragma unroll
+                for (int u = 0; u < AHEAD; ++u)
+#pragma unroll
+                    for (int i = 0; i < FM; ++i)
+#pragma unroll
+                        for (int j = 0; j < FN; ++j) v[u][i][j] = scratch_get(buf, at(w + u < parts ? w + u : parts - 1, i, j));
+#pragma unroll
+                for (int u = 0; u < AHEAD; ++u) {
+                    if (w + u >= parts) break;
+#pragma unroll
+                    for (int i = 0; i < FM; ++i)
+#pragma unroll
+                        for (int j = 0; j < FN; ++j) acc[i][j] += v[u][i][j];
+                }
+            }
+        }
+        __syncthreads();                            // (the flag's word is free for the epilogue)
     }
 
     const int act = (p.epi == EPI_RELU || p.epi == EPI_BIAS_RELU) ? 1
@@ -372,35 +508,49 @@ __global__ __launch_bounds__(GWM * GWN * 64, 2) void gemm_mfma_gather_kernel(Pro
     }
 }
 
-template <typename T, int MODE, int GBM>
-hipError_t launch_gather_mode(const Problem& p, hipStream_t stream) {
+// parts: workgroups that share a tile's k-tiles (1: none, and no scratch memory)
+template <typename T, int MODE, int GBM, bool FAST, bool DEEP, bool SPLIT = false>
+hipError_t launch_gather_mode(const Problem& p, hipStream_t stream, int parts = 1, Scratch scratch = Scratch{}) {
+    constexpr int GBK = DEEP ? 64 : 32, THREADS = DEEP ? 512 : 256;
     constexpr int LDS_BYTES = 2 * (GBM + GBN) * GBK * 2;
-    auto kern = gemm_mfma_gather_kernel<T, MODE, GBM>;
+    static_assert(LDS_BYTES <= 64 * 1024, "launched without a raised limit");
+    auto kern = gemm_mfma_gather_kernel<T, MODE, GBM, FAST, DEEP, SPLIT>;
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     DeviceShape ds;
     e = device_shape(dev, &ds);
     if (e != hipSuccess) return e;
-    TileMap tm{};
+    TileMapOf<MODE> tm{};
+    if constexpr (MODE == MODE_CONV) {
+        tm.pix = FastDiv::of(p.conv.OH * p.conv.OW);
+        tm.ow = FastDiv::of(p.conv.OW);
+    }
     tm.tiles_m = (p.M + GBM - 1) / GBM;
     tm.tiles_n = (p.N + GBN - 1) / GBN;
     tm.tiles_per_batch = tm.tiles_m * tm.tiles_n;
-    const long long total = (long long)tm.tiles_per_batch * p.batch;
+    const long long total = (long long)tm.tiles_per_batch * p.batch * parts;
     if (total <= 0 || total > 0x7FFFFFFFLL) return hipErrorInvalidValue;
     tm.total = (int)total;
     tm.group_m = 8;
     tm.xcds = ds.xcds;
     Problem pa = p;
-    void* args[] = {&pa, &tm};
-    return hipLaunchKernel((const void*)kern, dim3((unsigned)total), dim3(GWM * GWN * 64), args, LDS_BYTES, stream);
+    void* args[] = {&pa, &tm, &parts, &scratch};
+    return hipLaunchKernel((const void*)kern, dim3((unsigned)total), dim3(THREADS), args, LDS_BYTES, stream);
 }
 
-template <typename T, int GBM>
-hipError_t launch_gather_type(const Problem& p, hipStream_t stream) {
-    if (p.is_conv) return launch_gather_mode<T, MODE_CONV, GBM>(p, stream);
-    if (p.trans_b) return launch_gather_mode<T, MODE_TRANS_B, GBM>(p, stream);
-    return launch_gather_mode<T, MODE_DENSE, GBM>(p, stream);
+// Every offset of FAST, the taps of the last k-tile and what the last rows reach beyond the image included, stays below 2^31.
+bool gather_fast_offsets(const Problem& p) {
+    const int64_t lim = ((int64_t)1 << 31) - ((int64_t)1 << 20), row = (int64_t)p.conv.W * p.conv.Cin * 2;
+    return (int64_t)(p.M / (p.conv.OH * p.conv.OW)) * p.conv.H * row < lim && ((int64_t)p.K + 256) * p.ldb * 2 < lim;
+}
+
+template <typename T, int GBM, bool DEEP, bool SPLIT = false>
+hipError_t launch_gather_type(const Problem& p, hipStream_t stream, int parts = 1, Scratch scratch = Scratch{}) {
+    if (p.is_conv) return gather_fast_offsets(p) ? launch_gather_mode<T, MODE_CONV, GBM, true, DEEP, SPLIT>(p, stream, parts, scratch)
+                                                 : launch_gather_mode<T, MODE_CONV, GBM, false, DEEP, SPLIT>(p, stream, parts, scratch);
+    if (p.trans_b) return launch_gather_mode<T, MODE_TRANS_B, GBM, false, DEEP, SPLIT>(p, stream, parts, scratch);
+    return launch_gather_mode<T, MODE_DENSE, GBM, false, DEEP, SPLIT>(p, stream, parts, scratch);
 }
 
 }  // namespace
@@ -415,17 +565,17 @@ bool mfma_gather_supported(const Problem& p) {
     if (p.is_conv) {
         if (p.conv.transposed) return false;
         // tap -> (kh, kw) by multiplication is exact below 2^20 / KW taps
-        if ((int64_t)p.conv.KH * p.conv.KW + 16 >= ((int64_t)1 << 20) / p.conv.KW) return false;
+        if ((int64_t)p.conv.KH * p.conv.KW + 64 >= ((int64_t)1 << 20) / p.conv.KW) return false;
         const int64_t img = (int64_t)p.conv.H * p.conv.W * p.conv.Cin;
         if (img * 2 + 64 >= ((int64_t)1 << 31)) return false;
         a_elems = (int64_t)(p.M / (p.conv.OH * p.conv.OW)) * img;
         // the loop runs over taps * ceil8(Cin)
-        if ((int64_t)p.conv.KH * p.conv.KW * ((p.conv.Cin + 7) & ~7) + 4 * GBK >= ((int64_t)1 << 31)) return false;
+        if ((int64_t)p.conv.KH * p.conv.KW * ((p.conv.Cin + 7) & ~7) + 4 * 64 >= ((int64_t)1 << 31)) return false;
     } else {
         a_elems = (int64_t)(p.M - 1) * p.lda + p.K;
     }
     b_elems = p.trans_b ? (int64_t)(p.N - 1) * p.ldb + p.K : (int64_t)(p.K - 1) * p.ldb + p.N;
-    if ((int64_t)p.K + 4 * GBK >= ((int64_t)1 << 30)) return false;
+    if ((int64_t)p.K + 4 * 64 >= ((int64_t)1 << 30)) return false;
     return a_elems >= 8 && b_elems >= 8;
 }
 
@@ -441,14 +591,49 @@ static bool gather_rows64(const Problem& p) {
     return t128 <= 256 && (p.is_conv || t64 <= 256 || p.K <= 512);
 }
 
+// One workgroup per compute unit takes the deep form, several the other, of which a unit holds two or three (3 x 81 x 81 x 35 -> 512, 3 x 3,
+// stride 2, 316 tiles: 22.7 deep, 16.6; 6 x 108 x 108 x 3 -> 65: 15.9 and 10.8).
+static bool gather_deep(const Problem& p) {
+    return (long long)((p.M + 63) / 64) * ((p.N + GBN - 1) / GBN) * p.batch <= 256;
+}
+
+// Workgroups that share a tile (1: tiles are not split): up to one per compute unit, and up to eight, p of them from p (p + 2) k-tiles of 64 on,
+// because every part adds a k-tile's worth to the parts' meeting.  In us, unsplit first:
+// - 3 x 1657 x 8403, 13 tiles: 59 and 16 with 8 parts; 14 x 4459 x 8768, 35 tiles: 66 and 21 with 6; 36 x 10083 x 11392, 79 tiles: 103 and 48
+//   with 3; 640 x 448 x 1927: 20.3 and 13.7 with 3, 14.1 with 4, 15.6 with 6; convolutions 2 x 15 x 15 x 100 -> 64, 7 x 7: 60 and 17.6, 1 x 18 x 18 x
+//   61 -> 32, 7 x 7, stride 2, one tile: 40 and 15.2; 3 x 21 x 21 x 100 -> 127, 3 x 3: 18.7 and 14.5;
+// - what short ones do not give back: 64 x 1003 x 501: 11.6 and 11.9, 300 x 300 x 301: 9.7 and 10.7, 130 x 2496 x 970, 60 tiles: 10.7 and 10.7;
+//   convolutions of 2 and 3 k-tiles: 9.3 and 9.8, 8.6 and 9.3.
+static int gather_parts(const Problem& p) {
+    const long long tiles = (long long)((p.M + 63) / 64) * ((p.N + GBN - 1) / GBN) * p.batch;
+    const long long kt = ((p.is_conv ? (long long)p.conv.KH * p.conv.KW * ((p.conv.Cin + 7) & ~7) : p.K) + 63) / 64;
+    if (tiles > 128 || kt < (p.is_conv ? 8 : 12)) return 1;
+    const long long room = (long long)kScratchBytes / (64 * GBN * 4) / tiles;        // the parts' sums have to fit
+    int parts = 1;
+    while (parts < 8 && (parts + 1) * tiles <= 256 && parts < room && (parts + 1) * (parts + 3) <= kt) ++parts;
+    return parts;
+}
+
 // force_cfg: 0 the 128-row tiles, 1 the 64-row ones, otherwise by the rule.
 hipError_t launch_mfma_gather(const Problem& p, hipStream_t stream, int force_cfg, const char** name) {
+    const bool bf16 = p.in_dtype == DT_BF16;
     if (force_cfg == 1 || (force_cfg != 0 && gather_rows64(p))) {
-        *name = "mfma16_gather_64x128x32_w2x2";
-        return p.in_dtype == DT_BF16 ? launch_gather_type<bf16_t, 64>(p, stream) : launch_gather_type<f16_t, 64>(p, stream);
+        if (!gather_deep(p)) {
+            *name = "mfma16_gather_64x128x32_w2x2";
+            return bf16 ? launch_gather_type<bf16_t, 64, false>(p, stream) : launch_gather_type<f16_t, 64, false>(p, stream);
+        }
+        const int parts = gather_parts(p);
+        int dev = 0;
+        Scratch scratch;
+        if (parts > 1 && hipGetDevice(&dev) == hipSuccess && stream_scratch(dev, stream, &scratch)) {
+            *name = "mfma16_gather_64x128x64_w4x2_split";
+            return bf16 ? launch_gather_type<bf16_t, 64, true, true>(p, stream, parts, scratch) : launch_gather_type<f16_t, 64, true, true>(p, stream, parts, scratch);
+        }
+        *name = "mfma16_gather_64x128x64_w4x2";
+        return bf16 ? launch_gather_type<bf16_t, 64, true>(p, stream) : launch_gather_type<f16_t, 64, true>(p, stream);
     }
     *name = "mfma16_gather_128x128x32_w2x2";
-    return p.in_dtype == DT_BF16 ? launch_gather_type<bf16_t, 128>(p, stream) : launch_gather_type<f16_t, 128>(p, stream);
+    return bf16 ? launch_gather_type<bf16_t, 128, false>(p, stream) : launch_gather_type<f16_t, 128, false>(p, stream);
 }
 
 }  // namespace pbk

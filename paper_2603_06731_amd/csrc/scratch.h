@@ -9,7 +9,7 @@
 
 namespace pbk {
 
-constexpr size_t kScratchBytes = (size_t)4 << 20;    // partial results
+constexpr size_t kScratchBytes = (size_t)8 << 20;    // partial results
 constexpr int kScratchTickets = 4096;                // one per output tile; every launch leaves them at zero
 
 struct Scratch {
