@@ -29,8 +29,8 @@ hipError_t launch_typed_modes(const Problem& q, hipStream_t stream, int group_m)
 template <typename T, typename TO>
 hipError_t launch_fp8_cfg(const Problem& q, hipStream_t stream, int cfg, int group_m) {
     switch (cfg) {
-    case 1: return launch_typed_modes<T, TO, 128, 128, 64, 2, 2, 2, 2>(q, stream, group_m);
-    case 2: return launch_typed_modes<T, TO, 128, 128, 64, 2, 2, 4, 1>(q, stream, group_m);
+    case 1: return launch_typed_modes<T, TO, 128, 128, 64, 2, 4, 2, 2>(q, stream, group_m);
+    case 2: return launch_typed_modes<T, TO, 128, 128, 64, 2, 4, 4, 1>(q, stream, group_m);
     case 4: return launch_typed_modes<T, TO, 256, 256, 64, 2, 4, 2, 1>(q, stream, group_m);
     case 9:     // both operands k-major: 16x16x128 blocks in the pair pipeline (one MFMA k-step per pair of k-tiles)
         if (q.trans_b && !q.is_conv)

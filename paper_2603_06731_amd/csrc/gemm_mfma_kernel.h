@@ -1158,7 +1158,17 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
     #pragma unroll
             for (int j = 0; j < FN; ++j) bf[j] = read_b1(sb, ks, j);
         };
-        static_assert(FM + FN <= FM * FN, "a step has at least as many MFMA groups as fragments to read under it");
+        constexpr int RPM = (FM + FN + FM * FN - 1) / (FM * FN);        // fragments to read after an MFMA group of a step
+        // fragment reads number k RPM .. of a step: those of A, then those of B
+        auto read_group = [&](int k, const char* sa, const char* sb, int ks, Frag<CH> (&a)[FM], Frag<CH> (&bq)[FN]) __attribute__((always_inline)) {
+    #pragma unroll
+            for (int q = 0; q < RPM; ++q) {
+                const int f = k * RPM + q;
+                if (f < FM) a[f] = read_a1(sa, ks, f);
+                else if (f < FM + FN) bq[f - FM] = read_b1(sb, ks, f - FM);
+            }
+            if (k * RPM < FM + FN) __builtin_amdgcn_sched_barrier(0);
+        };
 
         // Fragments are double-buffered in registers across k16 steps AND across
         // k-tiles: the reads of step ks+1 go, one fragment at a time, between the MFMAs
@@ -1218,11 +1228,7 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
             const char* sb = sa + A_BYTES;
     #pragma unroll
             for (int ks = 0; ks < KSUB - 1; ++ks) {
-                auto mid = [&](int k) {
-                    if (k < FM) af[(ks + 1) & 1][k] = read_a1(sa, ks + 1, k);
-                    else if (k < FM + FN) bf[(ks + 1) & 1][k - FM] = read_b1(sb, ks + 1, k - FM);
-                    if (k < FM + FN) __builtin_amdgcn_sched_barrier(0);
-                };
+                auto mid = [&](int k) { read_group(k, sa, sb, ks + 1, af[(ks + 1) & 1], bf[(ks + 1) & 1]); };
                 if (PRIO) __builtin_amdgcn_s_setprio(2);
                 if (SPREAD) mfma_step_loading(ks & 1, ks, mid); else mfma_step(ks & 1, mid);
                 if (PRIO) __builtin_amdgcn_s_setprio(0);
@@ -1236,10 +1242,7 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
             }
             const char* na = lds + next_stage * STAGE;
             auto mid_next = [&](int k) {
-                if (!have_next) return;
-                if (k < FM) af[0][k] = read_a1(na, 0, k);
-                else if (k < FM + FN) bf[0][k - FM] = read_b1(na + A_BYTES, 0, k - FM);
-                if (k < FM + FN) __builtin_amdgcn_sched_barrier(0);
+                if (have_next) read_group(k, na, na + A_BYTES, 0, af[0], bf[0]);
             };
             if (PRIO) __builtin_amdgcn_s_setprio(2);
             if (SPREAD) mfma_step_loading((KSUB - 1) & 1, KSUB - 1, mid_next); else mfma_step((KSUB - 1) & 1, mid_next);

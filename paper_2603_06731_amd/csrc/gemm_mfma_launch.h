@@ -17,8 +17,9 @@ struct MfmaConfig {
 // size model, Sec. 4.3): id -> workgroup tile and wave grid.
 static const MfmaConfig kMfmaConfigs[] = {
     {0, 128, 256, 32, 1, 4, 3, "mfma_128x256x32_w1x4_s3_occ2"},
-    {1, 128, 128, 64, 2, 2, 2, "mfma_128x128x64_w2x2_s2"},
-    {2, 128, 128, 64, 2, 2, 4, "mfma_128x128x64_w2x2_s4"},          // 1 with a deeper ring: at most one tile per compute unit
+    // (1 and 2 go by the names they have always had, whose wave grid is the one of their first form)
+    {1, 128, 128, 64, 2, 4, 2, "mfma_128x128x64_w2x2_s2"},
+    {2, 128, 128, 64, 2, 4, 4, "mfma_128x128x64_w2x2_s4"},          // 1 with a deeper ring: at most one tile per compute unit
     {3, 256, 256, 32, 2, 4, 4, "mfma_256x256x32_w2x4_s4"},          // measured and retired, not built
     {4, 256, 256, 64, 2, 4, 2, "mfma_256x256x64_w2x4_s2"},          // 8-bit types only
     {5, 256, 256, 32, 2, 4, 4, "mfma16_256x256x32_w2x4_s4"},        // 16x16x32 MFMA blocks (16-bit types)
@@ -178,8 +179,13 @@ template <typename T, unsigned MASK>
 hipError_t launch_config(const Problem& p, hipStream_t stream, int cfg, int group_m) {
     switch (cfg) {
     PBK_CASE(0, 128, 256, 32, 1, 4, 3, 2)
-    PBK_CASE(1, 128, 128, 64, 2, 2, 2, 2)
-    PBK_CASE(2, 128, 128, 64, 2, 2, 4)
+    // 128 x 128 tiles on eight waves of 64 x 32: two waves per SIMD fill each other's waits for LDS, barriers and address code where one
+    // workgroup has a compute unit, four where two have it.  With four waves of 64 x 64 on 32 x 32 blocks, before and after: 2048 x 2048 x 4096
+    // 36.7 and 34.4 us, 2048 x 2048 x 256 8.8 and 7.7, 32 x 28 x 28 x 128 -> 128, 3 x 3, 16.7 and 14.4, 16 x 56 x 56 x 96 -> 64, 3 x 3 (two per unit), 22.1
+    // and 18.1; 32 x 32 blocks on eight waves: 36.7, 7.8, 14.9, 21.2.  K-tiles of 32 in four stages for two per unit: 17.9 there, 8 to 25 % behind from
+    // K = 1024 on (rows of 64 bytes).
+    PBK_CASE(1, 128, 128, 64, 2, 4, 2, 2, 16)
+    PBK_CASE(2, 128, 128, 64, 2, 4, 4, 1, 16)
     // 3, 4 (32x32 blocks) are not built for the 16-bit types: their 16x16 twins 5-7 replaced them
     PBK_CASE(5, 256, 256, 32, 2, 4, 4, 1, 16)
     PBK_CASE(6, 128, 256, 32, 1, 4, 3, 2, 16)
@@ -191,7 +197,7 @@ hipError_t launch_config(const Problem& p, hipStream_t stream, int cfg, int grou
 
 // configuration groups of the 16-bit translation units (gemm_mfma_16bit.hip, once per type and group)
 constexpr unsigned kGroupMask16[] = {
-    (1u << 0) | (1u << 1) | (1u << 2),   // 0: the 32x32-block configurations
+    (1u << 0) | (1u << 1) | (1u << 2),   // 0: the 32x32-block configuration and the 128 x 128 tiles
     (1u << 5),                        // 1: 256x256x32, plain ring
     (1u << 6),                        // 2: 128x256x32, two workgroups per compute unit
     (1u << 7),                        // 3: A staged 64 deep
