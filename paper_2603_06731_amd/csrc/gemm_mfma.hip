@@ -70,12 +70,16 @@ static int square_config(const Problem& p) {
 static int choose_config(const Problem& p) {
     long long t = (long long)((p.M + 127) / 128) * ((p.N + 255) / 256) * p.batch;
     long long t256 = (long long)((p.M + 255) / 256) * ((p.N + 255) / 256) * p.batch;
+    const long long t128 = (long long)((p.M + 127) / 128) * ((p.N + 127) / 128) * p.batch;
     if (p.trans_b && !p.is_conv && p.K >= 1024) {
         // k-major B, long contraction: the 128x256 configurations are slow there (1044 us against
         // 874 us for 256x256x32 on 8192^3); short ones (K = 128) follow the general rule below
         // (9: both operands staged 64 deep, one barrier per pair of k-tiles: 715 against 800 us on 8192^3,
         // 5-7 % ahead of 5 from K = 1024 up and down to 4096^2 outputs)
-        if (p.M >= 256 && p.N >= 256 && t256 >= 128) return 9;
+        // Up to two 128 x 128 tiles per compute unit those are ahead, which leave no unit without work (2048 x 4096, 128 tiles of 256 x 256:
+        // K = 1024 25.5 against 21.6 us, 4096 70.5 against 62.4, 8192 138 against 135); from the next one on they take a second round
+        // (2048 x 5120 x 1024: 25.9 against 32.3).
+        if (p.M >= 256 && p.N >= 256 && t128 > 512) return 9;
         return square_config(p);
     }
     // Long contractions over many tiles: one 256x256x32 workgroup per CU with a 4-stage ring.
@@ -91,9 +95,17 @@ static int choose_config(const Problem& p) {
     // convolutions whose channel count is a multiple of 64 (the image is then staged in 64-deep pieces): 9 from one
     // round of 256x256 tiles and K = 1024 up (32x56x56x256 -> 256, 3x3: 131 against 151 us; 64x28x28x256 -> 512: 121
     // against 133 us; K = 576 equal; 1x1 filters and fewer than 100 tiles: 6 or 1 stay ahead by 10-15 %)
-    if (p.is_conv && p.conv.Cin % 64 == 0 && p.M >= 256 && p.N >= 256 && t256 >= 256 && p.K >= 1024)
+    // (also within one round of them, once the 128x256 ones leave units with one workgroup and others with two: 24 x 28 x 28 x 256 -> 512, 3 x 3:
+    // 51.3 against 46.9 us, 16 x 56 x 56 x 128 -> 256: 31.8 and 30.5; K = 576 even, 1 x 1 with K = 256 29.1 and 30.9)
+    if (p.is_conv && p.conv.Cin % 64 == 0 && p.M >= 256 && p.N >= 256 && t > 256 && p.K >= 1024)
         return 9;
-    if (p.M >= 128 && p.N >= 256 && t >= 256) return 6;
+    // One round of 256x256 tiles where the 128x256 ones leave units with one workgroup and others with two (2304 x 4096, 144 tiles: K = 768 22.6
+    // against 23.2 us, 1024 26.5 and 27.9, 2048 42.5 and 45.8, 4096 76 and 85; 4096 x 4096: 1024 33.0 and 34.2, 4096 99 and 112; K = 512: within 1 %;
+    // k-major B: 2304 x 4096, K = 512 17.9 and 19.5, 896 23.4 and 27.9; 4096 x 4096: 512 20.5 and 22.6).
+    if (!p.is_conv && p.M >= 256 && p.N >= 256 && t > 256 && t256 <= 256 && p.K >= (p.trans_b ? 512 : 768)) return 9;
+    // (256 tiles of 128x256 leave every unit with one workgroup, where two of 128x128 are ahead: 2048 x 4096, K = 512 16.3 against 15.0 us, 1024 22.6
+    // and 21.2, 2048 37.0 and 36.0, 4096 64.1 and 65.0)
+    if (p.M >= 128 && p.N >= 256 && (t > 256 || (t == 256 && p.K >= 4096))) return 6;
     return square_config(p);
 }
 
@@ -164,12 +176,16 @@ hipError_t launch_mfma(const Problem& p, hipStream_t stream, int force_cfg, cons
         return launch_mfma_f32(p, stream, c, 8);
     }
     if (p.in_dtype == DT_INT8) {
-        // measured: the 256x256 tile with the deep k-tile is the fastest of the three built for int8
-        long long t256 = (long long)((p.M + 255) / 256) * ((p.N + 255) / 256) * p.batch;
-        // (with both operands k-major the 16x16x64 blocks: 0.54 against 0.59 ms on 8192^3)
+        // Up to two 128x128 tiles per compute unit those: they fill each other's waits in the long epilogue (32 x 28 x 28 x 128 -> 256, 3 x 3, 392
+        // tiles: 17.8 us, with 256x256 28.3, with 128x256 23.3).  More tiles: both operands k-major the 16x16x64 blocks (0.54 against 0.59 ms on
+        // 8192^3); a convolution 128x256, two per unit (64 x 28 x 28 x 64 -> 256, 3 x 3: 27.4 with 128x128, 26.8 with 256x256, 23.0; 48 x 56 x 56 x 128 ->
+        // 256: 75, 88, 74; 64 x 56 x 56 x 256 -> 256: 164, 180, 154); a row-major product 256x256, but 128x128 where the epilogue is most of the time
+        // (200704 x 256, K = 64: 52 and 68, 256: 65 and 87).
+        const long long t128 = (long long)((p.M + 127) / 128) * ((p.N + 127) / 128) * p.batch;
         const bool kmajor = p.trans_b && !p.is_conv;
+        const bool large = p.M >= 256 && p.N >= 256 && t128 > 512;
         int c = (force_cfg == 0 || force_cfg == 1 || force_cfg == 2 || force_cfg == 4 || force_cfg == 8 || force_cfg == 9) ? force_cfg
-                : (p.M >= 256 && p.N >= 256 && t256 >= 128) ? (kmajor ? 9 : 4) : square_config(p);
+                : !large || (!kmajor && p.K < (p.is_conv ? 256 : 512)) ? square_config(p) : kmajor ? 9 : p.is_conv ? 0 : 4;
         if ((c == 8 || c == 9) && !kmajor) c = 4;       // the 16x16 blocks are built for k-major operands only
         *name = kMfmaConfigs[c].name;
         const int gm = group_m_override() > 0 ? group_m_override() : 8;
@@ -185,8 +201,14 @@ hipError_t launch_mfma(const Problem& p, hipStream_t stream, int force_cfg, cons
         // only the 64-deep configurations are built for it
         const bool kmajor = p.trans_b && !p.is_conv;
         if (force_cfg != 1 && force_cfg != 2 && force_cfg != 4 && !(force_cfg == 9 && kmajor)) {       // (also a forced 5-8)
-            long long t256 = (long long)((p.M + 255) / 256) * ((p.N + 255) / 256) * p.batch;
-            cfg = (p.M >= 256 && p.N >= 256 && t256 >= 128) ? (kmajor ? 9 : 4) : square_config(p);
+            // Two 128x128 tiles per compute unit before 256x256 ones, as in 16 bits (e4m3, k-major B: 2048 x 4096 x 4096 40.1 against 35.3 us, x 8192
+            // 70.5 and 62.7, 3072 x 3072 x 1024, 576 tiles, 17.5 and 20.9).  With a row-major B, whose 8-bit transposing reads two small workgroups
+            // hide from each other, they stay ahead until the traffic of many tiles and a long contraction decides (3072 x 2048 x 4096: 58.2 and 29.2;
+            // 8192 x 8192 x 2048: 187 and 143; 4096 x 4096 x 8192: 128 and 118; 8192 x 4096 x 4096: 153 and 154; 8192^3: 451 and 461).
+            // A convolution's 256x256 tiles spill registers (32 x 56 x 56 x 256 -> 256, 3 x 3: 560 and 80 us).
+            const long long t128 = (long long)((p.M + 127) / 128) * ((p.N + 127) / 128) * p.batch;
+            const bool large = p.M >= 256 && p.N >= 256 && (kmajor ? t128 > 512 : !p.is_conv && t128 > 2048 && p.K >= 4096);
+            cfg = large ? (kmajor ? 9 : 4) : square_config(p);
         } else {
             cfg = force_cfg;
         }

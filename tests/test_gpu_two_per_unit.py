@@ -1,0 +1,84 @@
+"""Where 128 x 128 tiles give way to larger ones: either side of each line of the rule, against float64."""
+import pytest
+
+import workloads as wl
+import pbk_testlib as T
+
+pytestmark = pytest.mark.gpu
+
+BF16, E4M3 = wl.DTYPE_BF16, wl.DTYPE_FP8_E4M3
+PAIR, WIDE, SQUARE = "a64_b6_pair", "128x256x32", "128x128x64"
+
+
+@pytest.mark.parametrize("dtype,M,N,K,trans_b,kernel", [
+    (BF16, 2048, 4096, 512, 0, SQUARE), (BF16, 2049, 4096, 512, 0, WIDE), (BF16, 2049, 4096, 768, 0, PAIR), (BF16, 2048, 4096, 4096, 0, WIDE),
+    (BF16, 2049, 4096, 504, 1, WIDE), (BF16, 2049, 4096, 512, 1, PAIR), (BF16, 2048, 4096, 1024, 1, SQUARE), (BF16, 2049, 4096, 1024, 1, PAIR),
+    (BF16, 4097, 4096, 768, 0, WIDE),
+    (E4M3, 2048, 4096, 512, 1, SQUARE), (E4M3, 2049, 4096, 512, 1, PAIR), (E4M3, 2049, 4096, 512, 0, SQUARE), (E4M3, 4096, 8192, 4096, 0, SQUARE),
+    (E4M3, 4097, 8192, 4096, 0, "256x256x64"), (E4M3, 4097, 8192, 4080, 0, SQUARE),
+])
+def test_dispatch(dtype, M, N, K, trans_b, kernel):
+    import torch
+    import paper_2603_06731_amd as pbk
+    tdt = torch.bfloat16 if dtype == BF16 else torch.float8_e4m3fn
+    g = torch.Generator(device="cuda").manual_seed(7)
+    A = torch.randn(M, K, generator=g, device="cuda").to(tdt)
+    B = (torch.randn(N, K, generator=g, device="cuda") if trans_b else torch.randn(K, N, generator=g, device="cuda")).to(tdt)
+    C = torch.empty(M, N, device="cuda", dtype=torch.bfloat16)
+    raw = (lambda x: x) if dtype == BF16 else (lambda x: x.view(torch.uint8))
+    with T.forced_kernel(None):
+        st = pbk.pbk_matmul(raw(A), raw(B), C, None, M, N, K, K, K if trans_b else N, N, dtype, BF16, trans_b, 1.0, wl.configs.EPI_NONE)
+    assert st == 0 and kernel in pbk.pbk_last_kernel(), pbk.pbk_last_kernel()
+    rows = torch.tensor([0, 1, 63, 64, 127, 128, M // 2, M - 2, M - 1], device="cuda")
+    a, b = A[rows].to(torch.float64), B.to(torch.float64)
+    b = b.t().contiguous() if trans_b else b
+    ref = a @ b
+    # rounded once to bf16; the sums in fp32 (FP8: the instruction's own, 1e-4 to 2e-4 of the output's scale)
+    bound = 2.0 ** -8 * ref.abs() + (4e-4 if dtype == E4M3 else 1e-5) * K ** 0.5 + 1e-5 * (a.abs() @ b.abs())
+    assert torch.all((C[rows].double() - ref).abs() <= bound)
+
+
+def conv_case(dtype, n, hw, cin, cout, k):
+    w = wl.Workload("units_conv", "conv", dtype, BF16, wl.configs.EPI_BIAS_RELU, n=n, H=hw, W=hw, Cin=cin, Cout=cout, KH=k, KW=k,
+                    pad=(k // 2, k // 2), dist_b=("normal", float((2.0 / (k * k * cin)) ** 0.5)))
+    st, out = T.run_workload(w, T.upload(wl.make_inputs(w)))
+    assert st == 0
+    return T.to_host_f64(out, w.out_dtype)
+
+
+@pytest.mark.parametrize("dtype,n,hw,cin,cout,k,kernel", [
+    (BF16, 17, 45, 128, 256, 3, PAIR),          # 269 tiles of 128 x 256, 135 of 256 x 256
+    (BF16, 17, 45, 112, 256, 3, WIDE),          # channels that k-tiles of 64 do not divide
+    (E4M3, 17, 45, 64, 256, 3, SQUARE),
+])
+def test_dispatch_conv(dtype, n, hw, cin, cout, k, kernel):
+    import numpy as np
+    import paper_2603_06731_amd as pbk
+    with T.forced_kernel(None):
+        got = conv_case(dtype, n, hw, cin, cout, k)
+    assert kernel in pbk.pbk_last_kernel(), pbk.pbk_last_kernel()
+    with T.forced_kernel("generic"):            # the kernel without matrix units: fp32 products and sums in another order
+        ref = conv_case(dtype, n, hw, cin, cout, k)
+    # both rounded once to bf16 (2^-8 of the value between them), fp32 sums (FP8: the instruction's own) at a scale of about 1
+    assert np.all(np.abs(got - ref) <= 2.0 ** -7 * np.abs(ref) + 2e-3)
+
+
+@pytest.mark.parametrize("n,hw,cin,cout,k,kernel", [
+    (16, 45, 32, 256, 3, SQUARE), (17, 45, 32, 256, 3, WIDE), (17, 45, 16, 256, 3, SQUARE), (64, 32, 256, 272, 1, SQUARE), (64, 32, 512, 272, 1, "256x256x64"),
+])
+def test_dispatch_int8(n, hw, cin, cout, k, kernel):
+    """506 and 538 tiles of 128 x 128; a short contraction; 1 x 1 filters, which run as row-major products.  Codes as without matrix units."""
+    import torch
+    import paper_2603_06731_amd as pbk
+    g = torch.Generator(device="cuda").manual_seed(9)
+    x = (torch.randn(n, hw, hw, cin, generator=g, device="cuda") * 40).round().clamp(-128, 127).to(torch.int8)
+    f = (torch.randn(k, k, cin, cout, generator=g, device="cuda") * 30).round().clamp(-128, 127).to(torch.int8)
+    par = [torch.rand(cout, generator=g, device="cuda") + 0.5 for _ in range(6)]
+    par[0] *= 3.0 / (40.0 * 30.0 * (k * k * cin) ** 0.5)
+    out = [torch.empty(n, hw, hw, cout, device="cuda", dtype=torch.int8) for _ in range(2)]
+    for force, y in ((None, out[0]), ("generic", out[1])):
+        with T.forced_kernel(force):
+            st = pbk.pbk_conv2d_nhwc_int8_bn(x, f, y, n, hw, hw, cin, cout, k, k, 1, 1, k // 2, k // 2, 1, 1, par[0], par[1], 0.05, par[2], par[3], 1e-5,
+                                             par[4], par[5], 1, 0.06, pbk.PBK_INT8)
+        assert st == 0 and (force or kernel) in pbk.pbk_last_kernel(), pbk.pbk_last_kernel()
+    assert torch.equal(out[0], out[1])
