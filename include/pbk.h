@@ -325,7 +325,7 @@ const char* pbk_last_kernel(void);
  *                 batch entry (as many as the head dimension has 32-column groups, at most), each with its own columns of V;
  *                 "decode:8" the keys split over workgroups, up to 96 entries, with any context of two steps of 32 keys.
  * Attention takes "generic", "mfma" (the kernel of whole sequences; "mfma:1" all waves on the same keys, "mfma:2" the keys in
- * two halves where that form is built) and "decode", and chooses automatically under the others.  A problem the choice cannot run, and
+ * two halves, "mfma:3" and "mfma:4" 64 queries per workgroup and the keys in two and four parts, where these forms are built) and "decode", and chooses automatically under the others.  A problem the choice cannot run, and
  * "decode" for anything but attention, gives PBK_ERR_UNSUPPORTED.  NULL or "" returns to the default.  The default
  * is automatic choice, or what the environment variable PBK_FORCE_KERNEL (same strings) held when the process made its first
  * call.  An unknown string is PBK_ERR_UNSUPPORTED and changes nothing.

@@ -21,11 +21,14 @@
 // basic blocks, and the compiler then sinks the softmax arithmetic out of the
 // MFMA slots it was written into.
 //
-// SPLIT = 2: with too few workgroups for that, a workgroup has two such groups of
-// four waves, each with LDS tiles of its own and half of the key tiles, for the same
-// 128 queries; at the end the second group's output, reference points and sums go
+// SPLIT > 1: with too few workgroups for that, a workgroup has two or four such groups of
+// waves, each with LDS tiles of its own and its share of the key tiles, for the same
+// queries; at the end the other groups' outputs, reference points and sums go
 // through LDS to the first.  The chain of tiles is the bound there: 16 x 2048 x 64, causal:
 // 26.6 -> 23.5 us; 16 x 4096 x 128, causal: 102 -> 79; 6 x 4096 x 64: 44.6 -> 37.1.
+// QW = 2: a workgroup owns 64 queries, two waves of 32 per group.  There are twice as many of them, and under the causal diagonal a
+// long one and a short one share a compute unit, which otherwise waits for the longest: 16 x 2048 x 64, causal: 23.3 -> 18.9 us; 16 x 577 x
+// 64: 10.8 -> 8.3 (attention_form).
 //
 // Register layouts (v_mfma_f32_32x32x16, D[i][j] += sum_k A[i][k] B[k][j]; a lane
 // supplies row i = lane%32 of A and column j = lane%32 of B, 8 consecutive k
@@ -78,26 +81,28 @@ __device__ __forceinline__ void dma16_s(int4v rsrc, unsigned lds_addr, unsigned 
 // CAUSAL: query q attends to keys <= q + (Nk - Nq).  The key tiles beyond the workgroup's last visible key
 // are not visited at all; in the blocks that the diagonal crosses the hidden scores are set to -inf like
 // the keys beyond Nk.
-template <typename T, int D, bool HAS_BIAS, bool PRE, bool CAUSAL, int SPLIT>
-__global__ __launch_bounds__(ATT_NW * SPLIT * 64, 2) void attention_mfma_kernel(AttnProblem p, int q_tiles, int total, int xcds) {
+// QW: waves of 32 queries each; SPLIT: groups of QW waves, each with its share of the key tiles
+template <typename T, int D, bool HAS_BIAS, bool PRE, bool CAUSAL, int SPLIT, int QW = ATT_NW>
+__global__ __launch_bounds__(QW * SPLIT * 64, 2) void attention_mfma_kernel(AttnProblem p, int q_tiles, int total, int xcds) {
     constexpr int KS = D / 16;                    // k16 steps of Q K^T
     constexpr int JD = D / 32;                    // 32-wide blocks of the head dimension
     constexpr int NPV = 2 * JD;                   // MFMAs of O^T += V^T P^T per 32-key block
     constexpr int TILE = ATT_BKV * D * 2;         // bytes of one K or V tile
     constexpr int BLKS = TILE / 1024;             // 1 KiB wave-loads per tile
-    constexpr int CPW = BLKS / ATT_NW;            // per wave
-    static_assert(SPLIT == 1 || (SPLIT == 2 && !HAS_BIAS), "the bias is addressed by the key of the whole range");
-    static_assert(BLKS % ATT_NW == 0 && CPW >= 1, "tile must split evenly over the waves");
+    constexpr int BQ = QW * 32;                   // query rows per workgroup
+    constexpr int CPW = BLKS / QW;                // per wave
+    static_assert(SPLIT == 1 || !HAS_BIAS, "the bias is addressed by the key of the whole range");
+    static_assert(BLKS % QW == 0 && CPW >= 1, "tile must split evenly over the waves");
     constexpr int CPR = D / 8;                    // 16-byte slots per row
     constexpr int ROWS = 64 / CPR;                // rows per wave-load
     constexpr float LOG2E = 1.4426950408889634f;
 
-    // K slot 0 | K slot 1 | V slot 0 | V slot 1, once per group of ATT_NW waves
+    // K slot 0 | K slot 1 | V slot 0 | V slot 1, once per group of QW waves
     extern __shared__ __attribute__((aligned(1024))) char lds_all[];
 
     const int lane = threadIdx.x & 63;
     const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int grp = SPLIT == 1 ? 0 : wave_all / ATT_NW, wave = SPLIT == 1 ? wave_all : wave_all % ATT_NW;
+    const int grp = SPLIT == 1 ? 0 : wave_all / QW, wave = SPLIT == 1 ? wave_all : wave_all % QW;
     char* const lds = lds_all + grp * (4 * TILE);
     const int h = lane >> 5, col = lane & 31;
 
@@ -108,8 +113,10 @@ __global__ __launch_bounds__(ATT_NW * SPLIT * 64, 2) void attention_mfma_kernel(
     const int id = xcd * xq + (xcd < xr ? xcd : xr) + local;
     const int b = id / q_tiles;
     // (causal: the last query tiles have the most keys to visit and are started first)
-    const int q_tile = CAUSAL ? q_tiles - 1 - (id - b * q_tiles) : id - b * q_tiles;
-    const int q0 = q_tile * ATT_BQ + wave * 32;
+    // (two small workgroups on a compute unit: every other entry the other way round, so that a long one and a short one share it)
+    const bool forward = !CAUSAL || (QW < ATT_NW && (b & 1) && total <= 512);
+    const int q_tile = forward ? id - b * q_tiles : q_tiles - 1 - (id - b * q_tiles);
+    const int q0 = q_tile * BQ + wave * 32;
     int c_off = p.Nk - p.Nq;                       // causal: key visible iff key <= query + c_off
 
     const char* Kb = (const char*)p.K + (int64_t)b * p.stride_k * 2;
@@ -118,26 +125,22 @@ __global__ __launch_bounds__(ATT_NW * SPLIT * 64, 2) void attention_mfma_kernel(
     int Nk = p.Nk, NT = (Nk + ATT_BKV - 1) / ATT_BKV;
     if (CAUSAL) {
         // the workgroup's last visible key (at least one tile is walked, so that every wave meets the barriers)
-        const long long last = (long long)q_tile * ATT_BQ + ATT_BQ - 1 + c_off;
+        const long long last = (long long)q_tile * BQ + BQ - 1 + c_off;
         const int nt_vis = last < 0 ? 1 : (int)(last / ATT_BKV) + 1;
         NT = nt_vis < NT ? nt_vis : NT;
     }
-    if (SPLIT == 2) {
-        // Each group of waves takes half of the tiles and counts keys from its own first one.  Both walk NT tiles and
+    if (SPLIT > 1) {
+        // Each group of waves takes its share of the tiles and counts keys from its own first one.  All walk NT tiles and
         // meet the same barriers; what lies beyond a group's Nk (which may be <= 0) arrives as zeros and is masked.
-        const int half = (NT + 1) / 2;
-        const long long end = (long long)NT * ATT_BKV;             // (causal: hidden tiles stay unread)
+        const int share = (NT + SPLIT - 1) / SPLIT;
+        const long long end = (long long)NT * ATT_BKV, first = (long long)grp * share * ATT_BKV;             // (causal: hidden tiles stay unread)
         if (end < Nk) Nk = (int)end;
-        if (grp == 0) {
-            if (half * ATT_BKV < Nk) Nk = half * ATT_BKV;
-        } else {
-            const int first = half * ATT_BKV;
-            Nk -= first;
-            c_off -= first;
-            Kb += (int64_t)first * p.ldk * 2;
-            Vb += (int64_t)first * p.ldv * 2;
-        }
-        NT = half;
+        Nk = (int)(Nk - first);
+        if ((long long)share * ATT_BKV < Nk) Nk = share * ATT_BKV;
+        c_off = (int)(c_off - first);
+        Kb += first * p.ldk * 2;
+        Vb += first * p.ldv * 2;
+        NT = share;
     }
 
     // ---- per-lane source offsets of the direct-to-LDS loads (lane i lands at byte 16 i)
@@ -511,35 +514,48 @@ __global__ __launch_bounds__(ATT_NW * SPLIT * 64, 2) void attention_mfma_kernel(
     }
     if (t < NT) tile(t, IntTag<0>{}, TailNo{});
 
-    // ---- the second group's result is brought to the common reference point and added by the first (same wave, same lane)
+    // ---- the other groups' results are brought to the common reference point and added by the first (same wave, same lane)
     float l_tot = l_run + __shfl_xor(l_run, 32);
-    if constexpr (SPLIT == 2) {
+    if constexpr (SPLIT > 1) {
         constexpr int WAVE_F4 = (JD * 4 + 1) * 64;                // 16-byte pieces per wave: the outputs, then (m, l)
-        static_assert(ATT_NW * WAVE_F4 * 16 <= SPLIT * 4 * TILE, "LDS");
-        f32x4* part = (f32x4*)lds_all + wave * WAVE_F4 + lane;
+        static_assert((SPLIT - 1) * QW * WAVE_F4 * 16 <= SPLIT * 4 * TILE, "LDS");
+        f32x4* part = (f32x4*)lds_all + wave * WAVE_F4 + lane;    // of group 1; group g: + (g - 1) GROUP_F4
+        constexpr int GROUP_F4 = QW * WAVE_F4;
         __syncthreads();                                          // every tile has been read for the last time
-        if (grp == 1) {
+        if (grp > 0) {
+            f32x4* mine = part + (grp - 1) * GROUP_F4;
 #pragma unroll
             for (int j = 0; j < JD; ++j)
 #pragma unroll
                 for (int g = 0; g < 4; ++g)
-                    part[(j * 4 + g) * 64] = f32x4{o_acc[j][g * 4], o_acc[j][g * 4 + 1], o_acc[j][g * 4 + 2], o_acc[j][g * 4 + 3]};
-            part[JD * 4 * 64] = f32x4{m_run, l_tot, 0.0f, 0.0f};
+                    mine[(j * 4 + g) * 64] = f32x4{o_acc[j][g * 4], o_acc[j][g * 4 + 1], o_acc[j][g * 4 + 2], o_acc[j][g * 4 + 3]};
+            mine[JD * 4 * 64] = f32x4{m_run, l_tot, 0.0f, 0.0f};
         }
         __syncthreads();
-        if (grp == 1) return;
-        const f32x4 ml = part[JD * 4 * 64];
-        const float m = fmaxf(m_run, ml[0]), m_sub = m == -INFINITY ? 0.0f : m;
-        const float f0 = fast_exp2(m_run - m_sub), f1 = fast_exp2(ml[0] - m_sub);
-        l_tot = fmaf(ml[1], f1, l_tot * f0);
+        if (grp > 0) return;
+        float m = m_run;
+#pragma unroll
+        for (int s = 0; s < SPLIT - 1; ++s) m = fmaxf(m, part[s * GROUP_F4 + JD * 4 * 64][0]);
+        const float m_sub = m == -INFINITY ? 0.0f : m, f0 = fast_exp2(m_run - m_sub);
+        l_tot *= f0;
 #pragma unroll
         for (int j = 0; j < JD; ++j)
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const f32x4 v = part[(j * 4 + g) * 64];
+            for (int e = 0; e < 16; ++e) o_acc[j][e] *= f0;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) o_acc[j][g * 4 + e] = fmaf(v[e], f1, o_acc[j][g * 4 + e] * f0);
-            }
+        for (int s = 0; s < SPLIT - 1; ++s) {
+            const f32x4 ml = part[s * GROUP_F4 + JD * 4 * 64];
+            const float f1 = fast_exp2(ml[0] - m_sub);
+            l_tot = fmaf(ml[1], f1, l_tot);
+#pragma unroll
+            for (int j = 0; j < JD; ++j)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const f32x4 v = part[s * GROUP_F4 + (j * 4 + g) * 64];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) o_acc[j][g * 4 + e] = fmaf(v[e], f1, o_acc[j][g * 4 + e]);
+                }
+        }
     }
 
     // ---- normalise and store: the lane holds, for query q0 + lane%32, d = 32 j + 8 g + 4 h + 0..3
@@ -558,19 +574,27 @@ __global__ __launch_bounds__(ATT_NW * SPLIT * 64, 2) void attention_mfma_kernel(
     }
 }
 
-template <typename T, int D>
-hipError_t launch_d(const AttnProblem& p, hipStream_t stream, bool split) {
-    const int lds_bytes = (split ? 2 : 1) * 2 * 2 * ATT_BKV * D * 2;
-    const void* kern = split ? (p.causal ? (const void*)attention_mfma_kernel<T, D, false, false, true, 2>
-                                         : (const void*)attention_mfma_kernel<T, D, false, false, false, 2>)
-                       : p.causal ? (const void*)attention_mfma_kernel<T, D, false, false, true, 1>
-                       : p.bias ? (const void*)attention_mfma_kernel<T, D, true, true, false, 1>
-                       : p.alpha > 0.0f ? (const void*)attention_mfma_kernel<T, D, false, false, false, 1>
-                                        : (const void*)attention_mfma_kernel<T, D, false, true, false, 1>;
+// The forms: 128 queries with all waves on the same keys (1), with the key tiles in two halves (2); 64 queries with the key tiles in two (3) and
+// four (4, D up to 64: the groups' tiles have to fit the LDS) parts.
+enum : int { FORM_Q128 = 1, FORM_Q128_X2, FORM_Q64_X2, FORM_Q64_X4 };
+
+template <typename T, int D, int SPLIT, int QW>
+hipError_t launch_form(const AttnProblem& p, hipStream_t stream) {
+    const int lds_bytes = SPLIT * 2 * 2 * ATT_BKV * D * 2;
+    const void* kern;
+    if constexpr (SPLIT > 1) {
+        kern = p.causal ? (const void*)attention_mfma_kernel<T, D, false, false, true, SPLIT, QW>
+                        : (const void*)attention_mfma_kernel<T, D, false, false, false, SPLIT, QW>;
+    } else {
+        kern = p.causal ? (const void*)attention_mfma_kernel<T, D, false, false, true, 1>
+               : p.bias ? (const void*)attention_mfma_kernel<T, D, true, true, false, 1>
+               : p.alpha > 0.0f ? (const void*)attention_mfma_kernel<T, D, false, false, false, 1>
+                                : (const void*)attention_mfma_kernel<T, D, false, true, false, 1>;
+    }
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
-    if (split) {                                   // up to 128 KiB of LDS
+    if (SPLIT > 1) {                               // up to 128 KiB of LDS
         static std::atomic<unsigned> attr_done[2]; // bit per device, for either form
         const unsigned bit = 1u << (dev & 31);
         if (!(attr_done[p.causal ? 1 : 0].load(std::memory_order_acquire) & bit)) {
@@ -583,30 +607,36 @@ hipError_t launch_d(const AttnProblem& p, hipStream_t stream, bool split) {
     e = device_shape(dev, &ds);
     if (e != hipSuccess) return e;
     int xcds = ds.xcds;
-    int q_tiles = (p.Nq + ATT_BQ - 1) / ATT_BQ;
+    int q_tiles = (int)(((long long)p.Nq + QW * 32 - 1) / (QW * 32));
     long long total = (long long)q_tiles * p.batch;
     if (total <= 0 || total > 0x7FFFFFFFLL) return hipErrorInvalidValue;
     int tot = (int)total;
     AttnProblem pa = p;
     void* args[] = {&pa, &q_tiles, &tot, &xcds};
-    return hipLaunchKernel(kern, dim3((unsigned)total), dim3(ATT_NW * (split ? 2 : 1) * 64), args, lds_bytes, stream);
+    return hipLaunchKernel(kern, dim3((unsigned)total), dim3(QW * SPLIT * 64), args, lds_bytes, stream);
+}
+
+template <typename T, int D>
+hipError_t launch_d(const AttnProblem& p, hipStream_t stream, int form) {
+    switch (form) {
+    case FORM_Q128_X2: return launch_form<T, D, 2, 4>(p, stream);
+    case FORM_Q64_X2: return launch_form<T, D, 2, 2>(p, stream);
+    case FORM_Q64_X4: if constexpr (D <= 64) return launch_form<T, D, 4, 2>(p, stream); else return hipErrorInvalidValue;
+    default: return launch_form<T, D, 1, 4>(p, stream);
+    }
 }
 
 template <typename T>
-hipError_t launch_t(const AttnProblem& p, hipStream_t stream, bool split, const char** name) {
+hipError_t launch_t(const AttnProblem& p, hipStream_t stream, int form, const char** name) {
+#define PBK_ATT_NAMES(d) {{"attn_mfma_q128_kv64_d" #d, "attn_mfma_q128_kv64_d" #d "_causal"}, {"attn_mfma_q128_kv64x2_d" #d, "attn_mfma_q128_kv64x2_d" #d "_causal"}, \
+                          {"attn_mfma_q64_kv64x2_d" #d, "attn_mfma_q64_kv64x2_d" #d "_causal"}, {"attn_mfma_q64_kv64x4_d" #d, "attn_mfma_q64_kv64x4_d" #d "_causal"}}
+    static const char* const names[3][4][2] = {PBK_ATT_NAMES(32), PBK_ATT_NAMES(64), PBK_ATT_NAMES(128)};
+#undef PBK_ATT_NAMES
+    *name = names[p.D == 32 ? 0 : p.D == 64 ? 1 : 2][form - 1][p.causal ? 1 : 0];
     switch (p.D) {
-    case 32:
-        *name = split ? (p.causal ? "attn_mfma_q128_kv64x2_d32_causal" : "attn_mfma_q128_kv64x2_d32")
-                      : (p.causal ? "attn_mfma_q128_kv64_d32_causal" : "attn_mfma_q128_kv64_d32");
-        return launch_d<T, 32>(p, stream, split);
-    case 64:
-        *name = split ? (p.causal ? "attn_mfma_q128_kv64x2_d64_causal" : "attn_mfma_q128_kv64x2_d64")
-                      : (p.causal ? "attn_mfma_q128_kv64_d64_causal" : "attn_mfma_q128_kv64_d64");
-        return launch_d<T, 64>(p, stream, split);
-    case 128:
-        *name = split ? (p.causal ? "attn_mfma_q128_kv64x2_d128_causal" : "attn_mfma_q128_kv64x2_d128")
-                      : (p.causal ? "attn_mfma_q128_kv64_d128_causal" : "attn_mfma_q128_kv64_d128");
-        return launch_d<T, 128>(p, stream, split);
+    case 32: return launch_d<T, 32>(p, stream, form);
+    case 64: return launch_d<T, 64>(p, stream, form);
+    case 128: return launch_d<T, 128>(p, stream, form);
     default: return hipErrorInvalidValue;
     }
 }
@@ -639,18 +669,46 @@ bool attention_mfma_supported(const AttnProblem& p) {
 // A full round of entries with one query tile each at D = 128 (240 to 256) is bound by memory, not by the chain, below 3072 keys
 // (256 entries of 64 queries, K and V from memory: 2048 keys 53.6 against 54.7 us, 3072 78.3 against 77.2; of 128 queries: 57.0
 // against 59.0, 82.4 against 82.1; 224 entries of 64: 50.0 against 49.0, 73.4 against 69.2).
+static bool triangle_of(const AttnProblem& p) { return p.causal && p.Nk <= (long long)p.Nq + p.Nq / 4; }      // otherwise the query tiles see about the same keys
 static bool split_preferred(const AttnProblem& p) {
     const long long total = (long long)((p.Nq + ATT_BQ - 1) / ATT_BQ) * p.batch;
-    const bool triangle = p.causal && p.Nk <= (long long)p.Nq + p.Nq / 4;      // otherwise the query tiles see about the same keys
+    const bool triangle = triangle_of(p);
     if (total <= 256) return p.Nk >= (p.D == 128 && p.batch > 240 ? 3072 : p.D < 128 || triangle ? 1024 : 2048);
     return total <= 512 && ((triangle && p.Nk >= 4096) || (p.D == 32 && p.Nk >= 2048));
 }
 
-// force_cfg: 1 all waves on the same keys, 2 the keys in two halves (no bias, alpha > 0), otherwise by the rule.
+// 64 queries per workgroup, two (or four) groups of waves: twice the workgroups where those of 128 queries leave compute units without one or with
+// a single chain.  Times in us, the better form of 128 queries first:
+// - up to one per unit from two tiles of keys on: 16 x 577 x 64: 10.8 and 8.3, 20 x 300 x 128: 10.8 and 9.8, 16 x 1024 x 128 20.5 and 16.4, 10 x 100 x 64,
+//   causal, 6.3 and 5.5; the keys in four parts, up to D = 64, from 2048 keys on: 8 x 2048 x 64 21.2, 16.3 and 14.9, 16 entries of 64 queries, 8192
+//   keys, 65.6, 50.1 and 40.9 (16 x 1024, causal: 14.7, 11.5 and 12.4; more than 128 entries are bound by memory: 256 x 64 x 1024 x 64 16.4, 15.2 and
+//   15.6).  Up to 64 queries there are no more workgroups than before, so only where the
+//   keys are split anyway (128 x 64 x 2048 x 128: 33.7 and 32.0; but 64 x 64 x 64 x 64 4.7 and 5.6, 256 x 33 x 300 x 128 10.9 and 12.3);
+// - two per unit (D up to 64; at D = 128 their tiles do not fit the LDS together) under the diagonal, where a long one and a short one share a unit
+//   (16 x 2048 x 64: 23.3 and 18.9, 8 x 4096: 38.3 and 35.2; 24 x 1000: 15.0 and 15.6, 64 x 300: 8.3 and 9.6); without it the 128-row ones move half the keys
+//   (12 x 2048 x 64: 21.6 and 22.2);
+// - up to three under the diagonal for middling contexts (24 x 2048 x 64: 32.2 and 29.4, 18 x 2500: 38.6 and 35.1; 22 x 2900: 42.7 and 46.4, 42 x 1536: 27.8
+//   and 31.8, 64 x 700: 14.8 and 18.6);
+// - at D = 32, whose steps are short, from 1024 keys on (12 x 3000: 37.6 and 30.5, causal 31.8 and 25.1, 48 x 1024: 15.9 and 13.1; 64 x 300: 6.1 and 6.6;
+//   16 x 4096: 51.8 and 54.1, causal 48.9 and 38.4; 32 x 2048: 28.2 and 29.1, causal 28.1 and 28.4).
+static int attention_form(const AttnProblem& p) {
+    const bool split = split_preferred(p), triangle = triangle_of(p);
+    const long long total = ((long long)p.Nq + 63) / 64 * p.batch;
+    if (total <= 256 && (p.Nq > 64 ? p.Nk >= 96 : split)) return p.D <= 64 && p.Nk >= 2048 && p.batch <= 128 ? FORM_Q64_X4 : FORM_Q64_X2;
+    if (p.D == 64 && triangle && (total <= 512 ? p.Nk >= 1280 : total <= 768 && p.Nk >= 1536 && p.Nk < 3072)) return FORM_Q64_X2;
+    if (p.D == 32 && p.Nk >= 1024 && (total <= 768 || (triangle && total <= 1024 && p.Nk >= 3072))) return FORM_Q64_X2;
+    return split ? FORM_Q128_X2 : FORM_Q128;
+}
+
+// force_cfg: one of the forms (the split ones: no bias, alpha > 0), otherwise by the rule.
 hipError_t launch_attention_mfma(const AttnProblem& p, hipStream_t stream, int force_cfg, const char** name) {
     const bool can = !p.bias && p.alpha > 0.0f;
-    const bool split = can && (force_cfg == 2 || (force_cfg != 1 && split_preferred(p)));
-    return p.dtype == DT_BF16 ? launch_t<bf16_t>(p, stream, split, name) : launch_t<f16_t>(p, stream, split, name);
+    int form = FORM_Q128;
+    if (can) form = force_cfg >= FORM_Q128 && force_cfg <= (p.D == 128 ? FORM_Q64_X2 : FORM_Q64_X4) ? force_cfg : attention_form(p);
+    const hipError_t e = p.dtype == DT_BF16 ? launch_t<bf16_t>(p, stream, form, name) : launch_t<f16_t>(p, stream, form, name);
+    // (short contexts, which the forms of 128 queries do not split, go by a name of their own: 128 keys at a time)
+    if (form == FORM_Q64_X2 && force_cfg != FORM_Q64_X2 && !split_preferred(p)) *name = p.causal ? "attn_mfma_q64_kv128_causal" : "attn_mfma_q64_kv128";
+    return e;
 }
 
 }  // namespace pbk
