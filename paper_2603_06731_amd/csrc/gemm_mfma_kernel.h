@@ -581,6 +581,7 @@ struct EpiCtx {
                             (((uintptr_t)p.C + (uintptr_t)c_batch) % 16 == 0);
 #pragma unroll
         for (int j = 0; j < FN; ++j) {
+            if (col0 + j * RB >= p.N) break;        // (wave-uniform)
 #pragma unroll
             for (int g = 0; g < G; ++g) {
                 const int lcol = lcol_of(j, g);
@@ -762,7 +763,9 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
     const int t = threadIdx.x;
     const int lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int wm = wave / WN, wn = wave % WN;
+    // (IDLE: the second row of waves starts in the middle, so that the waves of any half of the columns are spread over all four SIMDs)
+    constexpr bool IDLE = BN == 128 && WM == 2 && WN == 4;
+    const int wm = wave / WN, wn = IDLE ? (wave + wm * (WN / 2)) % WN : wave % WN;
 
     int b, tile_m, tile_n;
     map_tile(tmap, blockIdx.x, b, tile_m, tile_n);
@@ -790,6 +793,9 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
         tap_w = ct.nw; tap_dh = tmap.h.d; tap_dw = tmap.w.d;
     }
     const int m0 = tile_m * BM, n0 = tile_n * BN;
+    // A wave without a column of C (up to 64 columns: half of the waves) fetches its share of the tiles and leaves the matrix and vector units to
+    // the others.
+    const bool idle = IDLE && n0 + wn * WTN >= p.N;
     constexpr bool INT8 = E8 && CH == 1;
     QuantColumn qcol;                       // of column n0 + t, for the epilogue: on its way while the k loop runs
     if constexpr (INT8) qcol.load(p, n0 + (t < BN ? t : 0));
@@ -1102,7 +1108,20 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
         }
     };
 
-    if constexpr (!S16) {
+    auto idle_tile = [&](int, int, bool have_next, auto newer_tag, int newer_rt, auto spread_tag, auto) {
+        constexpr int NEWER = decltype(newer_tag)::value;
+        if (decltype(spread_tag)::value) {
+#pragma unroll
+            for (int r = 0; r < LOADS; ++r) issue_piece(r, TailNo{});
+        }
+        if (!have_next) return;
+        if (NEWER >= 0) wait_vmcnt<(NEWER >= 0 ? NEWER : 0) * LOADS>();
+        else wait_newer(newer_rt);
+        __syncthreads();
+    };
+    if (IDLE && idle) {
+        main_loop([]() {}, idle_tile, BoolTag<false>{});
+    } else if constexpr (!S16) {
         // one fragment: A rows block i, B columns block j of k16 step ks
         auto read_a1 = [&](const char* sa, int ks, int i) -> Frag<CH> {
             Frag<CH> f;
@@ -1901,6 +1920,7 @@ __global__ __launch_bounds__(WM * WN * 64, (OCC * WM * WN + 3) / 4) void gemm_mf
     // holds what, so that the global stores are 16 bytes per lane along rows:
     // every store instruction writes whole 128-byte (or longer) row segments.
     __syncthreads();                           // all waves are done reading the last stage
+    if (IDLE && idle && !INT8) return;         // (int8 codes: its part of the tile's stores)
     // The epilogue reads the problem from the kernel's argument block again.  Held in scalar registers through the k loop, what only
     // the epilogue needs spilled others to vector lanes (a transposed convolution's epilogue had 10000 such moves, over all its forms).
     auto args = __builtin_amdgcn_kernarg_segment_ptr();
