@@ -47,10 +47,10 @@ bool mfma_preferred(const Problem& p) {
 }
 
 // 128 x 128 tiles: with at most one per compute unit (256), the four-stage ring (three k-tiles in flight) covers the memory latency
-// that two workgroups per unit hide from each other otherwise: bf16 2048 x 2048 x 4096 36.2 against 52.2 us, 577 x 4096 x 1024
-// 11.7 against 16.0, FP8 512 x 4096 x 4096 16.1 against 27.5.  Beyond one round two workgroups share a unit (4 x 32 x 28 x 28
-// rows of a transposed convolution, 784 tiles: 52.8 against 79.2 us).
-// Filling the deeper ring costs more than it gives
+// that two workgroups per unit hide from each other otherwise: bf16 2048 x 2048 x 4096 34.4 against 49.4 us, 577 x 4096 x 1024
+// 11.1 against 15.0, FP8 512 x 4096 x 4096 15.3 against 26.1.  Beyond one round two workgroups share a unit (4 x 32 x 28 x 28
+// rows of a transposed convolution, 784 tiles: 42.4 against 56.1 us).
+// Filling the deeper ring costs more than it gives (figures of four waves per tile)
 // - in a convolution whose k-tiles span taps, so that every address is divided out, up to some eight k-tiles (3 x 3, bf16 32 -> 64, five:
 //   12.5 against 12.1 us; int8 64 -> 128, five: 25.0 against 24.4; bf16 96 -> 128, fourteen: 4 % ahead);
 // - in a 16-bit product of three or four k-tiles up to some 160 tiles (577 x 4096 x 256: 7.4 against 7.2 us; 1536 x 2048 x 256,

@@ -9,7 +9,7 @@ hipError_t launch_mfma_int8(const Problem& p, hipStream_t stream, int cfg, int g
     const Problem q = to_k_units(p);
     switch (cfg) {
     case 0: return launch_typed_modes<int8_t, bf16_t, 128, 256, 32, 1, 4, 3, 2>(q, stream, group_m);
-    // (eight waves, as for the 16-bit types: 32 x 28 x 28 x 128 -> 128, 3 x 3, with batch norm 15.9 -> 12.6 us, 64 x 56 x 56 x 64 -> 64, 1 x 1, 35.3 -> 29.6,
+    // (eight waves, as for the 16-bit types: 32 x 28 x 28 x 128 -> 128, 3 x 3, with batch norm 15.9 -> 12.6 us, 64 x 56 x 56 x 64 -> 64, 1 x 1, 35.3 -> 29.6 (25.7 since waves without columns only fetch),
     // 2 x 14 x 14 x 64 -> 64, 1 x 1, 9.5 -> 7.0: the epilogue's chains of 32-bit operations fill each other's waits too)
     case 1: return launch_typed_modes<int8_t, bf16_t, 128, 128, 64, 2, 4, 2, 2>(q, stream, group_m);
     case 2: return launch_typed_modes<int8_t, bf16_t, 128, 128, 64, 2, 4, 4, 1>(q, stream, group_m);

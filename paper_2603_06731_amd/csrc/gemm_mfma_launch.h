@@ -182,7 +182,7 @@ hipError_t launch_config(const Problem& p, hipStream_t stream, int cfg, int grou
     // 128 x 128 tiles on eight waves of 64 x 32: two waves per SIMD fill each other's waits for LDS, barriers and address code where one
     // workgroup has a compute unit, four where two have it.  With four waves of 64 x 64 on 32 x 32 blocks, before and after: 2048 x 2048 x 4096
     // 36.7 and 34.4 us, 2048 x 2048 x 256 8.8 and 7.7, 32 x 28 x 28 x 128 -> 128, 3 x 3, 16.7 and 14.4, 16 x 56 x 56 x 96 -> 64, 3 x 3 (two per unit), 22.1
-    // and 18.1; 32 x 32 blocks on eight waves: 36.7, 7.8, 14.9, 21.2.  K-tiles of 32 in four stages for two per unit: 17.9 there, 8 to 25 % behind from
+    // and 18.1 (16.4 since waves without columns only fetch); 32 x 32 blocks on eight waves: 36.7, 7.8, 14.9, 21.2.  K-tiles of 32 in four stages for two per unit: 17.9 there, 8 to 25 % behind from
     // K = 1024 on (rows of 64 bytes).
     PBK_CASE(1, 128, 128, 64, 2, 4, 2, 2, 16)
     PBK_CASE(2, 128, 128, 64, 2, 4, 4, 1, 16)

@@ -9,7 +9,7 @@
 // What bounds it: the chain of rounds of a workgroup that is alone on its compute unit (N = 1024: 64 x 64 tiles 5.4 us and
 // 0.47 us per round, 32 x 64 tiles 4.2 and 0.34, with 32 workgroups on the chip as with 256); with two on a unit, its load
 // path, 70 to 84 GB/s.  577 x 1024 x 4096 with bias and residual (304 tiles of 32 x 64, two on 48 of the units): 48.6 us with
-// 128 x 128 tiles (40 of them), 22.0 here.  Reading the next round's fragments under this
+// 128 x 128 tiles (40 of them), 20.1 here with 64 x 64 tiles.  Reading the next round's fragments under this
 // round's MFMAs, with loads issued between them, was 10 % slower (its ring has one stage less in flight).
 //
 // LDS images: k-major operands (A, B with trans_b) [rows][128 k], 16-byte chunk index XORed with row % 16; row-major B
