@@ -360,13 +360,13 @@ static int decode_split(const AttnProblem& p) { return p.batch > 128 ? 1 : p.bat
 // each (16 entries, context 8192, D = 128, operands from memory: 33.3 us with 3 parts, 22.2 with 6, 19.4 with 10, 20.1 with 12, 21.0 with
 // 16; context 2048: 13.1 with 2, 10.6 with 4, 10.1 with 6, 10.6 with 8).  The meeting costs some 3 us, which a short context
 // does not give back, nor do two parts a middling one.  Unsplit first:
-// - D = 128: 16 x 1024: 7.6 against 8.6, x 2048: 11.4 against 10.1; 64 x 2048: 19.0 against 17.6; 96 x 2048: 22.3 against 23.0, x 4096: 41.1
+// - D = 128: 16 x 1024: 7.6 against 8.6, x 2048: 11.4 against 10.1; 64 x 2048: 19.0 against 17.6, 52 x 1932: 12.5 against 13.0; 96 x 2048: 22.3 against 23.0, x 4096: 41.1
 //   against 40.2; 128 x 8192: 90 against 96;
 // - D = 64: 16 x 2048: 8.5 against 8.7, x 4096: 17.5 against 10.3; 96 x 4096: 24.8 against 22.3; 128 x 8192: 49.5 and 49.5;
 // - D = 32: 16 x 3072: 7.7 against 8.0, x 4096: 9.0 against 7.9; 96 x 4096: 15.0 against 13.4.
 static int decode_parts(const AttnProblem& p, int force) {
     if ((force > 0 && force < 8) || p.batch > 96) return 1;
-    const int least = p.batch > 64 ? 4096 : p.D == 128 ? 1536 : p.D == 64 ? 2560 : 3584;
+    const int least = p.batch > 64 ? 4096 : p.D == 128 ? (p.batch > 32 ? 2048 : 1536) : p.D == 64 ? 2560 : 3584;
     if (force != 8 && p.Nk < least) return 1;
     const int most = force == 8 ? (p.Nk + DEC_KB - 1) / DEC_KB : p.Nk / 384;        // (chosen by hand: a step of keys is enough)
     int parts = 192 / p.batch;

@@ -408,7 +408,8 @@ bool mfma_tile64_preferred(const Problem& p) {
 // - the parts' meeting takes some 3 us, which short contractions do not give back: 128 x 1024 x 1024: 6.4 and 6.9, 20 x 1024 x 1024: 6.3 and
 //   6.3, 376 x 576 x 1856: 8.4 and 8.2; a convolution, whose rounds take longer, 784 x 128 x 1152: 8.0 and 7.6;
 // - up to 16 rows against ksplit: 8 x 1024 x 4096: 7.0 and 8.0, 14 x 1472 x 6144: 13.8 and 9.2, 16 x 4096 x 4096: 13.2 and 10.3, 8 x 1024 x
-//   16384: 33.6 and 12.5, but 6 x 3456 x 2368: 6.7 and 7.9;
+//   16384: 33.6 and 12.5, but 6 x 3456 x 2368: 6.7 and 7.9; with a row-major B of many columns its workgroups read at the rate of the memory
+//   already: 1 x 4736 x 4672 10.1 and 11.4, 4 x 8192 x 4096 14.7 and 15.1 (8 x 4096 x 4096 12.0 and 10.5, 16 x 8192 x 4096 16.9 and 15.4);
 // - more tiles: 1024 x 320 x 4096, 160 tiles: 14.2 and 13.8, 1024 x 480 x 4096: 14.9 and 15.8.
 static int tile64_parts(const Problem& p, bool forced) {
     const long long tiles = (long long)((p.M + 31) / 32) * ((p.N + 63) / 64) * p.batch;
@@ -416,6 +417,7 @@ static int tile64_parts(const Problem& p, bool forced) {
     if (tiles > 128) return 1;
     if (!forced && rounds < (p.is_conv ? 9 : 12)) return 1;
     if (!forced && p.M <= 16 && !p.is_conv && (p.K < 4096 || (int64_t)p.N * p.K < (p.trans_b ? 4000000 : 6000000))) return 1;
+    if (!forced && p.M <= 8 && p.N > 4096 && !p.is_conv && !p.trans_b) return 1;
     int parts = (int)((192 + tiles / 2) / tiles);
     const int most = forced ? rounds : rounds / 4;
     parts = parts < 8 ? parts : 8;
