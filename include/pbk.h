@@ -314,7 +314,8 @@ const char* pbk_last_kernel(void);
  *   "mfma"        the matrix-unit path with its automatic tile choice, "mfma:<id>" one tile configuration (one that is
  *                 not built for the operands: the automatic choice; operands that the direct-to-LDS kernel
  *                 cannot take go to the gathering matrix-unit kernel instead);
- *   "gather"      that kernel: "gather:0" with 128-row tiles, "gather:1" with 64-row tiles;
+ *   "gather"      that kernel: "gather:0" with 128-row tiles, "gather:1" with 64-row tiles, "gather:2" and "gather:3" the same with the 64-bit
+ *                 addresses that convolutions of image tensors or weights from 2 GiB on take;
  *   "small"       the fp32 kernel that loads its operands straight into registers;
  *   "bstat"       the B-stationary kernel for short contractions (K <= 256) over many rows;
  *   "ksplit"      a few rows, k split over the waves: "ksplit:0" 64 columns per workgroup (32 where a row-major B has no aligned

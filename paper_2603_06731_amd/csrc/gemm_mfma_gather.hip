@@ -77,7 +77,7 @@ __device__ __forceinline__ int4v piece_fix(int4v v, int meta) {
     return int4v{keep(w0, 0), keep(w1, 1), keep(w2, 2), keep(w3, 3)};
 }
 
-// FAST (convolutions whose image tensor and weights are below 2 GiB each): the k-tiles before the careful ones are fetched with 32-bit
+// FAST (convolutions whose image tensor and weights are below 2 GiB each; the others work out 64-bit addresses for every piece): the k-tiles before the careful ones are fetched with 32-bit
 // offsets that only ever grow by constants from one k-tile to the next; what must not be read has the out-of-range offset, for
 // which a buffer load gives zeros.  (With a tap worked out by multiplication, 64-bit addresses and the tests of a piece joined by && for
 // every piece of every k-tile, the address code took longer than the loads: 8 x 44 x 44 x 127 -> 512, 3 x 3, stride 2: 25.4 against 24.0 us.)
@@ -212,10 +212,14 @@ __global__ __launch_bounds__(DEEP ? 512 : 256, 2) void gemm_mfma_gather_kernel(P
             b_ok[i] = n0 + b_chunk * 8 < p.N;
             // (a piece beyond N reads column N - 1 onwards: it stays inside B wherever the careful path is not taken)
             b_cur[i] = Bbase + (int64_t)(b_ok[i] ? n0 + b_chunk * 8 : p.N - 1) * 2;
-            if (CONV) { b_tap[i] = (kt0 * GBK + b_row[i]) / Cp; b_c[i] = kt0 * GBK + b_row[i] - b_tap[i] * Cp; }
-            if constexpr (FAST)
-                b_off[i] = (unsigned)((b_tap[i] * p.conv.Cin + b_c[i]) * (int)p.ldb * 2) + (unsigned)((b_ok[i] ? n0 + b_chunk * 8 : p.N - 1) * 2);
-            else b_cur[i] += ((int64_t)kt0 * GBK + b_row[i]) * p.ldb * 2;
+            if constexpr (CONV) {        // (b_cur stays in row 0: the padded K axis gives the row)
+                b_tap[i] = (kt0 * GBK + b_row[i]) / Cp;
+                b_c[i] = kt0 * GBK + b_row[i] - b_tap[i] * Cp;
+                if constexpr (FAST)
+                    b_off[i] = (unsigned)((b_tap[i] * p.conv.Cin + b_c[i]) * (int)p.ldb * 2) + (unsigned)((b_ok[i] ? n0 + b_chunk * 8 : p.N - 1) * 2);
+            } else {
+                b_cur[i] += ((int64_t)kt0 * GBK + b_row[i]) * p.ldb * 2;
+            }
         }
     }
     const int64_t b_step = TRANS_B ? GBK * 2 : (int64_t)GBK * p.ldb * 2;     // dense: B's advance per k-tile
@@ -545,10 +549,11 @@ bool gather_fast_offsets(const Problem& p) {
     return (int64_t)(p.M / (p.conv.OH * p.conv.OW)) * p.conv.H * row < lim && ((int64_t)p.K + 256) * p.ldb * 2 < lim;
 }
 
+// fast: a convolution with 32-bit offsets
 template <typename T, int GBM, bool DEEP, bool SPLIT = false>
-hipError_t launch_gather_type(const Problem& p, hipStream_t stream, int parts = 1, Scratch scratch = Scratch{}) {
-    if (p.is_conv) return gather_fast_offsets(p) ? launch_gather_mode<T, MODE_CONV, GBM, true, DEEP, SPLIT>(p, stream, parts, scratch)
-                                                 : launch_gather_mode<T, MODE_CONV, GBM, false, DEEP, SPLIT>(p, stream, parts, scratch);
+hipError_t launch_gather_type(const Problem& p, hipStream_t stream, bool fast, int parts = 1, Scratch scratch = Scratch{}) {
+    if (p.is_conv) return fast ? launch_gather_mode<T, MODE_CONV, GBM, true, DEEP, SPLIT>(p, stream, parts, scratch)
+                               : launch_gather_mode<T, MODE_CONV, GBM, false, DEEP, SPLIT>(p, stream, parts, scratch);
     if (p.trans_b) return launch_gather_mode<T, MODE_TRANS_B, GBM, false, DEEP, SPLIT>(p, stream, parts, scratch);
     return launch_gather_mode<T, MODE_DENSE, GBM, false, DEEP, SPLIT>(p, stream, parts, scratch);
 }
@@ -614,26 +619,29 @@ static int gather_parts(const Problem& p) {
     return parts;
 }
 
-// force_cfg: 0 the 128-row tiles, 1 the 64-row ones, otherwise by the rule.
+// force_cfg: 0 the 128-row tiles, 1 the 64-row ones, 2 and 3 the same with a convolution's 64-bit addresses, otherwise by the rule.
 hipError_t launch_mfma_gather(const Problem& p, hipStream_t stream, int force_cfg, const char** name) {
-    const bool bf16 = p.in_dtype == DT_BF16;
+    const bool bf16 = p.in_dtype == DT_BF16, fast = p.is_conv && force_cfg < 2 && gather_fast_offsets(p);
+    const bool wide = p.is_conv && !fast;          // 64-bit addresses, by a name of their own
+    if (force_cfg >= 2) force_cfg -= 2;
     if (force_cfg == 1 || (force_cfg != 0 && gather_rows64(p))) {
         if (!gather_deep(p)) {
-            *name = "mfma16_gather_64x128x32_w2x2";
-            return bf16 ? launch_gather_type<bf16_t, 64, false>(p, stream) : launch_gather_type<f16_t, 64, false>(p, stream);
+            *name = wide ? "mfma16_gather_64x128x32_w2x2_a64" : "mfma16_gather_64x128x32_w2x2";
+            return bf16 ? launch_gather_type<bf16_t, 64, false>(p, stream, fast) : launch_gather_type<f16_t, 64, false>(p, stream, fast);
         }
         const int parts = gather_parts(p);
         int dev = 0;
         Scratch scratch;
         if (parts > 1 && hipGetDevice(&dev) == hipSuccess && stream_scratch(dev, stream, &scratch)) {
-            *name = "mfma16_gather_64x128x64_w4x2_split";
-            return bf16 ? launch_gather_type<bf16_t, 64, true, true>(p, stream, parts, scratch) : launch_gather_type<f16_t, 64, true, true>(p, stream, parts, scratch);
+            *name = wide ? "mfma16_gather_64x128x64_w4x2_a64_split" : "mfma16_gather_64x128x64_w4x2_split";
+            return bf16 ? launch_gather_type<bf16_t, 64, true, true>(p, stream, fast, parts, scratch)
+                        : launch_gather_type<f16_t, 64, true, true>(p, stream, fast, parts, scratch);
         }
-        *name = "mfma16_gather_64x128x64_w4x2";
-        return bf16 ? launch_gather_type<bf16_t, 64, true>(p, stream) : launch_gather_type<f16_t, 64, true>(p, stream);
+        *name = wide ? "mfma16_gather_64x128x64_w4x2_a64" : "mfma16_gather_64x128x64_w4x2";
+        return bf16 ? launch_gather_type<bf16_t, 64, true>(p, stream, fast) : launch_gather_type<f16_t, 64, true>(p, stream, fast);
     }
-    *name = "mfma16_gather_128x128x32_w2x2";
-    return bf16 ? launch_gather_type<bf16_t, 128, false>(p, stream) : launch_gather_type<f16_t, 128, false>(p, stream);
+    *name = wide ? "mfma16_gather_128x128x32_w2x2_a64" : "mfma16_gather_128x128x32_w2x2";
+    return bf16 ? launch_gather_type<bf16_t, 128, false>(p, stream, fast) : launch_gather_type<f16_t, 128, false>(p, stream, fast);
 }
 
 }  // namespace pbk
