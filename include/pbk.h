@@ -18,8 +18,10 @@
  *    several workgroups, which exchange partial results through scratch memory
  *    of the library's own: 8 MiB per stream, obtained at the stream's first
  *    such call, for up to 32 streams of a device, kept until
- *    pbk_release_scratch().  Where there is none (the stream is being captured,
- *    more streams, no memory) the call runs without a split.
+ *    pbk_release_scratch(); a further stream takes over the memory of the one
+ *    that has been idle longest.  Where there is none (the stream is being
+ *    captured, 32 others are at work with theirs, no memory) the call runs
+ *    without a split.
  *  - Calls only enqueue work on `stream` (a hipStream_t; NULL = the default
  *    stream) and return; ordering is stream ordering.
  *  - Matrices are row-major with leading dimensions in ELEMENTS.

@@ -298,9 +298,9 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void attention_decode_kernel(AttnP
     }
 }
 
-// parts: workgroups that share an entry's keys (1: none, and no scratch memory)
+// parts: workgroups that share an entry's keys, in scratch memory (1: none, no scratch memory)
 template <typename T, int D, int DV, int NW, bool SPLIT = false>
-hipError_t launch_split(const AttnProblem& p, hipStream_t stream, int parts = 1, Scratch scratch = Scratch{}) {
+hipError_t launch_split(const AttnProblem& p, hipStream_t stream, int parts = 1, const ScratchUse* use = nullptr) {
     constexpr int LDS_BYTES = NW * DEC_KB * (D + DV) * 2;
     const void* kern = p.causal ? (const void*)attention_decode_kernel<T, D, DV, NW, true, SPLIT>
                                 : (const void*)attention_decode_kernel<T, D, DV, NW, false, SPLIT>;
@@ -322,8 +322,9 @@ hipError_t launch_split(const AttnProblem& p, hipStream_t stream, int parts = 1,
     if (n <= 0 || n > 0x7FFFFFFFLL) return hipErrorInvalidValue;
     int total = (int)n;
     AttnProblem pa = p;
+    Scratch scratch = use ? use->mem() : Scratch{};
     void* args[] = {&pa, &total, &xcds, &parts, &scratch};
-    return hipLaunchKernel(kern, dim3((unsigned)total), dim3(NW * 64), args, LDS_BYTES, stream);
+    return launch_with(use, kern, dim3((unsigned)total), dim3(NW * 64), args, LDS_BYTES, stream);
 }
 
 template <typename T>
@@ -339,11 +340,11 @@ hipError_t launch_type(const AttnProblem& p, hipStream_t stream, int split) {
 }
 
 template <typename T>
-hipError_t launch_keys(const AttnProblem& p, hipStream_t stream, int parts, Scratch scratch) {
+hipError_t launch_keys(const AttnProblem& p, hipStream_t stream, int parts, const ScratchUse* use) {
     switch (p.D) {
-    case 32: return launch_split<T, 32, 32, 16, true>(p, stream, parts, scratch);
-    case 64: return launch_split<T, 64, 64, 16, true>(p, stream, parts, scratch);
-    case 128: return launch_split<T, 128, 128, 8, true>(p, stream, parts, scratch);
+    case 32: return launch_split<T, 32, 32, 16, true>(p, stream, parts, use);
+    case 64: return launch_split<T, 64, 64, 16, true>(p, stream, parts, use);
+    case 128: return launch_split<T, 128, 128, 8, true>(p, stream, parts, use);
     default: return hipErrorInvalidValue;
     }
 }
@@ -403,11 +404,12 @@ bool attention_decode_preferred(const AttnProblem& p) {
 hipError_t launch_attention_decode(const AttnProblem& p, hipStream_t stream, int force_split, const char** name) {
     const int parts = decode_parts(p, force_split);
     int dev = 0;
-    Scratch scratch;
     static_assert(96 <= kScratchTickets && 192 * (128 * 16 + 64) * 4 <= kScratchBytes, "what decode_parts asks for at most");
-    if (parts > 1 && hipGetDevice(&dev) == hipSuccess && stream_scratch(dev, stream, &scratch)) {
-        *name = p.causal ? "attn_mfma_decode_q16_kv32_split_causal" : "attn_mfma_decode_q16_kv32_split";
-        return p.dtype == DT_BF16 ? launch_keys<bf16_t>(p, stream, parts, scratch) : launch_keys<f16_t>(p, stream, parts, scratch);
+    if (parts > 1 && hipGetDevice(&dev) == hipSuccess) {
+        if (const ScratchUse use(dev, stream); use) {
+            *name = p.causal ? "attn_mfma_decode_q16_kv32_split_causal" : "attn_mfma_decode_q16_kv32_split";
+            return p.dtype == DT_BF16 ? launch_keys<bf16_t>(p, stream, parts, &use) : launch_keys<f16_t>(p, stream, parts, &use);
+        }
     }
     const int split = force_split > 0 && force_split < 8 ? force_split : decode_split(p);
     static const char* const names[3][2] = {{"attn_mfma_decode_q16_kv32_c1", "attn_mfma_decode_q16_kv32_c1_causal"},

@@ -512,9 +512,9 @@ __global__ __launch_bounds__(DEEP ? 512 : 256, 2) void gemm_mfma_gather_kernel(P
     }
 }
 
-// parts: workgroups that share a tile's k-tiles (1: none, and no scratch memory)
+// parts: workgroups that share a tile's k-tiles, in scratch memory (1: none, no scratch memory)
 template <typename T, int MODE, int GBM, bool FAST, bool DEEP, bool SPLIT = false>
-hipError_t launch_gather_mode(const Problem& p, hipStream_t stream, int parts = 1, Scratch scratch = Scratch{}) {
+hipError_t launch_gather_mode(const Problem& p, hipStream_t stream, int parts = 1, const ScratchUse* use = nullptr) {
     constexpr int GBK = DEEP ? 64 : 32, THREADS = DEEP ? 512 : 256;
     constexpr int LDS_BYTES = 2 * (GBM + GBN) * GBK * 2;
     static_assert(LDS_BYTES <= 64 * 1024, "launched without a raised limit");
@@ -539,8 +539,9 @@ hipError_t launch_gather_mode(const Problem& p, hipStream_t stream, int parts = 
     tm.group_m = 8;
     tm.xcds = ds.xcds;
     Problem pa = p;
+    Scratch scratch = use ? use->mem() : Scratch{};
     void* args[] = {&pa, &tm, &parts, &scratch};
-    return hipLaunchKernel((const void*)kern, dim3((unsigned)total), dim3(THREADS), args, LDS_BYTES, stream);
+    return launch_with(use, (const void*)kern, dim3((unsigned)total), dim3(THREADS), args, LDS_BYTES, stream);
 }
 
 // Every offset of FAST, the taps of the last k-tile and what the last rows reach beyond the image included, stays below 2^31.
@@ -551,11 +552,11 @@ bool gather_fast_offsets(const Problem& p) {
 
 // fast: a convolution with 32-bit offsets
 template <typename T, int GBM, bool DEEP, bool SPLIT = false>
-hipError_t launch_gather_type(const Problem& p, hipStream_t stream, bool fast, int parts = 1, Scratch scratch = Scratch{}) {
-    if (p.is_conv) return fast ? launch_gather_mode<T, MODE_CONV, GBM, true, DEEP, SPLIT>(p, stream, parts, scratch)
-                               : launch_gather_mode<T, MODE_CONV, GBM, false, DEEP, SPLIT>(p, stream, parts, scratch);
-    if (p.trans_b) return launch_gather_mode<T, MODE_TRANS_B, GBM, false, DEEP, SPLIT>(p, stream, parts, scratch);
-    return launch_gather_mode<T, MODE_DENSE, GBM, false, DEEP, SPLIT>(p, stream, parts, scratch);
+hipError_t launch_gather_type(const Problem& p, hipStream_t stream, bool fast, int parts = 1, const ScratchUse* use = nullptr) {
+    if (p.is_conv) return fast ? launch_gather_mode<T, MODE_CONV, GBM, true, DEEP, SPLIT>(p, stream, parts, use)
+                               : launch_gather_mode<T, MODE_CONV, GBM, false, DEEP, SPLIT>(p, stream, parts, use);
+    if (p.trans_b) return launch_gather_mode<T, MODE_TRANS_B, GBM, false, DEEP, SPLIT>(p, stream, parts, use);
+    return launch_gather_mode<T, MODE_DENSE, GBM, false, DEEP, SPLIT>(p, stream, parts, use);
 }
 
 }  // namespace
@@ -631,11 +632,12 @@ hipError_t launch_mfma_gather(const Problem& p, hipStream_t stream, int force_cf
         }
         const int parts = gather_parts(p);
         int dev = 0;
-        Scratch scratch;
-        if (parts > 1 && hipGetDevice(&dev) == hipSuccess && stream_scratch(dev, stream, &scratch)) {
-            *name = wide ? "mfma16_gather_64x128x64_w4x2_a64_split" : "mfma16_gather_64x128x64_w4x2_split";
-            return bf16 ? launch_gather_type<bf16_t, 64, true, true>(p, stream, fast, parts, scratch)
-                        : launch_gather_type<f16_t, 64, true, true>(p, stream, fast, parts, scratch);
+        if (parts > 1 && hipGetDevice(&dev) == hipSuccess) {
+            if (const ScratchUse use(dev, stream); use) {
+                *name = wide ? "mfma16_gather_64x128x64_w4x2_a64_split" : "mfma16_gather_64x128x64_w4x2_split";
+                return bf16 ? launch_gather_type<bf16_t, 64, true, true>(p, stream, fast, parts, &use)
+                            : launch_gather_type<f16_t, 64, true, true>(p, stream, fast, parts, &use);
+            }
         }
         *name = wide ? "mfma16_gather_64x128x64_w4x2_a64" : "mfma16_gather_64x128x64_w4x2";
         return bf16 ? launch_gather_type<bf16_t, 64, true>(p, stream, fast) : launch_gather_type<f16_t, 64, true>(p, stream, fast);

@@ -304,9 +304,9 @@ __global__ __launch_bounds__(T64_NW * 64, 1) void gemm_mfma_tile64_kernel(Proble
     }
 }
 
-// parts: workgroups that share a tile's rounds (1: none, and no scratch memory)
+// parts: workgroups that share a tile's rounds, in scratch memory (1: none, no scratch memory)
 template <typename T, int MODE, int BM, int NSTAGE, bool SPLIT>
-hipError_t launch_tile(const Problem& p, hipStream_t stream, int parts, Scratch scratch) {
+hipError_t launch_tile(const Problem& p, hipStream_t stream, int parts, const ScratchUse* use) {
     constexpr int LDS_BYTES = NSTAGE * (BM + T64_BN) * T64_BK * 2;
     auto kern = gemm_mfma_tile64_kernel<T, MODE, BM, NSTAGE, SPLIT>;
     static std::atomic<unsigned> attr_done{0};      // bit per device
@@ -334,17 +334,18 @@ hipError_t launch_tile(const Problem& p, hipStream_t stream, int parts, Scratch 
     auto magic = [](int d) { return d > 1 ? (unsigned)(((1ull << 32) + d - 1) / d) : 0u; };
     unsigned cin_magic = p.is_conv ? magic(p.conv.Cin) : 0, kw_magic = p.is_conv ? magic(p.conv.KW) : 0;
     Problem pa = p;
+    Scratch scratch = use ? use->mem() : Scratch{};
     void* args[] = {&pa, &tm, &cin_magic, &kw_magic, &parts, &scratch};
-    return hipLaunchKernel((const void*)kern, dim3((unsigned)total), dim3(T64_NW * 64), args, LDS_BYTES, stream);
+    return launch_with(use, (const void*)kern, dim3((unsigned)total), dim3(T64_NW * 64), args, LDS_BYTES, stream);
 }
 
 constexpr int kDeepK = 16;               // tile64_choice only
 
 template <typename T, int BM, int NSTAGE, bool SPLIT = false>
-hipError_t launch_mode(const Problem& p, hipStream_t stream, int parts = 1, Scratch scratch = Scratch{}) {
-    if (p.is_conv) return launch_tile<T, MODE_CONV, BM, NSTAGE, SPLIT>(p, stream, parts, scratch);
-    return p.trans_b ? launch_tile<T, MODE_TRANS_B, BM, NSTAGE, SPLIT>(p, stream, parts, scratch)
-                     : launch_tile<T, MODE_DENSE, BM, NSTAGE, SPLIT>(p, stream, parts, scratch);
+hipError_t launch_mode(const Problem& p, hipStream_t stream, int parts = 1, const ScratchUse* use = nullptr) {
+    if (p.is_conv) return launch_tile<T, MODE_CONV, BM, NSTAGE, SPLIT>(p, stream, parts, use);
+    return p.trans_b ? launch_tile<T, MODE_TRANS_B, BM, NSTAGE, SPLIT>(p, stream, parts, use)
+                     : launch_tile<T, MODE_DENSE, BM, NSTAGE, SPLIT>(p, stream, parts, use);
 }
 
 template <typename T>
@@ -430,10 +431,11 @@ bool launch_mfma_tile64_split(const Problem& p, hipStream_t stream, bool forced,
     static_assert(128 <= kScratchTickets && 256 * 32 * T64_BN * 4 <= kScratchBytes, "up to 192 + 128 / 2 parts");
     const int parts = tile64_parts(p, forced);
     int dev = 0;
-    Scratch scratch;
-    if (parts <= 1 || hipGetDevice(&dev) != hipSuccess || !stream_scratch(dev, stream, &scratch)) return false;
+    if (parts <= 1 || hipGetDevice(&dev) != hipSuccess) return false;
+    const ScratchUse use(dev, stream);
+    if (!use) return false;
     *name = "mfma16_tile64_32x64_s3_split";
-    *e = p.in_dtype == DT_BF16 ? launch_mode<bf16_t, 32, 3, true>(p, stream, parts, scratch) : launch_mode<f16_t, 32, 3, true>(p, stream, parts, scratch);
+    *e = p.in_dtype == DT_BF16 ? launch_mode<bf16_t, 32, 3, true>(p, stream, parts, &use) : launch_mode<f16_t, 32, 3, true>(p, stream, parts, &use);
     return true;
 }
 

@@ -1,55 +1,105 @@
 // Scratch memory per stream (scratch.h).
+#include <atomic>
 #include <mutex>
+#include <hip/hip_ext.h>
 #include "../../include/pbk.h"
 #include "scratch.h"
 
 namespace pbk {
+
+struct ScratchEntry {
+    hipStream_t stream;
+    char* base;                     // tickets, then data
+    unsigned long long id;          // of the allocation
+    hipEvent_t done;                // of the last launch that uses the memory
+    std::atomic<int> users;         // calls between finding the entry and their launch
+    unsigned long long last;        // when it was found last
+};
+
 namespace {
 
 constexpr int kDevices = 32;
 constexpr size_t kTicketBytes = (size_t)kScratchTickets * sizeof(unsigned);
 
-struct Entry { hipStream_t stream; char* base; };     // tickets, then data
-struct Pool { Entry entries[kScratchStreams]; int n; };
+struct Pool { ScratchEntry entries[kScratchStreams]; int n; unsigned long long uses; };
 
 std::mutex g_mutex;
 Pool g_pools[kDevices];
 
-// Allocating while some other thread captures a stream would disturb that capture.
+// Allocating, or asking for an event, while some other thread captures a stream would disturb that capture.
 struct RelaxedCapture {
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
     bool ok = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
     ~RelaxedCapture() { if (ok) (void)hipThreadExchangeStreamCaptureMode(&mode); }
 };
 
+bool ok(hipError_t e) {
+    if (e == hipSuccess) return true;
+    (void)hipGetLastError();
+    return false;
+}
+
+unsigned long long allocation_id(char* base) {
+    unsigned long long id = 0;
+    return ok(hipPointerGetAttribute(&id, HIP_POINTER_ATTRIBUTE_BUFFER_ID, base)) ? id : 0;
+}
+
+// An entry for a stream that has none.
+ScratchEntry* obtain(Pool& pool, hipStream_t stream) {
+    RelaxedCapture relaxed;
+    ScratchEntry* e = nullptr;
+    if (pool.n == kScratchStreams) {
+        // (never one that is at work: this stream would wait for a stranger, which might wait for what this one does next)
+        for (ScratchEntry& x : pool.entries)
+            if (x.users.load() == 0 && (!e || x.last < e->last) && ok(hipEventQuery(x.done))) e = &x;
+        if (e) e->stream = stream;
+        return e;
+    }
+    e = &pool.entries[pool.n];
+    void* base = nullptr;
+    if (!ok(hipMalloc(&base, kTicketBytes + kScratchBytes))) return nullptr;
+    e->stream = stream;
+    e->base = (char*)base;
+    e->id = allocation_id(e->base);
+    if (ok(hipEventCreateWithFlags(&e->done, hipEventDisableTiming))) {
+        if (ok(hipMemsetAsync(base, 0, kTicketBytes, stream)) && ok(hipEventRecord(e->done, stream))) {
+            ++pool.n;
+            return e;
+        }
+        (void)hipEventDestroy(e->done);
+    }
+    (void)hipFree(base);            // (waits for the clearing)
+    return nullptr;
+}
+
 }  // namespace
 
-// A stream's entry is found by its handle.  A handle comes back with another stream only after hipStreamDestroy of the first, which
-// returns when the work of that stream has ended (measured: 200 queued kernels of 55 us, 10.7 ms), so the memory is idle then.
-bool stream_scratch(int dev, hipStream_t stream, Scratch* out) {
-    if (dev < 0 || dev >= kDevices || stream == hipStreamPerThread || stream == hipStreamLegacy) return false;
+ScratchUse::ScratchUse(int dev, hipStream_t stream) {
+    if (dev < 0 || dev >= kDevices || stream == hipStreamPerThread || stream == hipStreamLegacy) return;
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &status) != hipSuccess) { (void)hipGetLastError(); return false; }
-    if (status != hipStreamCaptureStatusNone) return false;
+    if (!ok(hipStreamIsCapturing(stream, &status)) || status != hipStreamCaptureStatusNone) return;
     std::lock_guard<std::mutex> lock(g_mutex);
     Pool& pool = g_pools[dev];
-    for (int i = 0; i < pool.n; ++i)
-        if (pool.entries[i].stream == stream) {
-            *out = Scratch{pool.entries[i].base + kTicketBytes, (unsigned*)pool.entries[i].base};
-            return true;
-        }
-    if (pool.n == kScratchStreams) return false;
-    RelaxedCapture relaxed;
-    void* base = nullptr;
-    if (hipMalloc(&base, kTicketBytes + kScratchBytes) != hipSuccess) { (void)hipGetLastError(); return false; }
-    if (hipMemsetAsync(base, 0, kTicketBytes, stream) != hipSuccess) {
-        (void)hipGetLastError();
-        (void)hipFree(base);
-        return false;
-    }
-    pool.entries[pool.n++] = Entry{stream, (char*)base};
-    *out = Scratch{(char*)base + kTicketBytes, (unsigned*)base};
-    return true;
+    // hipDeviceReset takes memory and events of all entries away; other memory may lie there afterwards
+    if (pool.n && allocation_id(pool.entries[0].base) != pool.entries[0].id) pool.n = 0;
+    ScratchEntry* e = nullptr;
+    for (int i = 0; i < pool.n && !e; ++i)
+        if (pool.entries[i].stream == stream) e = &pool.entries[i];
+    if (!e) e = obtain(pool, stream);
+    if (!e || !ok(hipStreamWaitEvent(stream, e->done, 0))) return;
+    e->users.fetch_add(1);
+    e->last = ++pool.uses;
+    entry = e;
+}
+
+ScratchUse::~ScratchUse() { if (entry) entry->users.fetch_sub(1); }
+
+Scratch ScratchUse::mem() const { return entry ? Scratch{entry->base + kTicketBytes, (unsigned*)entry->base} : Scratch{}; }
+hipEvent_t ScratchUse::done() const { return entry ? entry->done : nullptr; }
+
+hipError_t launch_with(const ScratchUse* use, const void* kern, dim3 grid, dim3 block, void** args, size_t lds_bytes, hipStream_t stream) {
+    if (!use || !*use) return hipLaunchKernel(kern, grid, block, args, lds_bytes, stream);
+    return hipExtLaunchKernel(kern, grid, block, args, lds_bytes, stream, nullptr, use->done(), 0);
 }
 
 }  // namespace pbk
@@ -61,8 +111,12 @@ extern "C" pbk_status pbk_release_scratch(void) {
     if (dev < 0 || dev >= kDevices) return PBK_OK;
     std::lock_guard<std::mutex> lock(g_mutex);
     Pool& pool = g_pools[dev];
+    if (pool.n && allocation_id(pool.entries[0].base) != pool.entries[0].id) pool.n = 0;
     if (pool.n && hipDeviceSynchronize() != hipSuccess) return PBK_ERR_HIP;
-    for (int i = 0; i < pool.n; ++i) (void)hipFree(pool.entries[i].base);
+    for (int i = 0; i < pool.n; ++i) {
+        (void)hipEventDestroy(pool.entries[i].done);
+        (void)hipFree(pool.entries[i].base);
+    }
     pool.n = 0;
     return PBK_OK;
 }
