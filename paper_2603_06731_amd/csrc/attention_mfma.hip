@@ -705,10 +705,7 @@ hipError_t launch_attention_mfma(const AttnProblem& p, hipStream_t stream, int f
     const bool can = !p.bias && p.alpha > 0.0f;
     int form = FORM_Q128;
     if (can) form = force_cfg >= FORM_Q128 && force_cfg <= (p.D == 128 ? FORM_Q64_X2 : FORM_Q64_X4) ? force_cfg : attention_form(p);
-    const hipError_t e = p.dtype == DT_BF16 ? launch_t<bf16_t>(p, stream, form, name) : launch_t<f16_t>(p, stream, form, name);
-    // (short contexts, which the forms of 128 queries do not split, go by a name of their own: 128 keys at a time)
-    if (form == FORM_Q64_X2 && force_cfg != FORM_Q64_X2 && !split_preferred(p)) *name = p.causal ? "attn_mfma_q64_kv128_causal" : "attn_mfma_q64_kv128";
-    return e;
+    return p.dtype == DT_BF16 ? launch_t<bf16_t>(p, stream, form, name) : launch_t<f16_t>(p, stream, form, name);
 }
 
 }  // namespace pbk

@@ -162,7 +162,7 @@ static hipError_t launch_convt(const Problem& p_in, hipStream_t stream, int forc
     p.conv.transposed = classes ? 2 : 1;
     const int cfg = classes ? (force_cfg == 1 || force_cfg == 2 ? force_cfg : square_config(p))
                             : (force_cfg == 0 || force_cfg == 1 || force_cfg == 6 ? force_cfg : wide ? 6 : 1);
-    *name = !classes ? kMfmaConfigs[cfg].name : cfg == 1 ? "mfma_128x128x64_w2x2_s2_classes" : "mfma_128x128x64_w2x2_s4_classes";
+    *name = !classes ? mfma_config_name(cfg, false) : cfg == 1 ? "mfma16_128x128x64_w2x4_s2_classes" : "mfma16_128x128x64_w2x4_s4_classes";
     const int group_m = group_m_override() > 0 ? group_m_override() : 8;
     return p.in_dtype == DT_BF16 ? launch_mfma_bf16(p, stream, cfg, group_m) : launch_mfma_f16(p, stream, cfg, group_m);
 }
@@ -187,7 +187,7 @@ hipError_t launch_mfma(const Problem& p, hipStream_t stream, int force_cfg, cons
         int c = (force_cfg == 0 || force_cfg == 1 || force_cfg == 2 || force_cfg == 4 || force_cfg == 8 || force_cfg == 9) ? force_cfg
                 : !large || (!kmajor && p.K < (p.is_conv ? 256 : 512)) ? square_config(p) : kmajor ? 9 : p.is_conv ? 0 : 4;
         if ((c == 8 || c == 9) && !kmajor) c = 4;       // the 16x16 blocks are built for k-major operands only
-        *name = kMfmaConfigs[c].name;
+        *name = mfma_config_name(c, true);
         const int gm = group_m_override() > 0 ? group_m_override() : 8;
         return launch_mfma_int8(p, stream, c, gm);
     }
@@ -214,7 +214,7 @@ hipError_t launch_mfma(const Problem& p, hipStream_t stream, int force_cfg, cons
         }
     }
     const int group_m = group_m_override() > 0 ? group_m_override() : 8;
-    *name = kMfmaConfigs[cfg].name;
+    *name = mfma_config_name(cfg, fp8);
     if (fp8) return launch_mfma_fp8(p, stream, cfg, group_m);
     return p.in_dtype == DT_BF16 ? launch_mfma_bf16(p, stream, cfg, group_m)
                                  : launch_mfma_f16(p, stream, cfg, group_m);

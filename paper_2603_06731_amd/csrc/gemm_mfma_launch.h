@@ -11,15 +11,15 @@ struct MfmaConfig {
     int id;
     int bm, bn, bk, wm, wn, stages;
     const char* name;
+    const char* name8 = nullptr;       // 8-bit types, where their blocks are others
 };
 
 // Tile configurations (the static stand-in for the paper's analytical tile
 // size model, Sec. 4.3): id -> workgroup tile and wave grid.
 static const MfmaConfig kMfmaConfigs[] = {
     {0, 128, 256, 32, 1, 4, 3, "mfma_128x256x32_w1x4_s3_occ2"},
-    // (1 and 2 go by the names they have always had, whose wave grid is the one of their first form)
-    {1, 128, 128, 64, 2, 4, 2, "mfma_128x128x64_w2x2_s2"},
-    {2, 128, 128, 64, 2, 4, 4, "mfma_128x128x64_w2x2_s4"},          // 1 with a deeper ring: at most one tile per compute unit
+    {1, 128, 128, 64, 2, 4, 2, "mfma16_128x128x64_w2x4_s2", "mfma_128x128x64_w2x4_s2"},
+    {2, 128, 128, 64, 2, 4, 4, "mfma16_128x128x64_w2x4_s4", "mfma_128x128x64_w2x4_s4"},      // 1 with a deeper ring: at most one tile per compute unit
     {3, 256, 256, 32, 2, 4, 4, "mfma_256x256x32_w2x4_s4"},          // measured and retired, not built
     {4, 256, 256, 64, 2, 4, 2, "mfma_256x256x64_w2x4_s2"},          // 8-bit types only
     {5, 256, 256, 32, 2, 4, 4, "mfma16_256x256x32_w2x4_s4"},        // 16x16x32 MFMA blocks (16-bit types)
@@ -29,6 +29,7 @@ static const MfmaConfig kMfmaConfigs[] = {
     {9, 256, 256, 32, 2, 4, 5, "mfma16_256x256x32_w2x4_a64_b6_pair"},   // as 7 with six B stages, one barrier per two k-tiles
 };
 static const int kNumMfmaConfigs = sizeof(kMfmaConfigs) / sizeof(kMfmaConfigs[0]);
+inline const char* mfma_config_name(int c, bool e8) { return e8 && kMfmaConfigs[c].name8 ? kMfmaConfigs[c].name8 : kMfmaConfigs[c].name; }
 
 // XCD (accelerator complex die, each with its own L2) and compute unit counts of a device,
 // asked once per device.  Workgroup ids are dealt round-robin to the XCDs, which the block

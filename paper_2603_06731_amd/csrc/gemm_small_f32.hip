@@ -222,11 +222,10 @@ static hipError_t launch_blocks(const Problem& p, hipStream_t stream) {
 // 800: 34 and 28; 4096: 53 and 33, K = 64: 7.5 and 7.4).
 hipError_t launch_small_f32(const Problem& p, hipStream_t stream, const char** name) {
     if (tiles16(p) <= 2400) {
-        // (beyond one tile per SIMD under a name of its own: not a small problem any more)
-        *name = tiles16(p) <= 1024 ? "small_f32_16x16_mfma4_wave_per_tile" : "direct_f32_16x16_mfma4";
+        *name = "small_f32_16x16_mfma4";
         return launch_blocks<1>(p, stream);
     }
-    *name = "direct_f32_32x32_mfma4";
+    *name = "small_f32_32x32_mfma4";
     return launch_blocks<2>(p, stream);
 }
 

@@ -71,7 +71,7 @@ def test_sizes(D, force, name, dtype, causal):
 
 
 @pytest.mark.parametrize("batch,Nq,Nk,D,causal,name", [
-    (4, 65, 96, 64, 0, "q64_kv128"), (4, 65, 95, 64, 0, "q128_kv64_"), (4, 64, 96, 128, 0, "q128_kv64_"), (128, 128, 128, 128, 1, "q64_kv128"),
+    (4, 65, 96, 64, 0, "q64_kv64x2"), (4, 65, 95, 64, 0, "q128_kv64_"), (4, 64, 96, 128, 0, "q128_kv64_"), (128, 128, 128, 128, 1, "q64_kv64x2"),
     (129, 128, 128, 128, 1, "q128_kv64_"), (2, 64, 2048, 64, 0, "q64_kv64x4"), (2, 200, 2047, 64, 1, "q64_kv64x2"), (2, 200, 2048, 128, 1, "q64_kv64x2"),
     (16, 2048, 2048, 64, 1, "q64_kv64x2"), (16, 2048, 2048, 64, 0, "q128_kv64x2"), (25, 1280, 1280, 64, 1, "q64_kv64x2"), (25, 1279, 1279, 64, 1, "q128_kv64x2"),
     (24, 2048, 2048, 64, 1, "q64_"), (25, 2048, 2048, 64, 1, "q128_kv64_"), (48, 1024, 1024, 32, 0, "q64_"), (49, 1024, 1024, 32, 0, "q128_kv64_"),

@@ -11,14 +11,14 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("trans_b", [0, 1])
 @pytest.mark.parametrize("M,N,K,lds,kernel", [
-    (16, 16, 4096, (None, None, None), "small_f32"),           # sixteen waves
-    (33, 130, 1037, (None, None, None), "small_f32"),          # waves with unequal shares, the last one ragged
-    (520, 512, 250, (None, None, None), "direct_f32_16x16"),   # beyond one tile per SIMD
-    (768, 783, 67, (None, None, None), "direct_f32_16x16"),    # 2352 tiles: odd N, no pairs of columns
-    (785, 786, 131, (None, None, None), "direct_f32_32x32"),   # 2500: N even, rows of B only 8-byte aligned, last pair at the edge
-    (800, 770, 64, (None, 786, 772), "direct_f32_32x32"),      # one full register set, padded rows
-    (801, 801, 65, (68, 804, 803), "direct_f32_32x32"),        # everything odd
-    (1024, 1024, 128, (None, None, None), "direct_f32_32x32"),
+    (16, 16, 4096, (None, None, None), "small_f32_16x16"),           # sixteen waves
+    (33, 130, 1037, (None, None, None), "small_f32_16x16"),          # waves with unequal shares, the last one ragged
+    (520, 512, 250, (None, None, None), "small_f32_16x16"),   # beyond one tile per SIMD
+    (768, 783, 67, (None, None, None), "small_f32_16x16"),    # 2352 tiles: odd N, no pairs of columns
+    (785, 786, 131, (None, None, None), "small_f32_32x32"),   # 2500: N even, rows of B only 8-byte aligned, last pair at the edge
+    (800, 770, 64, (None, 786, 772), "small_f32_32x32"),      # one full register set, padded rows
+    (801, 801, 65, (68, 804, 803), "small_f32_32x32"),        # everything odd
+    (1024, 1024, 128, (None, None, None), "small_f32_32x32"),
     (1025, 1024, 32, (None, None, None), "mfma_f32"),          # 4160 tiles
 ])
 def test_parity_and_dispatch(M, N, K, lds, kernel, trans_b):
@@ -32,9 +32,9 @@ def test_parity_and_dispatch(M, N, K, lds, kernel, trans_b):
 
 def test_residual_and_batch():
     err, kern = run(790, 780, 40, 0, C.EPI_GELU_TANH, residual=True)
-    assert "direct_f32_32x32" in kern and err <= T.TOL_F32, (kern, err)
+    assert "small_f32_32x32" in kern and err <= T.TOL_F32, (kern, err)
     err, kern = run(100, 900, 150, 0, C.EPI_BIAS, batch=8)
-    assert "direct_f32_32x32" in kern and err <= T.TOL_F32, (kern, err)
+    assert "small_f32_32x32" in kern and err <= T.TOL_F32, (kern, err)
 
 
 def test_repeats():

@@ -31,7 +31,7 @@ def test_matmul(force, dtype, out_dtype, epi, trans_b):
     for batch, M, N, K, pad in SHAPES:
         err, kern = run_case(batch, M, N, K, dtype, out_dtype, trans_b, epi, pad_ld=pad, force=force,
                              bias_on=epi != C.EPI_NONE)
-        assert force.split(":")[0].replace("mfma", "128x128x64_w2x2_s4") in kern
+        assert force.split(":")[0].replace("mfma", "128x128x64_w2x4_s4") in kern
         assert err <= TOL[out_dtype], (batch, M, N, K, err)
 
 
@@ -54,7 +54,7 @@ def test_conv(case, dtype, force):
     host = wl.make_inputs(w)
     with T.forced_kernel(force):
         st, out = T.run_workload(w, T.upload(host))
-    assert st == 0 and force.split(":")[0].replace("mfma", "128x128x64_w2x2_s4") in pbk.pbk_last_kernel(), pbk.pbk_last_kernel()
+    assert st == 0 and force.split(":")[0].replace("mfma", "128x128x64_w2x4_s4") in pbk.pbk_last_kernel(), pbk.pbk_last_kernel()
     ref, pre = T.oracle_full(w, host)
     err = T.rel_err(T.to_host_f64(out, w.out_dtype).reshape(ref.shape), ref, pre)
     assert err <= TOL[dtype], err
@@ -63,7 +63,7 @@ def test_conv(case, dtype, force):
 @pytest.mark.parametrize("M,N,K,trans_b,kernel", [
     (16, 512, 512, 0, "ksplit"), (17, 512, 512, 0, "tile64_32x64"), (8, 8192, 512, 1, "tile64_32x64"), (8, 4096, 512, 1, "ksplit"),
     (16, 4098, 512, 0, "ksplit_16x32"), (3, 8196, 512, 0, "ksplit_16x64"), (3, 8197, 512, 0, "gather"), (16, 512, 504, 0, "tile64"), (256, 4096, 512, 0, "tile64_64x64_s4"), (1024, 2048, 512, 0, "tile64_64x64_s2"),
-    (1152, 2048, 512, 0, "128x128x64_w2x2_s4"), (512, 512, 120, 0, "128x128x64_w2x2_s4"),
+    (1152, 2048, 512, 0, "128x128x64_w2x4_s4"), (512, 512, 120, 0, "128x128x64_w2x4_s4"),
 ])
 def test_dispatch(M, N, K, trans_b, kernel):
     """Either side of each line of the rule, with the automatic choice."""
@@ -73,7 +73,7 @@ def test_dispatch(M, N, K, trans_b, kernel):
 
 
 @pytest.mark.parametrize("M,N,K,kernel", [
-    (1280, 2048, 128, "w2x2_s4"), (1280, 2048, 136, "w2x2_s2"), (1280, 2048, 256, "w2x2_s2"), (1280, 2048, 264, "w2x2_s4"), (1408, 2048, 256, "w2x2_s4"),
+    (1280, 2048, 128, "w2x4_s4"), (1280, 2048, 136, "w2x4_s2"), (1280, 2048, 256, "w2x4_s2"), (1280, 2048, 264, "w2x4_s4"), (1408, 2048, 256, "w2x4_s4"),
 ])
 def test_dispatch_ring(M, N, K, kernel):
     """160 and 176 tiles of 128 x 128: the deeper ring with two k-tiles, or five, or more tiles."""
@@ -83,7 +83,7 @@ def test_dispatch_ring(M, N, K, kernel):
 
 
 @pytest.mark.parametrize("hw,Cin,Cout,k,kernel", [
-    (69, 56, 136, 3, "w2x2_s2"), (69, 64, 136, 3, "w2x2_s4"), (69, 24, 136, 5, "w2x2_s4"),
+    (69, 56, 136, 3, "w2x4_s2"), (69, 64, 136, 3, "w2x4_s4"), (69, 24, 136, 5, "w2x4_s4"),
 ])
 def test_dispatch_ring_conv(hw, Cin, Cout, k, kernel):
     """More than 128 tiles of a convolution: eight k-tiles that span taps, nine that do not, ten that do."""

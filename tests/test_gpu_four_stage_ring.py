@@ -23,7 +23,7 @@ def ran_on_the_ring():
     """Every case below forces the configuration; the name of the last kernel shows that it ran."""
     import paper_2603_06731_amd as pbk
     yield
-    assert "128x128x64_w2x2_s4" in pbk.pbk_last_kernel(), pbk.pbk_last_kernel()
+    assert "128x128x64_w2x4_s4" in pbk.pbk_last_kernel(), pbk.pbk_last_kernel()
 
 
 @pytest.mark.parametrize("dtype,out_dtype", [(BF16, BF16), (F16, F32)])

@@ -25,7 +25,7 @@ def repeats(call, out, force, name):
 
 
 @pytest.mark.parametrize("force,name", [("ksplit:0", "16x64"), ("ksplit:1", "16x32"), ("tile64:0", "64x64_s4"), ("tile64:1", "32x64_s3"), ("tile64:2", "64x64_s2"),
-                                        ("mfma:2", "w2x2_s4"), ("gather:0", "gather_128"), ("gather:1", "gather_64")])
+                                        ("mfma:2", "w2x4_s4"), ("gather:0", "gather_128"), ("gather:1", "gather_64")])
 def test_matmul(force, name):
     import torch
     import paper_2603_06731_amd as pbk
@@ -55,7 +55,7 @@ def test_attention(force, name, batch, Nq, Nk, D, causal):
     repeats(call, out, force, name)
 
 
-@pytest.mark.parametrize("force,name", [("mfma:1", "w2x2_s2"), ("mfma:2", "w2x2_s4"), ("mfma:6", "128x256")])
+@pytest.mark.parametrize("force,name", [("mfma:1", "w2x4_s2"), ("mfma:2", "w2x4_s4"), ("mfma:6", "128x256")])
 def test_transposed_convolution(force, name):
     import torch
     import paper_2603_06731_amd as pbk

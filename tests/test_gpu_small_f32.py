@@ -88,6 +88,8 @@ def test_small_f32_batched_and_residual():
 
 def test_dispatcher_keeps_larger_fp32_problems_off_the_small_kernel():
     err, kern = run(700, 600, 64, 0, C.EPI_NONE)               # 1672 tiles of 16 x 16
+    assert "small_f32_16x16" in kern and err <= T.TOL_F32, (kern, err)
+    err, kern = run(1040, 1030, 64, 0, C.EPI_NONE)             # 4225
     assert "small_f32" not in kern and err <= T.TOL_F32, (kern, err)
     err, kern = run(70, 45, 33, 0, C.EPI_NONE, force="generic")
     assert "generic" in kern and err <= T.TOL_F32, (kern, err)
