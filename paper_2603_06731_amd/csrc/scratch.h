@@ -24,9 +24,11 @@ struct Scratch {
 // - Up to kScratchStreams streams per device; another one takes over the memory that has been idle longest, if any is idle.
 // A handle says little about a stream: it may come back with another one after hipStreamDestroy, which need not wait for the work of the
 // first.  So every launch records an event, and the next one with the same memory waits for it on the device, which on one and the same stream
-// is no wait.  (Recorded as the launch's stop event: with hipEventRecord behind it a launch of 2.5 us took 6.4 us in a stream of them, so 4.0;
-// one of 55 us 58 and 55.  Calls that are split, without an event and with it: 32 x 1024 x 2048 7.49 and 7.51 us, attention 16 x 8192 x 128 17.64 and
-// 17.65.)
+// is no wait.  The null stream is always the same, and does without.
+// How the event is recorded: behind the launch, where the launches before have ended, and otherwise as the launch's stop event.  In a stream of launches of
+// 2.5 us, one takes 6.4 us with hipEventRecord and 4.0 with a stop event (55 us: 58 and 55), but where each is waited for, the stop event costs 2 to 5 us
+// and hipEventRecord nothing.  Attention 29 x 4 x 1959, D = 128, without events, with them: 10.65 and 10.64 us in a stream, 22.3 and 22.9 waited for; 32 x 1024 x
+// 1536: 7.10 and 7.14, 18.8 and 19.5.
 struct ScratchEntry;
 class ScratchUse {
 public:
@@ -36,9 +38,10 @@ public:
     ScratchUse& operator=(const ScratchUse&) = delete;
     explicit operator bool() const { return entry != nullptr; }
     Scratch mem() const;
-    hipEvent_t done() const;
+    hipError_t launch(const void* kern, dim3 grid, dim3 block, void** args, size_t lds_bytes, hipStream_t stream) const;
 private:
     ScratchEntry* entry = nullptr;
+    bool idle = false;              // the launches before have ended
 };
 constexpr int kScratchStreams = 32;
 

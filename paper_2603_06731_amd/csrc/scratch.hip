@@ -11,7 +11,7 @@ struct ScratchEntry {
     hipStream_t stream;
     char* base;                     // tickets, then data
     unsigned long long id;          // of the allocation
-    hipEvent_t done;                // of the last launch that uses the memory
+    hipEvent_t done;                // of the last launch that uses the memory (not for the null stream)
     std::atomic<int> users;         // calls between finding the entry and their launch
     unsigned long long last;        // when it was found last
 };
@@ -51,7 +51,7 @@ ScratchEntry* obtain(Pool& pool, hipStream_t stream) {
     if (pool.n == kScratchStreams) {
         // (never one that is at work: this stream would wait for a stranger, which might wait for what this one does next)
         for (ScratchEntry& x : pool.entries)
-            if (x.users.load() == 0 && (!e || x.last < e->last) && ok(hipEventQuery(x.done))) e = &x;
+            if (x.stream && x.users.load() == 0 && (!e || x.last < e->last) && ok(hipEventQuery(x.done))) e = &x;
         if (e) e->stream = stream;
         return e;
     }
@@ -86,7 +86,12 @@ ScratchUse::ScratchUse(int dev, hipStream_t stream) {
     for (int i = 0; i < pool.n && !e; ++i)
         if (pool.entries[i].stream == stream) e = &pool.entries[i];
     if (!e) e = obtain(pool, stream);
-    if (!e || !ok(hipStreamWaitEvent(stream, e->done, 0))) return;
+    if (!e) return;
+    if (stream) {
+        RelaxedCapture relaxed;
+        idle = ok(hipEventQuery(e->done));
+        if (!idle && !ok(hipStreamWaitEvent(stream, e->done, 0))) return;
+    }
     e->users.fetch_add(1);
     e->last = ++pool.uses;
     entry = e;
@@ -94,12 +99,17 @@ ScratchUse::ScratchUse(int dev, hipStream_t stream) {
 
 ScratchUse::~ScratchUse() { if (entry) entry->users.fetch_sub(1); }
 
-Scratch ScratchUse::mem() const { return entry ? Scratch{entry->base + kTicketBytes, (unsigned*)entry->base} : Scratch{}; }
-hipEvent_t ScratchUse::done() const { return entry ? entry->done : nullptr; }
+// (no entry, or the null stream's: nothing to record)
+hipError_t ScratchUse::launch(const void* kern, dim3 grid, dim3 block, void** args, size_t lds_bytes, hipStream_t stream) const {
+    if (!entry || !entry->stream) return hipLaunchKernel(kern, grid, block, args, lds_bytes, stream);
+    if (!idle) return hipExtLaunchKernel(kern, grid, block, args, lds_bytes, stream, nullptr, entry->done, 0);
+    const hipError_t e = hipLaunchKernel(kern, grid, block, args, lds_bytes, stream);
+    return e == hipSuccess ? hipEventRecord(entry->done, stream) : e;
+}
 
+Scratch ScratchUse::mem() const { return entry ? Scratch{entry->base + kTicketBytes, (unsigned*)entry->base} : Scratch{}; }
 hipError_t launch_with(const ScratchUse* use, const void* kern, dim3 grid, dim3 block, void** args, size_t lds_bytes, hipStream_t stream) {
-    if (!use || !*use) return hipLaunchKernel(kern, grid, block, args, lds_bytes, stream);
-    return hipExtLaunchKernel(kern, grid, block, args, lds_bytes, stream, nullptr, use->done(), 0);
+    return use ? use->launch(kern, grid, block, args, lds_bytes, stream) : hipLaunchKernel(kern, grid, block, args, lds_bytes, stream);
 }
 
 }  // namespace pbk

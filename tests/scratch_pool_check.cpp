@@ -35,6 +35,10 @@ static int enqueue(hipStream_t s, char* memory) {
     return id;
 }
 static void end_all() { for (Work& w : g_work) w.ended = true; }
+static void end_last() {                                   // and what it comes after
+    g_work.back().ended = true;
+    for (int i : g_work.back().after) g_work[i].ended = true;
+}
 static void destroy_and_create(hipStream_t s) { g_order[s].clear(); }     // the handle comes back, the work goes on
 
 extern "C" {
@@ -82,7 +86,7 @@ hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
     }
     return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t s) { enqueue(s, nullptr); return hipSuccess; }
+hipError_t hipLaunchKernel(const void*, dim3, dim3, void** args, size_t, hipStream_t s) { enqueue(s, (char*)args[0]); return hipSuccess; }
 hipError_t hipExtLaunchKernel(const void*, dim3, dim3, void** args, size_t, hipStream_t s, hipEvent_t, hipEvent_t stop, int) {
     g_events[stop] = enqueue(s, (char*)args[0]);
     return hipSuccess;
@@ -105,7 +109,8 @@ static char* call(hipStream_t s) { const ScratchUse use(0, s); return use ? laun
 int main() {
     // a stream keeps its memory; another has other memory
     char* a = call(stream(0));
-    CHECK(a && call(stream(0)) == a && call(nullptr) != a);
+    char* null_stream = call(nullptr);
+    CHECK(a && call(stream(0)) == a && null_stream && null_stream != a && call(nullptr) == null_stream);
     // the handle comes back while the first stream's work goes on
     for (int i = 0; i < 5; ++i) { destroy_and_create(stream(0)); CHECK(call(stream(0)) == a && call(stream(0)) == a); }
     // none for the handles of each thread's own stream, under capture, or on a device out of range
@@ -125,19 +130,18 @@ int main() {
     CHECK(g_memory.size() == (size_t)pbk::kScratchStreams);
     // one more: nothing while all are at work, then what has been idle longest, but not what a call is about to use
     CHECK(!call(stream(100)) && g_last == hipSuccess);
-    g_work.back().ended = true;                                  // (the last call's)
+    end_last();
     char* last = call(stream(100));
     CHECK(last && owner[last] == pbk::kScratchStreams - 2);
     end_all();
     call(stream(0));
-    call(nullptr);
     end_all();
-    char* b = call(stream(101));                                 // (stream(1)'s was used longest ago)
+    char* b = call(stream(101));                                 // (stream(1)'s was used longest ago but for the null stream's, which stays)
     CHECK(b && b != a && b != last && owner[b] == 1);
     {
         end_all();
         const ScratchUse held(0, stream(0));
-        call(nullptr), call(stream(100)), call(stream(101));
+        call(stream(100)), call(stream(101));
         for (int i = 2; i < pbk::kScratchStreams - 2; ++i) call(stream(i));
         CHECK(!call(stream(102)));                               // idle is what the call in between is about to use, and nothing else
         CHECK(launch(held, stream(0)) == a);
@@ -146,7 +150,7 @@ int main() {
     CHECK(g_memory.size() == (size_t)pbk::kScratchStreams);
     // streams that come and go
     for (int i = 0; i < 100; ++i) { CHECK(call(stream(120 + i))); if (i % 3 == 0) end_all(); }
-    CHECK(g_memory.size() == (size_t)pbk::kScratchStreams);
+    CHECK(g_memory.size() == (size_t)pbk::kScratchStreams && call(nullptr) == null_stream);
 
     // after hipDeviceReset: nothing of what was there is used or given back
     std::set<char*> old;

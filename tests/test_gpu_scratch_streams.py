@@ -116,7 +116,7 @@ def test_next_to_a_capture(problem):
     torch.cuda.synchronize()
     with torch.cuda.graph(graph):
         assert S.call(a, b, cap, stream=torch.cuda.current_stream()) == 0 and not split()
-        for s, o in zip(streams, outs):
+        for s, o in list(zip(streams, outs)) * 2:
             assert S.call(a, b, o, stream=s) == 0
         assert S.call(a, b, cap, stream=torch.cuda.current_stream()) == 0 and not split()
     for _ in range(3):
