@@ -20,7 +20,7 @@ static const MfmaConfig kMfmaConfigs[] = {
     {0, 128, 256, 32, 1, 4, 3, "mfma_128x256x32_w1x4_s3_occ2"},
     {1, 128, 128, 64, 2, 4, 2, "mfma16_128x128x64_w2x4_s2", "mfma_128x128x64_w2x4_s2"},
     {2, 128, 128, 64, 2, 4, 4, "mfma16_128x128x64_w2x4_s4", "mfma_128x128x64_w2x4_s4"},      // 1 with a deeper ring: at most one tile per compute unit
-    {3, 256, 256, 32, 2, 4, 4, "mfma_256x256x32_w2x4_s4"},          // measured and retired, not built
+    {3, 128, 128, 64, 2, 2, 2, "mfma_128x128x64_w2x2_s2"},          // 16-bit plain matrices of one or two k-tiles
     {4, 256, 256, 64, 2, 4, 2, "mfma_256x256x64_w2x4_s2"},          // 8-bit types only
     {5, 256, 256, 32, 2, 4, 4, "mfma16_256x256x32_w2x4_s4"},        // 16x16x32 MFMA blocks (16-bit types)
     {6, 128, 256, 32, 1, 4, 3, "mfma16_128x256x32_w1x4_s3_occ2"},
@@ -151,6 +151,11 @@ hipError_t launch_modes(const Problem& p, hipStream_t stream, int group_m) {
         if (p.trans_b) return launch_one<T, T, BM, BN, BK, WM, WN, MODE_TRANS_B, NSTAGE, OCC, MI, ASTG>(p, stream, group_m);
         return launch_one<T, T, BM, BN, BK, WM, WN, MODE_DENSE, NSTAGE, OCC, MI, ASTG>(p, stream, group_m);
     } else {
+    if constexpr (BM == 128 && BN == 128 && BK == 64 && WM == 2 && WN == 2) {
+        if (p.is_conv) return hipErrorInvalidValue;
+        if (p.trans_b) return launch_one<T, T, BM, BN, BK, WM, WN, MODE_TRANS_B, NSTAGE, OCC, MI>(p, stream, group_m);
+        return launch_one<T, T, BM, BN, BK, WM, WN, MODE_DENSE, NSTAGE, OCC, MI>(p, stream, group_m);
+    } else {
     if (p.is_conv && p.conv.transposed) {
         // by residue classes (2): configurations 1 and 2; all taps (1): configurations 0, 1 and 6
         if constexpr (BM == 128 && BN == 128 && BK == 64) {
@@ -165,6 +170,7 @@ hipError_t launch_modes(const Problem& p, hipStream_t stream, int group_m) {
     if (p.is_conv) return launch_one<T, T, BM, BN, BK, WM, WN, MODE_CONV, NSTAGE, OCC, MI>(p, stream, group_m);
     if (p.trans_b) return launch_one<T, T, BM, BN, BK, WM, WN, MODE_TRANS_B, NSTAGE, OCC, MI>(p, stream, group_m);
     return launch_one<T, T, BM, BN, BK, WM, WN, MODE_DENSE, NSTAGE, OCC, MI, ASTG>(p, stream, group_m);
+    }
     }
 }
 
@@ -187,7 +193,8 @@ hipError_t launch_config(const Problem& p, hipStream_t stream, int cfg, int grou
     // K = 1024 on (rows of 64 bytes).
     PBK_CASE(1, 128, 128, 64, 2, 4, 2, 2, 16)
     PBK_CASE(2, 128, 128, 64, 2, 4, 4, 1, 16)
-    // 3, 4 (32x32 blocks) are not built for the 16-bit types: their 16x16 twins 5-7 replaced them
+    PBK_CASE(3, 128, 128, 64, 2, 2, 2)
+    // 4 (32x32 blocks) is not built for the 16-bit types
     PBK_CASE(5, 256, 256, 32, 2, 4, 4, 1, 16)
     PBK_CASE(6, 128, 256, 32, 1, 4, 3, 2, 16)
     PBK_CASE(7, 256, 256, 32, 2, 4, 4, 1, 16, 1)
@@ -199,7 +206,7 @@ hipError_t launch_config(const Problem& p, hipStream_t stream, int cfg, int grou
 // configuration groups of the 16-bit translation units (gemm_mfma_16bit.hip, once per type and group)
 constexpr unsigned kGroupMask16[] = {
     (1u << 0) | (1u << 1) | (1u << 2),   // 0: the 32x32-block configuration and the 128 x 128 tiles
-    (1u << 5),                        // 1: 256x256x32, plain ring
+    (1u << 5) | (1u << 3),            // 1: 256x256x32, plain ring; 128 x 128 tiles on four waves
     (1u << 6),                        // 2: 128x256x32, two workgroups per compute unit
     (1u << 7),                        // 3: A staged 64 deep
     (1u << 9),                        // 4: ... with six B stages and one barrier per pair of k-tiles
