@@ -194,12 +194,46 @@ bool small_f32_supported(const Problem& p) {
     return tiles <= 0x7FFFFFFFLL;
 }
 
-static long long tiles16(const Problem& p) { return (long long)((p.M + 15) / 16) * ((p.N + 15) / 16) * p.batch; }
+static long long tiles_of(const Problem& p, int n) { return (long long)((p.M + n - 1) / n) * ((p.N + n - 1) / n) * p.batch; }
+
+// 32 x 32 tiles from some 2400 tiles of 16 x 16 on (2025 tiles, 720 x 720 x 1024: 25 against 31 us; 2304, 768 x 768 x 256: 9.8 and 11.7; 2500, 800 x 800 x
+// 800: 34 and 28; 4096: 53 and 33, K = 64: 7.5 and 7.4), except (their time first)
+// - where half of them would be empty (16 x 38416 x 64 10.6 and 7.0, 65536 x 16 x 256 31 and 19), unless a row-major B of many columns is read for a long
+//   time (5 x 60001 x 512 50 and 53, 1000 of 3 x 50 x 1024 85 and 113; 1 x 65536 x 256 27 and 25, 16 x 50000 x 1024 77 and 63);
+// - where there are more of them than the SIMDs have waves for at once, unless not by much and a row-major B is read for long (40 x 21001 x 64, 1314 of
+//   them, 11.4 and 9.5, x 256 25.5 and 28.5, k-major 23.5 and 19.5; 450 of 33 x 46 x 64, 1800 of them, 15.0 and 10.7).
+static bool blocks32(const Problem& p) {
+    const long long t16 = tiles_of(p, 16), t32 = tiles_of(p, 32);
+    if (t16 <= 2400) return false;
+    if (p.M <= 16 || p.N <= 16) return p.M <= 16 && !p.trans_b && t16 > 3500 && p.K >= 512;
+    return t32 <= 1024 || (t32 <= 1320 && !p.trans_b && p.K > 100);
+}
 
 // Up to 4096 tiles of 16 x 16, which are 1024 waves of 32 x 32, one per SIMD (in us, against 128 x 128 tiles of the main kernel):
-// 512 x 512 x 512: 7.9 against 35.5, 800 x 800 x 800: 28 against 56, 1024 x 1024 x 1024: 33 against 69, x 64: 7.4 against 10.3; 1280 x 1280 x
-// 1024: 75 against 70, 1536 x 1536 x 512: 57 against 39.
-bool small_f32_preferred(const Problem& p) { return tiles16(p) <= 4096 && p.K <= 4096; }
+// 512 x 512 x 512: 7.9 against 35.5, 800 x 800 x 800: 28 against 56, 1024 x 1024 x 1024: 33 against 69, x 64: 7.4 against 9.2, but x 32: 7.5 and 7.2 (1000 x
+// 1001 x 32, k-major B, rows of C not aligned: 9.7 and 13.5); 1280 x 1280 x 1024: 75 against 70, 1536 x 1536 x 512: 57 against 39.
+// With more than nine tiles per compute unit the generic kernel, whose tiles are 64 x 64, is ahead in some cases (its time first):
+// - short contractions, and one to three rows or columns, so that most of every tile is empty: 1 x 38416 x 16 5.0 and 5.8, x 32: 6.4 and 7.0, x 40: 7.5 and
+//   7.4; 2 x 65536 x 16 6.4 and 8.1; 65536 x 1 x 16 6.2 and 7.0; 1000 of 3 x 50 x 16 7.0 and 8.1; but 1 x 36000 x 16 5.0 and 4.5, 4 x 65536 x 16 8.4 and 8.1, 2000 of
+//   2 x 30 x 16 8.6 and 7.5;
+// - short contractions, whose time are the stores, if rows of C are not aligned and the generic kernel's tiles not empty either: 4000 x 250 x 16 8.3 and
+//   9.6, x 32: 9.5 and 9.8, x 40: 10.5 and 9.9; 250 of 60 x 63 x 40 9.4 and 10.2, x 64: 10.5 and 9.9; 64 x 16001 x 40 10.7 and 11.0; but aligned, 48 x 16384 x
+//   16, 7.8 and 7.0, and 1000 of 30 x 30 x 16 8.4 and 7.8;
+// - far more 32 x 32 tiles than waves at once, except for a middling contraction or with a k-major B: 450 of 33 x 46, K = 16 7.3 and 8.7, 64 10.7 and 10.7,
+//   128 15.3 and 18.0, 512 43 and 62 (k-major 15 and 12, 42 and 36).
+bool small_f32_preferred(const Problem& p) {
+    const long long t = tiles_of(p, 16);
+    if (t > 4096 || p.K > 4096) return false;
+    if (t <= 2304) return true;
+    const bool aligned = p.ldc % 4 == 0 && p.stride_c % 4 == 0 && (uintptr_t)p.C % 16 == 0;
+    if (mfma_supported(p) && mfma_preferred(p)) return p.K > 32 || !aligned;         // (otherwise against the generic kernel)
+    if (p.M < 4 || p.N < 4) return p.K > 32 || (p.M < 48 && p.N < 48);
+    if (t <= 2400 || p.M <= 16 || p.N <= 16) return true;
+    const long long t32 = tiles_of(p, 32);
+    if (t32 > 1320) return p.K >= 64 && (p.K == 64 || p.trans_b);
+    if (t32 > 1024) return p.K > 40;
+    return aligned || p.K > (!p.trans_b && (p.M <= 64 || p.N <= 64) ? 48 : 32) || 2ll * p.M * p.N * p.batch < 4096 * tiles_of(p, 64);
+}
 
 // Waves per tile: as many as the SIMDs (1024) have room for, with 128 k or more for each (256 x 256 x 256: 4.4 us with 1, 4.0 with 2 or 4, 4.7
 // with 8; 128 x 128 x 1024: 10.7, 7.1, 5.4, 5.9; 512 x 512 x 512: 7.9, 8.0, 8.8, 8.9).
@@ -218,10 +252,8 @@ static hipError_t launch_blocks(const Problem& p, hipStream_t stream) {
     return hipLaunchKernel(kern, dim3((unsigned)blocks), dim3(64 * waves), args, 0, stream);
 }
 
-// 32 x 32 from some 2400 tiles of 16 x 16 on (2025 tiles, 720 x 720 x 1024: 25 against 31 us; 2304, 768 x 768 x 256: 9.8 and 11.7; 2500, 800 x 800 x
-// 800: 34 and 28; 4096: 53 and 33, K = 64: 7.5 and 7.4).
 hipError_t launch_small_f32(const Problem& p, hipStream_t stream, const char** name) {
-    if (tiles16(p) <= 2400) {
+    if (!blocks32(p)) {
         *name = "small_f32_16x16_mfma4";
         return launch_blocks<1>(p, stream);
     }

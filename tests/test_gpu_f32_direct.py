@@ -20,6 +20,15 @@ pytestmark = pytest.mark.gpu
     (801, 801, 65, (68, 804, 803), "small_f32_32x32"),        # everything odd
     (1024, 1024, 128, (None, None, None), "small_f32_32x32"),
     (1025, 1024, 32, (None, None, None), "mfma_f32"),          # 4160 tiles
+    (1024, 1024, 32, (None, None, None), "mfma_f32"),          # 4096, a short contraction
+    (1, 36864, 16, (None, None, None), "small_f32_16x16"), (1, 36865, 16, (None, None, None), "generic"),     # 2304 and 2305 tiles, mostly empty
+    (3, 38401, 32, (None, None, None), "generic"), (3, 38401, 33, (None, None, None), "small_f32_16x16"),
+    (4, 38401, 20, (None, None, None), "small_f32_16x16"), (38401, 5, 20, (None, None, None), "small_f32_16x16"),   # 2401, half of a 32 x 32 tile empty
+    (16, 56000, 512, (None, None, None), "small_f32_16x16"),   # 3500
+    (33, 15000, 48, (None, None, None), "small_f32_32x32"),    # 938 tiles of 32 x 32
+    (33, 20000, 41, (None, None, None), "small_f32_16x16"), (33, 20000, 40, (None, None, None), "generic"),   # 1250: more than waves at once
+    (801, 803, 33, (None, None, None), "small_f32_32x32"), (801, 803, 30, (None, None, None), "generic"),     # rows of C not aligned
+    (60, 16001, 32, (None, None, None), "generic"),
 ])
 def test_parity_and_dispatch(M, N, K, lds, kernel, trans_b):
     lda, ldb, ldc = lds
@@ -28,6 +37,16 @@ def test_parity_and_dispatch(M, N, K, lds, kernel, trans_b):
     err, kern = run(M, N, K, trans_b, C.EPI_BIAS_RELU, lda=lda, ldb=ldb, ldc=ldc, alpha=0.75)
     assert kernel in kern, kern
     assert err <= T.TOL_F32, err
+
+
+@pytest.mark.parametrize("batch,M,N,K,trans_b,kernel", [
+    (1000, 3, 50, 16, 0, "generic"), (1000, 3, 50, 33, 0, "small_f32_16x16"), (1000, 3, 50, 512, 0, "small_f32_32x32"),
+    (1000, 3, 50, 512, 1, "small_f32_16x16"), (2000, 2, 30, 16, 0, "small_f32_16x16"), (1000, 30, 30, 16, 0, "small_f32_32x32"),
+    (450, 33, 46, 64, 0, "small_f32_16x16"), (450, 33, 46, 65, 0, "generic"), (450, 33, 46, 65, 1, "small_f32_16x16"), (450, 33, 46, 63, 1, "generic"),
+])
+def test_dispatch_of_batches(batch, M, N, K, trans_b, kernel):
+    err, kern = run(M, N, K, trans_b, C.EPI_NONE, batch=batch)
+    assert kernel in kern and err <= T.TOL_F32, (kern, err)
 
 
 def test_residual_and_batch():
