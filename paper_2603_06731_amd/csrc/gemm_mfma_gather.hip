@@ -585,6 +585,23 @@ bool mfma_gather_supported(const Problem& p) {
     return a_elems >= 8 && b_elems >= 8;
 }
 
+// Against the generic kernel, whose tiles are 64 x 64 (its time in us first): with 4096 outputs or more per entry from 16 k on.  With fewer
+// - from 64 k and 16 columns on, where most of a tile would be empty otherwise (a convolution of 81 x 32 outputs, K = 75: 19.1 and 9.3; 36 x 32,
+//   K = 2989: 401 and 15; 1 x 17 x 65: 9.4 and 6.9, 1 x 4001 x 257: 27 and 8.7, 250 x 16 x 1001: 117 and 11);
+// - but not many entries that fill as many of its tiles as of these ones, which are larger, with a short contraction (17 x 17 to 63 x 63: 400 of
+//   K = 65 12.8 to 15.9 and 9.2 to 12.7, 520: 13.5 to 19.7 and 14.9 to 18.8, 1500: 21.2 to 26.1 and 24.2 to 36.3; K = 97: 1500 27.6 to 33.4 and 23.8 to 34.4,
+//   k-major B 24.5 to 35.2 and 24.2 to 34.0, 4000 54 to 101 and 59 to 98; K = 129: 8000 135 to 237 and 136 to 208; with three of its tiles to two of these,
+//   1 x 129 and 30 x 130, 2000 of K = 65: 62 to 78 and 59 to 70, k-major B 55 to 70 and 59 to 72; with more of them, 100 x 17, 1 x 70 and 3 x 513: 1.2 to 1.6 times
+//   as fast with any number).
+bool mfma_gather_preferred(const Problem& p) {
+    if (p.K < 16) return false;
+    if ((long long)p.M * p.N >= 4096) return true;
+    if (p.K < 64 || p.N < 16) return false;
+    const long long theirs = (long long)((p.M + 63) / 64) * ((p.N + 63) / 64), ours = (long long)((p.M + 127) / 128) * ((p.N + 127) / 128);
+    if (2 * theirs > 3 * ours || (2 * theirs == 3 * ours && !p.trans_b)) return true;
+    return p.K >= (ours * p.batch <= 512 ? 64 : ours * p.batch <= 2048 ? 96 : 128);
+}
+
 // Up to one round of 64-row tiles on the 256 compute units the 64-row tile wins, because a workgroup alone on its unit is bound by
 // latency (8 x 44 x 44 x 127 -> 512, 3 x 3, stride 2, 224 tiles: 33.4 -> 25.4 us; 577 x 1021 x 4096, 80 tiles: 49.9 -> 35.0).  Where they
 // take a second round and the larger ones do not, a plain product gains only up to K = 512 (1024 x 2049: K = 259 1.11 times

@@ -91,10 +91,9 @@ pbk_status dispatch(const pbk::Problem& p_in, hipStream_t stream) {
     hipError_t e;
     const bool can_mfma = pbk::mfma_supported(p);
     // operands the direct-to-LDS kernel cannot take (ragged K, N, leading dimensions, channel counts,
-    // unaligned bases) still run on the matrix units, staged through registers, when there is enough work (a convolution of 81 x 32 outputs,
-    // K = 75: 9.3 against 19.1 us on the generic kernel; 36 x 32, K = 2989: 15 against 401; with a few columns most of a tile would be empty)
+    // unaligned bases) still run on the matrix units, staged through registers, when there is enough work
     const bool can_gather = pbk::mfma_gather_supported(p);
-    const bool want_gather = !can_mfma && can_gather && p.K >= 16 && ((long long)p.M * p.N >= 4096 || (p.K >= 64 && p.N >= 16));
+    const bool want_gather = !can_mfma && can_gather && pbk::mfma_gather_preferred(p);
     // fp32 problems of up to some thousand 16 x 16 tiles: the operands go straight to registers
     const bool can_small = pbk::small_f32_supported(p);
     // short contractions over many rows: the B-stationary kernel

@@ -94,6 +94,7 @@ hipError_t launch_mfma(const Problem& p, hipStream_t stream, int force_cfg, cons
 // The matrix-unit kernel that gathers its tiles element by element: 16-bit operands of any alignment, K, N
 // and leading dimensions; convolutions with at least 8 input channels.
 bool mfma_gather_supported(const Problem& p);
+bool mfma_gather_preferred(const Problem& p);
 hipError_t launch_mfma_gather(const Problem& p, hipStream_t stream, int force_cfg, const char** name);
 
 // Short contractions (K <= 256) over many rows: B stationary in registers, the workgroup walks down M.
