@@ -1,5 +1,5 @@
-"""Distance from 64 bits of the kernels that split a contraction or the keys of an attention over waves, beside that of the kernel
-that walks it in one piece: relative 2-norm over some problems of the sizes that the automatic choice gives them.
+"""Distance from 64 bits of the kernels that split a contraction or the keys of an attention over waves or workgroups, beside that of the
+kernel that walks it in one piece: relative 2-norm over some problems of the sizes that the automatic choice gives them.
 
 A split changes the order of fp32 sums and, for attention, which power of two the 16-bit weights are scaled by.  Neither may cost
 precision.  The bound: the ratio of the two distances is a ratio of two sample deviations over n >= 2e5 rounding errors,
@@ -12,7 +12,7 @@ import pbk_testlib as T
 
 pytestmark = pytest.mark.gpu
 
-BF16, F16 = wl.DTYPE_BF16, wl.DTYPE_F16
+BF16, F16, F32 = wl.DTYPE_BF16, wl.DTYPE_F16, wl.DTYPE_F32
 
 
 class Distance:
@@ -54,7 +54,7 @@ def gen(seed):
 
 def types(dtype):
     import torch
-    return torch.bfloat16 if dtype == BF16 else torch.float16
+    return {BF16: torch.bfloat16, F16: torch.float16, F32: torch.float32}[dtype]
 
 
 def attention_problems(sizes, dtype, causal):
@@ -95,6 +95,20 @@ def test_attention_two_groups(dtype, causal):
     compare(attention_problems(sizes, dtype, causal), "mfma:1", "mfma:2", "kv64x2")
 
 
+@pytest.mark.parametrize("dtype", [BF16, F16])
+def test_attention_keys_over_workgroups(dtype):
+    sizes = [(96, 16, 4096, 128), (64, 8, 2560, 64), (16, 16, 8192, 128), (33, 8, 3584, 32), (24, 4, 5000, 64)]
+    compare(attention_problems(sizes, dtype, 1), "decode:4", "decode:8", "split")
+
+
+@pytest.mark.parametrize("causal", [0, 1])
+@pytest.mark.parametrize("dtype", [BF16, F16])
+@pytest.mark.parametrize("now,name", [("mfma:3", "q64_kv64x2"), ("mfma:4", "q64_kv64x4")])
+def test_attention_64_queries(now, name, dtype, causal):
+    sizes = [(16, 577, 577, 64), (8, 2048, 2048, 64), (12, 1024, 1024, 32)] + ([(16, 300, 1024, 128)] if now == "mfma:3" else [])
+    compare(attention_problems(sizes, dtype, causal), "mfma:1", now, name)
+
+
 def matmul_problems(sizes, dtype):
     import torch
     import paper_2603_06731_amd as pbk
@@ -117,6 +131,19 @@ def test_matmul(dtype, now, name):
     sizes = [(16, 4096, 4096, 0), (8, 14336, 1024, 0), (16, 2048, 512, 1), (9, 4096, 8192, 1)] if now == "ksplit" else [
         (577, 1024, 1024, 0), (300, 512, 4096, 1), (256, 512, 512, 0)]
     compare(matmul_problems(sizes, dtype), "mfma:1", now, name)
+
+
+@pytest.mark.parametrize("dtype", [BF16, F16])
+@pytest.mark.parametrize("before,now,name", [("tile64:1", "tile64:8", "split"), ("gather:0", "gather:1", "split")])
+def test_matmul_over_workgroups(dtype, before, now, name):
+    odd = 3 if now == "gather:1" else 0
+    compare(matmul_problems([(256, 1024, 4096 + odd, 0), (48, 1024, 16384 + odd, 1), (130, 1000, 1536 + odd, 1)], dtype), before, now, name)
+
+
+@pytest.mark.parametrize("before", ["mfma:1", "generic"])
+def test_f32(before):
+    """k over the waves of a tile: partial sums of K / waves terms, no further from 64 bits than one sum of K."""
+    compare(matmul_problems([(256, 256, 256, 0), (128, 160, 1024, 1), (512, 512, 512, 0), (800, 800, 320, 1)], F32), before, "small", "small_f32")
 
 
 @pytest.mark.parametrize("now", ["tile64:0", "tile64:1"])
