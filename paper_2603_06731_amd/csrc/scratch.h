@@ -20,7 +20,7 @@ struct Scratch {
 // The scratch memory of `stream` on device `dev` (the current one) for one launch, which has to go through launch_with() while this object lives.
 // False where there is none: the caller then takes a kernel that needs none.
 // - Not while the stream is being captured: a graph is replayed on any stream, and next to eager work on this one.
-// - Not for the handles that stand for another stream in each thread.
+// - Not for the handles that stand for another stream in each thread, and not for a stream of another device.
 // - Up to kScratchStreams streams per device; another one takes over the memory that has been idle longest, if any is idle.
 // A handle says little about a stream: it may come back with another one after hipStreamDestroy, which need not wait for the work of the
 // first.  So every launch records an event, and the next one with the same memory waits for it on the device, which on one and the same stream

@@ -76,6 +76,9 @@ ScratchEntry* obtain(Pool& pool, hipStream_t stream) {
 
 ScratchUse::ScratchUse(int dev, hipStream_t stream) {
     if (dev < 0 || dev >= kDevices || stream == hipStreamPerThread || stream == hipStreamLegacy) return;
+    // (the handle of a stream of another device: events and memory would be the wrong ones)
+    hipDevice_t of = dev;
+    if (stream && (!ok(hipStreamGetDevice(stream, &of)) || of != dev)) return;
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
     if (!ok(hipStreamIsCapturing(stream, &status)) || status != hipStreamCaptureStatusNone) return;
     std::lock_guard<std::mutex> lock(g_mutex);

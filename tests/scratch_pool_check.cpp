@@ -21,6 +21,7 @@ static unsigned long long g_ids = 0;
 static hipError_t g_last = hipSuccess;
 static bool g_capturing = false, g_full = false;
 static int g_frees = 0;
+static hipStream_t g_foreign = nullptr;                    // a stream of device 1
 
 static int enqueue(hipStream_t s, char* memory) {
     Work w;
@@ -47,6 +48,7 @@ hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* s) {
     *s = g_capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
     return hipSuccess;
 }
+hipError_t hipStreamGetDevice(hipStream_t s, hipDevice_t* d) { *d = s == g_foreign ? 1 : 0; return hipSuccess; }
 hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode*) { return hipSuccess; }
 hipError_t hipMalloc(void** p, size_t) {
     if (g_full) return g_last = hipErrorOutOfMemory;
@@ -119,6 +121,9 @@ int main() {
     CHECK(!call(stream(0)) && !call(stream(1)));
     g_capturing = false;
     CHECK(!ScratchUse(-1, stream(0)) && !ScratchUse(32, stream(0)));
+    g_foreign = stream(0);                                       // the handle comes back with a stream of another device
+    CHECK(!call(stream(0)));
+    g_foreign = nullptr;
     // no memory: no scratch, and no error left behind
     g_full = true;
     CHECK(!call(stream(1)) && g_last == hipSuccess);
