@@ -253,9 +253,6 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void attention_decode_kernel(AttnP
         *(int2v*)((char*)p.O + ((int64_t)b * p.stride_o + (int64_t)q * p.ldo + d) * 2) =
             int2v{(int)pack2<T>(o[0] * inv, o[1] * inv), (int)pack2<T>(o[2] * inv, o[3] * inv)};
     };
-    // scratch memory of a part: PIECES pieces of the output at its reference points, then reference point and sum per query
-    constexpr int PART = PIECES * 4 + 64;
-    float* part_of_entry = SPLIT ? (float*)scratch.data + (size_t)b * parts * PART : nullptr;
     f32x4 v[AHEAD];
     const int e = threadIdx.x, q = e & 15;         // a piece of the output, its query
     static_assert(PIECES <= NW * 64, "one piece per thread");

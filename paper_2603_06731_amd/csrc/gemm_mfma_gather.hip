@@ -116,19 +116,19 @@ __global__ __launch_bounds__(DEEP ? 512 : 256, 2) void gemm_mfma_gather_kernel(P
     const int Cp = CONV ? (p.conv.Cin + 7) & ~7 : 0;
     const int taps = CONV ? p.conv.KH * p.conv.KW : 0;
     const int Kloop = CONV ? taps * Cp : p.K;
-    // the last addresses from which 16 bytes can be read (each operand holds at least 8 elements)
     // this workgroup's k-tiles: kt0 .. kt1 - 1
     const int KT = (Kloop + GBK - 1) / GBK;
     const int each = SPLIT ? KT / parts : KT, rest = SPLIT ? KT - each * parts : 0;
     const int kt0 = SPLIT ? part * each + (part < rest ? part : rest) : 0, kt1 = SPLIT ? kt0 + each + (part < rest ? 1 : 0) : KT;
+    // the last addresses from which 16 bytes can be read (each operand holds at least 8 elements)
     const int64_t a_elems = CONV ? (int64_t)(p.M / (p.conv.OH * p.conv.OW)) * p.conv.H * p.conv.W * p.conv.Cin
                                  : (int64_t)(p.M - 1) * p.lda + p.K;
     const int64_t b_elems = TRANS_B ? (int64_t)(p.N - 1) * p.ldb + p.K : (int64_t)(p.K - 1) * p.ldb + p.N;
     const char* a_last16 = Abase + a_elems * 2 - 16;
     const char* b_last16 = Bbase + b_elems * 2 - 16;
 
-    // ---- A (k-major source): piece = (row, chunk of 8 k); eight neighbouring threads cover a row of the k-tile.
-    // The thread's pieces differ in the row only (+64).
+    // ---- A (k-major source): piece = (row, chunk of 8 k); CPR neighbouring threads cover a row of the k-tile.
+    // The thread's pieces differ in the row only (+ NT / CPR).
     constexpr int CPR = GBK / 8, NPR = GBN / 8;       // pieces per row of a k-major tile, per k-row of an n-major one
     const int a_chunk = t % CPR;
     int a_row[PA];
@@ -192,7 +192,7 @@ __global__ __launch_bounds__(DEEP ? 512 : 256, 2) void gemm_mfma_gather_kernel(P
     }
     // ---- B: k-major source (trans_b): pieces like A's.  n-major source (row-major B, the weights of a
     // convolution): a piece is eight neighbouring n of one k-row: b_row = k-row in the tile, b_chunk = which
-    // eight n; the thread's two pieces differ in the k-row only (+32).
+    // eight n; the thread's pieces differ in the k-row only (+ NT / NPR).
     const int b_chunk = TRANS_B ? t % CPR : t % NPR;
     int b_row[PB];
     bool b_ok[PB];

@@ -1,6 +1,6 @@
-// Small fp32 contractions (the 256^3 case of the paper's Sec. 4.3 walk-through and its kind): a few
-// hundred output tiles at most, where the time is launch plus one memory latency and a tile-per-workgroup
-// kernel of the usual size would leave most compute units idle.
+// Small fp32 contractions (the 256^3 case of the paper's Sec. 4.3 walk-through and its kind): up to some
+// thousand output tiles, where the time is launch plus one memory latency, or a tile-per-workgroup kernel of
+// the usual size would leave most compute units idle.
 //
 // A workgroup of up to 16 waves computes a 16 x 16 tile of C with v_mfma_f32_16x16x4_f32 (true binary32 products and sums), each
 // wave over a contiguous share of k; the waves' sums meet in LDS and are added in wave order.  Nothing else is staged: a lane

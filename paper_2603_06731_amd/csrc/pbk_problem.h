@@ -80,7 +80,7 @@ __host__ __device__ inline bool epi_has_bias(int epi) {
 // Launchers.  Each returns hipSuccess or the launch error; `name` receives a
 // static string naming the configuration that ran.
 hipError_t launch_generic(const Problem& p, hipStream_t stream, const char** name);
-// small fp32 matmuls, one wave per 16 x 16 tile
+// fp32 matmuls of up to some thousand 16 x 16 tiles: the operands go straight to registers
 bool small_f32_supported(const Problem& p);
 bool small_f32_preferred(const Problem& p);
 hipError_t launch_small_f32(const Problem& p, hipStream_t stream, const char** name);
@@ -91,8 +91,8 @@ bool mfma_supported(const Problem& p);
 bool mfma_preferred(const Problem& p);
 hipError_t launch_mfma(const Problem& p, hipStream_t stream, int force_cfg, const char** name);
 
-// The matrix-unit kernel that gathers its tiles element by element: 16-bit operands of any alignment, K, N
-// and leading dimensions; convolutions with at least 8 input channels.
+// The matrix-unit kernel that stages its tiles through registers: 16-bit operands of any alignment, K, N, leading
+// dimensions and channel counts.
 bool mfma_gather_supported(const Problem& p);
 bool mfma_gather_preferred(const Problem& p);
 hipError_t launch_mfma_gather(const Problem& p, hipStream_t stream, int force_cfg, const char** name);
