@@ -57,12 +57,14 @@ bool mfma_preferred(const Problem& p) {
 //   192 tiles: 7.7 against 7.6, 2048 x 2048 x 256: 8.1 against 8.3; with two k-tiles or five it is even or ahead).
 // Two tiles per unit, one k-tile or one and a half, and an epilogue that loads nothing: the time is starting the waves and storing, of which four
 // waves per tile are the lesser part, with rows of 128 bytes in a store instead of 64 (3, 16-bit plain products, eight waves first: 12 x 704 x 704 x 32
-// 6.88 and 6.55 us, 33 x 320 x 320 x 64 5.95 and 5.74, 32 x 384 x 384 x 96 7.18 and 6.90; K = 128 even, 192 8.08 and 8.43 for 12 x 704 x 704; with a bias
-// 6.83 and 7.23, with fp32 results 8.12 and 8.43; 468 tiles even, 512: 7.68 and 7.84; 60000 x 128 x 64: 7.35 and 7.85).
+// 6.88 and 6.55 us, 33 x 320 x 320 x 64 5.95 and 5.74, 32 x 384 x 384 x 96 7.18 and 6.90; 192 8.08 and 8.43 for 12 x 704 x 704; with a bias
+// 6.83 and 7.23, with fp32 results 8.12 and 8.43; 468 tiles even, 512: 7.68 and 7.84; 60000 x 128 x 64: 7.35 and 7.85).  Where few units have two tiles,
+// up to two and a half (k-major B: 17 x 512 x 512 x 128, 272 tiles, 7.15 and 6.76, x 160 8.11 and 7.94, x 192 7.70 and 7.82; 9 x 768 x 768 x 128, 324 tiles, 7.35 and
+// 7.25; 40 x 384 x 384 x 128, 360 tiles, 7.58 and 7.73).
 static int square_config(const Problem& p) {
     const long long t = (long long)((p.M + 127) / 128) * ((p.N + 127) / 128) * p.batch;
     const bool b8 = p.in_dtype != DT_BF16 && p.in_dtype != DT_F16;
-    if (t > 256) return !b8 && !p.is_conv && p.K <= 96 && t <= 448 && p.N >= 256 && p.out_dtype != DT_F32 && !epi_has_bias(p.epi) && !p.R ? 3 : 1;
+    if (t > 256) return !b8 && !p.is_conv && p.K <= (t <= 330 ? 160 : 96) && t <= 448 && p.N >= 256 && p.out_dtype != DT_F32 && !epi_has_bias(p.epi) && !p.R ? 3 : 1;
     const int bk = b8 ? 128 : 64, kt = (p.K + bk - 1) / bk;        // values per k-tile, k-tiles
     if (p.is_conv) return p.conv.Cin % bk != 0 && kt <= 8 ? 1 : 2;
     return !b8 && kt >= 3 && kt <= 4 && t <= 160 ? 1 : 2;

@@ -27,12 +27,13 @@ def test_parity(k, trans_b, dtype, out_dtype, epi):
 
 
 @pytest.mark.parametrize("batch,M,N,K,out_dtype,epi,four", [
-    (33, 264, 320, 96, BF16, C.EPI_NONE, True), (33, 264, 320, 104, BF16, C.EPI_NONE, False), (33, 264, 320, 32, F32, C.EPI_NONE, False),
+    (33, 264, 320, 160, BF16, C.EPI_NONE, True), (33, 264, 320, 168, BF16, C.EPI_NONE, False),
+    (37, 264, 320, 96, BF16, C.EPI_NONE, True), (37, 264, 320, 104, BF16, C.EPI_NONE, False), (33, 264, 320, 32, F32, C.EPI_NONE, False),
     (33, 264, 320, 32, BF16, C.EPI_BIAS, False), (33, 264, 320, 32, BF16, C.EPI_RELU, True), (16, 384, 640, 64, BF16, C.EPI_NONE, False),
     (129, 100, 248, 64, BF16, C.EPI_NONE, False), (112, 130, 256, 64, BF16, C.EPI_NONE, True), (113, 130, 256, 64, BF16, C.EPI_NONE, False),
 ])
 def test_dispatch(batch, M, N, K, out_dtype, epi, four):
-    """297 tiles; 240; 258 with few columns, 448, 452."""
+    """297 tiles; 333; 240; 258 with few columns, 448, 452."""
     err, kern = run_case(batch, M, N, K, BF16, out_dtype, 0, epi, force=None, bias_on=epi == C.EPI_BIAS)
     assert ("128x128x64_w2x2_s2" in kern) == four, kern
     assert err <= TOL[out_dtype], err
