@@ -680,7 +680,8 @@ static bool split_preferred(const AttnProblem& p) {
 // 64 queries per workgroup, two (or four) groups of waves: twice the workgroups where those of 128 queries leave compute units without one or with
 // a single chain.  Times in us, the better form of 128 queries first:
 // - up to one per unit from two tiles of keys on: 16 x 577 x 64: 10.8 and 8.3, 20 x 300 x 128: 10.8 and 9.8, 16 x 1024 x 128 20.5 and 16.4, 10 x 100 x 64,
-//   causal, 6.3 and 5.5; the keys in four parts, up to D = 64, from 2048 keys on: 8 x 2048 x 64 21.2, 16.3 and 14.9, 16 entries of 64 queries, 8192
+//   causal, 6.3 and 5.5, but not three tiles of keys under the diagonal, two rounds for either group, at D = 32 (24 x 150: 5.2 and 5.4) or nearly full (24 x 192 x
+//   64: 6.6 and 6.9, x 128: 8.7 and 9.3; 24 x 150 x 64: 6.6 and 6.3); the keys in four parts, up to D = 64, from 2048 keys on: 8 x 2048 x 64 21.2, 16.3 and 14.9, 16 entries of 64 queries, 8192
 //   keys, 65.6, 50.1 and 40.9 (16 x 1024, causal: 14.7, 11.5 and 12.4; more than 128 entries are bound by memory: 256 x 64 x 1024 x 64 16.4, 15.2 and
 //   15.6).  Up to 64 queries there are no more workgroups than before, so only where the
 //   keys are split anyway (128 x 64 x 2048 x 128: 33.7 and 32.0; but 64 x 64 x 64 x 64 4.7 and 5.6, 256 x 33 x 300 x 128 10.9 and 12.3);
@@ -694,7 +695,8 @@ static bool split_preferred(const AttnProblem& p) {
 static int attention_form(const AttnProblem& p) {
     const bool split = split_preferred(p), triangle = triangle_of(p);
     const long long total = ((long long)p.Nq + 63) / 64 * p.batch;
-    if (total <= 256 && (p.Nq > 64 ? p.Nk >= 96 : split)) return p.D <= 64 && p.Nk >= 2048 && p.batch <= 128 ? FORM_Q64_X4 : FORM_Q64_X2;
+    const bool three = triangle && p.Nk > 128 && p.Nk <= 192 && (p.D == 32 || p.Nk > 176);
+    if (total <= 256 && (p.Nq > 64 ? p.Nk >= 96 && !three : split)) return p.D <= 64 && p.Nk >= 2048 && p.batch <= 128 ? FORM_Q64_X4 : FORM_Q64_X2;
     if (p.D == 64 && triangle && (total <= 512 ? p.Nk >= 1280 : total <= 768 && p.Nk >= 1536 && p.Nk < 3072)) return FORM_Q64_X2;
     if (p.D == 32 && p.Nk >= 1024 && (total <= 768 || (triangle && total <= 1024 && p.Nk >= 3072))) return FORM_Q64_X2;
     return split ? FORM_Q128_X2 : FORM_Q128;

@@ -74,6 +74,8 @@ def test_sizes(D, force, name, dtype, causal):
     (4, 65, 96, 64, 0, "q64_kv64x2"), (4, 65, 95, 64, 0, "q128_kv64_"), (4, 64, 96, 128, 0, "q128_kv64_"), (128, 128, 128, 128, 1, "q64_kv64x2"),
     (129, 128, 128, 128, 1, "q128_kv64_"), (2, 64, 2048, 64, 0, "q64_kv64x4"), (2, 200, 2047, 64, 1, "q64_kv64x2"), (2, 200, 2048, 128, 1, "q64_kv64x2"),
     (16, 2048, 2048, 64, 1, "q64_kv64x2"), (16, 2048, 2048, 64, 0, "q128_kv64x2"), (25, 1280, 1280, 64, 1, "q64_kv64x2"), (25, 1279, 1279, 64, 1, "q128_kv64x2"),
+    (4, 150, 128, 32, 1, "q64_kv64x2"), (4, 150, 129, 32, 1, "q128_kv64_"), (4, 192, 192, 32, 1, "q128_kv64_"), (4, 193, 193, 32, 1, "q64_kv64x2"),
+    (4, 150, 150, 32, 0, "q64_kv64x2"), (4, 176, 176, 64, 1, "q64_kv64x2"), (4, 177, 177, 128, 1, "q128_kv64_"),
     (24, 2048, 2048, 64, 1, "q64_"), (25, 2048, 2048, 64, 1, "q128_kv64_"), (48, 1024, 1024, 32, 0, "q64_"), (49, 1024, 1024, 32, 0, "q128_kv64_"),
 ])
 def test_dispatch(batch, Nq, Nk, D, causal, name):
