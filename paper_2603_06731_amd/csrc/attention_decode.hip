@@ -362,6 +362,8 @@ static int decode_split(const AttnProblem& p) { return p.batch > 128 ? 1 : p.bat
 //   against 40.2; 128 x 8192: 90 against 96;
 // - D = 64: 16 x 2048: 8.5 against 8.7, x 4096: 17.5 against 10.3; 96 x 4096: 24.8 against 22.3; 128 x 8192: 49.5 and 49.5;
 // - D = 32: 16 x 3072: 7.7 against 8.0, x 4096: 9.0 against 7.9; 96 x 4096: 15.0 against 13.4.
+// Keys and values in the caches already shift the line up: near it the split then costs up to a tenth (D = 64, 64 x 2560: 10.3 against 11.5, from memory
+// 15.7 against 12.8; 55 x 2867 10.8 against 11.3, from memory 16.6 against 12.6; D = 128, 64 x 2048 13.8 against 15.3, from memory 19.1 against 17.3).
 static int decode_parts(const AttnProblem& p, int force) {
     if ((force > 0 && force < 8) || p.batch > 96) return 1;
     const int least = p.batch > 64 ? 4096 : p.D == 128 ? (p.batch > 32 ? 2048 : 1536) : p.D == 64 ? 2560 : 3584;

@@ -411,7 +411,10 @@ bool mfma_tile64_preferred(const Problem& p) {
 // - up to 16 rows against ksplit: 8 x 1024 x 4096: 7.0 and 8.0, 14 x 1472 x 6144: 13.8 and 9.2, 16 x 4096 x 4096: 13.2 and 10.3, 8 x 1024 x
 //   16384: 33.6 and 12.5, but 6 x 3456 x 2368: 6.7 and 7.9; with a row-major B of many columns its workgroups read at the rate of the memory
 //   already: 1 x 4736 x 4672 10.1 and 11.4, 4 x 8192 x 4096 14.7 and 15.1 (8 x 4096 x 4096 12.0 and 10.5, 16 x 8192 x 4096 16.9 and 15.4);
-// - more tiles: 1024 x 320 x 4096, 160 tiles: 14.2 and 13.8, 1024 x 480 x 4096: 14.9 and 15.8.
+// - more tiles: 1024 x 320 x 4096, 160 tiles: 14.2 and 13.8, 1024 x 480 x 4096: 14.9 and 15.8;
+// - two parts only, from 77 tiles on, give back less: with operands in the caches, 256 x 1024 x 1536 7.7 and 8.7, x 1792 8.3 and 9.0, x 2304 9.6 and 9.7; from
+//   memory, as the weights of a model come, 9.95 and 9.24, 11.0 and 9.7, 12.8 and 10.7; 61 x 3328 x 1536 7.6 and 8.3, from memory 10.3 and 9.3; 3 x 3
+//   convolutions 8 x 14 x 14 x 128 -> 128 8.3 and 8.8, from memory 8.4 and 8.5, 6 x 14 x 14 x 160 -> 128 9.7 and 8.6.
 static int tile64_parts(const Problem& p, bool forced) {
     const long long tiles = (long long)((p.M + 31) / 32) * ((p.N + 63) / 64) * p.batch;
     const int rounds = (p.K + T64_BK - 1) / T64_BK;
@@ -422,6 +425,7 @@ static int tile64_parts(const Problem& p, bool forced) {
     int parts = (int)((192 + tiles / 2) / tiles);
     const int most = forced ? rounds : rounds / 4;
     parts = parts < 8 ? parts : 8;
+    if (!forced && parts == 2 && rounds < (p.is_conv ? 11 : 14)) return 1;
     return parts < most ? parts : most;
 }
 

@@ -72,6 +72,7 @@ def reference(a, b, trans_b=0):
 
 @pytest.mark.parametrize("M,N,K,trans_b,kernel", [
     (32, 1024, 1408, 0, "tile64_32x64_s3"), (32, 1024, 1416, 0, "split"),                                     # eleven rounds, twelve
+    (96, 1600, 1664, 0, "split"), (96, 1664, 1664, 0, "tile64_32x64_s3"), (96, 1664, 1672, 0, "split"),        # 75 tiles; 78, thirteen rounds and fourteen
     (256, 1024, 4096, 1, "split"), (257, 1024, 4096, 1, "tile64_32x64_s3"),                                   # 128 tiles, 144
     (16, 1024, 5856, 0, "ksplit"), (16, 1024, 5864, 0, "split"),                                              # values of B
     (16, 8192, 4096, 0, "split"), (16, 8256, 4096, 0, "ksplit"),
@@ -91,6 +92,20 @@ def test_dispatch(M, N, K, trans_b, kernel):
     ref = reference(a, b, trans_b)
     # one rounding to bf16 (2^-9 of the value), fp32 sums of K terms of order K^-1/2
     assert torch.all((out.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-4)
+
+
+@pytest.mark.parametrize("n,Cin,split", [(4, 128, True), (8, 128, False), (8, 144, True), (8, 152, True)])
+def test_dispatch_conv(n, Cin, split):
+    """50 tiles and 98, in two parts from eleven rounds on."""
+    import paper_2603_06731_amd as pbk
+    w = wl.Workload("tile64_split_rule", "conv", BF16, BF16, C.EPI_BIAS_RELU, n=n, H=14, W=14, Cin=Cin, Cout=128, KH=3, KW=3, pad=(1, 1),
+                    dist_b=("normal", float(np.sqrt(2.0 / (9 * Cin)))))
+    host = wl.make_inputs(w)
+    st, out = T.run_workload(w, T.upload(host))
+    assert st == 0 and ("_split" in pbk.pbk_last_kernel()) == split and "tile64" in pbk.pbk_last_kernel(), pbk.pbk_last_kernel()
+    ref, pre = T.oracle_full(w, host)
+    err = T.rel_err(T.to_host_f64(out, w.out_dtype).reshape(ref.shape), ref, pre)
+    assert err <= TOL[BF16], err
 
 
 def test_repeats_streams_and_residual():
