@@ -27,8 +27,8 @@
 // through LDS to the first.  The chain of tiles is the bound there: 16 x 2048 x 64, causal:
 // 26.6 -> 23.5 us; 16 x 4096 x 128, causal: 102 -> 79; 6 x 4096 x 64: 44.6 -> 37.1.
 // QW = 2: a workgroup owns 64 queries, two waves of 32 per group.  There are twice as many of them, and under the causal diagonal a
-// long one and a short one share a compute unit, which otherwise waits for the longest: 16 x 2048 x 64, causal: 23.3 -> 18.9 us; 16 x 577 x
-// 64: 10.8 -> 8.3 (attention_form).
+// long one and a short one share a compute unit, which otherwise waits for the longest: 16 x 2048 x 64, causal: 23.2 -> 18.9 to 20.4 us by card; 16 x
+// 577 x 64: 10.8 -> 8.3 (attention_form).
 //
 // Register layouts (v_mfma_f32_32x32x16, D[i][j] += sum_k A[i][k] B[k][j]; a lane
 // supplies row i = lane%32 of A and column j = lane%32 of B, 8 consecutive k
@@ -686,7 +686,7 @@ static bool split_preferred(const AttnProblem& p) {
 //   15.6).  Up to 64 queries there are no more workgroups than before, so only where the
 //   keys are split anyway (128 x 64 x 2048 x 128: 33.7 and 32.0; but 64 x 64 x 64 x 64 4.7 and 5.6, 256 x 33 x 300 x 128 10.9 and 12.3);
 // - two per unit (D up to 64; at D = 128 their tiles do not fit the LDS together) under the diagonal, where a long one and a short one share a unit
-//   (16 x 2048 x 64: 23.3 and 18.9, 8 x 4096: 38.3 and 35.2; 24 x 1000: 15.0 and 15.6, 64 x 300: 8.3 and 9.6); without it the 128-row ones move half the keys
+//   (16 x 2048 x 64: 23.2 and 18.9 to 20.4 by card, 8 x 4096: 38.3 and 35.2; 24 x 1000: 15.0 and 15.6, 64 x 300: 8.3 and 9.6); without it the 128-row ones move half the keys
 //   (12 x 2048 x 64: 21.6 and 22.2);
 // - up to three under the diagonal for middling contexts (24 x 2048 x 64: 32.2 and 29.4, 18 x 2500: 38.6 and 35.1; 22 x 2900: 42.7 and 46.4, 42 x 1536: 27.8
 //   and 31.8, 64 x 700: 14.8 and 18.6);
