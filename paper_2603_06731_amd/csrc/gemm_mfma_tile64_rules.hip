@@ -98,6 +98,8 @@ bool mfma_tile64_preferred(const Problem& p) {
 //   2 x 4096 x 2560 8.2/12.4 and 9.2/10.2; 65 to 85 tiles: 2 x 4224 x 4096 9.2/14.1 and 10.2/11.6, x 5760 13.0/20.4 and 12.0/14.3, 8 x 5120 x
 //   13312 78 and 32; 86 to 128: 1 x 7552 x 5760 15.4/19.9 and 17.1/18.6, 1 x 6208 x 8192 22.1/23.7 and 20.2/21.4, 8 x 4096 x 14336 57 and 28; more than 8 rows
 //   from 4096 on: 12 x 6976 x 5696 14.8/22.3 and 15.7/18.0, 16 x 8192 x 4096 16.9 and 15.4; k-major 8 x 1024 x 4096 7.0 and 8.0.
+//   Results in fp32 only with four parts and more, whose four sums each are as many as ksplit's sixteen (its distance from 64 bits first, of the result: 16 x
+//   8192 x 4096, two parts, 1.15e-7 and 1.35e-7, 3 x 8200 x 5640, three, 1.28e-7 and 1.31e-7, 8 x 4096 x 14336, four, 1.86e-7 and 1.81e-7).
 //
 // Convolutions, whose addresses cost vector instructions that a second workgroup hides: up to two workgroups per unit, each with about five rounds
 // (batch x 14 x 14, 3 x 3; whole tiles, then by parts): 152 tiles, 36 rounds: 18.9 and 14.5 with 3; 104 tiles 18.8 and 12.5 with 4; 93 tiles, 36:
@@ -118,7 +120,7 @@ static int tile64_parts64(const Problem& p) {
     if (t32 <= 256) return p.K >= 5632 ? std::min(512 / (int)t64, 5) : 1;
     return t64 <= 170 ? (p.K >= 3328 ? 3 : 1) : p.K >= 4096 && p.M > 256 ? 2 : 1;
 }
-static int tile64_parts(const Problem& p, bool forced) {
+static int tile64_parts_of(const Problem& p, bool forced) {
     const long long all = (long long)((p.M + 31) / 32) * ((p.N + 63) / 64) * p.batch;
     const int rounds = (tile64_k(p) + T64_BK - 1) / T64_BK;
     if (all > 256) return 1;
@@ -140,6 +142,12 @@ static int tile64_parts(const Problem& p, bool forced) {
     if (rounds >= (p.M <= 16 ? 72 : 48)) parts = std::max(parts, std::min(256 / tiles, 5));
     if (!forced && parts == 2 && rounds < 14) return 1;
     return std::min(parts, forced ? rounds : rounds / 4);
+}
+
+static int tile64_parts(const Problem& p, bool forced) {
+    const int parts = tile64_parts_of(p, forced);
+    const bool ksplit_adds_sixteen = p.M <= 16 && !p.is_conv && !p.trans_b && !bits8(p) && p.out_dtype == DT_F32;
+    return !forced && ksplit_adds_sixteen && parts < 4 ? 1 : parts;
 }
 
 bool mfma_tile64_split_preferred(const Problem& p) { return tile64_parts(p, false) > 1 || tile64_parts64(p) > 1; }

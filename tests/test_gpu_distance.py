@@ -167,3 +167,25 @@ def test_convolution(now):
             ref = w.double().permute(3, 2, 0, 1).reshape(co, -1).cpu() @ cols
             yield call, ref.reshape(n, co, oh, oh).permute(0, 2, 3, 1).cuda()
     compare(problems(), "mfma:1", now, "tile64")
+
+
+@pytest.mark.parametrize("dtype", [BF16, F16])
+def test_few_rows_f32_results(dtype):
+    """Up to 16 rows over a row-major B with fp32 results: the automatic choice is no further from 64 bits than sixteen sums of k / 16 values."""
+    import torch
+    import paper_2603_06731_amd as pbk
+    for M, N, K in [(8, 14336, 4096), (16, 13184, 4992), (5, 8256, 2048), (16, 8192, 4096), (8, 5504, 6144), (3, 8200, 5640), (8, 4096, 14336), (16, 1024, 4888)]:
+        dist = {f: Distance() for f in ("ksplit", None)}
+        for seed in range(-(-200000 // (M * N))):
+            g = gen(seed)
+            A = torch.randn(M, K, generator=g, device="cuda").to(types(dtype))
+            B = (torch.randn(K, N, generator=g, device="cuda") * K ** -0.5).to(types(dtype))
+            ref = A.double() @ B.double()
+            for force in dist:
+                out = torch.empty(M, N, device="cuda")
+                with T.forced_kernel(force):
+                    assert pbk.pbk_matmul(A, B, out, None, M, N, K, K, N, N, dtype, F32, 0, 1.0, 0) == 0
+                dist[force].add(out, ref)
+        ratio = dist[None].rel() / dist["ksplit"].rel()
+        print(M, N, K, pbk.pbk_last_kernel(), f"{dist['ksplit'].rel():.3e} {ratio:.4f}", flush=True)
+        assert dist[None].n >= 2e5 and ratio <= 1.01, (M, N, K, ratio)
