@@ -728,12 +728,19 @@ static int gather_form(const Problem& p) {
 //   61 -> 32, 7 x 7, stride 2, one tile: 40 and 15.2; 3 x 21 x 21 x 100 -> 127, 3 x 3: 18.7 and 14.5;
 // - what short ones do not give back: 64 x 1003 x 501: 11.6 and 11.9, 300 x 300 x 301: 9.7 and 10.7, 130 x 2496 x 970, 60 tiles: 10.7 and 10.7;
 //   convolutions of 2 and 3 k-tiles: 9.3 and 9.8, 8.6 and 9.3.
-static int gather_parts(const Problem& p) {
+// rows: a row of taps is one tap.  The k-tiles are those of the K axis that the kernel then walks, up to eight times shorter than with a tap each (8 x 8 over one
+// channel: one k-tile for eight; two parts of it, one of them empty, 8.1, whole 5.9), and cost more each, so that three parts pay sooner with few tiles: up
+// to 32 from six k-tiles on, up to 64 from nine (whole, 2 parts, 3: 11 tiles, 6 k-tiles, 11.7, 11.2 and 10.9; 18, 7 11.6, 11.5 and 11.1; 50, 7 11.2, 11.7 and 12.2; 22, 9 13.7,
+// 12.2 and 11.3; 48, 11 15.5, 13.5 and 13.2; 61, 13 16.5, 14.8 and 14.8; 81, 11 16.2, 15.5 and 16.9; 13, 5 11.2, 11.8 and 11.6; 112, 7 11.0 and 12.7).
+static int gather_parts(const Problem& p, bool rows) {
     const long long tiles = (long long)((p.M + 63) / 64) * ((p.N + GBN - 1) / GBN) * p.batch;
-    const long long kt = ((p.is_conv ? (long long)p.conv.KH * p.conv.KW * ((p.conv.Cin + 7) & ~7) : p.K) + 63) / 64;
+    const long long tap = rows ? (long long)p.conv.KW * p.conv.Cin : p.conv.Cin, taps = rows ? p.conv.KH : (long long)p.conv.KH * p.conv.KW;
+    const long long kt = ((p.is_conv ? taps * ((tap + 7) & ~7LL) : p.K) + 63) / 64;
+    if (rows && kt < 15 && kt >= (tiles <= 32 ? 6 : tiles <= 64 ? 9 : 15)) return 3;
     if (tiles > 128 || kt < (p.is_conv ? 8 : 12)) return 1;
     const long long room = (long long)kScratchBytes / (64 * GBN * 4) / tiles;        // the parts' sums have to fit
     int parts = 1;
+    static_assert(3 * 64 * 64 * GBN * 4 <= kScratchBytes, "three parts of 64 tiles");
     while (parts < 8 && (parts + 1) * tiles <= 256 && parts < room && (parts + 1) * (parts + 3) <= kt) ++parts;
     return parts;
 }
@@ -749,7 +756,7 @@ hipError_t launch_mfma_gather(const Problem& p, hipStream_t stream, int force_cf
     if (force_cfg == 1 || force_cfg == 3) form = form == GATHER_DEEP64 ? GATHER_DEEP64 : GATHER_64;
     if (force_cfg == 4 || force_cfg == 5) form = GATHER_DEEP128;
     if (form == GATHER_DEEP64) {
-        const int parts = gather_parts(p);
+        const int parts = gather_parts(p, p.is_conv && fast && gather_rows_of_taps(p, false));
         int dev = 0;
         if (parts > 1 && hipGetDevice(&dev) == hipSuccess) {
             if (const ScratchUse use(dev, stream); use) {

@@ -70,3 +70,23 @@ def test_nan_reaches_only_its_windows(case):
         got = y.double().cpu()
         assert torch.all((got - ref).abs()[clean] <= 2.0 ** -8 * ref.abs()[clean] + 1e-4)
     assert hit.any() and not hit.all()
+
+
+@pytest.mark.parametrize("n,hw,Cin,k,split", [
+    (2, 16, 1, 8, False), (2, 30, 1, 9, False),         # one k-tile, three
+    (1, 16, 35, 3, True), (1, 16, 11, 5, False),        # four tiles of 64 rows: six k-tiles, five
+    (9, 16, 3, 11, False), (9, 16, 11, 7, True),        # 36 tiles: seven, nine
+    (17, 16, 3, 11, False), (17, 16, 11, 7, True),      # 68: two parts from eight on
+])
+def test_parts(n, hw, Cin, k, split):
+    """Workgroups share a tile by the k-tiles that are walked, not by those of a tap each: none is without one."""
+    import paper_2603_06731_amd as pbk
+    w = wl.Workload("taps_parts", "conv", BF16, BF16, C.EPI_BIAS_RELU, n=n, H=hw, W=hw, Cin=Cin, Cout=24, KH=k, KW=k, pad=(k // 2, (k - 1) // 2) if k % 2 else (0, 0),
+                    dist_b=("normal", float(np.sqrt(2.0 / (k * k * Cin)))))
+    host = wl.make_inputs(w)
+    with T.forced_kernel(None):
+        st, out = T.run_workload(w, T.upload(host))
+    assert st == 0 and "gather_64x128x64" in pbk.pbk_last_kernel() and ("split" in pbk.pbk_last_kernel()) == split, pbk.pbk_last_kernel()
+    ref, pre = T.oracle_full(w, host)
+    err = T.rel_err(T.to_host_f64(out, w.out_dtype).reshape(ref.shape), ref, pre)
+    assert err <= T.TIGHT[BF16], err
