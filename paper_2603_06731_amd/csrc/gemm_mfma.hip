@@ -39,10 +39,15 @@ bool mfma_supported(const Problem& p) {
     return true;
 }
 
+// A launch holds fewer than 2^32 threads: from so many tiles on the forms with 512 threads a tile cannot be launched (2^23 small entries of a batched
+// product, or 2^30 rows).
+static constexpr long long kTilesOf512 = 1LL << 23;
+static long long square_tiles(const Problem& p) { return (long long)((p.M + 127) / 128) * ((p.N + 127) / 128) * p.batch; }
+
 // fp32 operands take the staged kernel only when there is enough work to fill the chip with 128-row tiles.  (Plain products of up to
 // 4096 tiles of 16 x 16 take the kernel without staging before this is asked: small_f32_preferred.)
 bool mfma_preferred(const Problem& p) {
-    if (p.in_dtype != DT_F32) return true;
+    if (p.in_dtype != DT_F32) return p.in_dtype == DT_BF16 || p.in_dtype == DT_F16 || square_tiles(p) < kTilesOf512;      // (8-bit types: 512 threads in every form)
     long long t = (long long)((p.M + 127) / 128) * ((p.N + 127) / 128) * p.batch;
     return p.M >= 128 && p.N >= 128 && t >= 64;
 }
@@ -63,8 +68,9 @@ bool mfma_preferred(const Problem& p) {
 // up to two and a half (k-major B: 17 x 512 x 512 x 128, 272 tiles, 7.15 and 6.76, x 160 8.11 and 7.94, x 192 7.70 and 7.82; 9 x 768 x 768 x 128, 324 tiles, 7.35 and
 // 7.25; 40 x 384 x 384 x 128, 360 tiles, 7.58 and 7.73).
 static int square_config(const Problem& p) {
-    const long long t = (long long)((p.M + 127) / 128) * ((p.N + 127) / 128) * p.batch;
+    const long long t = square_tiles(p);
     const bool b8 = p.in_dtype != DT_BF16 && p.in_dtype != DT_F16;
+    if (t >= kTilesOf512 && !b8) return p.is_conv ? 6 : 3;        // 256 threads a tile
     if (t > 256) return !b8 && !p.is_conv && p.K <= (t <= 330 ? 160 : 96) && t <= 448 && p.N >= 256 && p.out_dtype != DT_F32 && !epi_has_bias(p.epi) && !p.R ? 3 : 1;
     const int bk = b8 ? 128 : 64, kt = (p.K + bk - 1) / bk;        // values per k-tile, k-tiles
     if (p.is_conv) return p.conv.Cin % bk != 0 && kt <= 8 ? 1 : 2;
@@ -170,9 +176,9 @@ static int choose_config(const Problem& p) {
 static bool convt_classes_fit(const Problem& p) {
     // where k-tiles (up to 64 deep) span taps, any weight row is reached from the first one with a 32-bit offset
     if (p.conv.Cin % 64 != 0 && (int64_t)p.K * p.ldb * 2 >= ((int64_t)1 << 31)) return false;
-    // A launch holds fewer than 2^32 threads: 2^24 tiles of 256.  (A stride beyond the image makes nearly every output pixel a
+    // A launch holds fewer than 2^32 threads: fewer than 2^23 tiles of 512.  (A stride beyond the image makes nearly every output pixel a
     // class, and a tile, of its own.)
-    return convt_row_tiles(p, 128) * ((p.N + 127) / 128) < (1 << 24);
+    return convt_row_tiles(p, 128) * ((p.N + 127) / 128) < kTilesOf512;
 }
 
 // Classes, or all taps for every output pixel?  By how much the longest class shortens the k loop.  Its rows of C are apart, its tiles
@@ -243,7 +249,7 @@ static hipError_t launch_convt(const Problem& p_in, hipStream_t stream, int forc
         }
         *name = cfg >= 14 ? names[cfg - 14] : cfg == 1 ? "mfma16_128x128x64_w2x4_s2_classes" : "mfma16_128x128x64_w2x4_s4_classes";
     } else {
-        if (cfg != 0 && cfg != 1 && cfg != 6) cfg = wide ? 6 : 1;
+        if (cfg != 0 && cfg != 1 && cfg != 6) cfg = wide || square_tiles(p) >= kTilesOf512 ? 6 : 1;
         *name = mfma_config_name(cfg, false);
     }
     const int group_m = group_m_override() > 0 ? group_m_override() : 8;

@@ -116,6 +116,25 @@ def test_more_classes_than_a_launch_holds(force):
     assert bool((y == bias.bfloat16()).all())
 
 
+@pytest.mark.parametrize("force", [None, "mfma:2", "mfma:14"])
+def test_more_tiles_than_a_launch_holds(force):
+    """Strides of 4096 and 3000: 12 million classes, fewer than a launch holds with 256 threads each, more than with the 512 of these tiles."""
+    s, Cin = (4096, 3000), 128
+    assert 2 ** 23 <= s[0] * s[1] < 2 ** 24
+    geom = (1, 2, 2, Cin, 8, 2, 2, s, (0, 0), (1, 1))
+    x, w, bias = operands(geom, 6)
+    y, kern = transpose(x, w, bias, geom, force)
+    assert "mfma" in kern and "classes" not in kern, kern
+    for ih in range(2):
+        for iw in range(2):
+            for kh in range(2):
+                for kw in range(2):
+                    at = y[0, ih * s[0] + kh, iw * s[1] + kw]
+                    assert close(at, bias + x[0, ih, iw].float() @ w[kh, kw].float()), (ih, iw, kh, kw)
+                    at.copy_(bias)
+    assert bool((y == bias.bfloat16()).all())
+
+
 @pytest.mark.parametrize("case", CASES)
 def test_residue_classes_ring(case):
     """The classes themselves, also where the automatic choice keeps all taps in the loop."""

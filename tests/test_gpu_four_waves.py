@@ -37,3 +37,23 @@ def test_dispatch(batch, M, N, K, out_dtype, epi, four):
     err, kern = run_case(batch, M, N, K, BF16, out_dtype, 0, epi, force=None, bias_on=epi == C.EPI_BIAS)
     assert ("128x128x64_w2x2_s2" in kern) == four, kern
     assert err <= TOL[out_dtype], err
+
+
+@pytest.mark.parametrize("dtype,kernel", [("bf16", "128x128x64_w2x2"), ("e4m3", "generic")])
+def test_more_entries_than_a_launch_holds(dtype, kernel):
+    """2^23 entries of one row, each with a tile of its own, which has 512 threads on eight waves: a launch holds fewer than 2^32 threads.  B is shared
+    (stride 0)."""
+    import torch
+    import paper_2603_06731_amd as pbk
+    n, k = 2 ** 23, 16
+    g = torch.Generator(device="cuda").manual_seed(3)
+    td, code, raw = (torch.bfloat16, pbk.PBK_BF16, lambda x: x) if dtype == "bf16" else (torch.float8_e4m3fn, pbk.PBK_FP8_E4M3, lambda x: x.view(torch.uint8))
+    A, B = (torch.randn(r, k, generator=g, device="cuda").to(td) for r in (n, k))
+    out = torch.full((n, k), float("nan"), dtype=torch.bfloat16, device="cuda")
+    with T.forced_kernel(None):
+        st = pbk.pbk_batched_matmul(raw(A), raw(B), out, None, n, 1, k, k, k, k, k, k, 0, k, code, pbk.PBK_BF16, 0, 1.0, 0)
+    assert st == 0 and kernel in pbk.pbk_last_kernel(), (st, pbk.pbk_last_kernel())
+    for i in range(0, n, 2 ** 20):
+        ref = A[i:i + 2 ** 20].float() @ B.float()
+        # one rounding to bf16 (2^-9 of the value), fp32 sums of sixteen terms of order one
+        assert bool(((out[i:i + 2 ** 20].float() - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-5).all())
