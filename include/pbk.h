@@ -325,8 +325,8 @@ const char* pbk_last_kernel(void);
  *   "bstat"       the B-stationary kernel for short contractions (K <= 256) over many rows;
  *   "ksplit"      a few rows, k split over the waves: "ksplit:0" 64 columns per workgroup (32 where a row-major B has no aligned
  *                 8-byte pieces), "ksplit:1" 32;
- *   "tile64"      64-wide tiles: "tile64:0" 64 x 64 with a deep ring, "tile64:1" 32 x 64, "tile64:2" 64 x 64, two per compute unit,
- *                 "tile64:8" 32 x 64 with the contraction split over workgroups as well (not split: as "tile64:1");
+ *   "tile64"      64-wide tiles: "tile64:0" 64 x 64 with a deep ring, "tile64:1" 32 x 64, "tile64:2" 64 x 64, two per compute unit
+ *                 (0 and 2: 16-bit types), "tile64:8" 32 x 64 with the contraction split over workgroups as well (not split: as "tile64:1");
  *   "decode"      attention of up to 16 queries, keys split over the waves: "decode:1", "decode:2", "decode:4" workgroups per
  *                 batch entry (as many as the head dimension has 32-column groups, at most), each with its own columns of V;
  *                 "decode:8" the keys split over workgroups, up to 96 entries, with any context of two steps of 32 keys.

@@ -37,6 +37,7 @@ static hipError_t launch_tile64(const Problem& p, hipStream_t stream, int cfg, i
     default: return launch_tile64_e5m2(to_k_units(p), stream, cfg, parts, use);
     }
 }
+bool mfma_tile64_built(const Problem& p, int cfg) { return !bits8(p) || (cfg != 0 && cfg != 2); }       // 8-bit types: 32 x 64 only
 static int tile64_k(const Problem& p) { return bits8(p) ? p.K / 2 : p.K; }
 static int tile64_choice(const Problem& p) {
     const int K = tile64_k(p);

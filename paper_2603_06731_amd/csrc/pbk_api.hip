@@ -101,7 +101,7 @@ pbk_status dispatch(const pbk::Problem& p_in, hipStream_t stream) {
     // a few rows, or too few 128-wide tiles for the chip: the contraction is split over the waves of a workgroup
     const bool can_ksplit = pbk::mfma_ksplit_supported(p), can_tile64 = pbk::mfma_tile64_supported(p);
     if ((force == FORCE_MFMA && !can_mfma && !can_gather) || (force == FORCE_GATHER && !can_gather) || (force == FORCE_SMALL && !can_small) ||
-        (force == FORCE_BSTAT && !can_bstat) || (force == FORCE_KSPLIT && !can_ksplit) || (force == FORCE_TILE64 && !can_tile64) ||
+        (force == FORCE_BSTAT && !can_bstat) || (force == FORCE_KSPLIT && !can_ksplit) || (force == FORCE_TILE64 && !(can_tile64 && pbk::mfma_tile64_built(p, cfg))) ||
         force == FORCE_DECODE)
         return PBK_ERR_UNSUPPORTED;
     // (a call that finds no scratch memory goes on to the kernels that need none)

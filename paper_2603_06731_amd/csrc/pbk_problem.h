@@ -108,6 +108,7 @@ bool mfma_ksplit_supported(const Problem& p);
 bool mfma_ksplit_preferred(const Problem& p);
 hipError_t launch_mfma_ksplit(const Problem& p, hipStream_t stream, int force_cfg, const char** name);
 bool mfma_tile64_supported(const Problem& p);
+bool mfma_tile64_built(const Problem& p, int force_cfg);       // the form of this id, for the problem's type (-1: any)
 bool mfma_tile64_preferred(const Problem& p);
 hipError_t launch_mfma_tile64(const Problem& p, hipStream_t stream, int force_cfg, const char** name);
 // tile64 with the contraction split over workgroups as well, in scratch memory of the stream; launch: false where the problem is not

@@ -105,3 +105,20 @@ def test_dispatch_int8(m, n, k, tile64):
     got, kernel = run_matmul(A, B, q, 1, True, None)
     assert ("tile64" in kernel) == tile64, kernel
     assert np.array_equal(got, oracle.matmul_int8(A, B, trans_b=1, **q))
+
+
+@pytest.mark.parametrize("force", ["tile64:0", "tile64:2"])
+def test_forms_that_are_not_built(force):
+    """64 x 64 tiles are built for the 16-bit types: refused, and nothing is launched."""
+    import torch
+    import paper_2603_06731_amd as pbk
+    m, n, k = 64, 64, 256
+    a, b = (torch.ones(r, k, dtype=torch.int8, device="cuda") for r in (m, n))
+    out, scale = torch.full((m, n), 7, dtype=torch.int8, device="cuda"), torch.ones(n, device="cuda")
+    with T.forced_kernel(force):
+        st = pbk.pbk_matmul_int8(a, b, out, m, n, k, k, k, n, 1, scale, None, 0.0, None, None, 0, 1.0, INT8)
+        assert "not supported" in pbk.pbk_status_string(st), st
+        o = torch.full((m, n), 7.0, device="cuda")
+        st = pbk.pbk_matmul(a.view(torch.uint8), b.view(torch.uint8), o, None, m, n, k, k, k, n, E4M3, F32, 1, 1.0, C.EPI_NONE)
+        assert "not supported" in pbk.pbk_status_string(st), st
+    assert bool((out == 7).all()) and bool((o == 7).all())
