@@ -3,7 +3,9 @@
 // 256 x 256 x 256 in fp32, 4.9 us a call on the host, of which the launch and the choice of the kernel are the half.
 //
 // A function here returns None, and calls nothing, for anything but plain arguments (integers in range, floats, None, objects with data_ptr() or
-// cuda_stream): the binding then goes through ctypes, whose conversions and errors are the contract.
+// cuda_stream): the binding then goes through ctypes, whose conversions and errors are the contract.  What a data_ptr() or cuda_stream of the caller's
+// raises leaves this call as it is (but AttributeError and TypeError, which an object without one gives as well): nothing of the caller's runs again after it
+// has failed, and no interrupt is lost.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 #include <stdint.h>
@@ -26,10 +28,13 @@ bool as_address(PyObject* o, void*& v) {
     return true;
 }
 
-// the address that an attribute (called: a method) of `o` gives
+// the address that an attribute (called: a method) of `o` gives.  False with an exception set: the caller's own
 bool address_of(PyObject* o, PyObject* name, bool call, void*& v) {
     PyObject* r = call ? PyObject_CallMethodNoArgs(o, name) : PyObject_GetAttr(o, name);
-    if (!r) { PyErr_Clear(); return false; }
+    if (!r) {
+        if (PyErr_ExceptionMatches(PyExc_AttributeError) || PyErr_ExceptionMatches(PyExc_TypeError)) PyErr_Clear();
+        return false;
+    }
     const bool ok = as_address(r, v);
     Py_DECREF(r);
     return ok;
@@ -70,7 +75,10 @@ template <int ID, typename R, typename... A> struct Call<ID, R(A...)> {
     inline static R (*fn)(typename Passed<A>::type...) = nullptr;      // set by bind(): the library is loaded later than this module
     template <size_t... I> static PyObject* run(PyObject* const* args, std::index_sequence<I...>) {
         std::tuple<typename Passed<A>::type...> v;
-        if (!(get(args[I], std::get<I>(v)) && ...)) Py_RETURN_NONE;
+        if (!(get(args[I], std::get<I>(v)) && ...)) {
+            if (PyErr_Occurred()) return nullptr;
+            Py_RETURN_NONE;
+        }
         R r;
         Py_BEGIN_ALLOW_THREADS
         r = fn(std::get<I>(v)...);

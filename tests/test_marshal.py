@@ -103,3 +103,30 @@ def test_keywords_and_missing_arguments(monkeypatch):
     assert pbk.pbk_matmul(*args[:-1]) == 0
     with pytest.raises(TypeError):
         pbk.pbk_matmul(*args[:-2])
+
+
+@pytest.mark.parametrize("error", [KeyboardInterrupt, MemoryError, RuntimeError, AttributeError, TypeError])
+def test_an_error_of_the_callers_own(error):
+    """What a data_ptr() or cuda_stream raises reaches the caller, and the method does not run once more behind its back (AttributeError and TypeError
+    are also what an object without one gives: ctypes judges them)."""
+    class Once:
+        calls = 0
+
+        def data_ptr(self):
+            self.calls += 1
+            if self.calls == 1:
+                raise error("once")
+            return 4096
+
+        cuda_stream = property(data_ptr)
+
+    for at in (0, -1):
+        args = arguments("pbk_matmul")
+        assert pbk.pbk_matmul(*args) == 0
+        args[at] = one = Once()
+        if error in (AttributeError, TypeError):
+            assert binding._marshal.pbk_matmul(*args) is None and one.calls == 1
+            continue
+        with pytest.raises(error, match="once"):
+            pbk.pbk_matmul(*args)
+        assert one.calls == 1
