@@ -70,16 +70,23 @@ def _compile(src, force: bool) -> str:
 
 
 def build_marshal(force: bool = False) -> None:
-    """Compile the binding's marshalling module; without Python's headers the binding works through ctypes alone."""
+    """Compile the binding's marshalling module.  Without Python's headers or a C++ compiler the binding works through ctypes alone; a module
+    of earlier sources does not stay behind then."""
     src, include = os.path.join(CSRC, "marshal.cpp"), sysconfig.get_paths()["include"]
-    if not os.path.exists(os.path.join(include, "Python.h")):
-        print(f"{include}/Python.h is missing: the Python binding will marshal through ctypes")
-        return
     newest = max(os.path.getmtime(src), os.path.getmtime(os.path.join(os.path.dirname(HERE), "include", "pbk.h")))
-    if force or not os.path.exists(MARSHAL) or os.path.getmtime(MARSHAL) < newest:
-        tmp = MARSHAL + f".tmp{os.getpid()}"
+    if not force and os.path.exists(MARSHAL) and os.path.getmtime(MARSHAL) >= newest:
+        return
+    tmp = MARSHAL + f".tmp{os.getpid()}"
+    try:
+        if not os.path.exists(os.path.join(include, "Python.h")):
+            raise OSError(f"{include}/Python.h is missing")
         subprocess.check_call([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", f"-I{include}", src, "-o", tmp])
         os.replace(tmp, MARSHAL)
+    except (OSError, subprocess.CalledProcessError) as e:
+        for path in (tmp, MARSHAL):
+            if os.path.exists(path):
+                os.remove(path)
+        print(f"{e}: the Python binding will marshal through ctypes")
 
 
 def build(force: bool = False, jobs: int = 8) -> str:
