@@ -280,21 +280,24 @@ __global__ __launch_bounds__(SWAVES * 64, 2) void gemm_mfma_bstat_kernel(Problem
     }
 }
 
-// Steps that a workgroup walks: for one to six rounds of the slots of the chip (two workgroups per compute unit) the shortest walk that makes no more, and of
-// these the one that costs least.  A round costs its walk and half a step to start with (B is fetched once per workgroup); a last round that is partly
-// filled costs half of what is missing, because its workgroups have more of the memory to themselves.  One walk per slot at most, before: 37 x 1984 x
-// 1984 x 32, 296 columns of tiles on 512 slots, 87 us with one walk of 31 steps each, 71, 69, 66, 66 and 65 with 2, 3, 4, 5 and 8; 34 x 1856 x 1856 x 64 67 and
-// 52 (8); 48 x 1536 x 1536 x 128 68.6 and 60.8 (3); 40 x 640 x 640 x 64 11.7 and 10.0 (5); 64 x 2048 x 2048 x 128, 512 columns, stays on one.
-int walk_steps(int steps, long long cols, long long slots) {
+// Steps that a workgroup walks: for one to six rounds of the chip's slots (two workgroups per compute unit), by halves, the shortest walk that makes no more, and
+// of these the one that costs least: n workgroups per unit, each its walk and about a step to start with (B is fetched once per workgroup).  The last one
+// of an odd number has its unit to itself: with pieces of B up to 64 deep it then ends sooner, with deeper ones it takes as long as two.
+// us: 37 x 1984 x 1984 x 32, 296 columns of tiles on 512 slots, 87 with one walk of 31 steps each, 71, 69, 66, 66 and 65 with 2, 3, 4, 5 and 8; 34 x 1856 x
+// 1856 x 64 67 and 52 (8); 48 x 1536 x 1536 x 128 68.6 and 60.8 (3); 34 x 896 x 896 x 64, walks of 5, 3 and 2 of 14 steps: 13.9, 13.4 and 14.9; 45 x 768 x 768 x
+// 128, 4 and 2 of 12: 15.1 and 18.3, 25 x 1536 x 1536 x 128, 8 and 4 of 24: 25.4 and 28.6, 16 x 1280 x 1280 x 256, 4 and 2 of 20: 20.2 and 23.6.  Over 494 shapes with
+// all their walks this choice is 1.6 % behind the best one from memory and 1.2 from the caches up to K = 64, 0.3 and 0.1 beyond.
+int walk_steps(int steps, long long cols, long long units, bool shallow) {
     int best = steps;
-    double least = 0.0;
-    for (int rounds = 1; rounds <= 6; ++rounds) {
-        const long long parts = rounds * slots / cols;
+    long long least = 0;
+    for (int per_unit = 2; per_unit <= 12; ++per_unit) {
+        const long long parts = per_unit * units / cols;
         if (parts < 1) continue;
         const int walk = parts >= steps ? 1 : (int)((steps + parts - 1) / parts);
-        const double x = (double)((steps + walk - 1) / walk * cols) / (double)slots;
-        const double full = (double)(long long)(x + 0.999999), cost = 0.5 * (full + (x > 1.0 ? x : 1.0)) * (walk + 0.5);
-        if (least == 0.0 || cost < least) { least = cost; best = walk; }
+        long long n = ((long long)((steps + walk - 1) / walk) * cols + units - 1) / units;
+        if (n < 2) n = 2;
+        const long long cost = (10 * n + (n % 2 ? (shallow ? -2 : 10) : 0)) * (5 * walk + (shallow ? 4 : 5));
+        if (least == 0 || cost < least) { least = cost; best = walk; }
         if (walk == 1) break;
     }
     return best;
@@ -324,7 +327,7 @@ hipError_t launch_bstat_one(const Problem& p, hipStream_t stream) {
     map.tiles_n = (p.N + SBN - 1) / SBN;
     const int steps = (p.M + SBM - 1) / SBM;
     const long long cols = (long long)map.tiles_n * p.batch;
-    const int chunk_steps = walk_steps(steps, cols, (long long)ds.cus * 2);
+    const int chunk_steps = walk_steps(steps, cols, (long long)ds.cus, KP == 1);
     map.chunk_rows = chunk_steps * SBM;
     map.msplit = (steps + chunk_steps - 1) / chunk_steps;
     const long long total = cols * map.msplit;
