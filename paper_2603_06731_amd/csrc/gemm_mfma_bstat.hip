@@ -368,14 +368,18 @@ bool mfma_bstat_supported(const Problem& p) {
 // 256-wide strip (us, the other kernels first):
 // - K up to 64 from 384 steps on (28 x 512 x 512, 448 steps: 7.13 and 6.71; 48 x 320 x 320 7.76 and 6.02; 33 x 704 x 704 13.9 and 10.7; 25088 x 256 7.40 and 6.85;
 //   26 x 384 x 384 x 32, 312: 5.25 and 5.65);
-// - up to 128 the same (16 x 640 x 640 7.93 and 7.40), but between one step and one and a half for every slot, which take two rounds (44 x 448 x 448, 616:
-//   10.4 and 11.6; 25 x 704 x 704 11.2 and 10.8, 38 x 640 x 640, 1140: 17.3 and 13.0);
-// - beyond that from 900 on (29 x 576 x 576 x 256, 783: 14.5 and 14.4, 22 x 640 x 640, 660: 13.8 and 15.6; 32 x 832 x 832 25.4 and 22.3).
+// - up to 128 the same for batched products, whose operands the layer before has left in the caches (from memory, from the caches: 8 x 1024 x 1024 9.2/8.4 and 9.9/7.9;
+//   plain ones, 32000 x 256 10.1/8.5 and 11.8/8.5, 12800 x 512 9.0/8.0 and 9.8/8.0, only from 768 steps on), but between one step and one and a half for every
+//   slot, which take two rounds (44 x 448 x 448, 616: 10.4 and 11.6; 25 x 704 x 704 11.2 and 10.8, 38 x 640 x 640, 1140: 17.3 and 13.0);
+// - up to 192 from 900 on (from memory 28800 x 512, 900: 16.7 and 15.5, 70400 x 256, 1100: 27.5 and 20.6);
+// - beyond that from the first step on that the 128 x 256 tiles do not hold in one round, two per unit, which are 2 to 5 % ahead before (59584 x 256, 931:
+//   19.9/16.1 and 20.6/16.6, 25 x 768 x 768, 900: 18.1/14.8 and 18.7/15.6; 70400 x 256, 1100: 30.2/23.2 and 23.4/19.5; 17600 x 1024, 1100: 25.6/22.6 and 21.2/18.7).
 bool mfma_bstat_preferred(const Problem& p) {
     if (p.M < 256 || p.N < 256) return false;
     const long long steps = (long long)((p.M + SBM - 1) / SBM) * ((p.N + SBN - 1) / SBN) * p.batch;
+    if (p.K > 192) return steps > 1024;
     if (p.K > 128) return steps >= 900;
-    return steps >= 384 && (p.K <= 64 || steps <= 512 || steps >= 768);
+    return steps >= (p.K <= 64 || p.batch > 1 ? 384 : 768) && (p.K <= 64 || steps <= 512 || steps >= 768);
 }
 
 hipError_t launch_mfma_bstat(const Problem& p, hipStream_t stream, const char** name) {
