@@ -198,12 +198,15 @@ static int convt_class_k(const Problem& p) {
     return ((p.conv.KH + h.step.d - 1) / h.step.d) * ((p.conv.KW + w.step.d - 1) / w.step.d) * p.conv.Cin;     // (at most K)
 }
 
-// Residue classes on 32 x 64 tiles (gemm_mfma_tile64.hip), as long as the 256 compute units hold all of them, two each, and two rounds of their k.  Times in
+// Residue classes on 32 x 64 tiles (gemm_mfma_tile64.hip), as long as the 256 compute units hold all of them, two each, or, of a single round of k and up to 64 columns, one each.  Times in
 // us, 128 x 128 tiles first: 140 tiles, Cin x taps of a class = 1024 12.8 and 9.9, 24 tiles, 512 9.4 and 7.8, 92 tiles, 256 7.8 and 6.9, 112 tiles, 128 7.7 and 6.4,
-// 512 tiles 7.7 and 7.2, 408 tiles, 1024 12.9 and 11.5, 332 tiles, 512 9.6 and 9.2, but 140 tiles, 64 5.9 and 6.4; 516 tiles, 256 7.8 and 11.1.
+// 408 tiles, 1024 12.9 and 11.5, 332 tiles, 512 9.6 and 9.2, but 140 tiles, 64 5.9 and 6.4; 516 tiles, 256 7.8 and 11.1; 128, up to 256 tiles 0.92 of the time
+// over 230 sizes, 257 to 512 tiles up to 64 columns 1.02 to 1.08 (8 x 53 x 9 x 128 -> 32, 2 x 2, stride 2, 6.7 and 7.2; 9 x 22 x 14 x 32 -> 32, 3 x 3, 6.8 and
+// 7.1), 128 columns 0.90 to 0.92 (10 x 13 x 12 x 32 -> 128, 4 x 4, 392 tiles, 8.0 and 7.2).
 // (Any weight row is reached from the first one with a 32-bit offset.)
 static bool convt_tile64(const Problem& p) {
-    return convt_class_k(p) >= 128 && convt_row_tiles(p, 32) * ((p.N + 63) / 64) <= 512 && ((int64_t)p.K + 128) * p.ldb * 2 < ((int64_t)1 << 31);
+    const int k = convt_class_k(p);
+    return k >= 128 && convt_row_tiles(p, 32) * ((p.N + 63) / 64) <= (k > 128 || p.N > 64 ? 512 : 256) && ((int64_t)p.K + 128) * p.ldb * 2 < ((int64_t)1 << 31);
 }
 static bool convt_by_class(const Problem& p, bool wide) {
     return p.K - convt_class_k(p) >= (!wide ? 128 : p.conv.Cin % 64 == 0 ? 320 : 640) && convt_classes_fit(p);

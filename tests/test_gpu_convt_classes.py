@@ -198,3 +198,11 @@ def test_tiles_of_64_columns(case, tiles64, dtype, out_dtype):
     import paper_2603_06731_amd as pbk
     test_residue_classes(case, dtype, out_dtype, None)
     assert pbk.pbk_last_kernel().endswith("tile64_32x64_s3_classes") == tiles64, pbk.pbk_last_kernel()
+
+
+@pytest.mark.parametrize("Cin,Cout,hw,tiles64", [(128, 64, 32, True), (128, 64, 33, False), (136, 64, 33, True), (128, 72, 24, True)])
+def test_tiles_of_64_columns_single_round(Cin, Cout, hw, tiles64):
+    """One tap a class: 128 values of k, a single round, up to 256 tiles; two rounds, and more than 64 columns, beyond."""
+    import paper_2603_06731_amd as pbk
+    test_residue_classes((2, hw, hw, Cin, Cout, 2, 2, (2, 2), (0, 0), (0, 0), (1, 1)), BF16, BF16, None)
+    assert ("tile64" in pbk.pbk_last_kernel()) == tiles64, pbk.pbk_last_kernel()
