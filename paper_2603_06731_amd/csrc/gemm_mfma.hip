@@ -121,10 +121,12 @@ static int pair_config8(const Problem& p, long long t128, int least) {
 // - k-major B from 512 on (2.5 to 20 %), and beyond 256 wherever there are more than 256 tiles of 128 x 256, whose k-major form is slow (2163 x 4608 x 320:
 //   16.1 and 13.3, 7133 x 3520 x 264 30.3 and 27.5; 1335 x 3904 x 448, 256 of them: 11.0 both);
 // - convolutions whose channels 64 divides (a 64-deep piece of the image lies inside one tap) from K = 512 on (16464 x 256 x 576: 13.4 and 13.0; 23520 x
-//   256 x 128: 8.5 and 8.9), up to 768 for at most three rounds (147392 x 256 x 576 53.8 and 51.9; five rounds, 144256 x 512 x 576: 93 and 100).
+//   256 x 128: 8.5 and 8.9), up to 768 for at most two rounds of fewer rows than 256 (3 x 3, 56 x 56 x 64, images -> channels, from memory and from the caches: 23 ->
+//   256, 160 rows, 37.7/32.7 and 33.4/29.8, 35 -> 256, 224 rows, 43.2/38.0 and 41.5/38.0; 256 rows, 20 -> 512 56.7/47.3 and 58.0/50.5, 38 -> 256 57.0/46.3 and
+//   57.0/49.4; three rounds, 50 -> 256 72.8/60.2 and 76.9/68.4, 47 -> 256, all full, 57.1/48.8 and 53.3/48.6).
 static bool pair_preferred(const Problem& p, const PairChoice& c, long long t, long long t128) {
     if (p.M < 128 || p.N <= 128 || c.cost > square_cost(t128, p.K)) return false;
-    if (p.is_conv) return p.conv.Cin % 64 == 0 && p.K >= 512 && (p.K >= 768 || c.rounds <= 3);
+    if (p.is_conv) return p.conv.Cin % 64 == 0 && p.K >= 512 && (p.K >= 768 || (c.rounds <= 2 && c.height < 256));
     if (p.trans_b) return p.K >= 512 || (p.K > 256 && t > 256);
     return p.K >= 640 || (p.K >= 320 && t > 256 && c.height < 256);
 }
