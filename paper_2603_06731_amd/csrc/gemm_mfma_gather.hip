@@ -710,7 +710,8 @@ bool mfma_gather_preferred(const Problem& p) {
 //   5 x 149 x 149 x 100 -> 64, 7 x 7, stride 2 93.2 and 80.4; 3 x 161 x 161 x 3 -> 64, 7 x 7, stride 2 19.1 and 16.3; 128-row tiles of four waves first: 1993 x
 //   1146 x 3993, k-major B 63.9 and 52.3, 2363 x 1394 x 663 20.8 and 19.2), but a short product (942 x 2430 x 241: 14.0 and 14.1);
 // - a convolution whose 64-row tiles a unit holds three of: those (2 x 134 x 134 x 100 -> 65, 7 x 7, 281 tiles of 128 rows: 126 and 117; 7 x 75 x 75 x 3 -> 65,
-//   7 x 7 26.7 and 24.6; 392 tiles, 4 x 112 x 112 x 35 -> 128, 3 x 3: 21.4 and 27.2);
+//   7 x 7 26.7 and 24.6; 392 tiles, 4 x 112 x 112 x 35 -> 128, 3 x 3: 21.4 and 27.2), unless they have up to 32 columns, a long contraction and taps that rows do
+//   not shorten (128-row ones first: 3 x 113 x 113 x 127 -> 32, 5 x 5, 81.3 and 87.8; 2 x 150 x 150 x 119 -> 32, 7 x 7, 146 and 156; x 100, which they shorten, 122 and 115);
 // - beyond that two 128-row ones per unit.
 enum : int { GATHER_128 = 0, GATHER_64, GATHER_DEEP64, GATHER_DEEP128 };
 static int gather_form(const Problem& p) {
@@ -718,7 +719,7 @@ static int gather_form(const Problem& p) {
     const long long t128 = (long long)((p.M + 127) / 128) * cols * p.batch, t64 = (long long)((p.M + 63) / 64) * cols * p.batch;
     if (t64 <= 256) return GATHER_DEEP64;
     if (t128 <= 256) return p.is_conv || p.K > 512 ? GATHER_DEEP128 : GATHER_64;
-    return p.is_conv && t64 <= 768 ? GATHER_64 : GATHER_128;
+    return p.is_conv && t64 <= 768 && !(p.N <= 32 && p.K >= 3072 && !gather_rows_of_taps(p, true)) ? GATHER_64 : GATHER_128;
 }
 
 // Workgroups that share a tile (1: tiles are not split): up to one per compute unit, and up to eight, p of them from p (p + 2) k-tiles of 64 on,

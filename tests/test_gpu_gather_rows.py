@@ -86,3 +86,11 @@ def test_dispatch_conv(hw, cout, kernel):
     """4225 rows x 4 columns of tiles: 268 of 64 rows; 8281: 260 of 128 rows; 12100: 760 of 64 rows; 12544: 784."""
     w = wl.Workload("gather_form", "conv", BF16, BF16, C.EPI_BIAS_RELU, n=1, H=hw + 1, W=hw + 1, Cin=9, Cout=cout, KH=2, KW=2, dist_b=("normal", 0.2))
     G.check_workload(w, kernel)
+
+
+@pytest.mark.parametrize("cin,cout,kernel", [(127, 32, "128x128x32"), (127, 40, "64x128x32"), (100, 32, "64x128x32")])
+def test_dispatch_conv_narrow(cin, cout, kernel):
+    """600 tiles of 64 rows, 7 x 7: up to 32 columns, with channels that a row of taps does not shorten, on 128 rows."""
+    w = wl.Workload("gather_narrow", "conv", BF16, BF16, C.EPI_BIAS_RELU, n=1, H=196, W=196, Cin=cin, Cout=cout, KH=7, KW=7, pad=(3, 3),
+                    dist_b=("normal", float(np.sqrt(2.0 / (49 * cin)))))
+    G.check_workload(w, kernel)
