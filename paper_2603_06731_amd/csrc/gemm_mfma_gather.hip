@@ -751,25 +751,30 @@ static int gather_parts(const Problem& p, bool rows) {
 hipError_t launch_mfma_gather(const Problem& p, hipStream_t stream, int force_cfg, const char** name) {
     const bool forced_wide = force_cfg == 2 || force_cfg == 3 || force_cfg == 5;
     const bool bf16 = p.in_dtype == DT_BF16, fast = p.is_conv && !forced_wide && gather_fast_offsets(p);
-    const int wide = p.is_conv && !fast;           // 64-bit addresses, by a name of their own
+    const int wide = p.is_conv && !fast;           // 64-bit addresses and rows of taps: by names of their own
     int form = gather_form(p);
     if (force_cfg == 0 || force_cfg == 2) form = GATHER_128;
     if (force_cfg == 1 || force_cfg == 3) form = form == GATHER_DEEP64 ? GATHER_DEEP64 : GATHER_64;
     if (force_cfg == 4 || force_cfg == 5) form = GATHER_DEEP128;
+    const int kind = wide ? 1 : p.is_conv && gather_rows_of_taps(p, form == GATHER_128) ? 2 : 0;
     if (form == GATHER_DEEP64) {
-        const int parts = gather_parts(p, p.is_conv && fast && gather_rows_of_taps(p, false));
+        const int parts = gather_parts(p, kind == 2);
         int dev = 0;
         if (parts > 1 && hipGetDevice(&dev) == hipSuccess) {
             if (const ScratchUse use(dev, stream); use) {
-                *name = wide ? "mfma16_gather_64x128x64_w4x2_a64_split" : "mfma16_gather_64x128x64_w4x2_split";
+                static const char* const split[3] = {"mfma16_gather_64x128x64_w4x2_split", "mfma16_gather_64x128x64_w4x2_a64_split", "mfma16_rows_gather_64x128x64_w4x2_split"};
+                *name = split[kind];
                 return bf16 ? launch_gather_type<bf16_t, 64, true, true>(p, stream, fast, parts, &use)
                             : launch_gather_type<f16_t, 64, true, true>(p, stream, fast, parts, &use);
             }
         }
     }
-    static const char* const names[4][2] = {{"mfma16_gather_128x128x32_w2x2", "mfma16_gather_128x128x32_w2x2_a64"}, {"mfma16_gather_64x128x32_w2x2", "mfma16_gather_64x128x32_w2x2_a64"},
-                                            {"mfma16_gather_64x128x64_w4x2", "mfma16_gather_64x128x64_w4x2_a64"}, {"mfma16_gather_128x128x64_w4x2", "mfma16_gather_128x128x64_w4x2_a64"}};
-    *name = names[form][wide];
+    static const char* const names[4][3] = {
+        {"mfma16_gather_128x128x32_w2x2", "mfma16_gather_128x128x32_w2x2_a64", "mfma16_rows_gather_128x128x32_w2x2"},
+        {"mfma16_gather_64x128x32_w2x2", "mfma16_gather_64x128x32_w2x2_a64", "mfma16_rows_gather_64x128x32_w2x2"},
+        {"mfma16_gather_64x128x64_w4x2", "mfma16_gather_64x128x64_w4x2_a64", "mfma16_rows_gather_64x128x64_w4x2"},
+        {"mfma16_gather_128x128x64_w4x2", "mfma16_gather_128x128x64_w4x2_a64", "mfma16_rows_gather_128x128x64_w4x2"}};
+    *name = names[form][kind];
     switch (form) {
     case GATHER_DEEP64: return bf16 ? launch_gather_type<bf16_t, 64, true>(p, stream, fast) : launch_gather_type<f16_t, 64, true>(p, stream, fast);
     case GATHER_DEEP128: return bf16 ? launch_gather_type<bf16_t, 128, true>(p, stream, fast) : launch_gather_type<f16_t, 128, true>(p, stream, fast);

@@ -90,3 +90,23 @@ def test_parts(n, hw, Cin, k, split):
     ref, pre = T.oracle_full(w, host)
     err = T.rel_err(T.to_host_f64(out, w.out_dtype).reshape(ref.shape), ref, pre)
     assert err <= T.TIGHT[BF16], err
+
+
+@pytest.mark.parametrize("force,Cin,KW,W,dil_w,rows", [
+    (None, 3, 7, 20, 1, True), (None, 3, 7, 20, 2, False), (None, 9, 1, 20, 1, False), (None, 7, 1, 20, 1, False),      # taps apart, a single one
+    (None, 1, 8, 20, 1, True), (None, 1, 7, 20, 1, False), (None, 1, 8, 7, 1, False),                                    # a row of taps, and an image's, of eight values
+    ("gather:0", 3, 3, 20, 1, True), ("gather:0", 127, 3, 20, 1, False), ("gather:1", 127, 3, 20, 1, True), ("gather:4", 127, 3, 20, 1, True),   # as long as a tap each
+    ("gather:4", 64, 3, 20, 1, True), ("gather:3", 3, 7, 20, 1, False),                                                  # 64-bit addresses
+])
+def test_choice(force, Cin, KW, W, dil_w, rows):
+    """Which convolutions walk a row of taps as one: either side of each line, by the kernel's name."""
+    import paper_2603_06731_amd as pbk
+    w = wl.Workload("taps_choice", "conv", F16, F16, C.EPI_BIAS, n=1, H=24, W=W, Cin=Cin, Cout=33, KH=9, KW=KW, pad=(4, KW // 2 * dil_w), dil=(1, dil_w),
+                    dist_b=("normal", float(np.sqrt(1.0 / (9 * KW * Cin)))))
+    host = wl.make_inputs(w)
+    with T.forced_kernel(force or "gather"):
+        st, out = T.run_workload(w, T.upload(host))
+    assert st == 0 and "gather" in pbk.pbk_last_kernel() and ("rows_gather" in pbk.pbk_last_kernel()) == rows, pbk.pbk_last_kernel()
+    ref, pre = T.oracle_full(w, host)
+    err = T.rel_err(T.to_host_f64(out, w.out_dtype).reshape(ref.shape), ref, pre)
+    assert err <= T.TIGHT[F16], err
