@@ -64,3 +64,51 @@ def test_transposed_convolution(force, name):
     w = torch.randn(4, 4, 264, 136, generator=g, device="cuda").bfloat16()
     out = torch.empty(8, 56, 56, 136, dtype=torch.bfloat16, device="cuda")
     repeats(lambda: pbk.pbk_conv2d_transpose_nhwc(x, w, out, None, 8, 28, 28, 264, 136, 4, 4, 2, 2, 1, 1, 0, 0, 1, 1, BF16, BF16, 1.0, 0), out, force, name)
+
+
+@pytest.mark.parametrize("M,N,K,trans_b,name", [
+    (577, 1024, 4096, 0, "tile64_64x64_s2_split"), (513, 1080, 3336, 1, "tile64_64x64_s2_split"), (128, 2304, 6144, 0, "tile64_32x64_s3_split"),
+    (2600, 5120, 1024, 1, "224x256x32"), (4097, 4096, 1024, 0, "160x256x32"),
+])
+def test_matmul_automatic(M, N, K, trans_b, name):
+    import torch
+    import paper_2603_06731_amd as pbk
+    g = torch.Generator(device="cuda").manual_seed(7)
+    a, b = (torch.randn(*s, generator=g, device="cuda").bfloat16() for s in ((M, K), (N, K) if trans_b else (K, N)))
+    out = torch.empty(M, N, dtype=torch.bfloat16, device="cuda")
+    repeats(lambda: pbk.pbk_matmul(a, b, out, None, M, N, K, K, K if trans_b else N, N, BF16, BF16, trans_b, 1.0, 0), out, None, name)
+
+
+@pytest.mark.parametrize("name", ["tile64_32x64_s3_split"])
+def test_fp8_split(name):
+    import torch
+    import paper_2603_06731_amd as pbk
+    M, N, K = 128, 2304, 8192
+    g = torch.Generator(device="cuda").manual_seed(7)
+    a, b = (torch.randn(r, K, generator=g, device="cuda").to(torch.float8_e4m3fn).view(torch.uint8) for r in (M, N))
+    out = torch.empty(M, N, dtype=torch.bfloat16, device="cuda")
+    repeats(lambda: pbk.pbk_matmul(a, b, out, None, M, N, K, K, K, N, wl.DTYPE_FP8_E4M3, BF16, 1, 1.0, 0), out, None, name)
+
+
+@pytest.mark.parametrize("force,name", [("mfma:14", "256x128x32"), ("mfma:15", "320x128x32"), ("mfma:16", "384x128x32"), ("mfma:17", "448x128x32"), (None, "tile64_32x64_s3_classes")])
+def test_transposed_convolution_tall(force, name):
+    import torch
+    import paper_2603_06731_amd as pbk
+    n, hw = (8, 28) if force else (2, 14)
+    g = torch.Generator(device="cuda").manual_seed(9)
+    x = torch.randn(n, hw, hw, 256, generator=g, device="cuda").bfloat16()
+    w = torch.randn(4, 4, 256, 136, generator=g, device="cuda").bfloat16()
+    out = torch.empty(n, 2 * hw, 2 * hw, 136, dtype=torch.bfloat16, device="cuda")
+    repeats(lambda: pbk.pbk_conv2d_transpose_nhwc(x, w, out, None, n, hw, hw, 256, 136, 4, 4, 2, 2, 1, 1, 0, 0, 1, 1, BF16, BF16, 1.0, 0), out, force, name)
+
+
+@pytest.mark.parametrize("force", ["gather:0", "gather:1", "gather:4", None])
+def test_rows_of_taps(force):
+    """... and, by the automatic choice, in three parts."""
+    import torch
+    import paper_2603_06731_amd as pbk
+    n, hw, Cin, Cout, k = (4, 40, 11, 72, 7) if force else (1, 20, 11, 72, 7)
+    g = torch.Generator(device="cuda").manual_seed(11)
+    x, w = torch.randn(n, hw, hw, Cin, generator=g, device="cuda").bfloat16(), torch.randn(k, k, Cin, Cout, generator=g, device="cuda").bfloat16()
+    out = torch.empty(n, hw, hw, Cout, dtype=torch.bfloat16, device="cuda")
+    repeats(lambda: pbk.pbk_conv2d_nhwc(x, w, out, None, n, hw, hw, Cin, Cout, k, k, 1, 1, 3, 3, 1, 1, BF16, BF16, 1.0, 0), out, force, "rows_gather" if force else "_split")

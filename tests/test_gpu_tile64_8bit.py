@@ -122,3 +122,34 @@ def test_forms_that_are_not_built(force):
         st = pbk.pbk_matmul(a.view(torch.uint8), b.view(torch.uint8), o, None, m, n, k, k, k, n, E4M3, F32, 1, 1.0, C.EPI_NONE)
         assert "not supported" in pbk.pbk_status_string(st), st
     assert bool((out == 7).all()) and bool((o == 7).all())
+
+
+@pytest.mark.parametrize("M,N,K,split", [(64, 512, 3056, True), (64, 512, 2816, False), (128, 2304, 8192, True), (128, 2304, 5888, False), (128, 2816, 8192, False)])
+def test_dispatch_split_fp8(M, N, K, split):
+    """16 tiles, 12 rounds of 256 and 11; 144 tiles, 32 and 23 (24); 176."""
+    import paper_2603_06731_amd as pbk
+    w = wl.Workload("t64_split_dispatch", "matmul", E4M3, BF16, C.EPI_BIAS, M=M, N=N, K=K, trans_b=1, dist_b=("normal", 1.0 / np.sqrt(K)))
+    check_full(w, expect_kernel="mfma8_tile64")
+    assert pbk.pbk_last_kernel().endswith("_split") == split, pbk.pbk_last_kernel()
+
+
+@pytest.mark.parametrize("m,n,k,split", [(64, 512, 3056, True), (64, 512, 2816, False), (128, 2304, 8192, True), (128, 2304, 5888, False)])
+def test_dispatch_split_int8(m, n, k, split):
+    import oracle
+    A, B, q = wl.int8_tensor((m, k), 1), wl.int8_tensor((n, k), 2), params(n, 3)
+    got, kernel = run_matmul(A, B, q, 1, True, None)
+    assert "mfma8_tile64" in kernel and kernel.endswith("_split") == split, kernel
+    assert np.array_equal(got, oracle.matmul_int8(A, B, trans_b=1, **q))
+
+
+@pytest.mark.parametrize("trans_b", [0, 1])
+def test_forced_split_is_one(trans_b):
+    """"tile64:8" splits whatever has two rounds of 256 values of k, and the other form never does."""
+    import oracle
+    for m, n, k in SHAPES:
+        n += trans_b * 5
+        A, B, q = wl.int8_tensor((m, k), 1), wl.int8_tensor((n, k) if trans_b else (k, n), 2), params(n, 3)
+        for force in FORMS:
+            got, kernel = run_matmul(A, B, q, trans_b, True, force)
+            assert kernel.endswith("_split") == (force == "tile64:8" and k > 256), (kernel, k)
+            assert np.array_equal(got, oracle.matmul_int8(A, B, trans_b=trans_b, **q))

@@ -122,3 +122,45 @@ def test_dispatch_narrow(n, hw, cin, cout, k, transposed, tile):
         st, out = T.run_workload(w, dev)
     ref = T.to_host_f64(out, w.out_dtype)
     assert st == 0 and np.all(np.abs(got - ref) <= 2.0 ** -7 * np.abs(ref) + 1e-4)
+
+
+@pytest.mark.parametrize("cfg", CFGS)
+@pytest.mark.parametrize("out", ["same", "f32"])
+@pytest.mark.parametrize("ldr,ldc", [(272, 272), (277, 264)])          # residual in whole 16-byte pieces, one element at a time
+def test_residual(cfg, out, ldr, ldc):
+    """The shortcut operand through the epilogue's passes, of 7 or 5 blocks of rows."""
+    import torch
+    import paper_2603_06731_amd as pbk
+    M, N, K = 2 * HEIGHT[cfg] - 5, 264, 200
+    g = torch.Generator(device="cuda").manual_seed(cfg)
+    td, code = (torch.bfloat16, BF16) if out == "same" else (torch.float32, F32)
+    A, B = torch.randn(M, K, generator=g, device="cuda").bfloat16(), (torch.randn(K, N, generator=g, device="cuda") * K ** -0.5).bfloat16()
+    R, bias = torch.randn(M, ldr, generator=g, device="cuda").to(td), torch.randn(N, generator=g, device="cuda")
+    C_ = torch.full((M, ldc), 7.0, device="cuda", dtype=td)
+    with T.forced_kernel(f"mfma:{cfg}"):
+        st = pbk.pbk_matmul_residual(A, B, C_, bias, R, M, N, K, K, N, ldc, ldr, BF16, code, 0, 0.5, 2.0, C.EPI_BIAS_RELU)
+    assert st == 0 and f"{HEIGHT[cfg]}x256x32" in pbk.pbk_last_kernel(), pbk.pbk_last_kernel()
+    ref = torch.relu(0.5 * (A.double() @ B.double()) + bias.double() + 2.0 * R[:, :N].double())
+    # one rounding to the output type (2^-9 of the value in bf16), fp32 sums of 200 terms of order K^-1/2 and three of order one
+    assert torch.all((C_[:, :N].double() - ref).abs() <= (2.0 ** -8 if out == "same" else 0.0) * ref.abs() + 1e-5)
+    assert torch.all(C_[:, N:] == 7.0)
+
+
+@pytest.mark.parametrize("cfg", CFGS + sorted(NARROW))
+@pytest.mark.parametrize("out", ["same", "f32"])
+def test_residual_conv(cfg, out):
+    import torch
+    import paper_2603_06731_amd as pbk
+    n, hw, Cin, Cout = 2, 27, 64, 72
+    g = torch.Generator(device="cuda").manual_seed(cfg)
+    td, code = (torch.float16, F16) if out == "same" else (torch.float32, F32)
+    x, w = torch.randn(n, hw, hw, Cin, generator=g, device="cuda").half(), (torch.randn(3, 3, Cin, Cout, generator=g, device="cuda") * (9 * Cin) ** -0.5).half()
+    r, y = torch.randn(n, hw, hw, Cout, generator=g, device="cuda").to(td), torch.empty(n, hw, hw, Cout, device="cuda", dtype=td)
+    with T.forced_kernel(f"mfma:{cfg}"):
+        st = pbk.pbk_conv2d_nhwc_residual(x, w, y, None, r, n, hw, hw, Cin, Cout, 3, 3, 1, 1, 1, 1, 1, 1, F16, code, 1.0, -0.5, C.EPI_RELU)
+    tile = f"{HEIGHT[cfg]}x256x32" if cfg in HEIGHT else f"{NARROW[cfg]}x128x32"
+    assert st == 0 and tile in pbk.pbk_last_kernel(), pbk.pbk_last_kernel()
+    ref = torch.nn.functional.conv2d(x.double().cpu().permute(0, 3, 1, 2), w.double().cpu().permute(3, 2, 0, 1), padding=1).permute(0, 2, 3, 1)
+    ref = torch.relu(ref - 0.5 * r.double().cpu())
+    # one rounding to the output type (2^-12 of the value in f16), fp32 sums of 576 terms of order one 24th
+    assert torch.all((y.double().cpu() - ref).abs() <= (2.0 ** -11 if out == "same" else 0.0) * ref.abs() + 1e-5)
