@@ -273,14 +273,16 @@ bool mfma_ksplit_supported(const Problem& p) {
 // and 24.8, 16 x 15296 x 14272 73 and 67, 12 x 10112 x 2944 11.9 and 11.4, 8 x 8768 x 960 5.9 and 6.2); up to four rows, whose A costs
 // this kernel less, later (4 x 12800 x 5120 31.4 and 28.3, but 4 x 8960 x 3072 11.1 and 11.6), and one or two of them only from 193 tiles on, which leave
 // few units without one (1 x 14336 x 4096, 224 tiles, 27.0 and 24.0 from memory, 21.3 and 20.2 from the caches, 13888, 217, 20.5 and 20.2, 17.9 and 18.0; 12288,
-// 192, 23.0 and 23.7, 17.8 and 18.4; 10240, 160, 21.8 and 23.2, 15.6 and 15.7; 8448, 132, 19.4 and 21.6, 13.5 and 14.5; 1 x 12288 x 8192 42.5 and 43.6); with more columns the two-per-unit tiles fill their last round badly (8 x 24576 x 4096 45.4 and 48.4).
+// 192, 23.0 and 23.7, 17.8 and 18.4; 10240, 160, 21.8 and 23.2, 15.6 and 15.7; 8448, 132, 19.4 and 21.6, 13.5 and 14.5; 1 x 12288 x 8192 42.5 and 43.6), unless
+// rows of B are a multiple of 1 KiB apart that is none of 4 KiB (11776 25.8 and 23.5, 18.9 and 17.8, 11264 24.9 and 23.2, 8704 24.6 and 22.5); with more columns the two-per-unit tiles fill their last round badly (8 x 24576 x 4096 45.4 and 48.4).
 // Results in fp32 stay here: sixteen sums of k / 16 values are nearer to 64 bits than four of k / 4 (8 x 14336 x 4096: 1.15e-7 and 1.88e-7 of the result, 16 x
 // 15296 x 14272 1.87e-7 and 3.69e-7); rounded to 16 bits both are 1.6615e-3 away.
 bool mfma_ksplit_preferred(const Problem& p) {
     if (p.M > 16 || p.K < 512) return false;
     if (ksplit_choice(p) == 1) return true;
     const long long tiles = (long long)((p.N + 63) / 64) * p.batch;
-    return !p.trans_b && (tiles <= (p.M <= 2 ? 192 : 128) || tiles > 256 || p.out_dtype == DT_F32 || p.K < (p.M <= 4 ? 4096 : 2048) || !mfma_tile64_supported(p) || !mfma_tile64_preferred(p));
+    const bool odd_kib = p.ldb % 512 == 0 && p.ldb % 2048 != 0;
+    return !p.trans_b && (tiles <= (p.M <= 2 && !odd_kib ? 192 : 128) || tiles > 256 || p.out_dtype == DT_F32 || p.K < (p.M <= 4 ? 4096 : 2048) || !mfma_tile64_supported(p) || !mfma_tile64_preferred(p));
 }
 
 hipError_t launch_mfma_ksplit(const Problem& p, hipStream_t stream, int cfg, const char** name) {

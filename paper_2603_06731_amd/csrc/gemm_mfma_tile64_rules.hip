@@ -91,16 +91,17 @@ bool mfma_tile64_preferred(const Problem& p) {
 // - 129 to 170 tiles: three parts, two workgroups on nearly every unit, against whole tiles on little more than half of the units: 128 x 2304 x 6144
 //   19.4/25.2 and 14.7/20.0, 64 x 5120 x 9216 44 and 33, 59 x 5440 x 2560 10.5 and 10.7, 64 x 4608 x 2048 9.1 and 9.4; up to 32 rows, whose whole tiles
 //   read close to the rate of the memory, later: 32 x 8448 x 6144 29.9 and 26.0, 4 x 9216 x 8192 36.4 and 32.2, 16 x 10240 x 4096 15.2/21.5 and 17.5/20.0.
-//   One or two rows over a row-major B, for which ksplit does as well from the memory and better from the caches (first), up to 144 tiles only: 1 x 8640 x 6144
-//   25.6/17.7 and 23.0/19.4, 1 x 9472, 148 tiles, 26.9/19.1 and 27.0/21.7, 1 x 10240 31.1/21.7 and 31.8/24.6, 1 x 10816 26.7/20.5 and 26.6/22.5
-//   (here: from memory / from the caches).
+//   One or two rows over a row-major B, ksplit first, from memory / from the caches: 1 x 8640 x 6144 25.6/17.7 and 23.0/19.4, 2 x 9792 x 8192 33.9/24.4 and
+//   32.2/26.1, x 15000 59.4/52.7 and 53.2/46.0, 1 x 10240 x 6144 31.1/21.7 and 31.8/24.6, 2 x 10816 x 8192 34.8/26.6 and 33.6/28.6.
 //   (FP8 128 x 2304 x 8192: 16.1 and 12.5, 96 x 3200 x 6144 13.1 and 11.6, 160 x 2048 x 4096 10.1 and 10.0.)
 // - Two parts only, from 86 tiles on, give back less: with operands in the caches, 256 x 1024 x 1536 7.7 and 8.7, x 1792 8.3 and 9.0, x 2304 9.6 and
 //   9.7; from memory 9.95 and 9.24, 11.0 and 9.7, 12.8 and 10.7; 61 x 3328 x 1536 7.6 and 8.3, from memory 10.3 and 9.3.
 // - Up to 16 rows, row-major B, against ksplit, which reads the same bytes without a meeting: 16 x 1664 x 3072 8.9/9.2 and 8.1/8.6, but 8 rows 8.0/8.3 and
 //   8.1/8.6, one 7.0/7.4 and 8.0/8.4; one row, 3136 x 3072 7.0/10.2 and 8.7/9.7, but 8 11.6 and 9.8 from memory; 8 x 4096 x 3072 9.9/15.1 and 9.2/11.1, 4 x 1024 x 4096 7.1/15.2 and 8.9/9.7, 8 x 2560 x 2560 9.4/14.4 and 7.9/9.6 but 4 x 3072 x 2560 8.6/13.3 and 8.2/9.9,
 //   2 x 4096 x 2560 8.2/12.4 and 9.2/10.2; 65 to 85 tiles: 2 x 4224 x 4096 9.2/14.1 and 10.2/11.6, x 5760 13.0/20.4 and 12.0/14.3, 8 x 5120 x
-//   13312 78 and 32; 86 to 128: 1 x 7552 x 5760 15.4/19.9 and 17.1/18.6, 1 x 6208 x 8192 22.1/23.7 and 20.2/21.4, 8 x 4096 x 14336 57 and 28; more than 8 rows
+//   13312 78 and 32; 86 to 128: 1 x 7552 x 5760 15.4/19.9 and 17.1/18.6, 1 x 6208 x 8192 22.1/23.7 and 20.2/21.4, 8 x 4096 x 14336 57 and 28; 1 x 1152 x 4992 12.5/7.6 and 9.7/9.1; ksplit reads rows of B
+//   a multiple of 512 bytes apart badly from memory, so that up to eight rows are split as early as nine there (4 x 2048 x 3584 15.6/6.4 and 9.8/8.6, 1 x 2560 x 3072
+//   14.9/5.8 and 9.9/8.0, 4 x 3072 x 4032 19.0/10.8 and 11.3/8.9, 8 x 1024 x 5760 18.3/8.6 and 10.2/9.3, 1 x 4096 x 3584 15.6/6.2 and 11.6/8.8); more than 8 rows
 //   from 4096 on: 12 x 6976 x 5696 14.8/22.3 and 15.7/18.0, 16 x 8192 x 4096 16.9 and 15.4; k-major 8 x 1024 x 4096 7.0 and 8.0.
 //   Results in fp32 only with four parts and more, whose four sums each are as many as ksplit's sixteen (its distance from 64 bits first, of the result: 16 x
 //   8192 x 4096, two parts, 1.15e-7 and 1.35e-7, 3 x 8200 x 5640, three, 1.28e-7 and 1.31e-7, 8 x 4096 x 14336, four, 1.86e-7 and 1.81e-7).
@@ -134,11 +135,12 @@ static int tile64_parts_of(const Problem& p, bool forced) {
         const int twice = std::min({512 / tiles, (rounds + 2) / 5, tiles <= 32 ? 8 : 6});
         return forced ? std::min({512 / tiles, rounds, 8}) : rounds < (tiles > 170 ? 24 : tiles > 128 ? 16 : 11) ? 1 : std::max(once, twice);
     }
-    if (tiles > 128) return tiles <= (p.M <= 2 && !p.trans_b ? 144 : 170) && rounds >= (p.M <= 32 ? 45 : 24) ? 3 : 1;
+    if (tiles > 128) return tiles <= 170 && rounds >= (p.M <= 32 ? 45 : 24) ? 3 : 1;
     if (!forced && rounds < 12) return 1;
     if (!forced && p.M <= 16) {
+        const bool early = p.M > 8 || p.ldb % 256 == 0;
         const bool fits = p.trans_b ? p.K >= 4096 && (int64_t)p.N * p.K >= 4000000
-                                    : p.K >= (tiles <= 64 ? (p.M > 4 ? 3072 : 4096) : p.M > 8 ? 4096 : tiles <= 85 ? 4608 : 6144) && (int64_t)p.N * p.K >= (p.M > 8 ? 5000000 : 6000000);
+                                    : p.K >= (tiles <= 64 ? (p.M > 4 || early ? 3072 : 4096) : p.M > 8 ? 4096 : tiles <= 85 ? 4608 : 6144) && (int64_t)p.N * p.K >= (early ? 5000000 : 6000000);
         if (!fits) return 1;
     }
     int parts = std::min((192 + tiles / 2) / tiles, 8);
