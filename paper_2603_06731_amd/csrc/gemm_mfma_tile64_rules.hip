@@ -101,7 +101,8 @@ bool mfma_tile64_preferred(const Problem& p) {
 //   2 x 4096 x 2560 8.2/12.4 and 9.2/10.2; 65 to 85 tiles: 2 x 4224 x 4096 9.2/14.1 and 10.2/11.6, x 5760 13.0/20.4 and 12.0/14.3, 8 x 5120 x
 //   13312 78 and 32; 86 to 128: 1 x 7552 x 5760 15.4/19.9 and 17.1/18.6, 1 x 6208 x 8192 22.1/23.7 and 20.2/21.4, 8 x 4096 x 14336 57 and 28; 1 x 1152 x 4992 12.5/7.6 and 9.7/9.1; ksplit reads rows of B
 //   a multiple of 512 bytes apart badly from memory, so that up to eight rows are split as early as nine there (4 x 2048 x 3584 15.6/6.4 and 9.8/8.6, 1 x 2560 x 3072
-//   14.9/5.8 and 9.9/8.0, 4 x 3072 x 4032 19.0/10.8 and 11.3/8.9, 8 x 1024 x 5760 18.3/8.6 and 10.2/9.3, 1 x 4096 x 3584 15.6/6.2 and 11.6/8.8); more than 8 rows
+//   14.9/5.8 and 9.9/8.0, 4 x 3072 x 4032 19.0/10.8 and 11.3/8.9, 8 x 1024 x 5760 18.3/8.6 and 10.2/9.3, 1 x 4096 x 3584 15.6/6.2 and 11.6/8.8), and so are 8-bit
+//   operands, which ksplit does not take (1 x 1408 x 4096, whole and split, 9.7 and 7.6); more than 8 rows
 //   from 4096 on: 12 x 6976 x 5696 14.8/22.3 and 15.7/18.0, 16 x 8192 x 4096 16.9 and 15.4; k-major 8 x 1024 x 4096 7.0 and 8.0.
 //   Results in fp32 only with four parts and more, whose four sums each are as many as ksplit's sixteen (its distance from 64 bits first, of the result: 16 x
 //   8192 x 4096, two parts, 1.15e-7 and 1.35e-7, 3 x 8200 x 5640, three, 1.28e-7 and 1.31e-7, 8 x 4096 x 14336, four, 1.86e-7 and 1.81e-7).
@@ -138,7 +139,7 @@ static int tile64_parts_of(const Problem& p, bool forced) {
     if (tiles > 128) return tiles <= 170 && rounds >= (p.M <= 32 ? 45 : 24) ? 3 : 1;
     if (!forced && rounds < 12) return 1;
     if (!forced && p.M <= 16) {
-        const bool early = p.M > 8 || p.ldb % 256 == 0;
+        const bool early = p.M > 8 || p.ldb % 256 == 0 || bits8(p);
         const bool fits = p.trans_b ? p.K >= 4096 && (int64_t)p.N * p.K >= 4000000
                                     : p.K >= (tiles <= 64 ? (p.M > 4 || early ? 3072 : 4096) : p.M > 8 ? 4096 : tiles <= 85 ? 4608 : 6144) && (int64_t)p.N * p.K >= (early ? 5000000 : 6000000);
         if (!fits) return 1;

@@ -133,6 +133,15 @@ def test_dispatch_split_fp8(M, N, K, split):
     assert pbk.pbk_last_kernel().endswith("_split") == split, pbk.pbk_last_kernel()
 
 
+@pytest.mark.parametrize("M,N,K,split", [(1, 1408, 4096, True), (8, 1408, 3536, False), (8, 1408, 3568, True), (2, 2000, 3056, False), (2, 2000, 3072, True)])
+def test_dispatch_split_few_rows_fp8(M, N, K, split):
+    """Up to 16 rows over a row-major B: five million values of B, and K = 3072."""
+    import paper_2603_06731_amd as pbk
+    w = wl.Workload("t64_split_few_rows", "matmul", E4M3, BF16, C.EPI_BIAS, M=M, N=N, K=K, dist_b=("normal", 1.0 / np.sqrt(K)))
+    check_full(w, expect_kernel="mfma8_tile64")
+    assert pbk.pbk_last_kernel().endswith("_split") == split, pbk.pbk_last_kernel()
+
+
 @pytest.mark.parametrize("m,n,k,split", [(64, 512, 3056, True), (64, 512, 2816, False), (128, 2304, 8192, True), (128, 2304, 5888, False)])
 def test_dispatch_split_int8(m, n, k, split):
     import oracle
