@@ -731,18 +731,20 @@ static int gather_form(const Problem& p) {
 //   convolutions of 2 and 3 k-tiles: 9.3 and 9.8, 8.6 and 9.3.
 // rows: a row of taps is one tap.  The k-tiles are those of the K axis that the kernel then walks, up to eight times shorter than with a tap each (8 x 8 over one
 // channel: one k-tile for eight; two parts of it, one of them empty, 8.1, whole 5.9), and cost more each, so that three parts pay sooner with few tiles: up
-// to 32 from six k-tiles on, up to 64 from nine (whole, 2 parts, 3: 11 tiles, 6 k-tiles, 11.7, 11.2 and 10.9; 18, 7 11.6, 11.5 and 11.1; 50, 7 11.2, 11.7 and 12.2; 22, 9 13.7,
-// 12.2 and 11.3; 48, 11 15.5, 13.5 and 13.2; 61, 13 16.5, 14.8 and 14.8; 81, 11 16.2, 15.5 and 16.9; 13, 5 11.2, 11.8 and 11.6; 112, 7 11.0 and 12.7).
+// to 32 from six k-tiles on, up to 40 from nine, up to 64 from eleven (whole, 2 parts, 3: 11 tiles, 6 k-tiles, 11.7, 11.2 and 10.9; 18, 7 11.6, 11.5 and 11.1; 50, 7 11.2,
+// 11.7 and 12.2; 22, 9 13.7, 12.2 and 11.3; 38, 9, 2 parts and 3, 12.3 and 11.9, 44 tiles 12.4 and 12.7; 48, 11 15.5, 13.5 and 13.2; 61, 13 16.5, 14.8 and 14.8; 81, 11 16.2,
+// 15.5 and 16.9; 13, 5 11.2, 11.8 and 11.6; 112, 7 11.0 and 12.7), and more parts a twelfth sooner (45 k-tiles, 5 and 6 parts: 16.3 and 15.8; 77, 7 and 8: 16.9 and 16.4).
 static int gather_parts(const Problem& p, bool rows) {
     const long long tiles = (long long)((p.M + 63) / 64) * ((p.N + GBN - 1) / GBN) * p.batch;
     const long long tap = rows ? (long long)p.conv.KW * p.conv.Cin : p.conv.Cin, taps = rows ? p.conv.KH : (long long)p.conv.KH * p.conv.KW;
     const long long kt = ((p.is_conv ? taps * ((tap + 7) & ~7LL) : p.K) + 63) / 64;
-    if (rows && kt < 15 && kt >= (tiles <= 32 ? 6 : tiles <= 64 ? 9 : 15)) return 3;
+    if (rows && kt < 15 && kt >= (tiles <= 32 ? 6 : tiles <= 40 ? 9 : tiles <= 64 ? 11 : 15)) return 3;
     if (tiles > 128 || kt < (p.is_conv ? 8 : 12)) return 1;
     const long long room = (long long)kScratchBytes / (64 * GBN * 4) / tiles;        // the parts' sums have to fit
     int parts = 1;
     static_assert(3 * 64 * 64 * GBN * 4 <= kScratchBytes, "three parts of 64 tiles");
-    while (parts < 8 && (parts + 1) * tiles <= 256 && parts < room && (parts + 1) * (parts + 3) <= kt) ++parts;
+    const long long worth = rows ? kt + kt / 12 : kt;
+    while (parts < 8 && (parts + 1) * tiles <= 256 && parts < room && (parts + 1) * (parts + 3) <= worth) ++parts;
     return parts;
 }
 

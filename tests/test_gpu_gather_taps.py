@@ -76,6 +76,7 @@ def test_nan_reaches_only_its_windows(case):
     (2, 16, 1, 8, False), (2, 30, 1, 9, False),         # one k-tile, three
     (1, 16, 35, 3, True), (1, 16, 11, 5, False),        # four tiles of 64 rows: six k-tiles, five
     (9, 16, 3, 11, False), (9, 16, 11, 7, True),        # 36 tiles: seven, nine
+    (11, 16, 11, 7, True), (11, 16, 13, 7, True),       # 44: nine (two parts), eleven (three)
     (17, 16, 3, 11, False), (17, 16, 11, 7, True),      # 68: two parts from eight on
 ])
 def test_parts(n, hw, Cin, k, split):
