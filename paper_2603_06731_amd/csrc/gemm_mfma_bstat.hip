@@ -372,12 +372,14 @@ bool mfma_bstat_supported(const Problem& p) {
 //   plain ones, 32000 x 256 10.1/8.5 and 11.8/8.5, 12800 x 512 9.0/8.0 and 9.8/8.0, only from 768 steps on), but between one step and one and a half for every
 //   slot, which take two rounds (44 x 448 x 448, 616: 10.4 and 11.6; 25 x 704 x 704 11.2 and 10.8, 38 x 640 x 640, 1140: 17.3 and 13.0);
 // - up to 192 from 900 on (from memory 28800 x 512, 900: 16.7 and 15.5, 70400 x 256, 1100: 27.5 and 20.6);
-// - beyond that from the first step on that the 128 x 256 tiles do not hold in one round, two per unit, which are 2 to 5 % ahead before (59584 x 256, 931:
-//   19.9/16.1 and 20.6/16.6, 25 x 768 x 768, 900: 18.1/14.8 and 18.7/15.6; 70400 x 256, 1100: 30.2/23.2 and 23.4/19.5; 17600 x 1024, 1100: 25.6/22.6 and 21.2/18.7).
+// - beyond that from the first step on that the 128 x 256 tiles do not hold in one round, two per unit, which are 2 to 6 % ahead before (one strip of columns, 59584 x 256,
+//   931: 19.9/16.1 and 20.6/16.6, 64000, 1000, 19.4/16.8 and 21.0/16.9; two, 31000 x 512, 970, 18.9/16.0 and 20.3/15.6; 10 x 1152 x 1152, 900, 16.8/14.2 and 18.0/14.4; 70400 x
+//   256, 1100: 30.2/23.2 and 23.4/19.5), and with more strips or batches, where those read more of B again, from 941 on (35 x 576 x 576, 945: 22.6/17.4 and 19.3/16.7, 17 x
+//   960 x 960, 1020, 22.9/17.6 and 20.0/17.0; 7900 x 2048, 992, 18.2/16.7 and 17.6/15.4, 16000 x 1024, 1000, 18.1/15.8 and 17.8/15.4).
 bool mfma_bstat_preferred(const Problem& p) {
     if (p.M < 256 || p.N < 256) return false;
     const long long steps = (long long)((p.M + SBM - 1) / SBM) * ((p.N + SBN - 1) / SBN) * p.batch;
-    if (p.K > 192) return steps > 1024;
+    if (p.K > 192) return steps > (p.batch > 1 || p.N > 512 ? 940 : 1024);
     if (p.K > 128) return steps >= 900;
     return steps >= (p.K <= 64 || p.batch > 1 ? 384 : 768) && (p.K <= 64 || steps <= 512 || steps >= 768);
 }

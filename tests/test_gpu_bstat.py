@@ -111,11 +111,12 @@ def test_bstat_dispatch_and_walks(batch, M, N, K, bstat):
 
 
 @pytest.mark.parametrize("batch,M,N,K,bstat", [
-    (64, 512, 512, 200, False), (64, 513, 512, 200, True), (57, 512, 512, 192, True), (1, 65536, 256, 256, False), (1, 65537, 256, 256, True),    # 1024 steps, 1152; 1025
+    (47, 640, 448, 200, False), (59, 512, 512, 200, True), (57, 512, 512, 192, True),                          # 940 steps, 944; 912
+    (1, 65536, 256, 256, False), (1, 65537, 256, 256, True), (1, 15040, 1024, 200, False), (1, 15041, 1024, 200, True),     # 1024, 1025; 940, 944
     (1, 24576, 256, 64, True), (1, 24576, 256, 72, False), (1, 49088, 256, 72, False), (1, 49152, 256, 72, True),                                # 384; 767, 768
 ])
 def test_bstat_dispatch_deep_and_plain(batch, M, N, K, bstat):
-    """Contractions beyond 192, from 1025 steps on; plain products from 64 to 128, from 768 on."""
+    """Contractions beyond 192, from 941 steps on, plain ones of up to 512 columns from 1025; plain products from 64 to 128, from 768 on."""
     err, kern = run_case(batch, M, N, K, BF16, BF16, 1, C.EPI_NONE, force=None, bias_on=False)
     assert ("bstat" in kern) == bstat, kern
     assert err <= T.TIGHT[BF16], err
