@@ -709,12 +709,12 @@ template <int MODE> using TileMapOf = typename TileMapSel<MODE>::type;
 // k-tile, so that each direct-to-LDS load moves whole 128-byte lines of A.  With 64-byte row
 // pieces every line of A is requested from L2 twice (once per k-tile; measured: 1.5 times the
 // L1->L2 read requests of the 64-deep configurations), and that path is as loaded as the MFMA pipe.
-// ASTG 2: the same staging of A with SIX stages of B (NSTAGE = 5 sizes the LDS: 2 x 32 + 6 x 16 KiB of the 160)
-// and one barrier per PAIR of k-tiles.  With a k-major B (MODE_TRANS_B) the six stages are three pieces of
+// ASTG 2: the same staging of A with SIX stages of B (two pieces of A and these are all of the LDS with 256 x 256: 2 x 32 + 6 x 16 of 160 KiB;
+// with 448 x 128: 2 x 56 + 6 x 8) and one barrier per PAIR of k-tiles.  With a k-major B (MODE_TRANS_B) the six stages are three pieces of
 // B staged 64 deep like A.  A convolution (MODE_CONV) takes the pair pipeline when Cin is a multiple of 64: a 64-deep
 // piece of the image then lies inside one filter tap.
-// In the pair pipeline BM may be any multiple of 32 up to 256: the two halves of a wave's 16-row blocks then differ by one, and so
-// may the waves' shares of a piece of A.
+// In the pair pipeline BM may be any multiple of 16 WM for which the LDS suffices (mfma_lds_bytes): the two halves of a wave's 16-row blocks may
+// differ by one, and so may the waves' shares of a piece of A.
 //
 // LDS bytes of a workgroup
 constexpr int mfma_lds_bytes(int BM, int BN, int BK, int NW, int NSTAGE, int ASTG) {

@@ -27,11 +27,11 @@ static const MfmaConfig kMfmaConfigs[] = {
     {7, 256, 256, 32, 2, 4, 4, "mfma16_256x256x32_w2x4_s4_a64"},    // A staged 64 deep (plain matrices)
     {8, 256, 256, 64, 2, 4, 2, "mfma16_256x256x64_w2x4_s2"},        // int8, both operands k-major (16x16x64 blocks)
     {9, 256, 256, 32, 2, 4, 5, "mfma16_256x256x32_w2x4_a64_b6_pair"},   // as 7 with six B stages, one barrier per two k-tiles
-    {10, 224, 256, 32, 2, 4, 5, "mfma16_224x256x32_w2x4_a64_b6_pair"},  // 9 with fewer rows, see pair_height
+    {10, 224, 256, 32, 2, 4, 5, "mfma16_224x256x32_w2x4_a64_b6_pair"},  // 9 with fewer rows, see pair_choice
     {11, 192, 256, 32, 2, 4, 5, "mfma16_192x256x32_w2x4_a64_b6_pair"},
     {12, 160, 256, 32, 2, 4, 5, "mfma16_160x256x32_w2x4_a64_b6_pair"},
     {13, 128, 256, 32, 2, 4, 5, "mfma16_128x256x32_w2x4_a64_b6_pair"},
-    {14, 256, 128, 32, 4, 2, 5, "mfma16_256x128x32_w4x2_a64_b6_pair"},  // convolutions of up to 128 columns
+    {14, 256, 128, 32, 4, 2, 5, "mfma16_256x128x32_w4x2_a64_b6_pair"},  // convolutions of up to 128 columns, transposed ones of any number, see tall_config
     {15, 320, 128, 32, 4, 2, 5, "mfma16_320x128x32_w4x2_a64_b6_pair"},
     {16, 384, 128, 32, 4, 2, 5, "mfma16_384x128x32_w4x2_a64_b6_pair"},
     {17, 448, 128, 32, 4, 2, 5, "mfma16_448x128x32_w4x2_a64_b6_pair"},
@@ -151,7 +151,7 @@ hipError_t launch_one(const Problem& p, hipStream_t stream, int group_m) {
 
 template <typename T, int BM, int BN, int BK, int WM, int WN, int NSTAGE, int OCC = 1, int MI = 32, int ASTG = 0>
 hipError_t launch_modes(const Problem& p, hipStream_t stream, int group_m) {
-    if constexpr (ASTG == 2) {            // built for plain matrices (B row-major or k-major) only
+    if constexpr (ASTG == 2) {            // 256 columns: plain matrices and convolutions; 128: convolutions and, by residue classes, transposed ones
         if (p.is_conv) {          // the image in 64-deep pieces: each must lie inside one filter tap
             if (p.conv.transposed == 1 || p.conv.Cin % 64 != 0) return hipErrorInvalidValue;
             if (p.conv.transposed) {
